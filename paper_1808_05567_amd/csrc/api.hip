@@ -37,6 +37,7 @@ struct IgemmPlan {
     IgemmArgs a{};
     size_t lds = 0;
     int grid = 0;
+    bool reg = false;  // the register-operand kernel (v.wk waves split the reduction of a tile)
 };
 
 struct BwdClass {  // one stride-parity class of the generic backward pass
@@ -45,6 +46,7 @@ struct BwdClass {  // one stride-parity class of the generic backward pass
     WtMergeArgs m{};      // all classes in one launch (merged == true)
     bool merged = false;
     size_t ws_off = 0;
+    size_t part_off = 0;  // of the partial results of a split reduction (p.a.ksplit > 1)
 };
 
 }  // namespace
@@ -55,6 +57,7 @@ struct conv_plan {
     conv_info_t info;
     IgemmPlan fwd;
     size_t fwd_ws = 0;  // bytes of fp32 partial results if the forward reduction is split
+    bool fwd_takes_ws = false;  // a result of few tiles: a NULL workspace is refused, split or not
     size_t fwd_stem_lds = 0;  // > 0: the plain forward pass runs on the resident-filter kernel (its LDS)
     // backward by data
     int bwd_mode = 0;  // 0 unsupported, 1 one launch (duality), 2 parity classes
@@ -102,6 +105,7 @@ struct conv_plan {
 namespace {
 
 const int kMaxLds = 160 * 1024;
+constexpr size_t kScratchBytes = (size_t)16 << 20;  // conv_noalloc_scratch_bytes
 
 // Largest number of rows of the padded row space (image n occupies rows
 // [n*Hs, (n+1)*Hs), output row oj of image n starts at n*Hs + oj*stride) that a
@@ -157,6 +161,9 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
     const int TK = wk * fk * 32, TM = wm * fm * 32, NT = 256;
     const int nent = ((R * S * npl + 1) / 2) * 2;
 
+    // (staged positions per thread that the variant is instantiated for)
+    const unsigned have_ppt = igemm_variant_ppts(IgemmVariant{dtype, wk, wm, fk, fm, npl, R, S, 0, nb});
+    if (have_ppt == 0) return pl;
     int ppt = -1;
     int TQ = std::min(Q, TM);
     int TR = std::max(1, TM / TQ);
@@ -173,20 +180,15 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
             LW = (TQ - 1) * cstride + S;
             LR = max_band_rows(N, P, TR, Hs, stride, R);
         }
-        const int need = ceil_div(LR * LW, NT);
         ppt = -1;
-        for (int cand = need; cand <= 16; ++cand) {
-            IgemmVariant v{dtype, wk, wm, fk, fm, npl, R, S, cand, nb};
-            if (igemm_variant_exists(v)) {
-                ppt = cand;
-                break;
-            }
-        }
+        for (int cand = 1; cand <= 16 && ppt < 0; ++cand)
+            if ((have_ppt >> cand & 1) && (long long)LR * LW <= (long long)cand * NT) ppt = cand;
+        if (ppt < 0) continue;
         // the plane pitch is a whole number of wave-level (64-lane) loads
         // (a single-step reduction never touches the second buffer)
         const size_t nbuf = ceil_div(Cb, npl) > 1 ? (size_t)nb : 1;
         const size_t lds = nbuf * ((size_t)nent * TK * 16 + (size_t)npl * ceil_div(LR * LW, 64) * 64 * 16);
-        if (ppt > 0 && lds <= lds_cap) break;
+        if (lds <= lds_cap) break;
     }
 
     IgemmArgs &a = pl.a;
@@ -228,7 +230,7 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
         a.gk = best_gk;
         a.kt_per = ceil_div(a.n_kt, a.gk);
         a.mq_per = ceil_div(a.n_mt * a.n_qt, 8 / a.gk);
-        a.per_xcd = a.kt_per * a.mq_per;
+        a.per_xcd = a.gk == 1 ? ceil_div(a.total, 8) : a.kt_per * a.mq_per;
     }
     a.n_stage = ceil_div(Cb, npl);
     a.st_per = a.n_stage;
@@ -263,6 +265,120 @@ double igemm_waste(const IgemmPlan &p, int N, int P, int Q, int Kp)
     return (p.a.n_mt * p.a.n_qt * TM * p.a.n_kt * TK) / ((double)N * P * Q * Kp);
 }
 
+// A plan of the register-operand kernel: fk x fm fragments per workgroup, nw waves (and, with
+// ksplit > 1, that many workgroups) that split the reduction.
+IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S, int stride,
+                  int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0, int zero_fill,
+                  const IgemmGeo &geo, int fk, int fm, int nw, int ksplit)
+{
+    IgemmPlan pl;
+    if (igemm_reg_depth(dtype, fk, fm, nw) == 0) return pl;
+    const int V = vlen_of(dtype);
+    // 32-bit byte offsets, exact small divisions and 24-bit products, as in try_igemm
+    const double in_units = (double)N * Cb * H * W, out_units = (double)N * (Kp / V) * OH * OW;
+    const double shift = std::max(0.0, (double)pad_h * W + pad_w);
+    if ((in_units + shift) * 16 > 4.0e9 || out_units * 16 > 4.0e9) return pl;
+    if ((double)N * P * Q + fm * 32 >= 4.0e6 || (double)R * S * Kp >= 8.0e6) return pl;
+    if ((double)(N + 1) * std::max(Cb + 1, Kp / V) * std::max(H, OH) >= 8.0e6) return pl;
+    IgemmArgs &a = pl.a;
+    memset(&a, 0, sizeof(a));
+    a.N = N; a.Cb = Cb; a.H = H; a.W = W; a.Kp = Kp; a.P = P; a.Q = Q; a.R = R; a.S = S;
+    a.stride = stride; a.cstride = geo.cstride > 0 ? geo.cstride : stride; a.pad_h = pad_h; a.pad_w = pad_w;
+    a.OH = OH; a.OW = OW; a.ostr = ostr; a.ostr_x = geo.ostr_x > 0 ? geo.ostr_x : ostr;
+    a.oy0 = oy0; a.ox0 = ox0; a.zero_fill = zero_fill;
+    a.out_kb = Kp / V;
+    a.inv_P = 1.0f / (float)(P * Q);
+    a.inv_TQ = 1.0f / (float)Q;
+    a.n_qt = 1;
+    a.n_mt = ceil_div(N * P * Q, fm * 32);
+    a.n_kt = ceil_div(Kp, fk * 32);
+    a.total = a.n_mt * a.n_kt;
+    a.n_stage = ceil_div(Cb, 2) * R * S;
+    a.st_per = ceil_div(a.n_stage, ksplit);
+    a.ksplit = ceil_div(a.n_stage, a.st_per);
+    // channel groups over the XCDs, as in try_igemm
+    const double in_b = in_units * 16, wt_b = (double)Cb * R * S * Kp * 16.0;
+    double best = 0;
+    a.gk = 1;
+    for (int gk = 1; gk <= 8 && gk <= a.n_kt && a.ksplit == 1; gk *= 2) {
+        if (a.n_kt % gk != 0) continue;
+        double cost = gk * in_b + (8.0 / gk) * wt_b;
+        if (wt_b / gk > 2.0e6) cost += 8.0 * in_b;
+        if (gk == 1 || cost < best) { best = cost; a.gk = gk; }
+    }
+    a.kt_per = ceil_div(a.n_kt, a.gk);
+    a.mq_per = ceil_div(a.n_mt, 8 / a.gk);
+    a.per_xcd = a.gk == 1 ? ceil_div(a.total * a.ksplit, 8) : a.kt_per * a.mq_per;
+    pl.v = IgemmVariant{dtype, nw, 1, fk, fm, 2, R, S, 0};
+    pl.lds = igemm_reg_lds_bytes(fk, fm, nw);
+    pl.grid = a.per_xcd * 8;
+    pl.reg = true;
+    pl.ok = true;
+    return pl;
+}
+
+// What a plan's launch takes, in microseconds, as far as the choice between kernels and tiles goes.
+// A workgroup alone on its CU takes `lone` clocks: a fixed part (set-up, first loads, stores) and
+// its steps, each bound by what it asks of the matrix cores, of the 64 B/clk into the CU or of
+// the LDS reads, whichever is slowest; workgroups that share a CU share those, `busy` clocks
+// each, and overlap the rest.  The CU with the most workgroups ends the launch.  The constants
+// are a least-squares fit (log of the time) to 11 000 launches: 38 ResNet-50 and Inception-v3
+// layers x N = 1 ... 256 x both types x every variant; rms error 4 - 16 %.  The plan with the
+// lowest estimate was on average 3 % behind the fastest variant, and 1.65 times as fast
+// as the large tiles (with their reduction split through memory) that these sizes ran on.
+double estimate_us(const IgemmPlan &p, bool scatter)
+{
+    const IgemmArgs &a = p.a;
+    const IgemmVariant &v = p.v;
+    const bool bf16 = v.dtype == CONV_BF16;
+    const double mfma = bf16 ? 32.0 : 256.0;  // clocks of the MFMAs of one 16-byte operand pair
+    const double frags = v.fk * v.fm;
+    const int RS = p.reg ? a.R * a.S : v.r * v.s;
+    struct Fit { double launch, fixed, step, c_mfma, c_load, c_read, busy; };
+    double lone, busy, launch;
+    int resident;
+    if (p.reg) {
+        const Fit f = bf16 ? Fit{2.3, 6340, 119, 2.81, 1.36, 0, 1860} : Fit{3.5, 4600, 380, 1.17, 1.2, 0, 1700};
+        const int depth = igemm_reg_depth(v.dtype, v.fk, v.fm, v.wk);
+        const double per = ceil_div(ceil_div(a.st_per, v.wk), depth) * depth;  // steps of a wave
+        const double simd_waves = v.wk / 4;
+        lone = f.fixed + per * std::max(frags * mfma * f.c_mfma * simd_waves, f.step) + (bf16 ? 22.0 : 0.0) * frags * v.wk;
+        busy = per * std::max(frags * mfma * f.c_mfma * simd_waves, v.wk * (v.fk + v.fm) * 16.0 * f.c_load) + f.busy;
+        // (waves per SIMD that the registers leave room for)
+        const int occ = frags == 1 ? (bf16 ? 5 : 6) : frags == 2 ? (bf16 ? 4 : 5) : 3;
+        resident = std::max(1, occ * 4 / v.wk);
+        launch = f.launch;
+    } else {
+        const bool small = v.fm <= 2;
+        const Fit f = small ? (bf16 ? Fit{2.2, 2400, 205, 1.65, 2.55, 1.28, 880} : Fit{3.0, 1890, 122, 1.04, 1.2, 1.0, 2000})
+                            : (bf16 ? Fit{0.9, 8780, 192, 1.23, 2.04, 1.49, 6000} : Fit{2.5, 6740, 222, 0.99, 1.2, 1.0, 7660});
+        const double waves = v.wk * v.wm, rounds = (RS * v.npl + 1) / 2;
+        const double bytes = (rounds * 2 * v.wk * v.fk * 32 + (double)v.npl * a.PLS) * 16;
+        const double step = std::max(std::max(rounds * frags * mfma * waves / 4 * f.c_mfma, bytes / 64 * f.c_load),
+                                     rounds * (v.fk + v.fm) * waves * 8 * f.c_read);
+        lone = f.fixed + a.n_stage * (step + f.step);
+        busy = a.n_stage * step + f.busy;
+        const int occ = frags * 16 > 128 ? 1 : frags <= 2 ? 4 : small ? 3 : 2;
+        resident = waves == 8 ? 1 : std::max(1, std::min((int)(kMaxLds / p.lds), occ));
+        launch = f.launch;
+    }
+    const int per_cu = ceil_div(p.grid, 256);
+    const int full = per_cu / resident, rest = per_cu - full * resident;
+    double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
+    t = t / 2.3e3 + launch;
+    const int V = vlen_of(v.dtype);
+    const double out = (double)a.N * (scatter ? (double)a.OH * a.OW : (double)a.P * a.Q) * (a.Kp / V) * 16;
+    if (a.ksplit > 1)  // the second launch, and the partial results there and back
+        t += (bf16 ? 1.9 : 1.7) + a.ksplit * out * (bf16 ? 2 : 1) * 2 / 4.0e6;
+    const double in = (double)a.N * a.Cb * (RS == 1 ? (double)a.P * a.Q : (double)a.H * a.W) * 16;
+    return std::max(t, launch + (in + out + (double)a.Cb * RS * a.Kp * 16) / 5.0e6);
+}
+
+hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t stream)
+{
+    return p.reg ? launch_igemm_reg(p.v, a, p.grid, stream) : launch_igemm(p.v, a, p.lds, p.grid, stream);
+}
+
 // Plan one launch of the implicit-GEMM kernel.
 //   input tensor:  N x Cb blocks x H x W;  result extent P x Q;  A rows Kp.
 // Candidates: 4 or 2 waves along channels, tile within half of the LDS (two
@@ -275,10 +391,52 @@ IgemmPlan plan_igemm_tile(int dtype, int N, int Cb, int H, int W, int Kp, int P,
 
 IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S,
                      int stride, int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0,
-                     int zero_fill, const IgemmGeo &geo = IgemmGeo{})
+                     int zero_fill, const IgemmGeo &geo = IgemmGeo{}, bool may_split = false)
 {
     IgemmPlan p = plan_igemm_tile(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr,
                                   oy0, ox0, zero_fill, geo);
+    // Results of few tiles: the smaller tiles, and the kernel that splits the reduction inside the
+    // workgroup, where the estimate says they are at least 5 % faster.  The plans above that
+    // were picked by measurement at N = 256 (eight waves, 128 x 256) stay, as does a first
+    // layer's, which runs on the resident-filter kernel.
+    const bool measured = p.ok && (p.v.wk * p.v.wm == 8 || (p.v.wk == 2 && p.v.wm == 2 && p.v.fk == 2 && p.v.fm == 4));
+    if (p.ok && !measured && !getenv("CONVMI_IGEMM_CAND") && igemm_stem_lds(p.v, p.a) == 0) {
+        const bool scatter = zero_fill != 0;
+        IgemmPlan best = p;
+        double best_us = 0.95 * estimate_us(p, scatter);
+        auto consider = [&](const IgemmPlan &c) {
+            if (!c.ok) return;
+            const double us = estimate_us(c, scatter);
+            if (us < best_us) {
+                best = c;
+                best_us = us;
+            }
+        };
+        for (int fk = 1; fk <= 2; ++fk)
+            for (int npl = 8; npl >= 2; npl /= 2) {
+                if ((R * S == 1) != (npl > 2)) continue;
+                consider(try_igemm(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0,
+                                   ox0, zero_fill, geo, 2, 2, fk, 2, (size_t)kMaxLds, 2, npl));
+            }
+        static const int kReg[][4] = {{1, 1, 4, 1}, {1, 1, 8, 1}, {2, 1, 8, 1}, {1, 2, 4, 1}, {2, 2, 4, 1},
+                                      {1, 1, 8, 2}, {1, 1, 8, 4}};
+        for (const auto &k : kReg) {
+            if (k[3] > 1 && (!may_split || dtype != CONV_F32)) continue;
+            consider(try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
+                             zero_fill, geo, k[0], k[1], k[2], k[3]));
+        }
+        p = best;
+    }
+    // (CONVMI_IGEMM_REG="fk,fm,waves,ksplit": one variant of the register-operand kernel wherever it
+    // exists; "0": never -- a tuning aid)
+    if (const char *env = getenv("CONVMI_IGEMM_REG")) {
+        int fk = 0, fm = 0, nw = 0, ks = 1;
+        if (sscanf(env, "%d,%d,%d,%d", &fk, &fm, &nw, &ks) >= 3 && ks >= 1 && (ks == 1 || may_split)) {
+            IgemmPlan c = try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
+                                  zero_fill, geo, fk, fm, nw, ks);
+            if (c.ok) return c;
+        }
+    }
     // One channel tile: every line of the input is staged by exactly one workgroup.  Loaded
     // non-temporally it does not displace the weights in the L2 nor settle in the last-level
     // cache on its way past.  The same with two channel tiles side by side on an XCD, as long as
@@ -293,7 +451,7 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
                       : mode == 1 ? true
                       : mode == 2 ? p.a.n_kt == 1
                                   : (p.a.n_kt == 1 || (p.a.gk == 1 && p.a.kt_per <= 2));
-    if (p.ok && want) {
+    if (p.ok && want && !p.reg) {
         IgemmVariant v = p.v;
         v.nt = 1;
         if (igemm_variant_exists(v)) p.v = v;
@@ -437,8 +595,13 @@ void plan_bwd(conv_plan *p)
     const int pad_h = p->pad_h, pad_w = p->pad_w;
     if (d.stride == 1 && pad_h <= d.R - 1 && pad_w <= d.S - 1) {
         BwdClass &b = p->bwd[0];
+        // Up to four fp32 copies of dI behind the weights where they keep to the static scratch of
+        // the entry point without a workspace: a split reduction changes nothing for its callers.
+        const size_t wt_b = ((size_t)f.Kb * d.R * d.S * f.Cp * f.vlen * es + 255) / 256 * 256;
+        const size_t copy_b = (size_t)d.N * f.Cp * d.H * d.W * sizeof(float);
         b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, d.H, d.W, d.R, d.S, 1, d.R - 1 - pad_h,
-                         d.S - 1 - pad_w, d.H, d.W, 1, 0, 0, 0);
+                         d.S - 1 - pad_w, d.H, d.W, 1, 0, 0, 0, IgemmGeo{}, wt_b + 4 * copy_b <= kScratchBytes);
+        b.part_off = wt_b;
         b.x = WtXformArgs{nullptr, nullptr, f.Cb, f.Kb, f.Cp, f.Kp, d.R, d.S, d.R, d.S,
                           1, 0, 0, d.R, d.S};
         b.ws_off = 0;
@@ -446,6 +609,7 @@ void plan_bwd(conv_plan *p)
             p->bwd_mode = 1;
             p->n_bwd = 1;
             p->bwd_ws = (size_t)f.Kb * d.R * d.S * f.Cp * f.vlen * es;
+            if (b.p.a.ksplit > 1) p->bwd_ws = wt_b + b.p.a.ksplit * copy_b;
         }
         return;
     }
@@ -1272,27 +1436,22 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
                               d.R <= 64 && d.S <= 64 && d.stride <= 64;
     p->fwd_ws = 0;
     if (tiled_domain) {
+        // Few tiles and a long reduction (small minibatch, inference): the reduction may be split
+        // over workgroups too, fp32 partial results in the workspace, summed in a fixed order.
+        // Such a layer's caller brings a workspace, whatever plan it ends up with.
+        const IgemmPlan base = plan_igemm_tile(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride,
+                                               pad_h, pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{});
+        p->fwd_takes_ws = base.ok && base.a.total <= 128 && base.a.n_stage >= 4;
         p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
-                            pad_w, f.P, f.Q, 1, 0, 0, 0);
-        // Few tiles and a long reduction (small minibatch, inference): split the reduction
-        // over more workgroups, fp32 partial results in the workspace, summed in a fixed order.
-        if (p->fwd.ok && p->fwd.a.total <= 128 && p->fwd.a.n_stage >= 4) {
-            IgemmArgs &a = p->fwd.a;
-            const int want = std::min(a.n_stage / 2, std::max(1, 512 / a.total));
-            if (want >= 2) {
-                a.st_per = ceil_div(a.n_stage, want);
-                a.ksplit = ceil_div(a.n_stage, a.st_per);
-                a.per_xcd = ceil_div(a.total * a.ksplit, 8);
-                p->fwd.grid = a.per_xcd * 8;
-                p->fwd_ws = (size_t)a.ksplit * d.N * f.Kp * f.P * f.Q * sizeof(float);
-            }
-        }
+                            pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, p->fwd_takes_ws);
+        if (p->fwd.ok && p->fwd.a.ksplit > 1)
+            p->fwd_ws = (size_t)p->fwd.a.ksplit * d.N * f.Kp * f.P * f.Q * sizeof(float);
         // A first layer (one channel block in, one reduction step, one channel tile): resident
         // workgroups that keep the filter in LDS and prefetch the next input tile.
         // (CONVMI_STEM=0 keeps one workgroup per tile: a tuning aid.)
         p->fwd.a.live_ch = f.Cb == 1 ? std::min(d.C, vlen_of(d.dtype)) : vlen_of(d.dtype);
         p->fwd_stem_lds = 0;
-        if (p->fwd.ok) {
+        if (p->fwd.ok && !p->fwd.reg) {
             const char *env = getenv("CONVMI_STEM");
             const size_t need = igemm_stem_lds(p->fwd.v, p->fwd.a);
             if (need > 0 && need <= (size_t)kMaxLds && !(env && atoi(env) == 0)) p->fwd_stem_lds = need;
@@ -1437,7 +1596,7 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     if (!h->fwd.ok) return CONV_EUNSUPPORTED;
     IgemmArgs a = h->fwd.a;
     const bool split = a.ksplit > 1;
-    if (split && !ws) return CONV_EWORKSPACE;
+    if (h->fwd_takes_ws && !ws) return CONV_EWORKSPACE;
     a.in = in;
     a.wt = wt;
     a.out = split ? ws : out;
@@ -1454,7 +1613,7 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     if (h->fwd_stem_lds && !(fused_ops && h->d.dtype == CONV_BF16))
         e = launch_igemm_stem(h->fwd.v, a, h->fwd_stem_lds, (hipStream_t)stream);
     else
-        e = launch_igemm(h->fwd.v, a, h->fwd.lds, h->fwd.grid, (hipStream_t)stream);
+        e = launch_plan(h->fwd, a, (hipStream_t)stream);
     if (e == hipSuccess && split)
         e = launch_split_reduce(h->d.dtype, static_cast<const float *>(ws), out,
                                 (size_t)h->d.N * h->info.Kp * h->info.P * h->info.Q, a.ksplit, scale,
@@ -1513,8 +1672,13 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
         IgemmArgs a = b.p.a;
         a.in = dout;
         a.wt = wt2;
-        a.out = din;
-        if (launch_igemm(b.p.v, a, b.p.lds, b.p.grid, s) != hipSuccess) return CONV_ELAUNCH;
+        void *part = a.ksplit > 1 ? static_cast<char *>(ws) + b.part_off : nullptr;
+        a.out = part ? part : din;
+        if (launch_plan(b.p, a, s) != hipSuccess) return CONV_ELAUNCH;
+        if (part && launch_split_reduce(h->d.dtype, static_cast<const float *>(part), din,
+                                        (size_t)h->d.N * h->info.Cp * h->d.H * h->d.W, a.ksplit, nullptr, nullptr,
+                                        nullptr, 0, h->d.H * h->d.W, h->info.Cb, s) != hipSuccess)
+            return CONV_ELAUNCH;
     }
     return CONV_OK;
 }
@@ -1659,7 +1823,6 @@ conv_status_t conv_upd_ws(conv_handle_t h, const void *in, const void *dout, voi
 // file-scope device array instead of a caller-provided workspace.
 // ---------------------------------------------------------------------------
 namespace {
-constexpr size_t kScratchBytes = (size_t)16 << 20;
 constexpr int kMaxDevices = 64;
 }  // namespace
 // Every GPU the library runs on holds its own copy of this array, at its own address, until
@@ -1776,6 +1939,14 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         const IgemmPlan *p = pass == 0 ? &h->fwd : &h->bwd[0].p;
         if (pass == 1 && h->bwd_mode == 0) return CONV_EUNSUPPORTED;
         if (!p->ok) return CONV_EUNSUPPORTED;
+        if (p->reg) {
+            snprintf(buf, buflen,
+                     "igemm_reg dt=%d waves=%d frags=%dx%d RS=%dx%d tiles=%d (m=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu "
+                     "steps=%d ksplit=%d launches=%d",
+                     p->v.dtype, p->v.wk, p->v.fk, p->v.fm, p->v.r, p->v.s, p->a.total, p->a.n_mt, p->a.n_kt,
+                     p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.ksplit, pass == 0 ? 1 : h->n_bwd);
+            return CONV_OK;
+        }
         snprintf(buf, buflen,
                  "igemm dt=%d waves=%dx%d frags=%dx%d npl=%d nt=%d RS=%dx%d ppt=%d TR=%d TQ=%d tiles=%d "
                  "(m=%d q=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu stages=%d ksplit=%d launches=%d",

@@ -61,14 +61,15 @@ struct IgemmArgs {
     int jstep;     // resident-filter kernel only: workgroups per XCD of its launch; a workgroup
                    // takes pixel tiles j, j + jstep, ... of its XCD (set at launch)
     // Tiles over the 8 XCDs: gk channel groups of kt_per channel tiles x 8/gk pixel groups
-    // of mq_per pixel tiles (per_xcd = kt_per * mq_per); unused when the reduction is split
+    // of mq_per pixel tiles (per_xcd = kt_per * mq_per).  gk == 1: equal runs of per_xcd tiles,
+    // channel tile fastest (the resident-filter kernel keeps to mq_per)
     int gk, kt_per, mq_per;
     // Channel tile kt of pixel tile mq starts its reduction at step
     // (kt * rot_k + mq * rot_m) mod (its number of steps) and wraps round (0, 0: all start at 0)
     int rot_k, rot_m;
     int n_stage;   // ceil(Cb / planes per stage)
-    // Reduction split (few tiles, long reduction): workgroup lin covers tile
-    // lin % total and reduction steps [sp*st_per, (sp+1)*st_per), sp = lin / total,
+    // Reduction split of the register-operand kernel (few tiles, long reduction, fp32): workgroup
+    // lin covers tile lin % total and reduction steps [sp*st_per, (sp+1)*st_per), sp = lin / total,
     // and writes an fp32 partial result, copy sp, for split_reduce to sum.
     int ksplit;    // number of splits (1: none, the result is written directly)
     int st_per;    // reduction steps per split
@@ -77,6 +78,7 @@ struct IgemmArgs {
     const float *bias;  // per output channel row, Kp entries, or null
     const void *resid;  // tensor of the output's layout and type added to the result, or null
     int relu;           // clamp at zero after the additions
+    int R, S;           // filter extent (the register-operand kernel takes it at run time)
 };
 
 // Optional geometry of a plan beyond the plain convolution's (0: as the strides say).
@@ -104,6 +106,16 @@ hipError_t ensure_dynamic_lds(const void *kernel, size_t bytes);
 hipError_t launch_igemm(const IgemmVariant &v, const IgemmArgs &a, size_t lds_bytes,
                         int grid, hipStream_t stream);
 bool igemm_variant_exists(const IgemmVariant &v);
+// Bit p is set where the variant (default input policy) exists with p staged pixels per thread.
+unsigned igemm_variant_ppts(const IgemmVariant &v);
+// The register-operand kernel for results of few tiles (any filter extent): a tile of fk*32
+// channels x fm*32 pixels of the flat pixel list, v.wk waves that split its reduction.
+// IgemmArgs::inv_P / inv_TQ hold 1 / (P*Q) and 1 / Q there, n_mt counts pixel tiles, a
+// reduction step is one tap of one pair of channel blocks.
+// (steps a wave keeps in flight; 0: no such variant)
+int igemm_reg_depth(int dtype, int fk, int fm, int nw);
+size_t igemm_reg_lds_bytes(int fk, int fm, int nw);
+hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream);
 // The resident-filter kernel for first layers (one channel block in, one reduction step, one
 // channel tile): LDS it needs for the plan, 0 if it does not serve it; and its launch (plain
 // store only: no fused operators).

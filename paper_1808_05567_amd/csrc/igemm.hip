@@ -104,6 +104,17 @@ static IgemmEntry g_igemm[] = {
     IGEMM_ENTRY_NB_NT(CONV_BF16, 2, 2, 1, 7, 4, 1, 1, 2, 2, 1),
     IGEMM_ENTRY_NB_NT(CONV_BF16, 2, 2, 1, 7, 4, 1, 1, 2, 3, 1),
     IGEMM_ENTRY_NB_NT(CONV_BF16, 4, 2, 2, 4, 8, 1, 1, 1, 2, 1),
+    // results of few tiles (small minibatches, small images): 64 x 128 and 128 x 128 tiles, picked
+    // by the planner's time estimate (see estimate_us)
+    IGEMM_ENTRY_SMALL(CONV_F32, 4, 1, 1, 1), IGEMM_ENTRY_SMALL(CONV_F32, 8, 1, 1, 1),
+    IGEMM_ENTRY_SMALL(CONV_F32, 2, 3, 3, 1), IGEMM_ENTRY_SMALL(CONV_F32, 2, 3, 3, 2),
+    IGEMM_ENTRY_SMALL(CONV_F32, 2, 3, 3, 3),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 4, 1, 1, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 8, 1, 1, 1),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 3, 3, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 2, 3, 3, 2),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 3, 3, 3),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 2, 2, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 2, 2, 2, 2),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 1, 2, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 2, 2, 1, 1),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 2, 1, 2),
 };
 
 static IgemmEntry *find_in(IgemmEntry *tab, int n, const IgemmVariant &v)
@@ -126,6 +137,24 @@ static IgemmEntry *find_igemm(const IgemmVariant &v)
 }
 
 bool igemm_variant_exists(const IgemmVariant &v) { return find_igemm(v) != nullptr; }
+
+unsigned igemm_variant_ppts(const IgemmVariant &v)
+{
+    unsigned bits = 0;
+    auto scan = [&](const IgemmEntry *tab, int n) {
+        for (int i = 0; i < n; ++i) {
+            const IgemmVariant &w = tab[i].v;
+            if (w.dtype == v.dtype && w.wk == v.wk && w.wm == v.wm && w.fk == v.fk && w.fm == v.fm &&
+                w.npl == v.npl && w.r == v.r && w.s == v.s && w.nb == v.nb && w.nt == 0)
+                bits |= 1u << w.ppt;
+        }
+    };
+    scan(g_igemm, (int)(sizeof(g_igemm) / sizeof(g_igemm[0])));
+    int n = 0;
+    const IgemmEntry *rect = igemm_rect_entries(&n);
+    scan(rect, n);
+    return bits;
+}
 
 // Sum of the fp32 partial results of a split reduction, copies ascending (a fixed
 // order: reproducible), written in the tensor's type.  One thread per 4 elements.

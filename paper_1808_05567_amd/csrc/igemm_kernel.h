@@ -163,26 +163,26 @@ __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 
     // fetched from beyond the L2 once per XCD that needs it), while its share of the weights,
     // 1/gk of them, stays resident in its L2 for the whole launch.  The planner picks gk so
     // that the bytes fetched from beyond the L2s, gk x input + (8/gk) x weights, are least.
+    // With one channel group (gk == 1) the tiles are dealt in one run, channel tile fastest, in
+    // equal shares: whole pixel tiles per XCD would give some XCDs up to n_kt tiles more than
+    // others, and one tile more than an XCD has CUs doubles the launch (252 tiles of the 160 -> 192
+    // 7x1 layer at N = 128, fp32: 33 tiles on some XCDs, 274 us; 32 at most, 157).
     const int bid = blockIdx.x;
-    int sp = 0, kt, rest;
-    if (a.ksplit > 1) {
-        // reduction split (few tiles): copy sp of tile lin % total, tiles in plain order
-        const int lin = (bid & 7) * a.per_xcd + (bid >> 3);
-        if (lin >= a.total * a.ksplit) return;
-        sp = lin / a.total;
-        const int tile = lin - sp * a.total;
-        kt = tile % a.n_kt;
-        rest = tile / a.n_kt;
+    const int x = bid & 7, j = bid >> 3;
+    int kt, rest;
+    if (a.gk == 1) {
+        const int lin = x * a.per_xcd + j;
+        if (lin >= a.total) return;
+        rest = lin / a.n_kt;
+        kt = lin - rest * a.n_kt;
     } else {
-        const int x = bid & 7, j = bid >> 3;
         const int kg = x % a.gk, mg = x / a.gk;
         const int mql = j / a.kt_per;
         kt = kg * a.kt_per + (j - mql * a.kt_per);
         rest = mg * a.mq_per + mql;
         if (kt >= a.n_kt || mql >= a.mq_per || rest >= a.n_mt * a.n_qt) return;
     }
-    const int sbeg = sp * a.st_per;                  // its first reduction step ...
-    const int nst = min(a.n_stage - sbeg, a.st_per);  // ... and how many (at least one)
+    const int nst = a.n_stage;
     const int qt = rest % a.n_qt;
     const int mt = rest / a.n_qt;
     // Workgroups that share a staged tile -- the channel tiles of one pixel tile share its input,
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 
         // (the workgroup's reduction starts at step rot and wraps round: see IgemmArgs::rot_k)
         int sr = st + rot;
         if (sr >= nst) sr -= nst;
-        const int cb0 = (sbeg + sr) * NPL;
+        const int cb0 = sr * NPL;
         unsigned char *wb = lds + (st % NB) * bufbytes;
         unsigned char *ib = wb + WBYTES;
         if (l < NPLG * PPT) {
@@ -471,31 +471,6 @@ __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 
     // offset; the per-lane offset is the pixel's.
     const size_t oplane = (size_t)a.OH * a.OW * 16;
     const size_t out_bytes = (size_t)a.N * Kb_out * oplane;
-    if (a.ksplit > 1) {
-        // partial result of this reduction split: fp32, the output tensor's element
-        // order (so for bf16 every byte offset doubles), copy sp
-        constexpr unsigned SC = (V == 8) ? 2u : 1u;
-        const rsrc_t rp = make_rsrc(static_cast<char *>(a.out) + (size_t)sp * out_bytes * SC, 0,
-                                    out_bytes * SC);
-#pragma unroll
-        for (int i = 0; i < FK; ++i) {
-#pragma unroll
-            for (int vq = 0; vq < 4; ++vq) {
-                const int krow0 = k0 + (wave_k * FK + i) * 32 + vq * 8;
-                if (krow0 >= a.Kp) continue;
-                const unsigned skip = (unsigned)(krow0 / V) * (unsigned)oplane;
-                const unsigned lane_off = (V == 4) ? (unsigned)h * (unsigned)oplane : (unsigned)h * 8u;
-#pragma unroll
-                for (int j = 0; j < FM; ++j) {
-                    const bool live = obyte[j] != kOutOfRange && krow0 + 4 * h < a.Kp;
-                    Elem<CONV_F32>::store4(rp, live ? (obyte[j] + lane_off) * SC : kOutOfRange, skip * SC,
-                                           acc[i][j][4 * vq + 0], acc[i][j][4 * vq + 1],
-                                           acc[i][j][4 * vq + 2], acc[i][j][4 * vq + 3]);
-                }
-            }
-        }
-        return;
-    }
     const rsrc_t ro = make_rsrc(a.out, 0, out_bytes);
     if (a.scale != nullptr || a.bias != nullptr || a.resid != nullptr || a.relu != 0) {
         // L() of Algorithm 4 on the finished accumulators: scale, bias, residual, ReLU (forward
@@ -646,6 +621,9 @@ struct IgemmEntry {
     IGEMM_ENTRY_NB_NT(DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, 0)
 #define IGEMM_ENTRY(DT, WK, WM, FK, FM, NPL, R, S, PPT) \
     IGEMM_ENTRY_NB(DT, WK, WM, FK, FM, NPL, R, S, PPT, 2)
+// 64 x 128 and 128 x 128 tiles, four waves
+#define IGEMM_ENTRY_SMALL(DT, NPL, R, S, PPT) \
+    IGEMM_ENTRY(DT, 2, 2, 1, 2, NPL, R, S, PPT), IGEMM_ENTRY(DT, 2, 2, 2, 2, NPL, R, S, PPT)
 
 
 // Entries of the rectangular-filter translation unit.

@@ -57,6 +57,14 @@ static IgemmEntry g_rect[] = {
     IGEMM_ENTRY(CONV_BF16, 1, 4, 1, 7, 1, 3, 3, 16),
     IGEMM_ENTRY(CONV_F32, 1, 4, 1, 7, 2, 2, 2, 4),
     IGEMM_ENTRY(CONV_F32, 1, 4, 1, 7, 2, 2, 2, 5),
+    // results of few tiles, as in igemm.hip
+    IGEMM_ENTRY_SMALL(CONV_F32, 2, 1, 7, 1), IGEMM_ENTRY_SMALL(CONV_F32, 2, 7, 1, 1),
+    IGEMM_ENTRY_SMALL(CONV_F32, 2, 7, 1, 2), IGEMM_ENTRY_SMALL(CONV_F32, 2, 1, 3, 1),
+    IGEMM_ENTRY_SMALL(CONV_F32, 2, 3, 1, 1),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 1, 7, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 2, 7, 1, 1),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 7, 1, 2), IGEMM_ENTRY_SMALL(CONV_BF16, 2, 1, 3, 1),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 3, 1, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 2, 5, 5, 1),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 2, 5, 5, 2),
 };
 
 IgemmEntry *igemm_rect_entries(int *count)

@@ -1,0 +1,279 @@
+// Implicit-GEMM direct convolution for results of few tiles: small minibatches, small images.
+//
+// The staged kernel (igemm_kernel.h) wants tiles of 64 x 512 or 128 x 224 results and walks the
+// whole reduction of a tile in one workgroup; with a few thousand result pixels that is a
+// handful of workgroups on 256 CUs, each a serial chain of up to 64 steps.  Here the chip is
+// filled from the other side: a workgroup owns a small tile (FK*32 channels x FM*32 pixels) and
+// its waves split the REDUCTION of that tile between them, each with the whole tile in
+// its accumulators.  The waves' sums meet in LDS at the end, added in wave order (one fixed
+// order), so one launch does it and no partial results go through memory.
+//
+// Operands go from memory straight into the registers the MFMAs take them from (a pixel's
+// channel block and a weight row's channel block are 16 bytes each, consecutive lanes take
+// consecutive pixels or rows): no LDS staging, no barrier in the main loop, so a wave only
+// waits for its own loads, D steps after they were issued.  The taps of one channel-block
+// pair are consecutive steps of a wave, so the pixels that neighbouring taps share come out of
+// the CU's vector L1.
+//
+// What bounds it: the bytes that go through the vector L1, 64 per clock and CU; per step a
+// wave loads FK + FM operands of 1 KiB and issues FK * FM MFMAs (bf16: 32 clocks each, fp32:
+// 4 x 64 clocks), so a 2 x 2 tile can keep a bf16 matrix core half busy and an fp32 one fully.
+// Larger results are better off sharing operands through LDS (see plan_igemm).
+#include <algorithm>
+
+#include "igemm_kernel.h"
+
+namespace convmi {
+
+// FK x FM accumulator tiles per wave, NW waves that split the reduction, D steps in flight.
+template <int DT, int FK, int FM, int NW, int D>
+__global__ __launch_bounds__(NW * 64, 2) void igemm_reg_kernel(const IgemmArgs a)
+{
+    using E_ = Elem<DT>;
+    constexpr int V = E_::V;
+    constexpr int TK = FK * 32, TM = FM * 32, NF = FK * FM, NT = NW * 64;
+    // fragments summed per round through LDS: as many as give every thread a 4-channel chunk
+    constexpr int G = (NT / 256 < NF) ? NT / 256 : NF;
+    static_assert(NF % G == 0, "whole rounds");
+
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    f32x4 *const xch = reinterpret_cast<f32x4 *>(lds);  // [G][NW][256] chunks of 4 channels
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5;
+    const int l32 = lane & 31;
+
+    // Workgroup -> tile: dealt over the XCDs as in igemm_kernel.
+    const int bid = blockIdx.x;
+    const int x = bid & 7, jx = bid >> 3;
+    int sp = 0, kt, mt;
+    if (a.gk == 1) {
+        int lin = x * a.per_xcd + jx;
+        if (lin >= a.total * a.ksplit) return;
+        sp = lin / a.total;  // (copy sp of a reduction split over workgroups)
+        lin -= sp * a.total;
+        mt = lin / a.n_kt;
+        kt = lin - mt * a.n_kt;
+    } else {
+        const int kg = x % a.gk, mg = x / a.gk;
+        const int mql = jx / a.kt_per;
+        kt = kg * a.kt_per + (jx - mql * a.kt_per);
+        mt = mg * a.mq_per + mql;
+        if (kt >= a.n_kt || mql >= a.mq_per || mt >= a.n_mt) return;
+    }
+    const int k0 = kt * TK, m0 = mt * TM;
+    const int PQ = a.P * a.Q, npix = a.N * PQ, HW = a.H * a.W, RS = a.R * a.S;
+    const float inv_PQ = a.inv_P, inv_Q = a.inv_TQ;  // (1 / (P*Q), 1 / Q in this kernel's plans)
+
+    // Operand addresses.  The input's buffer starts pad_h rows and pad_w pixels before the
+    // tensor, so that a lane's offset is its pixel's and the tap moves the scalar offset
+    // only; taps outside the image never load (their lanes carry kOutOfRange).
+    const long long shift = ((long long)a.pad_h * a.W + a.pad_w) * 16;
+    const rsrc_t rsrc_in = make_rsrc(static_cast<const char *>(a.in) - shift, 0,
+                                     (size_t)((long long)a.N * a.Cb * HW * 16 + shift));
+    const rsrc_t rsrc_wt = make_rsrc(a.wt, 0, (size_t)a.Cb * RS * a.Kp * 16);
+    unsigned b_off[FM], a_off[FK];
+    int ih0[FM], iw0[FM];
+#pragma unroll
+    for (int j = 0; j < FM; ++j) {
+        const int m = m0 + j * 32 + l32;
+        const int n = fast_div(m, inv_PQ);
+        const int rem = m - mul24(n, PQ);
+        const int oj = fast_div(rem, inv_Q);
+        const int oi = rem - mul24(oj, a.Q);
+        const int y = mul24(oj, a.stride), x = mul24(oi, a.cstride);
+        b_off[j] = (unsigned)(mul24(mul24(mul24(n, a.Cb) + h, a.H) + y, a.W) + x) * 16u;
+        // (a pixel beyond the last one: no row is inside the image)
+        ih0[j] = m < npix ? y - a.pad_h : 0x40000000;
+        iw0[j] = x - a.pad_w;
+    }
+#pragma unroll
+    for (int i = 0; i < FK; ++i) {
+        const int k = k0 + i * 32 + l32;
+        a_off[i] = k < a.Kp ? (unsigned)(mul24(h, RS * a.Kp) + k) * 16u : kOutOfRange;
+    }
+
+    // This wave's share of the reduction: steps [u0, u1), step u = (channel-block pair, r, s);
+    // the lane halves take the two blocks of the pair.
+    const int steps = ((a.Cb + 1) >> 1) * RS;
+    const int sbeg = sp * a.st_per;
+    const int nst = min(steps - sbeg, a.st_per);
+    const int per = (nst + NW - 1) / NW;
+    const int u0 = sbeg + min(wave * per, nst), u1 = sbeg + min(wave * per + per, nst);
+    int cp = u0 / RS;
+    int tap = u0 - cp * RS;
+    int r = tap / a.S;
+    int s = tap - r * a.S;
+    int u = u0;  // next step to load
+
+    u32x4 A[D][FK], B[D][FM];
+    auto load = [&](u32x4(&av)[FK], u32x4(&bv)[FM]) {
+        // (past the wave's share, and the upper half of an odd last pair: zeros on both sides)
+        const bool live = u < u1 && 2 * cp + h < a.Cb;
+        const unsigned sa = (unsigned)(2 * cp * RS + r * a.S + s) * (unsigned)a.Kp * 16u;
+        const unsigned sb = (unsigned)(2 * cp * HW + r * a.W + s) * 16u;
+#pragma unroll
+        for (int j = 0; j < FM; ++j) {
+            const bool in = live && (unsigned)(ih0[j] + r) < (unsigned)a.H && (unsigned)(iw0[j] + s) < (unsigned)a.W;
+            bv[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_in, in ? b_off[j] : kOutOfRange, u < u1 ? sb : 0u, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < FK; ++i)
+            av[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_wt, live ? a_off[i] : kOutOfRange, u < u1 ? sa : 0u, 0);
+        ++u;
+        if (++s == a.S) {
+            s = 0;
+            if (++r == a.R) {
+                r = 0;
+                ++cp;
+            }
+        }
+    };
+
+    f32x16 acc[FK][FM];
+#pragma unroll
+    for (int i = 0; i < FK; ++i)
+#pragma unroll
+        for (int j = 0; j < FM; ++j)
+#pragma unroll
+            for (int t = 0; t < 16; ++t) acc[i][j][t] = 0.0f;
+
+    if (u0 < u1) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(A[d], B[d]);
+        // (whole groups of D steps: what lies past u1 arrives as zeros)
+        for (int g = u0; g < u1; g += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+#pragma unroll
+                for (int i = 0; i < FK; ++i)
+#pragma unroll
+                    for (int j = 0; j < FM; ++j) E_::mma(A[d][i], B[d][j], acc[i][j]);
+                load(A[d], B[d]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+
+    // The waves' sums, G fragments per round: every wave writes its own, then each thread adds
+    // one chunk of 4 consecutive channels of one pixel over the waves, in wave order.
+    const size_t oplane = (size_t)a.OH * a.OW * 16;
+    const size_t out_bytes = (size_t)a.N * a.out_kb * oplane;
+    constexpr unsigned SC = (V == 8) ? 2u : 1u;  // a partial result is fp32 whatever the type
+    const rsrc_t ro = a.ksplit > 1 ? make_rsrc(static_cast<char *>(a.out) + (size_t)sp * out_bytes * SC, 0, out_bytes * SC)
+                                   : make_rsrc(a.out, 0, out_bytes);
+#pragma unroll
+    for (int f0 = 0; f0 < NF; f0 += G) {
+        if (f0 > 0) __syncthreads();
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const f32x16 &c = acc[(f0 + g) / FM][(f0 + g) % FM];
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                const f32x4 v = {c[4 * vq], c[4 * vq + 1], c[4 * vq + 2], c[4 * vq + 3]};
+                xch[(g * NW + wave) * 256 + vq * 64 + lane] = v;
+            }
+        }
+        __syncthreads();
+        const int g = tid >> 8, ch = tid & 255;  // (wave-uniform: 4 waves per fragment)
+        if (g < G) {
+            f32x4 v = xch[(g * NW) * 256 + ch];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += xch[(g * NW + w) * 256 + ch];
+            const int f = f0 + g, fi = f / FM, fj = f - fi * FM;
+            const int krow = k0 + fi * 32 + (ch >> 6) * 8 + 4 * h;
+            const int m = m0 + fj * 32 + l32;
+            const int n = fast_div(m, inv_PQ);
+            const int rem = m - mul24(n, PQ);
+            const int oj = fast_div(rem, inv_Q);
+            const int oi = rem - mul24(oj, a.Q);
+            bool ok = m < npix && krow < a.Kp;
+            int oy = mul24(oj, a.ostr) + a.oy0, ox = mul24(oi, a.ostr_x) + a.ox0, kb = krow / V;
+            if (a.shuffle) {  // the channel block is a position of the ostr x ostr_x cell
+                const int cy = kb / a.ostr_x;
+                oy += cy;
+                ox += kb - cy * a.ostr_x;
+                kb = 0;
+                ok = ok && oy < a.OH && ox < a.OW;
+            }
+            const unsigned pos = (unsigned)(mul24(mul24(mul24(n, a.out_kb) + kb, a.OH) + oy, a.OW) + ox) * 16u +
+                                 (V == 8 ? (unsigned)(krow & 4) * 2u : 0u);
+            if (a.ksplit > 1) {
+                Elem<CONV_F32>::store4(ro, ok ? pos * SC : kOutOfRange, 0, v[0], v[1], v[2], v[3]);
+            } else {
+                const unsigned off = ok ? pos : kOutOfRange;
+                float o[4] = {v[0], v[1], v[2], v[3]};
+                if (a.scale != nullptr || a.bias != nullptr || a.resid != nullptr || a.relu != 0) {
+                    float b4[4] = {0.f, 0.f, 0.f, 0.f}, s4[4] = {1.f, 1.f, 1.f, 1.f}, r4[4] = {0.f, 0.f, 0.f, 0.f};
+                    if (a.bias && krow < a.Kp) {
+                        const f32x4 b = *reinterpret_cast<const f32x4 *>(a.bias + krow);
+                        b4[0] = b[0]; b4[1] = b[1]; b4[2] = b[2]; b4[3] = b[3];
+                    }
+                    if (a.scale && krow < a.Kp) {
+                        const f32x4 q = *reinterpret_cast<const f32x4 *>(a.scale + krow);
+                        s4[0] = q[0]; s4[1] = q[1]; s4[2] = q[2]; s4[3] = q[3];
+                    }
+                    if (a.resid) E_::load4(make_rsrc(a.resid, 0, out_bytes), off, 0, r4);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        o[t] = o[t] * s4[t] + r4[t] + b4[t];
+                        if (a.relu) o[t] = fmaxf(o[t], 0.0f);
+                    }
+                }
+                E_::store4(ro, off, 0, o[0], o[1], o[2], o[3]);
+                if (a.zero_fill) {
+                    for (int dy = 0; dy < a.ostr; ++dy)
+                        for (int dx = 0; dx < a.ostr_x; ++dx) {
+                            if ((dy | dx) == 0) continue;
+                            const bool in = ok && oy + dy < a.OH && ox + dx < a.OW;
+                            E_::store4(ro, in ? off + (unsigned)(dy * a.OW + dx) * 16u : kOutOfRange, 0, 0.f, 0.f,
+                                       0.f, 0.f);
+                        }
+                }
+            }
+        }
+    }
+}
+
+#define REG_ENTRY(DT, FK, FM, NW, D) {DT, FK, FM, NW, D, igemm_reg_kernel<DT, FK, FM, NW, D>}
+static const struct RegEntry {
+    int dtype, fk, fm, nw, depth;
+    igemm_fn_t fn;
+} g_reg[] = {
+    REG_ENTRY(CONV_F32, 1, 1, 4, 6),  REG_ENTRY(CONV_F32, 1, 1, 8, 6),  REG_ENTRY(CONV_F32, 2, 1, 8, 4),
+    REG_ENTRY(CONV_F32, 1, 2, 4, 4),  REG_ENTRY(CONV_F32, 2, 2, 4, 3),
+    REG_ENTRY(CONV_BF16, 1, 1, 4, 8), REG_ENTRY(CONV_BF16, 1, 1, 8, 8), REG_ENTRY(CONV_BF16, 2, 1, 8, 5),
+    REG_ENTRY(CONV_BF16, 2, 2, 4, 4),
+};
+// (dropped after measuring 42 layers at N = 1 ... 256 under every variant: 16 waves, 2 x 4 fragments,
+// 1 x 2 and 2 x 2 fragments on eight waves: never more than 2 % ahead of the ones above)
+
+int igemm_reg_depth(int dtype, int fk, int fm, int nw)
+{
+    for (const RegEntry &e : g_reg)
+        if (e.dtype == dtype && e.fk == fk && e.fm == fm && e.nw == nw) return e.depth;
+    return 0;
+}
+
+size_t igemm_reg_lds_bytes(int fk, int fm, int nw)
+{
+    const int per_round = std::min(nw / 4, fk * fm);
+    return (size_t)per_round * nw * 4096;
+}
+
+hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream)
+{
+    for (const RegEntry &e : g_reg) {
+        if (e.dtype != v.dtype || e.fk != v.fk || e.fm != v.fm || e.nw != v.wk) continue;
+        const size_t lds = igemm_reg_lds_bytes(e.fk, e.fm, e.nw);
+        if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(e.fn), lds); err != hipSuccess)
+            return err;
+        hipLaunchKernelGGL(e.fn, dim3(grid), dim3(e.nw * 64), lds, stream, a);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidDeviceFunction;
+}
+
+}  // namespace convmi
