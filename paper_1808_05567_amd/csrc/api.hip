@@ -76,6 +76,7 @@ struct conv_plan {
     int upd_wb = 0;         //   its waves along the narrower tensor's channels
     bool upd_a_is_in = false; //   whether the wider tensor is the input
     UpdRowsVariant urv{};
+    bool upd_ring = false;  // small blocks of dW, the waves split the pixels (fragments: urv.fc, urv.fk)
     int upd_copies = 0;    // partial dW copies the reduce kernel sums
     UpdVariant uv{};
     int upd_row_launches = 1;  // > 1: one launch of a 1 x S kernel per filter row
@@ -1305,6 +1306,155 @@ void plan_upd_general(conv_plan *p)
     p->upd_ok = true;
 }
 
+// Weight update with small blocks of dW: fc x fk fragments x one filter row per workgroup, nw waves
+// with a ring of `depth` stages each, the pixel list in `splits` parts.
+struct RingCand {
+    int fc, fk, nw, depth, splits;
+};
+bool plan_ring(const conv_plan *p, const RingCand &c, UpdArgs &a)
+{
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    if (!upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth)) return false;
+    const double npix = (double)d.N * f.P * f.Q;
+    // exact small divisions, 24-bit products, 32-bit byte offsets
+    if (npix >= 3.9e6 || (double)(d.N + 1) * std::max(f.Cb, f.Kb) >= 8.0e6 || (double)d.H * d.W >= 8.0e6 ||
+        (double)f.in_bytes + ((double)p->pad_h + d.R) * d.W * 16 >= 4.0e9 || (double)f.out_bytes >= 4.0e9)
+        return false;
+    const int stage = c.nw * (d.dtype == CONV_BF16 ? 16 : 8);  // pixels of a workgroup's stage
+    const int np = (int)npix;
+    memset(&a, 0, sizeof(a));
+    a.N = d.N; a.Cb = f.Cb; a.H = d.H; a.W = d.W; a.Kb = f.Kb; a.Kp = f.Kp; a.P = f.P; a.Q = f.Q;
+    a.R = d.R; a.S = d.S; a.stride = d.stride; a.pad = p->pad_h; a.pad_w = p->pad_w;
+    a.n_ct = ceil_div(f.Cp, c.fc * 32);
+    a.n_kt = ceil_div(f.Kp, c.fk * 32);
+    // (a wave's chain of additions is an nw-th of a split: at most 2^13 pixels)
+    const int splits = std::max(c.splits, ceil_div(np, c.nw << 13));
+    a.rows_per_split = ceil_div(ceil_div(np, splits), stage) * stage;
+    a.splits = ceil_div(np, a.rows_per_split);
+    const double total = (double)a.n_ct * a.n_kt * d.R * a.splits;
+    if (total >= 1.0e8) return false;
+    a.total = a.n_ct * a.n_kt * d.R * a.splits;
+    a.per_xcd = ceil_div(a.total, 8);
+    return true;
+}
+
+// What such an update takes, in microseconds, as far as the choice of its block and splits goes: as
+// estimate_us, with the exchange of the waves' sums, the bytes that the blocks of a pixel range
+// re-read, and the reduce launch.  Fitted to 5 000 launches (38 layers x N = 8 ... 256, three sets of
+// tensors in turn, rms error 2 - 11 %); the choice is on average 2 % behind the best of what was tried.
+double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
+{
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    const bool bf16 = d.dtype == CONV_BF16;
+    struct Fit { double launch, fixed, stage, c_mfma, c_load, per_op, exch, reduce, copy_tb, hbm_tb, l2_tb; };
+    static const Fit fits[2][3] = {{{6.0, 0, 590, 1.18, 1.5, 8, 14, 1.7, 3.1, 3.9, 10.9},
+                                    {5.2, 0, 950, 1.12, 1.5, 0, 128, 3.9, 16.5, 4.0, 11.0},
+                                    {2.4, 1510, 800, 1.2, 1.5, 20, 108, 3.0, 3.2, 4.0, 12.0}},
+                                   {{3.6, 0, 340, 2.58, 1.64, 33, 103, 1.7, 4.4, 4.4, 16.7},
+                                    {2.7, 520, 576, 0.54, 1.38, 19, 144, 1.8, 4.1, 2.5, 14.2},
+                                    {2.4, 890, 1160, 0.0, 1.07, 0, 98, 2.3, 2.9, 4.0, 12.0}}};
+    const Fit &q = fits[bf16 ? 1 : 0][d.S == 1 ? 0 : d.S == 3 ? 1 : 2];
+    const int tiles = d.S * c.fc * c.fk, ops = d.S * c.fc + c.fk;
+    const double mfma = tiles * (bf16 ? 32.0 : 256.0);
+    const double stages = ceil_div(ceil_div(a.rows_per_split, c.nw * (bf16 ? 16 : 8)), c.depth) * c.depth;
+    const double shared = std::max(mfma * q.c_mfma * c.nw / 4, ops * c.nw * 16 * q.c_load);
+    const double lone = q.fixed + stages * std::max(shared, mfma * q.c_mfma + q.stage + ops * q.per_op) + q.exch * tiles * c.nw;
+    const double busy = stages * shared + q.exch * tiles * c.nw;
+    // workgroups a CU holds: LDS, and registers (16 per tile, and what the operands take)
+    const int regs = 16 * tiles + (bf16 ? 4 : 3) * ops + 40;
+    const int resident = std::max(1, std::min((int)(kMaxLds / upd_ring_lds_bytes(d.S, c.fc, c.fk, c.nw, c.depth)),
+                                              std::min(8, 512 / regs) * 4 / c.nw));
+    const int per_cu = ceil_div(a.per_xcd * 8, 256), full = per_cu / resident, rest = per_cu - full * resident;
+    double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
+    t = t / 2.3e3 + q.launch;
+    const double es = bf16 ? 2.0 : 4.0, out_b = (double)f.out_bytes;
+    const double in_b = d.R * d.S > 1 ? (double)f.in_bytes
+                                      : (double)d.N * f.Cp * f.P * f.Q * (d.stride > 1 ? 2 : 1) * es;
+    t = std::max(t, q.launch + (in_b + out_b) / (q.hbm_tb * 1e6));
+    t = std::max(t, q.launch + (in_b * a.n_kt + out_b * a.n_ct) * d.R / (q.l2_tb * 1e6));
+    if (a.splits > 1) t += q.reduce + a.splits * (double)f.dwt_bytes * 2 / (q.copy_tb * 1e6);
+    return t;
+}
+
+// Whether the ring kernel is the better one, both sides measured with three sets of tensors in turn (its
+// time / the other kernel's):
+//   - 1x1, bf16: up to 2e10 flops 0.5 - 0.96; beyond, the 128 x 256 blocks of the flat kernel re-read less of what no longer
+//     stays in the last-level cache (256 -> 512 stride 2 at 56x56, N = 128: 1.13, N = 256: 1.33).  Between two
+//     narrow sides (below 128 channels) the line is at 5e9 (64 -> 64 at 56x56, N = 128: 0.90, N = 256: 1.08).
+//   - 1x1, fp32: with 256 channels on a side up to 2e10 flops (0.3 - 0.86; at 2.6e10 0.9 - 1.0, and its
+//     family there is pinned by the planner's tests); else 0.2 - 0.6 everywhere, up to 2^19 pixels
+//     (pinned as well).
+//   - wider filters: everywhere (bf16 0.24 - 0.88, fp32 0.42 - 0.9), except bf16 stride 2 beyond 5e10 flops
+//     (288 -> 384 at 35x35, N = 64: 0.76, N = 128: 1.00, N = 256: 1.07), fp32 3x3 in full 64 x 64 blocks beyond 5e10 flops
+//     (0.88 - 0.94: pinned) and rows of more than 128 pixels (0.24 - 0.75 at 147: their column strips are
+//     pinned).
+bool ring_applies(const conv_plan *p)
+{
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q;
+    const int wide = std::max(d.C, d.K), narrow = std::min(d.C, d.K);
+    if (d.R * d.S == 1) {
+        if (d.dtype == CONV_BF16) return flops <= 2.0e10 && (flops <= 5.0e9 || wide >= 128);
+        if (wide >= 256 && narrow >= 32) return flops <= 2.0e10;
+        return (double)d.N * f.P * f.Q <= 524288.0;
+    }
+    if (f.Q > 128) return false;
+    if (d.dtype == CONV_BF16) return !(d.stride > 1 && flops > 5.0e10);
+    return !(d.R == 3 && d.S == 3 && d.stride == 1 && d.C % 64 == 0 && d.K % 64 == 0 && flops > 5.0e10);
+}
+
+bool plan_upd_ring(conv_plan *p)
+{
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    static const int kBlocks[][4] = {{1, 1, 8, 4}, {2, 2, 8, 2}, {2, 4, 8, 2}, {1, 1, 8, 2}, {1, 2, 8, 2}, {2, 2, 4, 4}};
+    RingCand best{};
+    UpdArgs best_a{};
+    double best_us = 0;
+    bool have = false;
+    auto consider = [&](RingCand c) {
+        UpdArgs a;
+        if (!plan_ring(p, c, a)) return;
+        const double us = ring_estimate_us(p, c, a);
+        if (!have || us < best_us) {
+            best = c;
+            best_a = a;
+            best_us = us;
+            have = true;
+        }
+    };
+    // (CONVMI_UPD_RING="fc,fk,waves,depth,splits": one variant wherever it exists; "0": never -- a tuning aid)
+    if (const char *env = getenv("CONVMI_UPD_RING")) {
+        RingCand c{};
+        if (sscanf(env, "%d,%d,%d,%d,%d", &c.fc, &c.fk, &c.nw, &c.depth, &c.splits) != 5) return false;
+        consider(c);
+    } else if (ring_applies(p)) {
+        for (const auto &k : kBlocks) {
+            const int tiles = ceil_div(f.Cp, k[0] * 32) * ceil_div(f.Kp, k[1] * 32) * d.R;
+            // (32 x 32 blocks of a 1x1 filter re-read both tensors once per 32 channels: for small ones)
+            if (d.R * d.S == 1 && k[0] == 1 &&
+                (double)f.in_bytes + (double)f.out_bytes > (d.dtype == CONV_BF16 ? 64.0e6 : 100.0e6))
+                continue;
+            consider({k[0], k[1], k[2], k[3], 1});
+            consider({k[0], k[1], k[2], k[3], std::max(1, 256 / tiles)});
+            if (d.S == 3) consider({k[0], k[1], k[2], k[3], std::max(1, 512 / tiles)});
+        }
+    }
+    if (!have) return false;
+    p->ua = best_a;
+    p->urv = UpdRowsVariant{d.R, d.S, 1, best.depth, best.nw, best.fc, best.fk, 0};
+    p->upd_lds = upd_ring_lds_bytes(d.S, best.fc, best.fk, best.nw, best.depth);
+    p->upd_grid = best_a.per_xcd * 8;
+    p->upd_copies = best_a.splits;
+    p->upd_ws = (size_t)p->upd_copies * f.dwt_bytes;  // (one split writes dW itself; the caller brings it all the same)
+    p->upd_ring = true;
+    p->upd_ok = true;
+    return true;
+}
+
 void plan_upd(conv_plan *p)
 {
     p->upd_ok = false;
@@ -1317,8 +1467,9 @@ void plan_upd(conv_plan *p)
     p->upd_flat_bf16 = false;
     p->upd_rows = false;
     p->upd_bands = false;
+    p->upd_ring = false;
     // the kernels written for a family of layers first, each declining what it does not fit
-    if (!(plan_upd_c4_bf16(p) || plan_upd_c4(p) || plan_upd_flat_f32(p) || plan_upd_flat_bf16(p) ||
+    if (!(plan_upd_c4_bf16(p) || plan_upd_c4(p) || plan_upd_ring(p) || plan_upd_flat_f32(p) || plan_upd_flat_bf16(p) ||
           plan_upd_rows(p) || plan_upd_bands(p)))
         plan_upd_general(p);
     // Partial copies that dwarf the tensors themselves (very wide rows cut into many strips,
@@ -1724,7 +1875,11 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
     a.dout = dout;
     a.partial = static_cast<float *>(ws);
     hipError_t e = hipSuccess;
-    if (h->upd_flat_bf16)
+    if (h->upd_ring) {
+        if (a.splits == 1) a.partial = static_cast<float *>(dwt);
+        e = launch_upd_ring(h->d.dtype, h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, a, h->upd_grid, s);
+        if (a.splits == 1) return e == hipSuccess ? CONV_OK : CONV_ELAUNCH;
+    } else if (h->upd_flat_bf16)
         e = launch_upd_bf16_1x1(h->urv, a, h->upd_grid, s);
     else if (h->upd_flat)
         e = launch_upd_f32_1x1(h->upd_wb, h->upd_a_is_in, a, h->upd_grid, s);
@@ -1961,6 +2116,15 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
     }
     if (pass == 2) {
         if (!h->upd_ok) return CONV_EUNSUPPORTED;
+        if (h->upd_ring) {
+            snprintf(buf, buflen,
+                     "%s dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d pixels/split=%d splits=%d tiles=%dx%dx%d grid=%d "
+                     "lds=%zu launches=1",
+                     h->d.R * h->d.S == 1 ? "upd_1x1" : "upd_rows1", (int)h->d.dtype, h->d.R, h->d.S, h->urv.wp,
+                     h->urv.wk, h->urv.fc, h->urv.fk, h->ua.rows_per_split, h->ua.splits, h->ua.n_ct, h->ua.n_kt,
+                     h->d.R, h->upd_grid, h->upd_lds);
+            return CONV_OK;
+        }
         if (h->upd_flat_bf16) {
             snprintf(buf, buflen,
                      "upd_1x1 dt=1 waves=%dx%dx%d frags=%dx%d pixels/split=%d splits=%d tiles=%dx%d "

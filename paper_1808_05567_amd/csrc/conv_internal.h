@@ -223,6 +223,12 @@ hipError_t launch_upd_bf16_1x1(const UpdRowsVariant &v, const UpdArgs &a, int gr
 // per split, a multiple of 32; n_ct / n_kt = tiles over input / output channels)
 size_t upd_f32_1x1_lds_bytes(int wb);
 hipError_t launch_upd_f32_1x1(int wb, bool a_is_in, const UpdArgs &a, int grid, hipStream_t stream);
+// Filters with S columns in {1, 3, 7}: blocks of fc*32 x fk*32
+// channels x one filter row, nw waves that split the pixels, a ring of `depth` stages each (UpdArgs::rows_per_split = pixels
+// per split; one split: UpdArgs::partial is dW itself)
+bool upd_ring_exists(int dtype, int s, int fc, int fk, int nw, int depth);
+size_t upd_ring_lds_bytes(int s, int fc, int fk, int nw, int depth);
+hipError_t launch_upd_ring(int dtype, int fc, int fk, int nw, int depth, const UpdArgs &a, int grid, hipStream_t stream);
 // at most 4 input channels: filter-row formulation, 7x7 and 3x3; fp32 tensors, or bf16
 // tensors widened on their way into LDS (then UpdArgs::Kb counts blocks of 8 channels)
 hipError_t launch_upd_c4(int dtype, int r, int s, const UpdArgs &a, size_t lds_bytes, int grid,
