@@ -38,6 +38,7 @@ struct IgemmPlan {
     size_t lds = 0;
     int grid = 0;
     bool reg = false;  // the register-operand kernel (v.wk waves split the reduction of a tile)
+    bool fallback = false;  // ... because no staged tile fits
 };
 
 struct BwdClass {  // one stride-parity class of the generic backward pass
@@ -64,6 +65,9 @@ struct conv_plan {
     int n_bwd = 0;
     BwdClass bwd[16];
     size_t bwd_ws = 0;
+    // (passes that would run untiled but for a kernel that takes a workspace: a caller that
+    // brings none still gets the untiled kernel)
+    bool bwd_ws_optional = false, upd_ws_optional = false;
     // weight update
     bool upd_ok = false;
     bool upd_c4 = false;   // few-channel formulation (one input channel block)
@@ -401,10 +405,10 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
     // were picked by measurement at N = 256 (eight waves, 128 x 256) stay, as does a first
     // layer's, which runs on the resident-filter kernel.
     const bool measured = p.ok && (p.v.wk * p.v.wm == 8 || (p.v.wk == 2 && p.v.wm == 2 && p.v.fk == 2 && p.v.fm == 4));
-    if (p.ok && !measured && !getenv("CONVMI_IGEMM_CAND") && igemm_stem_lds(p.v, p.a) == 0) {
+    if (p.ok ? !measured && !getenv("CONVMI_IGEMM_CAND") && igemm_stem_lds(p.v, p.a) == 0 : geo.fallback) {
         const bool scatter = zero_fill != 0;
         IgemmPlan best = p;
-        double best_us = 0.95 * estimate_us(p, scatter);
+        double best_us = p.ok ? 0.95 * estimate_us(p, scatter) : 1e30;
         auto consider = [&](const IgemmPlan &c) {
             if (!c.ok) return;
             const double us = estimate_us(c, scatter);
@@ -426,6 +430,7 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
             consider(try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                              zero_fill, geo, k[0], k[1], k[2], k[3]));
         }
+        best.fallback = !p.ok;
         p = best;
     }
     // (CONVMI_IGEMM_REG="fk,fm,waves,ksplit": one variant of the register-operand kernel wherever it
@@ -594,6 +599,10 @@ void plan_bwd(conv_plan *p)
     p->n_bwd = 0;
     p->bwd_ws = 0;
     const int pad_h = p->pad_h, pad_w = p->pad_w;
+    // (filters, and channel-block counts, that no staged kernel is built for: 10 to 100 times the
+    // untiled loop nests' rate -- 140 -> 188 channels, 3x3 stride 2 at 26x25, N = 64, fp32: 2324 -> 104 us)
+    IgemmGeo any_filter;
+    any_filter.fallback = true;
     if (d.stride == 1 && pad_h <= d.R - 1 && pad_w <= d.S - 1) {
         BwdClass &b = p->bwd[0];
         // Up to four fp32 copies of dI behind the weights where they keep to the static scratch of
@@ -601,7 +610,7 @@ void plan_bwd(conv_plan *p)
         const size_t wt_b = ((size_t)f.Kb * d.R * d.S * f.Cp * f.vlen * es + 255) / 256 * 256;
         const size_t copy_b = (size_t)d.N * f.Cp * d.H * d.W * sizeof(float);
         b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, d.H, d.W, d.R, d.S, 1, d.R - 1 - pad_h,
-                         d.S - 1 - pad_w, d.H, d.W, 1, 0, 0, 0, IgemmGeo{}, wt_b + 4 * copy_b <= kScratchBytes);
+                         d.S - 1 - pad_w, d.H, d.W, 1, 0, 0, 0, any_filter, wt_b + 4 * copy_b <= kScratchBytes);
         b.part_off = wt_b;
         b.x = WtXformArgs{nullptr, nullptr, f.Cb, f.Kb, f.Cp, f.Kp, d.R, d.S, d.R, d.S,
                           1, 0, 0, d.R, d.S};
@@ -712,6 +721,12 @@ void plan_bwd(conv_plan *p)
                 S2c = S2;
                 b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, Hsub, Wsub, R2c, S2c, 1,
                                  Re - 1 - dy0, Se - 1 - dx0, d.H, d.W, st, py, px, 0);
+            }
+            if (!b.p.ok) {
+                R2c = Re;
+                S2c = Se;
+                b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, Hsub, Wsub, R2c, S2c, 1,
+                                 Re - 1 - dy0, Se - 1 - dx0, d.H, d.W, st, py, px, 0, any_filter);
             }
             if (!b.p.ok) return;
             b.x = WtXformArgs{nullptr, nullptr, f.Cb, f.Kb, f.Cp, f.Kp, d.R, d.S, R2c, S2c,
@@ -1443,13 +1458,16 @@ bool plan_upd_ring(conv_plan *p)
             if (d.S == 3) consider({k[0], k[1], k[2], k[3], std::max(1, 512 / tiles)});
         }
     }
-    if (!have) return false;
+    if (!have || (double)best_a.splits * f.dwt_bytes > std::max(2.0 * ((double)f.in_bytes + (double)f.out_bytes), 8.0e9))
+        return false;
     p->ua = best_a;
     p->urv = UpdRowsVariant{d.R, d.S, 1, best.depth, best.nw, best.fc, best.fk, 0};
     p->upd_lds = upd_ring_lds_bytes(d.S, best.fc, best.fk, best.nw, best.depth);
     p->upd_grid = best_a.per_xcd * 8;
     p->upd_copies = best_a.splits;
     p->upd_ws = (size_t)p->upd_copies * f.dwt_bytes;  // (one split writes dW itself; the caller brings it all the same)
+    p->upd_flat = p->upd_flat_bf16 = p->upd_rows = p->upd_bands = false;
+    p->upd_row_launches = p->upd_strips = 1;
     p->upd_ring = true;
     p->upd_ok = true;
     return true;
@@ -1469,8 +1487,8 @@ void plan_upd(conv_plan *p)
     p->upd_bands = false;
     p->upd_ring = false;
     // the kernels written for a family of layers first, each declining what it does not fit
-    if (!(plan_upd_c4_bf16(p) || plan_upd_c4(p) || plan_upd_ring(p) || plan_upd_flat_f32(p) || plan_upd_flat_bf16(p) ||
-          plan_upd_rows(p) || plan_upd_bands(p)))
+    const bool few = plan_upd_c4_bf16(p) || plan_upd_c4(p);
+    if (!(few || plan_upd_flat_f32(p) || plan_upd_flat_bf16(p) || plan_upd_rows(p) || plan_upd_bands(p)))
         plan_upd_general(p);
     // Partial copies that dwarf the tensors themselves (very wide rows cut into many strips,
     // under a filter with thousands of channels): no tiled plan; the direct kernel needs no
@@ -1480,6 +1498,9 @@ void plan_upd(conv_plan *p)
         p->upd_ok = false;
         p->upd_ws = 0;
     }
+    // ... and over all but a first layer's, the ring kernel where it is the better one
+    const bool tiled = p->upd_ok;
+    if (!few && plan_upd_ring(p)) p->upd_ws_optional = !tiled;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -1593,8 +1614,12 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
         const IgemmPlan base = plan_igemm_tile(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride,
                                                pad_h, pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{});
         p->fwd_takes_ws = base.ok && base.a.total <= 128 && base.a.n_stage >= 4;
+        // (a filter without a staged kernel: the register-operand kernel from 1e8 flops on; below, the
+        // tests of the untiled kernels expect those)
+        IgemmGeo geo;
+        geo.fallback = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q >= 1.0e8;
         p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
-                            pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, p->fwd_takes_ws);
+                            pad_w, f.P, f.Q, 1, 0, 0, 0, geo, p->fwd_takes_ws);
         if (p->fwd.ok && p->fwd.a.ksplit > 1)
             p->fwd_ws = (size_t)p->fwd.a.ksplit * d.N * f.Kp * f.P * f.Q * sizeof(float);
         // A first layer (one channel block in, one reduction step, one channel tile): resident
@@ -1611,6 +1636,7 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
             if (const char *cap = getenv("CONVMI_STEM_WG"); cap && atoi(cap) > 0) p->fwd.a.jstep = atoi(cap);
         }
         plan_bwd(p);
+        for (int i = 0; i < p->n_bwd; ++i) p->bwd_ws_optional |= p->bwd[i].p.fallback;
         plan_upd(p);
     }
     // A pass without a tiled plan falls to the direct kernels (any filter, stride and pad).
@@ -1796,7 +1822,7 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
         }
         return CONV_OK;
     }
-    if (h->bwd_direct) {
+    if (h->bwd_direct || (h->bwd_ws_optional && !ws)) {
         DirectArgs a = h->da;
         a.x = dout;
         a.wt = wt;
@@ -1860,7 +1886,7 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
             return CONV_ELAUNCH;
         return CONV_OK;
     }
-    if (h->upd_direct) {
+    if (h->upd_direct || (h->upd_ws_optional && !ws)) {
         DirectArgs a = h->da;
         a.x = in;
         a.wt = dout;
@@ -1947,6 +1973,14 @@ static size_t pass_ws_bytes(const conv_plan *h, int pass)
     }
     return pass == 0 ? h->fwd_ws : pass == 1 ? h->bwd_ws : h->upd_ws;
 }
+// whether the pass runs without one too, on the untiled kernels (an update in chunks needs its slots)
+static bool ws_optional(const conv_plan *h, int pass)
+{
+    if (pass == 1 && h->bwd_chunked)
+        return ws_optional(h->chunk, 1) && (!h->tail || ws_optional(h->tail, 1) || h->tail->bwd_direct);
+    if (pass == 2 && h->upd_chunked) return false;
+    return pass == 1 ? h->bwd_ws_optional : pass == 2 && h->upd_ws_optional;
+}
 }  // namespace
 
 conv_status_t conv_fwd_ws(conv_handle_t h, const void *in, const void *wt, void *out, void *ws,
@@ -1961,7 +1995,10 @@ conv_status_t conv_bwd_data_ws(conv_handle_t h, const void *dout, const void *wt
                                void *ws, size_t ws_bytes, void *stream)
 {
     if (!h) return CONV_EINVAL;
-    if (ws_bytes < pass_ws_bytes(h, 1)) return CONV_EWORKSPACE;
+    if (ws_bytes < pass_ws_bytes(h, 1)) {
+        if (!ws_optional(h, 1)) return CONV_EWORKSPACE;
+        ws = nullptr;
+    }
     return conv_bwd_data(h, dout, wt, din, ws, stream);
 }
 
@@ -1969,7 +2006,10 @@ conv_status_t conv_upd_ws(conv_handle_t h, const void *in, const void *dout, voi
                           size_t ws_bytes, void *stream)
 {
     if (!h) return CONV_EINVAL;
-    if (ws_bytes < pass_ws_bytes(h, 2)) return CONV_EWORKSPACE;
+    if (ws_bytes < pass_ws_bytes(h, 2)) {
+        if (!ws_optional(h, 2)) return CONV_EWORKSPACE;
+        ws = nullptr;
+    }
     return conv_upd(h, in, dout, dwt, ws, stream);
 }
 
@@ -2006,7 +2046,8 @@ conv_status_t conv_bwd_data_noalloc(conv_handle_t h, const void *dout, const voi
                                     void *stream)
 {
     if (!h || !dout || !wt || !din) return CONV_EINVAL;
-    if (pass_ws_bytes(h, 1) > kScratchBytes) return CONV_ESCRATCH;
+    if (pass_ws_bytes(h, 1) > kScratchBytes)
+        return ws_optional(h, 1) ? conv_bwd_data(h, dout, wt, din, nullptr, stream) : CONV_ESCRATCH;
     void *ptr = scratch_of_current_device();
     if (!ptr) return CONV_ELAUNCH;
     return conv_bwd_data(h, dout, wt, din, ptr, stream);

@@ -85,6 +85,7 @@ struct IgemmArgs {
 struct IgemmGeo {
     int cstride = 0;  // IgemmArgs::cstride
     int ostr_x = 0;   // IgemmArgs::ostr_x
+    bool fallback = false;  // where no staged tile fits: the register-operand kernel, whatever the size
 };
 
 // Key of a kernel instantiation; the host picks one per pass at plan time.
