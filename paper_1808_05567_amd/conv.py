@@ -121,10 +121,29 @@ def _ptr(x):
     return x.data_ptr()
 
 
+_raw_stream = None  # current device -> its current stream's handle, once the runtime is up
+
+
+def _current_stream():
+    """Handle of the current device's current stream.  The public call builds a Stream object, 3 us
+    of a 7 us call; the handle alone takes 0.2 us."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        stream = torch.cuda.current_stream().cuda_stream  # (initialises the runtime if need be)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if device is None or raw is None:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        else:
+            _raw_stream = lambda: raw(device())  # noqa: E731
+        return stream
+    return _raw_stream()
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
