@@ -327,10 +327,11 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
 // its steps, each bound by what it asks of the matrix cores, of the 64 B/clk into the CU or of
 // the LDS reads, whichever is slowest; workgroups that share a CU share those, `busy` clocks
 // each, and overlap the rest.  The CU with the most workgroups ends the launch.  The constants
-// are a least-squares fit (log of the time) to 11 000 launches: 38 ResNet-50 and Inception-v3
-// layers x N = 1 ... 256 x both types x every variant; rms error 4 - 16 %.  The plan with the
-// lowest estimate was on average 3 % behind the fastest variant, and 1.65 times as fast
-// as the large tiles (with their reduction split through memory) that these sizes ran on.
+// are a least-squares fit (log of the time) to 4 300 launches: 34 ResNet-50 and Inception-v3
+// layers x N = 1 ... 128 x both types x every variant, three sets of tensors in turn; rms error
+// 6 - 15 %.  The plan with the lowest estimate was on average 1 % (fp32) and 2 % (bf16) behind the
+// fastest variant, and took 0.61 times as long as the large tiles that these sizes ran on before, their
+// reduction split through memory (0.55 / 0.29 times as long as those without the split).
 double estimate_us(const IgemmPlan &p, bool scatter)
 {
     const IgemmArgs &a = p.a;
@@ -340,23 +341,24 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     const double frags = v.fk * v.fm;
     const int RS = p.reg ? a.R * a.S : v.r * v.s;
     struct Fit { double launch, fixed, step, c_mfma, c_load, c_read, busy; };
-    double lone, busy, launch;
+    double lone, busy, launch, hbm = 4.8e6;
     int resident;
     if (p.reg) {
-        const Fit f = bf16 ? Fit{2.3, 6340, 119, 2.81, 1.36, 0, 1860} : Fit{3.5, 4600, 380, 1.17, 1.2, 0, 1700};
-        const int depth = igemm_reg_depth(v.dtype, v.fk, v.fm, v.wk);
-        const double per = ceil_div(ceil_div(a.st_per, v.wk), depth) * depth;  // steps of a wave
+        // (c_read: the exchange of the waves' sums, clocks per tile and wave)
+        const Fit f = bf16 ? Fit{2.6, 0, 256, 0, 1.26, 284, 1480} : Fit{3.9, 0, 441, 1.22, 1.2, 0, 1300};
+        const double per = ceil_div(a.st_per, v.wk);  // steps of a wave
         const double simd_waves = v.wk / 4;
-        lone = f.fixed + per * std::max(frags * mfma * f.c_mfma * simd_waves, f.step) + (bf16 ? 22.0 : 0.0) * frags * v.wk;
+        lone = f.fixed + per * std::max(frags * mfma * f.c_mfma * simd_waves, f.step) + f.c_read * frags * v.wk;
         busy = per * std::max(frags * mfma * f.c_mfma * simd_waves, v.wk * (v.fk + v.fm) * 16.0 * f.c_load) + f.busy;
         // (waves per SIMD that the registers leave room for)
-        const int occ = frags == 1 ? (bf16 ? 5 : 6) : frags == 2 ? (bf16 ? 4 : 5) : 3;
+        const int occ = frags == 1 ? 8 : frags == 2 ? (bf16 ? 7 : 6) : 3;
         resident = std::max(1, occ * 4 / v.wk);
         launch = f.launch;
+        if (bf16) hbm = 3.3e6;
     } else {
         const bool small = v.fm <= 2;
-        const Fit f = small ? (bf16 ? Fit{2.2, 2400, 205, 1.65, 2.55, 1.28, 880} : Fit{3.0, 1890, 122, 1.04, 1.2, 1.0, 2000})
-                            : (bf16 ? Fit{0.9, 8780, 192, 1.23, 2.04, 1.49, 6000} : Fit{2.5, 6740, 222, 0.99, 1.2, 1.0, 7660});
+        const Fit f = small ? (bf16 ? Fit{2.4, 1350, 298, 1.24, 2.65, 0.92, 800} : Fit{3.0, 245, 253, 1.03, 0.24, 1.0, 2220})
+                            : (bf16 ? Fit{1.1, 8760, 6, 1.33, 2.53, 1.62, 4920} : Fit{3.0, 6610, 248, 1.0, 1.2, 1.0, 7580});
         const double waves = v.wk * v.wm, rounds = (RS * v.npl + 1) / 2;
         const double bytes = (rounds * 2 * v.wk * v.fk * 32 + (double)v.npl * a.PLS) * 16;
         const double step = std::max(std::max(rounds * frags * mfma * waves / 4 * f.c_mfma, bytes / 64 * f.c_load),
@@ -376,7 +378,7 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     if (a.ksplit > 1)  // the second launch, and the partial results there and back
         t += (bf16 ? 1.9 : 1.7) + a.ksplit * out * (bf16 ? 2 : 1) * 2 / 4.0e6;
     const double in = (double)a.N * a.Cb * (RS == 1 ? (double)a.P * a.Q : (double)a.H * a.W) * 16;
-    return std::max(t, launch + (in + out + (double)a.Cb * RS * a.Kp * 16) / 5.0e6);
+    return std::max(t, launch + (in + out + (double)a.Cb * RS * a.Kp * 16) / hbm);
 }
 
 hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t stream)

@@ -27,7 +27,7 @@ namespace convmi {
 
 // FK x FM accumulator tiles per wave, NW waves that split the reduction, D steps in flight.
 template <int DT, int FK, int FM, int NW, int D>
-__global__ __launch_bounds__(NW * 64, 2) void igemm_reg_kernel(const IgemmArgs a)
+__global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kernel(const IgemmArgs a)
 {
     using E_ = Elem<DT>;
     constexpr int V = E_::V;
@@ -143,8 +143,9 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm_reg_kernel(const IgemmArgs a
     if (u0 < u1) {
 #pragma unroll
         for (int d = 0; d < D; ++d) load(A[d], B[d]);
-        // (whole groups of D steps: what lies past u1 arrives as zeros)
-        for (int g = u0; g < u1; g += D) {
+        // (loads past u1 ask for nothing: their lanes are out of range)
+        int g = u0;
+        for (; g + D < u1; g += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
 #pragma unroll
@@ -155,6 +156,15 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm_reg_kernel(const IgemmArgs a
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        // the last 1 .. D steps, already in registers
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (g + d < u1) {
+#pragma unroll
+                for (int i = 0; i < FK; ++i)
+#pragma unroll
+                    for (int j = 0; j < FM; ++j) E_::mma(A[d][i], B[d][j], acc[i][j]);
+            }
     }
 
     // The waves' sums, G fragments per round: every wave writes its own, then each thread adds
@@ -242,13 +252,15 @@ static const struct RegEntry {
     int dtype, fk, fm, nw, depth;
     igemm_fn_t fn;
 } g_reg[] = {
-    REG_ENTRY(CONV_F32, 1, 1, 4, 6),  REG_ENTRY(CONV_F32, 1, 1, 8, 6),  REG_ENTRY(CONV_F32, 2, 1, 8, 4),
-    REG_ENTRY(CONV_F32, 1, 2, 4, 4),  REG_ENTRY(CONV_F32, 2, 2, 4, 3),
-    REG_ENTRY(CONV_BF16, 1, 1, 4, 8), REG_ENTRY(CONV_BF16, 1, 1, 8, 8), REG_ENTRY(CONV_BF16, 2, 1, 8, 5),
-    REG_ENTRY(CONV_BF16, 2, 2, 4, 4),
+    REG_ENTRY(CONV_F32, 1, 1, 4, 4),  REG_ENTRY(CONV_F32, 1, 1, 8, 3),  REG_ENTRY(CONV_F32, 2, 1, 8, 3),
+    REG_ENTRY(CONV_F32, 1, 2, 4, 3),  REG_ENTRY(CONV_F32, 2, 2, 4, 3),
+    REG_ENTRY(CONV_BF16, 1, 1, 4, 3), REG_ENTRY(CONV_BF16, 1, 1, 8, 3), REG_ENTRY(CONV_BF16, 2, 1, 8, 2),
+    REG_ENTRY(CONV_BF16, 2, 2, 4, 3),
 };
 // (dropped after measuring 42 layers at N = 1 ... 256 under every variant: 16 waves, 2 x 4 fragments,
-// 1 x 2 and 2 x 2 fragments on eight waves: never more than 2 % ahead of the ones above)
+// 1 x 2 and 2 x 2 fragments on eight waves: never more than 2 % ahead of the ones above.  More steps in
+// flight: 5 to 12 cost 3 - 30 % against 2 to 4 in bf16, 1 - 5 % in fp32: waves per SIMD cover the loads
+// better than a wave's own depth does.)
 
 int igemm_reg_depth(int dtype, int fk, int fm, int nw)
 {
