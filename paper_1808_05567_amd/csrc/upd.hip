@@ -521,39 +521,44 @@ __global__ __launch_bounds__(256) void upd_bf16_kernel(const UpdArgs a)
             }
 }
 
-// dW[e] = sum_j partial[j][e] in a fixed order: 8 interleaved chains over j
-// (chain g takes j = g, g+8, ...), each ascending, then chains 0..7 ascending.
+// dW[e] = sum_j partial[j][e] in a fixed order: G interleaved chains over j (chain g takes
+// j = g, g+G, ...), each ascending, then chains 0..G-1 ascending.
+// Bound by the trip to memory where dW is small (a first layer: 256 copies of 36 - 100 KB), by
+// bandwidth otherwise, so a chain asks for eight copies before it adds the first, and the chains
+// are as many as leave each with one or two such groups.  (Eight chains of one load at a time:
+// 11 us for the 256 copies of a first layer, 38 us for the 1024 of a 32 -> 32 3x3 layer at 149x149;
+// and seven of eight threads idle where there are two copies.)
+template <int G>
 __global__ __launch_bounds__(256) void upd_reduce_kernel(const f32x4 *__restrict__ partial,
                                                          f32x4 *__restrict__ dwt, size_t n4,
                                                          int splits)
 {
-    __shared__ f32x4 part[8][32];
-    const int colt = threadIdx.x & 31;
-    const int g = threadIdx.x >> 5;
-    const size_t idx = (size_t)blockIdx.x * 32 + colt;
+    constexpr int COLS = 256 / G, AHEAD = 8;
+    const int colt = threadIdx.x % COLS;
+    const int g = threadIdx.x / COLS;
+    const size_t idx = (size_t)blockIdx.x * COLS + colt;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     if (idx < n4) {
-        for (int j = g; j < splits; j += 8) {
-            const f32x4 v = partial[(size_t)j * n4 + idx];
-            s[0] += v[0];
-            s[1] += v[1];
-            s[2] += v[2];
-            s[3] += v[3];
+        for (int j = g; j < splits; j += G * AHEAD) {
+            f32x4 v[AHEAD];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (j + u * G < splits) v[u] = partial[(size_t)(j + u * G) * n4 + idx];
+            }
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) s += v[u];
         }
     }
-    part[g][colt] = s;
-    __syncthreads();
-    if (g == 0 && idx < n4) {
-        f32x4 t = part[0][colt];
-        for (int q = 1; q < 8; ++q) {
-            const f32x4 v = part[q][colt];
-            t[0] += v[0];
-            t[1] += v[1];
-            t[2] += v[2];
-            t[3] += v[3];
-        }
-        dwt[idx] = t;
+    if constexpr (G > 1) {
+        __shared__ f32x4 part[G][COLS];
+        part[g][colt] = s;
+        __syncthreads();
+        if (g != 0) return;
+#pragma unroll
+        for (int q = 1; q < G; ++q) s += part[q][colt];
     }
+    if (idx < n4) dwt[idx] = s;
 }
 
 typedef void (*upd_fn_t)(const UpdArgs);
@@ -622,9 +627,18 @@ hipError_t launch_upd_reduce(const float *partial, float *dwt, size_t n_elems, i
                              hipStream_t stream)
 {
     const size_t n4 = n_elems / 4;
-    hipLaunchKernelGGL(upd_reduce_kernel, dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, stream,
-                       reinterpret_cast<const f32x4 *>(partial), reinterpret_cast<f32x4 *>(dwt), n4,
-                       splits);
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(partial);
+    f32x4 *dst = reinterpret_cast<f32x4 *>(dwt);
+    // (chains of at most one group of eight loads up to 256 copies)
+    if (splits <= 8)
+        hipLaunchKernelGGL(upd_reduce_kernel<1>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, src,
+                           dst, n4, splits);
+    else if (splits <= 64)
+        hipLaunchKernelGGL(upd_reduce_kernel<8>, dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, stream, src,
+                           dst, n4, splits);
+    else
+        hipLaunchKernelGGL(upd_reduce_kernel<32>, dim3((unsigned)((n4 + 7) / 8)), dim3(256), 0, stream, src,
+                           dst, n4, splits);
     return hipGetLastError();
 }
 

@@ -70,3 +70,21 @@ def test_ring_update_is_exact_on_integers_and_repeatable(shape, dtype, monkeypat
             assert np.array_equal(run_pass(L, "upd", I=I, dO=dO), ref.astype(np.float32))
     finally:
         L.close()
+
+
+@pytest.mark.parametrize("splits", [2, 8, 9, 64, 65, 257])
+def test_partial_copies_are_summed_whole(splits, monkeypatch):
+    """Numbers of partial copies around those at which the summing kernel changes its number of chains (8, 64)
+    and its groups of eight loads; small integers, so that the sums are exact."""
+    shape = (1, 20, 24, splits, 128, 3, 3, 1, 1)  # (a copy per row of 128 pixels)
+    N, C, K, H, W, R, S, stride, pad = shape
+    I = inputs.gen_small_ints((N, C, H, W), -3, 3, which=3)
+    dO = inputs.gen_small_ints((N, K, H, W), -3, 3, which=4)
+    ref = oracle.upd(I, dO, R, S, stride, pad)
+    monkeypatch.setenv("CONVMI_UPD_RING", "1,1,8,2,%d" % splits)
+    L = conv.ConvLayer(*shape, dtype=conv.CONV_BF16)
+    try:
+        assert "splits=%d " % splits in conv.conv_describe(L.h, conv.PASS_UPD)
+        assert np.array_equal(run_pass(L, "upd", I=I, dO=dO), ref.astype(np.float32))
+    finally:
+        L.close()
