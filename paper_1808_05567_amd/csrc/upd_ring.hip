@@ -1,4 +1,4 @@
-// Weight-gradient update (Algorithm 8 of the paper) for filters with 1, 3 or 7 columns, any
+// Weight-gradient update (Algorithm 8 of the paper) for filters with 1, 3, 5 or 7 columns, any
 // number of rows, any stride, pads per axis, both types.
 //
 //   dW[k,c,r,s] = sum over (n,oj,oi) of I[n,c,oj*stride-pad_h+r,oi*stride-pad_w+s] * dO[n,k,oj,oi]
@@ -245,7 +245,7 @@ static const struct UpdRingEntry {
 #define BOTH(S, FC, FK, NW, D) UPD_RING_ENTRY(CONV_F32, S, FC, FK, NW, D), UPD_RING_ENTRY(CONV_BF16, S, FC, FK, NW, D)
     BOTH(1, 1, 1, 8, 4), BOTH(1, 2, 2, 8, 2), BOTH(1, 2, 4, 8, 2),
     BOTH(3, 1, 1, 8, 2), BOTH(3, 1, 2, 8, 2), BOTH(3, 2, 2, 8, 2), BOTH(3, 2, 2, 4, 4),
-    BOTH(7, 1, 1, 8, 2),
+    BOTH(5, 1, 1, 8, 2), BOTH(7, 1, 1, 8, 2),
 };
 
 // (dropped after measuring 38 layers at N = 8 ... 256: deeper rings where they fit, 4 x 2 and 4 x 4

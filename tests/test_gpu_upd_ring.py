@@ -1,7 +1,7 @@
 """Weight update on the kernel with small blocks of dW (a filter row per workgroup, the waves split the
 pixels, operands through rings of LDS patches), under every variant it is built in, with one split (dW written
 directly) and several, against the oracle at the edges: pixel counts around a wave's stage, rows and images
-shorter than a run of four pixels, ragged channels both ways, strides, pads per axis, filters of 1, 3 and 7
+shorter than a run of four pixels, ragged channels both ways, strides, pads per axis, filters of 1, 3, 5 and 7
 columns.  Bars: gpu_util.assert_close for an fp32 result."""
 import numpy as np
 import pytest
@@ -13,7 +13,8 @@ from gpu_util import assert_close, make_inputs, run_pass
 
 pytestmark = pytest.mark.gpu
 
-VARIANTS = {1: ["1,1,8,4", "2,2,8,2", "2,4,8,2"], 3: ["1,1,8,2", "1,2,8,2", "2,2,8,2", "2,2,4,4"], 7: ["1,1,8,2"]}
+VARIANTS = {1: ["1,1,8,4", "2,2,8,2", "2,4,8,2"], 3: ["1,1,8,2", "1,2,8,2", "2,2,8,2", "2,2,4,4"], 5: ["1,1,8,2"],
+            7: ["1,1,8,2"]}
 
 # N, C, K, H, W, R, S, stride, pad
 SHAPES = [
@@ -29,6 +30,9 @@ SHAPES = [
     (2, 33, 65, 17, 6, 3, 1, 1, (1, 0)),
     (2, 48, 72, 17, 17, 7, 1, 1, (3, 0)),
     (2, 40, 48, 17, 17, 1, 7, 1, (0, 3)),
+    (2, 40, 36, 9, 11, 5, 5, 1, 2),         # five columns
+    (1, 24, 40, 12, 13, 5, 5, 2, 0),
+    (1, 12, 40, 5, 150, 3, 3, 1, 1),        # rows of more than 128 pixels
     (1, 24, 40, 10, 12, 7, 7, 2, 3),        # seven launches' worth of filter rows in one
     (2, 16, 24, 9, 7, 2, 3, 1, (1, 2)),     # an even number of filter rows, more padding than "same"
 ]
