@@ -9,44 +9,50 @@
 
 namespace convmi {
 
-// X[N][C][H][W] -> Xb[N][Cb][H][W][V]; one thread per 16-byte block.
-template <typename T, int V>
+// X[N][C][H][W] -> Xb[N][Cb][H][W][V]; one thread per 16-byte block.  I: the index type; 32 bits
+// wherever they hold it.  Bound by memory then; two 64-bit divisions per thread cost more than
+// the block's own traffic (64 images of 256 channels at 56x56 unpacked: fp32 96 -> 69 us, bf16
+// 59 -> 30; at 5.1 TB/s the copy takes 81 and 40, part of it stays in the last-level cache).  Two or four pixels
+// per thread, for wider accesses to the planes, measured no faster (pack: 10 - 40 % slower).
+template <typename T, int V, typename I>
 __global__ __launch_bounds__(256) void pack_act_kernel(const T *__restrict__ src, T *__restrict__ dst,
-                                                       int C, int Cb, size_t HW, size_t total)
+                                                       int C, int Cb, I HW, I total)
 {
     // (a grid has at most 2^32 work-items: larger tensors take several blocks per thread)
-    for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-    const size_t hw = idx % HW;
-    const size_t t = idx / HW;
-    const int cb = (int)(t % Cb);
-    const size_t n = t / Cb;
-    T v[V];
+    for (I idx = (I)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (I)gridDim.x * 256) {
+        const I t = idx / HW, hw = idx - t * HW;
+        const I n = t / (I)Cb;
+        const int cb = (int)(t - n * (I)Cb);
+        T v[V];
 #pragma unroll
-    for (int j = 0; j < V; ++j) {
-        const int c = cb * V + j;
-        v[j] = c < C ? src[(n * C + c) * HW + hw] : T(0);
-    }
-    T *d = dst + idx * V;
+        for (int j = 0; j < V; ++j) {
+            const int c = cb * V + j;
+            v[j] = c < C ? src[((size_t)n * C + c) * HW + hw] : T(0);
+        }
+        T *d = dst + (size_t)idx * V;
 #pragma unroll
-    for (int j = 0; j < V; ++j) d[j] = v[j];
+        for (int j = 0; j < V; ++j) d[j] = v[j];
     }
 }
 
-template <typename T, int V>
+template <typename T, int V, typename I>
 __global__ __launch_bounds__(256) void unpack_act_kernel(const T *__restrict__ src, T *__restrict__ dst,
-                                                         int C, int Cb, size_t HW, size_t total)
+                                                         int C, int Cb, I HW, I total)
 {
-    for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-    const size_t hw = idx % HW;
-    const size_t t = idx / HW;
-    const int cb = (int)(t % Cb);
-    const size_t n = t / Cb;
-    const T *s = src + idx * V;
+    for (I idx = (I)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (I)gridDim.x * 256) {
+        const I t = idx / HW, hw = idx - t * HW;
+        const I n = t / (I)Cb;
+        const int cb = (int)(t - n * (I)Cb);
+        // (the whole block is read before the first store: one 16-byte load)
+        const T *s = src + (size_t)idx * V;
+        T v[V];
 #pragma unroll
-    for (int j = 0; j < V; ++j) {
-        const int c = cb * V + j;
-        if (c < C) dst[(n * C + c) * HW + hw] = s[j];
-    }
+        for (int j = 0; j < V; ++j) v[j] = s[j];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const int c = cb * V + j;
+            if (c < C) dst[((size_t)n * C + c) * HW + hw] = v[j];
+        }
     }
 }
 
@@ -144,32 +150,50 @@ static inline int blocks_for(size_t total)
     return (int)(b < (1u << 22) ? b : (1u << 22));
 }
 
+template <typename T, int V, typename I>
+static void launch_act_as(bool pack, const void *src, void *dst, int C, int Cb, size_t HW, size_t total,
+                          hipStream_t stream)
+{
+    const dim3 grid(blocks_for(total));
+    if (pack)
+        hipLaunchKernelGGL((pack_act_kernel<T, V, I>), grid, dim3(256), 0, stream, (const T *)src, (T *)dst, C, Cb,
+                           (I)HW, (I)total);
+    else
+        hipLaunchKernelGGL((unpack_act_kernel<T, V, I>), grid, dim3(256), 0, stream, (const T *)src, (T *)dst, C, Cb,
+                           (I)HW, (I)total);
+}
+
+static hipError_t launch_act(int dtype, bool pack, const void *src, void *dst, int N, int C, int H, int W,
+                             hipStream_t stream)
+{
+    const int V = vlen_of(dtype), Cb = ceil_div(C, V);
+    const size_t HW = (size_t)H * W, total = (size_t)N * Cb * HW;
+    // (a round strides by at most 2^30 blocks: an index past the last one still fits 32 bits)
+    const bool small = total <= (3ull << 30);
+    if (dtype == CONV_BF16) {
+        if (small)
+            launch_act_as<uint16_t, 8, unsigned>(pack, src, dst, C, Cb, HW, total, stream);
+        else
+            launch_act_as<uint16_t, 8, size_t>(pack, src, dst, C, Cb, HW, total, stream);
+    } else {
+        if (small)
+            launch_act_as<uint32_t, 4, unsigned>(pack, src, dst, C, Cb, HW, total, stream);
+        else
+            launch_act_as<uint32_t, 4, size_t>(pack, src, dst, C, Cb, HW, total, stream);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_pack_act(int dtype, const void *nchw, void *blk, int N, int C, int H, int W,
                            hipStream_t stream)
 {
-    const int V = vlen_of(dtype), Cb = ceil_div(C, V);
-    const size_t total = (size_t)N * Cb * H * W;
-    if (dtype == CONV_BF16)
-        hipLaunchKernelGGL((pack_act_kernel<uint16_t, 8>), dim3(blocks_for(total)), dim3(256), 0, stream,
-                           (const uint16_t *)nchw, (uint16_t *)blk, C, Cb, (size_t)H * W, total);
-    else
-        hipLaunchKernelGGL((pack_act_kernel<uint32_t, 4>), dim3(blocks_for(total)), dim3(256), 0, stream,
-                           (const uint32_t *)nchw, (uint32_t *)blk, C, Cb, (size_t)H * W, total);
-    return hipGetLastError();
+    return launch_act(dtype, true, nchw, blk, N, C, H, W, stream);
 }
 
 hipError_t launch_unpack_act(int dtype, const void *blk, void *nchw, int N, int C, int H, int W,
                              hipStream_t stream)
 {
-    const int V = vlen_of(dtype), Cb = ceil_div(C, V);
-    const size_t total = (size_t)N * Cb * H * W;
-    if (dtype == CONV_BF16)
-        hipLaunchKernelGGL((unpack_act_kernel<uint16_t, 8>), dim3(blocks_for(total)), dim3(256), 0,
-                           stream, (const uint16_t *)blk, (uint16_t *)nchw, C, Cb, (size_t)H * W, total);
-    else
-        hipLaunchKernelGGL((unpack_act_kernel<uint32_t, 4>), dim3(blocks_for(total)), dim3(256), 0,
-                           stream, (const uint32_t *)blk, (uint32_t *)nchw, C, Cb, (size_t)H * W, total);
-    return hipGetLastError();
+    return launch_act(dtype, false, blk, nchw, N, C, H, W, stream);
 }
 
 hipError_t launch_pack_wt(int dtype, const void *kcrs, void *blk, int K, int C, int R, int S,
