@@ -754,7 +754,7 @@ bool plan_upd_c4_bf16(conv_plan *p)
         // one input channel block, bf16: (tap, channel) rows on the bf16 MFMA, eight waves,
         // two LDS buffers holding the bands as they sit in HBM
         auto plan_c4_bf16 = [&]() -> bool {
-            const int NPO = 8;  // planes of 8 output channels
+            const int NPO = f.Kp <= 32 ? 4 : 8;  // planes of 8 output channels
             const int NP = d.N * f.P;
             UpdArgs &a = p->ua;
             memset(&a, 0, sizeof(a));
@@ -820,7 +820,7 @@ bool plan_upd_c4(conv_plan *p)
         // (a plan that does not fit leaves the layer to the general kernels)
         auto plan_c4 = [&]() -> bool {
             // one input channel block: filter-row formulation, eight waves, two LDS buffers
-            const int NPO = 16;
+            const int NPO = f.Kp <= 32 ? 8 : 16;  // planes of 4 output channels
             const int Qp = (f.Q + 1) & ~1;
             const int NP = d.N * f.P;
             UpdArgs &a = p->ua;
@@ -1889,7 +1889,7 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
             if (st != CONV_OK) return st;
         }
         if (launch_upd_reduce(reinterpret_cast<const float *>(slots), static_cast<float *>(dwt),
-                              h->info.dwt_bytes / sizeof(float), h->n_chunks,
+                              h->info.dwt_bytes / sizeof(float), h->n_chunks, false,
                               (hipStream_t)stream) != hipSuccess)
             return CONV_ELAUNCH;
         return CONV_OK;
@@ -1963,7 +1963,7 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
         }
     if (e != hipSuccess) return CONV_ELAUNCH;
     if (launch_upd_reduce(a.partial, static_cast<float *>(dwt), h->info.dwt_bytes / sizeof(float),
-                          h->upd_copies, s) != hipSuccess)
+                          h->upd_copies, h->upd_c4_bf16, s) != hipSuccess)
         return CONV_ELAUNCH;
     return CONV_OK;
 }

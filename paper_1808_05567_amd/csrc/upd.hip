@@ -528,7 +528,9 @@ __global__ __launch_bounds__(256) void upd_bf16_kernel(const UpdArgs a)
 // are as many as leave each with one or two such groups.  (Eight chains of one load at a time:
 // 11 us for the 256 copies of a first layer, 38 us for the 1024 of a 32 -> 32 3x3 layer at 149x149;
 // and seven of eight threads idle where there are two copies.)
-template <int G>
+// HALF: the copies hold the lower four channel slots of eight-slot blocks (a first layer in bf16);
+// the upper four of dW are zeros.
+template <int G, bool HALF>
 __global__ __launch_bounds__(256) void upd_reduce_kernel(const f32x4 *__restrict__ partial,
                                                          f32x4 *__restrict__ dwt, size_t n4,
                                                          int splits)
@@ -558,7 +560,28 @@ __global__ __launch_bounds__(256) void upd_reduce_kernel(const f32x4 *__restrict
 #pragma unroll
         for (int q = 1; q < G; ++q) s += part[q][colt];
     }
-    if (idx < n4) dwt[idx] = s;
+    if (idx >= n4) return;
+    if constexpr (HALF) {
+        dwt[2 * idx] = s;
+        dwt[2 * idx + 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    } else {
+        dwt[idx] = s;
+    }
+}
+
+template <bool HALF>
+static void launch_upd_reduce_as(const f32x4 *src, f32x4 *dst, size_t n4, int splits, hipStream_t stream)
+{
+    // (chains of at most one group of eight loads up to 256 copies)
+    if (splits <= 8)
+        hipLaunchKernelGGL((upd_reduce_kernel<1, HALF>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, src,
+                           dst, n4, splits);
+    else if (splits <= 64)
+        hipLaunchKernelGGL((upd_reduce_kernel<8, HALF>), dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, stream, src,
+                           dst, n4, splits);
+    else
+        hipLaunchKernelGGL((upd_reduce_kernel<32, HALF>), dim3((unsigned)((n4 + 7) / 8)), dim3(256), 0, stream, src,
+                           dst, n4, splits);
 }
 
 typedef void (*upd_fn_t)(const UpdArgs);
@@ -623,22 +646,16 @@ hipError_t launch_upd(const UpdVariant &v, const UpdArgs &a, size_t lds_bytes, i
     return hipGetLastError();
 }
 
-hipError_t launch_upd_reduce(const float *partial, float *dwt, size_t n_elems, int splits,
+hipError_t launch_upd_reduce(const float *partial, float *dwt, size_t n_elems, int splits, bool half_blocks,
                              hipStream_t stream)
 {
     const size_t n4 = n_elems / 4;
     const f32x4 *src = reinterpret_cast<const f32x4 *>(partial);
     f32x4 *dst = reinterpret_cast<f32x4 *>(dwt);
-    // (chains of at most one group of eight loads up to 256 copies)
-    if (splits <= 8)
-        hipLaunchKernelGGL(upd_reduce_kernel<1>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, src,
-                           dst, n4, splits);
-    else if (splits <= 64)
-        hipLaunchKernelGGL(upd_reduce_kernel<8>, dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, stream, src,
-                           dst, n4, splits);
+    if (half_blocks)
+        launch_upd_reduce_as<true>(src, dst, n4 / 2, splits, stream);
     else
-        hipLaunchKernelGGL(upd_reduce_kernel<32>, dim3((unsigned)((n4 + 7) / 8)), dim3(256), 0, stream, src,
-                           dst, n4, splits);
+        launch_upd_reduce_as<false>(src, dst, n4, splits, stream);
     return hipGetLastError();
 }
 
