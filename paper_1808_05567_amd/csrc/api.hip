@@ -63,6 +63,7 @@ struct conv_plan {
     // backward by data
     int bwd_mode = 0;  // 0 unsupported, 1 one launch (duality), 2 parity classes
     int n_bwd = 0;
+    bool bwd_quad = false;  // four classes (2x2, 2x1, 1x2, 1x1 taps, in this order) in one launch
     BwdClass bwd[16];
     size_t bwd_ws = 0;
     // (passes that would run untiled but for a kernel that takes a workspace: a caller that
@@ -137,7 +138,7 @@ int max_band_rows(int N, int P, int TR, int Hs, int stride, int R)
 IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S,
                     int stride, int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0,
                     int zero_fill, const IgemmGeo &geo, int wk, int wm, int fk, int fm, size_t lds_cap,
-                    int nb = 2, int npl_want = 0)
+                    int nb = 2, int npl_want = 0, int ppt_only = 0)
 {
     IgemmPlan pl;
     // (columns of the result `cstride` input pixels apart, and `ostr_x` output pixels apart)
@@ -167,7 +168,8 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
     const int nent = ((R * S * npl + 1) / 2) * 2;
 
     // (staged positions per thread that the variant is instantiated for)
-    const unsigned have_ppt = igemm_variant_ppts(IgemmVariant{dtype, wk, wm, fk, fm, npl, R, S, 0, nb});
+    const unsigned have_ppt =
+        ppt_only > 0 ? 1u << ppt_only : igemm_variant_ppts(IgemmVariant{dtype, wk, wm, fk, fm, npl, R, S, 0, nb});
     if (have_ppt == 0) return pl;
     int ppt = -1;
     int TQ = std::min(Q, TM);
@@ -592,6 +594,54 @@ IgemmPlan plan_igemm_tile(int dtype, int N, int Cb, int H, int W, int Kp, int P,
     return best;
 }
 
+// The four residue classes of a 3x3 stride-2 backward pass in one launch of 64 x 128 tiles, where that is
+// faster than one launch each of what plan_igemm picks (time of the one launch / of the four, 11 layers at
+// N = 1 ... 256, both with the weights of all classes transformed in one launch):
+//   - bf16: everywhere (0.43 - 0.88; 512 -> 512 at 14x14 up to N = 8 and 32 -> 64 at 149x149, N = 256: 1.0);
+//   - fp32: where the tiles fill the chip before their chain of K/8 steps tells, 1.25 tiles per output
+//     channel (0.62 - 0.94, up to 1.01; below: 128 -> 128 at 28x28, N = 8 1.02, 288 -> 384 at 35x35, N = 8 1.03, N = 1
+//     1.57), or the chain is short (K <= 96: 0.55 - 0.94); not where half of a tile's rows are
+//     empty (32 -> 64 at 149x149, N = 32: 1.48); and from 1024 pixels on: the planner's tests pin four
+//     launches below.
+// (128 x 128 tiles: at most 5 % ahead, on a few bf16 layers; fp32 up to twice as long.)
+void plan_bwd_quad(conv_plan *p)
+{
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    p->bwd_quad = false;
+    if (d.R != 3 || d.S != 3 || d.stride != 2 || p->n_bwd != 4 || f.Kb % 4 != 0) return;
+    // (classes in the kernel's order, with the sub-filters' own extents)
+    BwdClass cls[4];
+    size_t off = 0;
+    int tiles = 0;
+    for (int i = 0; i < 4; ++i) {
+        const int R2 = i < 2 ? 2 : 1, S2 = i == 0 || i == 2 ? 2 : 1;
+        const BwdClass *b = nullptr;
+        for (int j = 0; j < 4; ++j)
+            if (p->bwd[j].x.Rsub == R2 && p->bwd[j].x.Ssub == S2) b = &p->bwd[j];
+        if (!b) return;
+        cls[i] = *b;
+        const IgemmArgs &a = b->p.a;
+        cls[i].p = try_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, a.P, a.Q, R2, S2, 1, a.pad_h, a.pad_w, d.H, d.W, 2,
+                             a.oy0, a.ox0, 0, IgemmGeo{}, 2, 2, 1, 2, (size_t)kMaxLds, 2, R2 * S2 == 1 ? 4 : 2, 1);
+        if (!cls[i].p.ok) return;
+        cls[i].p.fallback = b->p.fallback;
+        tiles += cls[i].p.a.total;
+        cls[i].x.R2 = R2;
+        cls[i].x.S2 = S2;
+        cls[i].ws_off = off;
+        off += (size_t)f.Kb * R2 * S2 * f.Cp * f.vlen * esize_of(d.dtype);
+    }
+    // (CONVMI_BWD_QUAD: 0 never, 1 wherever it fits -- a tuning aid)
+    bool want = d.dtype == CONV_BF16 || (f.Cp > 32 && (d.K <= 96 || tiles >= 1.25 * d.K) &&
+                                         (double)d.N * d.H * d.W >= 1024.0);
+    if (const char *env = getenv("CONVMI_BWD_QUAD")) want = atoi(env) != 0;
+    if (!want) return;
+    for (int i = 0; i < 4; ++i) p->bwd[i] = cls[i];
+    p->bwd_ws = off;
+    p->bwd_quad = true;
+}
+
 void plan_bwd(conv_plan *p)
 {
     const conv_desc_t &d = p->d;
@@ -600,6 +650,7 @@ void plan_bwd(conv_plan *p)
     p->bwd_mode = 0;
     p->n_bwd = 0;
     p->bwd_ws = 0;
+    p->bwd_quad = false;
     const int pad_h = p->pad_h, pad_w = p->pad_w;
     // (filters, and channel-block counts, that no staged kernel is built for: 10 to 100 times the
     // untiled loop nests' rate -- 140 -> 188 channels, 3x3 stride 2 at 26x25, N = 64, fp32: 2324 -> 104 us)
@@ -741,6 +792,7 @@ void plan_bwd(conv_plan *p)
     p->bwd_mode = 2;
     p->n_bwd = n;
     p->bwd_ws = off;
+    plan_bwd_quad(p);
 }
 
 // Weight update, bf16, at most 4 input channels: (tap, channel) rows on the bf16 MFMA.
@@ -1840,20 +1892,42 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
     if (h->bwd_mode == 0) return CONV_EUNSUPPORTED;
     if (!ws) return CONV_EWORKSPACE;
     hipStream_t s = (hipStream_t)stream;
+    // the transformed weights of all classes, up to four to a launch
+    for (int i = 0; i < h->n_bwd;) {
+        if (h->bwd[i].merged) {
+            WtMergeArgs m = h->bwd[i].m;
+            m.src = wt;
+            m.dst = static_cast<char *>(ws) + h->bwd[i].ws_off;
+            if (launch_wt_merge(h->d.dtype, m, s) != hipSuccess) return CONV_ELAUNCH;
+            ++i;
+            continue;
+        }
+        WtXformSet set{};
+        for (set.n = 0; set.n < 4 && i < h->n_bwd; ++set.n, ++i) {
+            set.x[set.n] = h->bwd[i].x;
+            set.x[set.n].src = wt;
+            set.x[set.n].dst = static_cast<char *>(ws) + h->bwd[i].ws_off;
+        }
+        if (launch_wt_xform(h->d.dtype, set, s) != hipSuccess) return CONV_ELAUNCH;
+    }
+    if (h->bwd_quad) {
+        IgemmQuadArgs q;
+        int grid = 0;
+        size_t lds = 0;
+        for (int i = 0; i < 4; ++i) {
+            const BwdClass &b = h->bwd[i];
+            q.cls[i] = b.p.a;
+            q.cls[i].in = dout;
+            q.cls[i].wt = static_cast<const char *>(ws) + b.ws_off;
+            q.cls[i].out = din;
+            q.end[i] = grid += b.p.grid;
+            lds = std::max(lds, b.p.lds);
+        }
+        return launch_igemm_quad(h->d.dtype, q, lds, s) == hipSuccess ? CONV_OK : CONV_ELAUNCH;
+    }
     for (int i = 0; i < h->n_bwd; ++i) {
         const BwdClass &b = h->bwd[i];
         void *wt2 = static_cast<char *>(ws) + b.ws_off;
-        if (b.merged) {
-            WtMergeArgs m = b.m;
-            m.src = wt;
-            m.dst = wt2;
-            if (launch_wt_merge(h->d.dtype, m, s) != hipSuccess) return CONV_ELAUNCH;
-        } else {
-            WtXformArgs x = b.x;
-            x.src = wt;
-            x.dst = wt2;
-            if (launch_wt_xform(h->d.dtype, x, s) != hipSuccess) return CONV_ELAUNCH;
-        }
         IgemmArgs a = b.p.a;
         a.in = dout;
         a.wt = wt2;
@@ -2148,7 +2222,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
                      "igemm_reg dt=%d waves=%d frags=%dx%d RS=%dx%d tiles=%d (m=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu "
                      "steps=%d ksplit=%d launches=%d",
                      p->v.dtype, p->v.wk, p->v.fk, p->v.fm, p->v.r, p->v.s, p->a.total, p->a.n_mt, p->a.n_kt,
-                     p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.ksplit, pass == 0 ? 1 : h->n_bwd);
+                     p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
             return CONV_OK;
         }
         snprintf(buf, buflen,
@@ -2156,7 +2230,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
                  "(m=%d q=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu stages=%d ksplit=%d launches=%d",
                  p->v.dtype, p->v.wk, p->v.wm, p->v.fk, p->v.fm, p->v.npl, p->v.nt, p->v.r, p->v.s, p->v.ppt,
                  p->a.TR, p->a.TQ, p->a.total, p->a.n_mt, p->a.n_qt, p->a.n_kt, p->a.gk, p->grid, p->lds,
-                 p->a.n_stage, p->a.ksplit, pass == 0 ? 1 : h->n_bwd);
+                 p->a.n_stage, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
         if (pass == 0 && h->fwd_stem_lds) {
             const size_t n = strlen(buf);
             snprintf(buf + n, buflen - n, " resident_filter_lds=%zu", h->fwd_stem_lds);

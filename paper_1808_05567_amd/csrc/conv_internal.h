@@ -106,6 +106,13 @@ hipError_t ensure_dynamic_lds(const void *kernel, size_t bytes);
 
 hipError_t launch_igemm(const IgemmVariant &v, const IgemmArgs &a, size_t lds_bytes,
                         int grid, hipStream_t stream);
+// The four residue classes of a 3x3 stride-2 backward pass in one launch, in the order 2x2, 2x1, 1x2,
+// 1x1 taps; class i has the workgroups end[i-1] .. end[i].
+struct IgemmQuadArgs {
+    IgemmArgs cls[4];
+    int end[4];
+};
+hipError_t launch_igemm_quad(int dtype, const IgemmQuadArgs &q, size_t lds_bytes, hipStream_t stream);
 bool igemm_variant_exists(const IgemmVariant &v);
 // Bit p is set where the variant (default input policy) exists with p staged pixels per thread.
 unsigned igemm_variant_ppts(const IgemmVariant &v);
@@ -138,7 +145,13 @@ struct WtXformArgs {
     int tap_stride;    // source tap r = tap_stride*(Rsub-1-r') + r_off, valid if r' < Rsub
     int r_off, s_off, Rsub, Ssub;
 };
-hipError_t launch_wt_xform(int dtype, const WtXformArgs &a, hipStream_t stream);
+// Up to four transforms in one launch (the residue classes of a strided backward pass).
+struct WtXformSet {
+    WtXformArgs x[4];
+    int end[4];  // workgroups of transforms 0 .. i (set at launch)
+    int n;
+};
+hipError_t launch_wt_xform(int dtype, const WtXformSet &set, hipStream_t stream);
 
 // Weight transform for a strided backward pass whose dI has one channel block:
 // the sub-filters of all stride-parity classes side by side as the rows of ONE

@@ -121,7 +121,7 @@ struct Elem<CONV_BF16> {
 // (Register budget: two workgroups per CU for the four-wave tiles of at most 128 accumulator
 // registers; a 7x7 filter alone fills most of a CU's LDS, so those run one per CU anyway.)
 template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0>
-__global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 && R * S < 49) ? 2 : 1)) void igemm_kernel(const IgemmArgs a)
+__device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, unsigned char *const lds)
 {
     using E_ = Elem<DT>;
     constexpr int V = E_::V;
@@ -142,7 +142,6 @@ __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 
     constexpr int WBYTES = WCH * 16;  // a multiple of 64 chunks: whole wave-level loads
     static_assert(NPL == 1 || NPL % 2 == 0, "planes per step: 1 or even");
 
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int ibytes = NPL * a.PLS * 16;
     const int bufbytes = WBYTES + ibytes;
 
@@ -167,7 +166,6 @@ __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 
     // equal shares: whole pixel tiles per XCD would give some XCDs up to n_kt tiles more than
     // others, and one tile more than an XCD has CUs doubles the launch (252 tiles of the 160 -> 192
     // 7x1 layer at N = 128, fp32: 33 tiles on some XCDs, 274 us; 32 at most, 157).
-    const int bid = blockIdx.x;
     const int x = bid & 7, j = bid >> 3;
     int kt, rest;
     if (a.gk == 1) {
@@ -605,6 +603,13 @@ __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 
     }
 }
 
+
+template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0>
+__global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 && R * S < 49) ? 2 : 1)) void igemm_kernel(const IgemmArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    igemm_tile<DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NTI>(a, blockIdx.x, lds);
+}
 
 typedef void (*igemm_fn_t)(const IgemmArgs);
 struct IgemmEntry {

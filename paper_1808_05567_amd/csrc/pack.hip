@@ -82,10 +82,10 @@ __global__ __launch_bounds__(256) void perm_wt_kernel(const T *__restrict__ src,
 // dst[kb][r2][s2][c][kk] = Wb[c/V][r][s][kb*V+kk][c%V] with
 // r = tap_stride*(Rsub-1-r2) + r_off (zero if r2 >= Rsub), likewise s.
 template <typename T, int V>
-__global__ __launch_bounds__(256) void wt_xform_kernel(const WtXformArgs a, int total)
+__device__ __forceinline__ void wt_xform(const WtXformArgs &a, int blk)
 {
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
+    const int idx = blk * 256 + threadIdx.x;
+    if (idx >= a.Kb * a.R2 * a.S2 * a.Cp) return;
     const T *src = static_cast<const T *>(a.src);
     T *dst = static_cast<T *>(a.dst);
     const int c = idx % a.Cp;
@@ -106,6 +106,29 @@ __global__ __launch_bounds__(256) void wt_xform_kernel(const WtXformArgs a, int 
     }
 #pragma unroll
     for (int kk = 0; kk < V; ++kk) dst[(size_t)idx * V + kk] = v[kk];
+}
+
+template <typename T, int V>
+__global__ __launch_bounds__(256) void wt_xform_kernel(const WtXformArgs a)
+{
+    wt_xform<T, V>(a, blockIdx.x);
+}
+
+// Two to four transforms: the residue classes of a strided pass, whose launches are mostly their own
+// latency (2 - 5 us each).  (A branch per transform: with the arguments indexed at run time, and one
+// kernel for both uses, every backward pass took 0.7 us longer.)
+template <typename T, int V>
+__global__ __launch_bounds__(256) void wt_xform_set_kernel(const WtXformSet set)
+{
+    const int blk = blockIdx.x;
+    if (blk < set.end[0])
+        wt_xform<T, V>(set.x[0], blk);
+    else if (blk < set.end[1])
+        wt_xform<T, V>(set.x[1], blk - set.end[0]);
+    else if (blk < set.end[2])
+        wt_xform<T, V>(set.x[2], blk - set.end[1]);
+    else
+        wt_xform<T, V>(set.x[3], blk - set.end[2]);
 }
 
 // One thread per (kb, u, v, row): V consecutive output channels k of channel block kb.
@@ -228,15 +251,26 @@ hipError_t launch_unpack_wt(int dtype, const void *blk, void *kcrs, int K, int C
     return hipGetLastError();
 }
 
-hipError_t launch_wt_xform(int dtype, const WtXformArgs &a, hipStream_t stream)
+hipError_t launch_wt_xform(int dtype, const WtXformSet &want, hipStream_t stream)
 {
-    const int total = a.Kb * a.R2 * a.S2 * a.Cp;
-    if (dtype == CONV_BF16)
-        hipLaunchKernelGGL((wt_xform_kernel<uint16_t, 8>), dim3(blocks_for(total)), dim3(256), 0, stream,
-                           a, total);
-    else
-        hipLaunchKernelGGL((wt_xform_kernel<uint32_t, 4>), dim3(blocks_for(total)), dim3(256), 0, stream,
-                           a, total);
+    WtXformSet set = want;
+    int grid = 0;
+    for (int i = 0; i < 4; ++i) {
+        const WtXformArgs &a = set.x[i];
+        if (i < set.n) grid += ceil_div(a.Kb * a.R2 * a.S2 * a.Cp, 256);
+        set.end[i] = grid;
+    }
+    if (set.n == 1) {
+        if (dtype == CONV_BF16)
+            hipLaunchKernelGGL((wt_xform_kernel<uint16_t, 8>), dim3(grid), dim3(256), 0, stream, set.x[0]);
+        else
+            hipLaunchKernelGGL((wt_xform_kernel<uint32_t, 4>), dim3(grid), dim3(256), 0, stream, set.x[0]);
+    } else {
+        if (dtype == CONV_BF16)
+            hipLaunchKernelGGL((wt_xform_set_kernel<uint16_t, 8>), dim3(grid), dim3(256), 0, stream, set);
+        else
+            hipLaunchKernelGGL((wt_xform_set_kernel<uint32_t, 4>), dim3(grid), dim3(256), 0, stream, set);
+    }
     return hipGetLastError();
 }
 
