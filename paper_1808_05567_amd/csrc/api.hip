@@ -345,6 +345,7 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     struct Fit { double launch, fixed, step, c_mfma, c_load, c_read, busy; };
     double lone, busy, launch, hbm = 4.8e6;
     int resident;
+    bool large = false;  // 224 or more pixels, or 64 x 512: a workgroup or two to a CU
     if (p.reg) {
         // (c_read: the exchange of the waves' sums, clocks per tile and wave)
         const Fit f = bf16 ? Fit{2.6, 0, 256, 0, 1.26, 284, 1480} : Fit{3.9, 0, 441, 1.22, 1.2, 0, 1300};
@@ -370,6 +371,7 @@ double estimate_us(const IgemmPlan &p, bool scatter)
         const int occ = frags * 16 > 128 ? 1 : frags <= 2 ? 4 : small ? 3 : 2;
         resident = waves == 8 ? 1 : std::max(1, std::min((int)(kMaxLds / p.lds), occ));
         launch = f.launch;
+        large = !small;
     }
     const int per_cu = ceil_div(p.grid, 256);
     const int full = per_cu / resident, rest = per_cu - full * resident;
@@ -380,7 +382,21 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     if (a.ksplit > 1)  // the second launch, and the partial results there and back
         t += (bf16 ? 1.9 : 1.7) + a.ksplit * out * (bf16 ? 2 : 1) * 2 / 4.0e6;
     const double in = (double)a.N * a.Cb * (RS == 1 ? (double)a.P * a.Q : (double)a.H * a.W) * 16;
-    return std::max(t, launch + (in + out + (double)a.Cb * RS * a.Kp * 16) / hbm);
+    const double bytes = in + out + (double)a.Cb * RS * a.Kp * 16;
+    // bf16, the rate at which a staged launch bound by memory moves its bytes: 128-pixel tiles, three
+    // workgroups to a CU, 6.5 - 7.3 TB/s up to the last-level cache's 256 MB (64 -> 256 at 56x56, N = 64: 20 us,
+    // 30 in the large tiles) and less beyond (5.6 up to 450 MB with several channel tiles: N = 192 54 us, 83; else
+    // 4.6), not where they are one step of four planes (32 -> 328 at 23x23, N = 128: 12.5 us, 11.7) or scatter;
+    // the large ones 4.8, or 6.2 where one channel tile lets the input pass by the caches (64 -> 80 at
+    // 73x73, N = 256: 75 us, 88 in small tiles), and less where they leave CUs with one workgroup or none
+    // (256 -> 64 at 56x56, N = 16: 112 tiles, 13 us; 7 in small tiles).
+    if (bf16 && !p.reg) {
+        if (large)
+            hbm = (a.n_kt == 1 ? 6.2e6 : 4.8e6) * std::min(1.0, a.total / (scatter ? 224.0 : 300.0));
+        else if (!scatter && !(a.n_stage == 1 && v.npl == 4))
+            hbm = bytes <= 2.56e8 ? 6.5e6 : a.n_kt > 1 && bytes <= 4.5e8 ? 5.6e6 : 4.6e6;
+    }
+    return std::max(t, launch + bytes / hbm);
 }
 
 hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t stream)
@@ -416,7 +432,8 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
         auto consider = [&](const IgemmPlan &c) {
             if (!c.ok) return;
             const double us = estimate_us(c, scatter);
-            if (us < best_us) {
+            // (of two staged ones bound by memory alike, where tiles abound, the one that reads its input less often)
+            if (us < best_us || (us == best_us && !c.reg && !best.reg && c.v.fk > best.v.fk && c.a.total >= 768)) {
                 best = c;
                 best_us = us;
             }
