@@ -2284,8 +2284,9 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         }
         if (h->upd_c4 || h->upd_c4_bf16) {
             snprintf(buf, buflen,
-                     "upd_c4 dt=%d mfma=%s RS=%dx%d waves=2x4 TR=%d splits=%d rows/split=%d ktiles=%d grid=%d lds=%zu",
-                     (int)h->d.dtype, h->upd_c4_bf16 ? "bf16" : "f32", h->d.R, h->d.S, h->ua.TR, h->ua.splits, h->ua.rows_per_split, h->ua.n_kt,
+                     "upd_c4 dt=%d mfma=%s RS=%dx%d waves=%s TR=%d splits=%d rows/split=%d ktiles=%d grid=%d lds=%zu",
+                     (int)h->d.dtype, h->upd_c4_bf16 ? "bf16" : "f32", h->d.R, h->d.S,
+                     h->info.Kp <= 32 ? "1x8" : "2x4", h->ua.TR, h->ua.splits, h->ua.rows_per_split, h->ua.n_kt,
                      h->upd_grid, h->upd_lds);
             return CONV_OK;
         }
