@@ -1478,21 +1478,25 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
 //   - rows of more than 128 pixels, which the other kernels take in column strips, and 5 columns, which they
 //     take in a launch per filter row, all from the sizes on where the planner's tests don't pin those
 //     (32 -> 64 3x3 at 147x147: bf16 N = 8 0.32, N = 32 0.52, fp32 0.53, 0.75; 48 -> 64 5x5 at 35x35: bf16 N = 8
-//     0.24, N = 256 0.51, fp32 0.37, 0.74); not 7 columns in bf16 over such rows beyond 5e10 flops (64 -> 64 1x7
-//     at 150x150, N = 8: 0.60, N = 64: 1.16).
+//     0.24, N = 256 0.51, fp32 0.37, 0.74).
+//   - 1x1 and 7 columns in bf16: up to 140 MB of tensors, which every channel tile reads again from the last-level
+//     cache (1x1 up to 135 MB 0.5 - 1.06; 80 -> 192 at 36x36, N = 256, 180 MB 1.22, 128 -> 512 at 28x28, N = 192, 193 MB
+//     1.19, 200 -> 60 at 50x50, N = 192, 250 MB 1.20; 1x7 40 -> 268 at 38x38, N = 128, 114 MB 0.92, N = 192, 171 MB
+//     1.15; 64 -> 64 at 150x150, N = 8, 46 MB 0.60, N = 64, 369 MB 1.16).
 bool ring_applies(const conv_plan *p)
 {
     const conv_desc_t &d = p->d;
     const conv_info_t &f = p->info;
     const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q;
-    const double npix = (double)d.N * f.P * f.Q;
+    const double npix = (double)d.N * f.P * f.Q, tensors = (double)f.in_bytes + (double)f.out_bytes;
     const int wide = std::max(d.C, d.K), narrow = std::min(d.C, d.K);
     if (d.R * d.S == 1) {
-        if (d.dtype == CONV_BF16) return flops <= 2.0e10 && (flops <= 5.0e9 || wide >= 128);
+        if (d.dtype == CONV_BF16) return flops <= 2.0e10 && (flops <= 5.0e9 || wide >= 128) && tensors <= 1.4e8;
         if (wide >= 256 && narrow >= 32) return flops <= 2.0e10;
         return npix <= 524288.0;
     }
-    if (f.Q > 128 && (npix < 65536.0 || (d.dtype == CONV_BF16 && d.S == 7 && flops > 5.0e10))) return false;
+    if (f.Q > 128 && npix < 65536.0) return false;
+    if (d.dtype == CONV_BF16 && d.S == 7 && tensors > 1.4e8) return false;
     if (d.S == 5 && npix < 8192.0) return false;
     if (d.dtype == CONV_BF16) return !(d.stride > 1 && flops > 5.0e10);
     return !(d.R == 3 && d.S == 3 && d.stride == 1 && d.C % 64 == 0 && d.K % 64 == 0 && flops > 5.0e10);
