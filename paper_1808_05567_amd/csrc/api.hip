@@ -133,6 +133,10 @@ int max_band_rows(int N, int P, int TR, int Hs, int stride, int R)
     return (int)std::min<long long>(best, 1 << 30);
 }
 
+// Whether the forward and backward kernels' 32-bit byte offsets (and the 32-bit size of a buffer
+// resource) reach all of the weights; conv_create takes up to 2^31 of them, 8 GB in fp32.
+bool weights_reach(int Cb, int Kp, int R, int S) { return (double)Cb * R * S * Kp * 16 <= 4.0e9; }
+
 // One candidate plan of the implicit-GEMM kernel: `wk` waves along channels,
 // dynamic LDS at most `lds_cap` bytes.  Returns ok=false if nothing fits.
 IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S,
@@ -255,7 +259,7 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
     // 32-bit index guards (offsets are kept in 16-byte units / elements)
     // tensors are addressed with 32-bit byte offsets
     const double in_units = (double)N * Cb * H * W, out_units = (double)N * (Kp / V) * OH * OW;
-    if (in_units * 16 > 4.0e9 || out_units * 16 > 4.0e9) return pl;
+    if (in_units * 16 > 4.0e9 || out_units * 16 > 4.0e9 || !weights_reach(Cb, Kp, R, S)) return pl;
     // the kernels divide small indices through a float reciprocal, exact below 2^22
     if ((double)(N + 1) * std::max(Hs, P) >= 4.0e6 || a.LRW >= (1 << 22)) return pl;
     // ... and multiply row indices (image x channel block x row) as 24-bit integers
@@ -284,7 +288,7 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
     // 32-bit byte offsets, exact small divisions and 24-bit products, as in try_igemm
     const double in_units = (double)N * Cb * H * W, out_units = (double)N * (Kp / V) * OH * OW;
     const double shift = std::max(0.0, (double)pad_h * W + pad_w);
-    if ((in_units + shift) * 16 > 4.0e9 || out_units * 16 > 4.0e9) return pl;
+    if ((in_units + shift) * 16 > 4.0e9 || out_units * 16 > 4.0e9 || !weights_reach(Cb, Kp, R, S)) return pl;
     if ((double)N * P * Q + fm * 32 >= 4.0e6 || (double)R * S * Kp >= 8.0e6) return pl;
     if ((double)(N + 1) * std::max(Cb + 1, Kp / V) * std::max(H, OH) >= 8.0e6) return pl;
     IgemmArgs &a = pl.a;
