@@ -38,7 +38,7 @@ struct IgemmPlan {
     size_t lds = 0;
     int grid = 0;
     bool reg = false;  // the register-operand kernel (v.wk waves split the reduction of a tile)
-    bool fallback = false;  // ... because no staged tile fits
+    bool fallback = false;  // ... because no staged tile fits (IgemmGeo::fallback)
 };
 
 struct BwdClass {  // one stride-parity class of the generic backward pass
@@ -66,9 +66,9 @@ struct conv_plan {
     bool bwd_quad = false;  // four classes (2x2, 2x1, 1x2, 1x1 taps, in this order) in one launch
     BwdClass bwd[16];
     size_t bwd_ws = 0;
-    // (passes that would run untiled but for a kernel that takes a workspace: a caller that
-    // brings none still gets the untiled kernel)
-    bool bwd_ws_optional = false, upd_ws_optional = false;
+    // (a backward pass that would run untiled but for the register-operand kernel, which takes a
+    // workspace: a caller that brings none still gets the untiled kernel)
+    bool bwd_ws_optional = false;
     // weight update
     bool upd_ok = false;
     bool upd_c4 = false;   // few-channel formulation (one input channel block)
@@ -298,6 +298,8 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
     a.OH = OH; a.OW = OW; a.ostr = ostr; a.ostr_x = geo.ostr_x > 0 ? geo.ostr_x : ostr;
     a.oy0 = oy0; a.ox0 = ox0; a.zero_fill = zero_fill;
     a.out_kb = Kp / V;
+    a.exact = geo.fallback ? 1 : 0;
+    a.no_taps = geo.no_taps ? 1 : 0;
     a.inv_P = 1.0f / (float)(P * Q);
     a.inv_TQ = 1.0f / (float)Q;
     a.n_qt = 1;
@@ -324,6 +326,7 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
     pl.lds = igemm_reg_lds_bytes(fk, fm, nw);
     pl.grid = a.per_xcd * 8;
     pl.reg = true;
+    pl.fallback = geo.fallback;
     pl.ok = true;
     return pl;
 }
@@ -422,8 +425,10 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
                      int stride, int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0,
                      int zero_fill, const IgemmGeo &geo = IgemmGeo{}, bool may_split = false)
 {
-    IgemmPlan p = plan_igemm_tile(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr,
-                                  oy0, ox0, zero_fill, geo);
+    IgemmPlan p;
+    if (!geo.fallback)
+        p = plan_igemm_tile(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
+                            zero_fill, geo);
     // Results of few tiles: the smaller tiles, and the kernel that splits the reduction inside the
     // workgroup, where the estimate says they are at least 5 % faster.  The plans above that
     // were picked by measurement at N = 256 (eight waves, 128 x 256) stay, as does a first
@@ -442,7 +447,7 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
                 best_us = us;
             }
         };
-        for (int fk = 1; fk <= 2; ++fk)
+        for (int fk = 1; fk <= 2 && p.ok; ++fk)
             for (int npl = 8; npl >= 2; npl /= 2) {
                 if ((R * S == 1) != (npl > 2)) continue;
                 consider(try_igemm(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0,
@@ -455,12 +460,11 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
             consider(try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                              zero_fill, geo, k[0], k[1], k[2], k[3]));
         }
-        best.fallback = !p.ok;
         p = best;
     }
     // (CONVMI_IGEMM_REG="fk,fm,waves,ksplit": one variant of the register-operand kernel wherever it
     // exists; "0": never -- a tuning aid)
-    if (const char *env = getenv("CONVMI_IGEMM_REG")) {
+    if (const char *env = getenv("CONVMI_IGEMM_REG"); env && (p.ok || geo.fallback)) {
         int fk = 0, fm = 0, nw = 0, ks = 1;
         if (sscanf(env, "%d,%d,%d,%d", &fk, &fm, &nw, &ks) >= 3 && ks >= 1 && (ks == 1 || may_split)) {
             IgemmPlan c = try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
@@ -646,7 +650,6 @@ void plan_bwd_quad(conv_plan *p)
         cls[i].p = try_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, a.P, a.Q, R2, S2, 1, a.pad_h, a.pad_w, d.H, d.W, 2,
                              a.oy0, a.ox0, 0, IgemmGeo{}, 2, 2, 1, 2, (size_t)kMaxLds, 2, R2 * S2 == 1 ? 4 : 2, 1);
         if (!cls[i].p.ok) return;
-        cls[i].p.fallback = b->p.fallback;
         tiles += cls[i].p.a.total;
         cls[i].x.R2 = R2;
         cls[i].x.S2 = S2;
@@ -683,8 +686,10 @@ void plan_bwd(conv_plan *p)
         // the entry point without a workspace: a split reduction changes nothing for its callers.
         const size_t wt_b = ((size_t)f.Kb * d.R * d.S * f.Cp * f.vlen * es + 255) / 256 * 256;
         const size_t copy_b = (size_t)d.N * f.Cp * d.H * d.W * sizeof(float);
-        b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, d.H, d.W, d.R, d.S, 1, d.R - 1 - pad_h,
-                         d.S - 1 - pad_w, d.H, d.W, 1, 0, 0, 0, any_filter, wt_b + 4 * copy_b <= kScratchBytes);
+        for (const IgemmGeo &geo : {IgemmGeo{}, any_filter})
+            if (!b.p.ok)
+                b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, d.H, d.W, d.R, d.S, 1, d.R - 1 - pad_h,
+                                 d.S - 1 - pad_w, d.H, d.W, 1, 0, 0, 0, geo, wt_b + 4 * copy_b <= kScratchBytes);
         b.part_off = wt_b;
         b.x = WtXformArgs{nullptr, nullptr, f.Cb, f.Kb, f.Cp, f.Kp, d.R, d.S, d.R, d.S,
                           1, 0, 0, d.R, d.S};
@@ -772,48 +777,57 @@ void plan_bwd(conv_plan *p)
     const int R2 = ceil_div(d.R, st), S2 = ceil_div(d.S, st);
     size_t off = 0;
     int n = 0;
-    for (int py = 0; py < st; ++py)
-        for (int px = 0; px < st; ++px) {
-            const int ry = (py + pad_h) % st, rx = (px + pad_w) % st;
-            const int Rsub = ry < d.R ? ceil_div(d.R - ry, st) : 0;
-            const int Ssub = rx < d.S ? ceil_div(d.S - rx, st) : 0;
-            const int dy0 = (py + pad_h) / st, dx0 = (px + pad_w) / st;
-            const int Hsub = py < d.H ? ceil_div(d.H - py, st) : 0;
-            const int Wsub = px < d.W ? ceil_div(d.W - px, st) : 0;
-            if (Hsub == 0 || Wsub == 0) continue;
-            BwdClass &b = p->bwd[n];
-            // With no tap in the class the sub-filter is all zero and the
-            // launch writes zeros, which is what Algorithm 6 leaves there.
-            const int Re = std::max(Rsub, 1), Se = std::max(Ssub, 1);
-            // the class's own sub-filter extent where a kernel exists for it, else
-            // the common extent with zero taps
-            int R2c = Re, S2c = Se;
-            b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, Hsub, Wsub, R2c, S2c, 1,
-                             Re - 1 - dy0, Se - 1 - dx0, d.H, d.W, st, py, px, 0);
+    bool fallback = false;  // (every class on the same kind of kernel: staged, or the exact ones)
+    for (int cls = 0; cls < st * st; ++cls) {
+        const int py = cls / st, px = cls % st;
+        const int ry = (py + pad_h) % st, rx = (px + pad_w) % st;
+        const int Rsub = ry < d.R ? ceil_div(d.R - ry, st) : 0;
+        const int Ssub = rx < d.S ? ceil_div(d.S - rx, st) : 0;
+        const int dy0 = (py + pad_h) / st, dx0 = (px + pad_w) / st;
+        const int Hsub = py < d.H ? ceil_div(d.H - py, st) : 0;
+        const int Wsub = px < d.W ? ceil_div(d.W - px, st) : 0;
+        if (Hsub == 0 || Wsub == 0) continue;
+        BwdClass &b = p->bwd[n];
+        // With no tap in the class the sub-filter is all zero and the
+        // launch writes zeros, which is what Algorithm 6 leaves there.
+        const int Re = std::max(Rsub, 1), Se = std::max(Ssub, 1);
+        // the class's own sub-filter extent where a kernel exists for it, else
+        // the common extent with zero taps
+        int R2c = Re, S2c = Se;
+        auto plan = [&](const IgemmGeo &geo) {
+            b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, Hsub, Wsub, R2c, S2c, 1, Re - 1 - dy0,
+                             Se - 1 - dx0, d.H, d.W, st, py, px, 0, geo);
+        };
+        if (fallback) {
+            any_filter.no_taps = Rsub == 0 || Ssub == 0;
+            plan(any_filter);
+            if (!b.p.ok) return;
+        } else {
+            plan(IgemmGeo{});
             if (!b.p.ok) {
                 R2c = R2;
                 S2c = S2;
-                b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, Hsub, Wsub, R2c, S2c, 1,
-                                 Re - 1 - dy0, Se - 1 - dx0, d.H, d.W, st, py, px, 0);
+                plan(IgemmGeo{});
             }
-            if (!b.p.ok) {
-                R2c = Re;
-                S2c = Se;
-                b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, Hsub, Wsub, R2c, S2c, 1,
-                                 Re - 1 - dy0, Se - 1 - dx0, d.H, d.W, st, py, px, 0, any_filter);
+            if (!b.p.ok) {  // from the first class again
+                fallback = true;
+                cls = -1;
+                n = 0;
+                off = 0;
+                continue;
             }
-            if (!b.p.ok) return;
-            b.x = WtXformArgs{nullptr, nullptr, f.Cb, f.Kb, f.Cp, f.Kp, d.R, d.S, R2c, S2c,
-                              st, ry, rx, Rsub, Ssub};
-            if (Rsub == 0 || Ssub == 0) { b.x.Rsub = 0; b.x.Ssub = 0; }
-            b.ws_off = off;
-            off += (size_t)f.Kb * R2c * S2c * f.Cp * f.vlen * es;
-            ++n;
         }
+        b.x = WtXformArgs{nullptr, nullptr, f.Cb, f.Kb, f.Cp, f.Kp, d.R, d.S, R2c, S2c,
+                          st, ry, rx, Rsub, Ssub};
+        if (Rsub == 0 || Ssub == 0) { b.x.Rsub = 0; b.x.Ssub = 0; }
+        b.ws_off = off;
+        off += (size_t)f.Kb * R2c * S2c * f.Cp * f.vlen * es;
+        ++n;
+    }
     p->bwd_mode = 2;
     p->n_bwd = n;
     p->bwd_ws = off;
-    plan_bwd_quad(p);
+    if (!fallback) plan_bwd_quad(p);
 }
 
 // Weight update, bf16, at most 4 input channels: (tap, channel) rows on the bf16 MFMA.
@@ -1583,9 +1597,10 @@ void plan_upd(conv_plan *p)
         p->upd_ok = false;
         p->upd_ws = 0;
     }
-    // ... and over all but a first layer's, the ring kernel where it is the better one
-    const bool tiled = p->upd_ok;
-    if (!few && plan_upd_ring(p)) p->upd_ws_optional = !tiled;
+    // ... and over all but a first layer's, the ring kernel where it is the better one.  (Not where the
+    // update is left to the untiled loop: that leaves the taps outside the image out, where the tiled
+    // kernels multiply dO by zero, and an infinite dO would make the difference a NaN.)
+    if (!few && p->upd_ok) plan_upd_ring(p);
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -1699,12 +1714,16 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
         const IgemmPlan base = plan_igemm_tile(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride,
                                                pad_h, pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{});
         p->fwd_takes_ws = base.ok && base.a.total <= 128 && base.a.n_stage >= 4;
+        p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
+                            pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, p->fwd_takes_ws);
         // (a filter without a staged kernel: the register-operand kernel from 1e8 flops on; below, the
         // tests of the untiled kernels expect those)
-        IgemmGeo geo;
-        geo.fallback = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q >= 1.0e8;
-        p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
-                            pad_w, f.P, f.Q, 1, 0, 0, 0, geo, p->fwd_takes_ws);
+        if (!p->fwd.ok && (2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q >= 1.0e8 || getenv("CONVMI_IGEMM_REG"))) {
+            IgemmGeo any_filter;
+            any_filter.fallback = true;
+            p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
+                                pad_w, f.P, f.Q, 1, 0, 0, 0, any_filter);
+        }
         if (p->fwd.ok && p->fwd.a.ksplit > 1)
             p->fwd_ws = (size_t)p->fwd.a.ksplit * d.N * f.Kp * f.P * f.Q * sizeof(float);
         // A first layer (one channel block in, one reduction step, one channel tile): resident
@@ -1721,7 +1740,7 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
             if (const char *cap = getenv("CONVMI_STEM_WG"); cap && atoi(cap) > 0) p->fwd.a.jstep = atoi(cap);
         }
         plan_bwd(p);
-        for (int i = 0; i < p->n_bwd; ++i) p->bwd_ws_optional |= p->bwd[i].p.fallback;
+        p->bwd_ws_optional = p->bwd_mode != 0 && p->bwd[0].p.fallback;
         plan_upd(p);
     }
     // A pass without a tiled plan falls to the direct kernels (any filter, stride and pad).
@@ -1993,7 +2012,7 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
             return CONV_ELAUNCH;
         return CONV_OK;
     }
-    if (h->upd_direct || (h->upd_ws_optional && !ws)) {
+    if (h->upd_direct) {
         DirectArgs a = h->da;
         a.x = in;
         a.wt = dout;
@@ -2080,13 +2099,11 @@ static size_t pass_ws_bytes(const conv_plan *h, int pass)
     }
     return pass == 0 ? h->fwd_ws : pass == 1 ? h->bwd_ws : h->upd_ws;
 }
-// whether the pass runs without one too, on the untiled kernels (an update in chunks needs its slots)
-static bool ws_optional(const conv_plan *h, int pass)
+// whether the backward pass runs without one too, on the untiled kernel
+static bool bwd_ws_optional(const conv_plan *h)
 {
-    if (pass == 1 && h->bwd_chunked)
-        return ws_optional(h->chunk, 1) && (!h->tail || ws_optional(h->tail, 1) || h->tail->bwd_direct);
-    if (pass == 2 && h->upd_chunked) return false;
-    return pass == 1 ? h->bwd_ws_optional : pass == 2 && h->upd_ws_optional;
+    if (h->bwd_chunked) return bwd_ws_optional(h->chunk) && (!h->tail || bwd_ws_optional(h->tail));
+    return h->bwd_direct || h->bwd_ws_optional;
 }
 }  // namespace
 
@@ -2103,7 +2120,7 @@ conv_status_t conv_bwd_data_ws(conv_handle_t h, const void *dout, const void *wt
 {
     if (!h) return CONV_EINVAL;
     if (ws_bytes < pass_ws_bytes(h, 1)) {
-        if (!ws_optional(h, 1)) return CONV_EWORKSPACE;
+        if (!bwd_ws_optional(h)) return CONV_EWORKSPACE;
         ws = nullptr;
     }
     return conv_bwd_data(h, dout, wt, din, ws, stream);
@@ -2113,10 +2130,7 @@ conv_status_t conv_upd_ws(conv_handle_t h, const void *in, const void *dout, voi
                           size_t ws_bytes, void *stream)
 {
     if (!h) return CONV_EINVAL;
-    if (ws_bytes < pass_ws_bytes(h, 2)) {
-        if (!ws_optional(h, 2)) return CONV_EWORKSPACE;
-        ws = nullptr;
-    }
+    if (ws_bytes < pass_ws_bytes(h, 2)) return CONV_EWORKSPACE;
     return conv_upd(h, in, dout, dwt, ws, stream);
 }
 
@@ -2154,7 +2168,7 @@ conv_status_t conv_bwd_data_noalloc(conv_handle_t h, const void *dout, const voi
 {
     if (!h || !dout || !wt || !din) return CONV_EINVAL;
     if (pass_ws_bytes(h, 1) > kScratchBytes)
-        return ws_optional(h, 1) ? conv_bwd_data(h, dout, wt, din, nullptr, stream) : CONV_ESCRATCH;
+        return bwd_ws_optional(h) ? conv_bwd_data(h, dout, wt, din, nullptr, stream) : CONV_ESCRATCH;
     void *ptr = scratch_of_current_device();
     if (!ptr) return CONV_ELAUNCH;
     return conv_bwd_data(h, dout, wt, din, ptr, stream);

@@ -79,13 +79,18 @@ struct IgemmArgs {
     const void *resid;  // tensor of the output's layout and type added to the result, or null
     int relu;           // clamp at zero after the additions
     int R, S;           // filter extent (the register-operand kernel takes it at run time)
+    int exact;          // register-operand kernel: taps outside the image contribute nothing, not zero times
+                        // the weight (which is NaN where the weight is infinite), as on the untiled loops
+    int no_taps;        // ... and this launch has no tap inside anywhere: a class of zeros
 };
 
 // Optional geometry of a plan beyond the plain convolution's (0: as the strides say).
 struct IgemmGeo {
     int cstride = 0;  // IgemmArgs::cstride
     int ostr_x = 0;   // IgemmArgs::ostr_x
-    bool fallback = false;  // where no staged tile fits: the register-operand kernel, whatever the size
+    bool fallback = false;  // no staged tile fits: the register-operand kernel, whatever the size, in its
+                            // exact form
+    bool no_taps = false;   // IgemmArgs::no_taps
 };
 
 // Key of a kernel instantiation; the host picks one per pass at plan time.

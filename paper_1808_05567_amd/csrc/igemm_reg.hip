@@ -25,8 +25,46 @@
 
 namespace convmi {
 
+template <int DT>
+__device__ __forceinline__ float widened(const void *base, size_t i)
+{
+    if constexpr (DT == CONV_BF16)
+        return __builtin_bit_cast(float, (unsigned)static_cast<const unsigned short *>(base)[i] << 16);
+    else
+        return static_cast<const float *>(base)[i];
+}
+
+// Four consecutive channels of one pixel, krow .. krow + 3 at (n, oj, oi), summed over steps [u0, u1) one
+// product at a time, taps outside the image left out (EXACT kernels, where the MFMAs' sum is NaN).
+template <int DT>
+__device__ __forceinline__ f32x4 sum_inside_image(const IgemmArgs &a, int n, int oj, int oi, int krow, int u0, int u1)
+{
+    constexpr int V = Elem<DT>::V;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    if (a.no_taps) return sum;
+    const int RS = a.R * a.S;
+    for (int u = u0; u < u1; ++u) {
+        const int cp = u / RS, tap = u - cp * RS, r = tap / a.S, s = tap - r * a.S;
+        const int y = oj * a.stride - a.pad_h + r, x = oi * a.cstride - a.pad_w + s;
+        if (y < 0 || y >= a.H || x < 0 || x >= a.W) continue;
+        for (int cb = 2 * cp; cb < min(2 * cp + 2, a.Cb); ++cb) {
+            const size_t in = ((size_t)n * a.Cb + cb) * a.H * a.W + (size_t)y * a.W + x;
+            const size_t wt = ((size_t)cb * RS + tap) * a.Kp + krow;
+            for (int c = 0; c < V; ++c) {
+                const float v = widened<DT>(a.in, in * V + c);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) sum[t] = fmaf(v, widened<DT>(a.wt, (wt + t) * V + c), sum[t]);
+            }
+        }
+    }
+    return sum;
+}
+
 // FK x FM accumulator tiles per wave, NW waves that split the reduction, D steps in flight.
-template <int DT, int FK, int FM, int NW, int D>
+// EXACT: for layers that would else run on the untiled loops, which leave the taps outside the image
+// out.  Here such a tap multiplies a weight by zero, which an infinite or NaN weight turns into NaN; a
+// sum that is NaN is therefore formed again without them.
+template <int DT, int FK, int FM, int NW, int D, bool EXACT>
 __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kernel(const IgemmArgs a)
 {
     using E_ = Elem<DT>;
@@ -200,6 +238,10 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
             const int oj = fast_div(rem, inv_Q);
             const int oi = rem - mul24(oj, a.Q);
             bool ok = m < npix && krow < a.Kp;
+            if constexpr (EXACT) {
+                if (ok && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]))
+                    v = sum_inside_image<DT>(a, n, oj, oi, krow, sbeg, sbeg + nst);
+            }
             int oy = mul24(oj, a.ostr) + a.oy0, ox = mul24(oi, a.ostr_x) + a.ox0, kb = krow / V;
             if (a.shuffle) {  // the channel block is a position of the ostr x ostr_x cell
                 const int cy = kb / a.ostr_x;
@@ -247,10 +289,11 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
     }
 }
 
-#define REG_ENTRY(DT, FK, FM, NW, D) {DT, FK, FM, NW, D, igemm_reg_kernel<DT, FK, FM, NW, D>}
+#define REG_ENTRY(DT, FK, FM, NW, D) \
+    {DT, FK, FM, NW, D, igemm_reg_kernel<DT, FK, FM, NW, D, false>, igemm_reg_kernel<DT, FK, FM, NW, D, true>}
 static const struct RegEntry {
     int dtype, fk, fm, nw, depth;
-    igemm_fn_t fn;
+    igemm_fn_t fn, exact_fn;
 } g_reg[] = {
     REG_ENTRY(CONV_F32, 1, 1, 4, 4),  REG_ENTRY(CONV_F32, 1, 1, 8, 3),  REG_ENTRY(CONV_F32, 2, 1, 8, 3),
     REG_ENTRY(CONV_F32, 1, 2, 4, 3),  REG_ENTRY(CONV_F32, 2, 2, 4, 3),
@@ -280,9 +323,10 @@ hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid,
     for (const RegEntry &e : g_reg) {
         if (e.dtype != v.dtype || e.fk != v.fk || e.fm != v.fm || e.nw != v.wk) continue;
         const size_t lds = igemm_reg_lds_bytes(e.fk, e.fm, e.nw);
-        if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(e.fn), lds); err != hipSuccess)
+        const igemm_fn_t fn = a.exact ? e.exact_fn : e.fn;
+        if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(fn), lds); err != hipSuccess)
             return err;
-        hipLaunchKernelGGL(e.fn, dim3(grid), dim3(e.nw * 64), lds, stream, a);
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(e.nw * 64), lds, stream, a);
         return hipGetLastError();
     }
     return hipErrorInvalidDeviceFunction;
