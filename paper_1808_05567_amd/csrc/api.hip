@@ -1629,7 +1629,12 @@ conv_status_t conv_create(const conv_desc_t *desc, conv_handle_t *out)
 }
 
 namespace {
-bool all_tiled(const conv_plan *q) { return q->fwd.ok && q->bwd_mode != 0 && q->upd_ok; }
+// Whether every pass has a kernel of its own; `staged`: without the register-operand kernel in the untiled
+// loops' place.
+bool all_tiled(const conv_plan *q, bool staged)
+{
+    return q->fwd.ok && q->bwd_mode != 0 && q->upd_ok && !(staged && (q->fwd.fallback || q->bwd_ws_optional));
+}
 conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w, int32_t max_images,
                           conv_handle_t *out);
 }  // namespace
@@ -1766,26 +1771,34 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
     // and more, which the tiled kernels' 32-bit byte offsets do not reach, or minibatches
     // whose linear row indices pass the kernels' exact-division range: the fewest equal
     // chunks whose plans are all tiled, for the passes that would else run untiled.
+    // `staged`: those plans do without the register-operand kernel in the untiled loops' place.  If there
+    // are none, chunks serve only the passes that this kernel takes (`exact`): the others, the
+    // update above all, stay on the untiled loops, with their treatment of infinities and no workspace.
     int nc = 0;
     const bool forced = max_images > 0;
+    bool exact = false;
     if (forced) {
         if (max_images < d.N) nc = max_images;
-    } else if (max_images == 0 && d.N >= 2 && !all_tiled(p) &&
+    } else if (max_images == 0 && d.N >= 2 && !all_tiled(p, true) &&
                ((double)std::max(f.in_bytes, f.out_bytes) >= 4.0e9 ||
                 (double)(d.N + 1) * std::max(d.H + 2 * pad_h, f.P) * std::max(f.Cb, f.Kb) >= 4.0e6)) {
-        // (if one image alone has no tiled plan, no chunk has)
-        conv_desc_t d1 = d;
-        d1.N = 1;
-        conv_handle_t q1 = nullptr;
-        const bool any = create_plan(&d1, pad_h, pad_w, -1, &q1) == CONV_OK && all_tiled(q1);
-        delete q1;
-        for (int k = 2; any && k <= 64 && k <= d.N && nc == 0; ++k) {
-            conv_desc_t dd = d;
-            dd.N = ceil_div(d.N, k);
-            conv_handle_t q = nullptr;
-            if (create_plan(&dd, pad_h, pad_w, -1, &q) != CONV_OK) break;
-            if (all_tiled(q)) nc = dd.N;
-            delete q;
+        for (const bool staged : {true, false}) {
+            // (if one image alone has no tiled plan, no chunk has)
+            conv_desc_t d1 = d;
+            d1.N = 1;
+            conv_handle_t q1 = nullptr;
+            const bool any = create_plan(&d1, pad_h, pad_w, -1, &q1) == CONV_OK && (!staged || all_tiled(q1, true));
+            delete q1;
+            for (int k = 2; any && k <= 64 && k <= d.N && nc == 0; ++k) {
+                conv_desc_t dd = d;
+                dd.N = ceil_div(d.N, k);
+                conv_handle_t q = nullptr;
+                if (create_plan(&dd, pad_h, pad_w, -1, &q) != CONV_OK) break;
+                if (all_tiled(q, staged)) nc = dd.N;
+                delete q;
+            }
+            exact = nc > 0 && !staged;
+            if (nc > 0) break;
         }
     }
     if (nc > 0) {
@@ -1803,9 +1816,12 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
         }
         p->n_chunks = n_chunks;
         p->chunk_n = nc;
-        p->fwd_chunked = forced || !p->fwd.ok;
-        p->bwd_chunked = forced || p->bwd_mode == 0;
-        p->upd_chunked = forced || !p->upd_ok;
+        auto all = [&](auto &&f) { return f(p->chunk) && (!p->tail || f(p->tail)); };
+        p->fwd_chunked = forced || (exact ? !p->fwd.ok && all([](const conv_plan *q) { return q->fwd.fallback || q->fwd_direct; })
+                                          : !p->fwd.ok || p->fwd.fallback);
+        p->bwd_chunked = forced || (exact ? p->bwd_mode == 0 && all([](const conv_plan *q) { return q->bwd_ws_optional || q->bwd_direct; })
+                                          : p->bwd_mode == 0 || p->bwd_ws_optional);
+        p->upd_chunked = forced || (!exact && !p->upd_ok);
         if (p->fwd_chunked) p->fwd_direct = false, p->fwd_ws = 0;
         if (p->bwd_chunked) p->bwd_direct = false, p->bwd_ws = 0;
         if (p->upd_chunked) p->upd_direct = false, p->upd_ws = 0;
