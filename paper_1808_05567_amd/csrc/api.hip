@@ -58,7 +58,6 @@ struct conv_plan {
     conv_info_t info;
     IgemmPlan fwd;
     size_t fwd_ws = 0;  // bytes of fp32 partial results if the forward reduction is split
-    bool fwd_takes_ws = false;  // a result of few tiles: a NULL workspace is refused, split or not
     size_t fwd_stem_lds = 0;  // > 0: the plain forward pass runs on the resident-filter kernel (its LDS)
     // backward by data
     int bwd_mode = 0;  // 0 unsupported, 1 one launch (duality), 2 parity classes
@@ -1715,12 +1714,11 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
     if (tiled_domain) {
         // Few tiles and a long reduction (small minibatch, inference): the reduction may be split
         // over workgroups too, fp32 partial results in the workspace, summed in a fixed order.
-        // Such a layer's caller brings a workspace, whatever plan it ends up with.
         const IgemmPlan base = plan_igemm_tile(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride,
                                                pad_h, pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{});
-        p->fwd_takes_ws = base.ok && base.a.total <= 128 && base.a.n_stage >= 4;
+        const bool few_tiles = base.ok && base.a.total <= 128 && base.a.n_stage >= 4;
         p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
-                            pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, p->fwd_takes_ws);
+                            pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, few_tiles);
         // (a filter without a staged kernel: the register-operand kernel from 1e8 flops on; below, the
         // tests of the untiled kernels expect those)
         if (!p->fwd.ok && (2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q >= 1.0e8 || getenv("CONVMI_IGEMM_REG"))) {
@@ -1893,7 +1891,7 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     if (!h->fwd.ok) return CONV_EUNSUPPORTED;
     IgemmArgs a = h->fwd.a;
     const bool split = a.ksplit > 1;
-    if (h->fwd_takes_ws && !ws) return CONV_EWORKSPACE;
+    if (split && !ws) return CONV_EWORKSPACE;
     a.in = in;
     a.wt = wt;
     a.out = split ? ws : out;
