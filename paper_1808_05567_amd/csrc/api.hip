@@ -132,6 +132,26 @@ int max_band_rows(int N, int P, int TR, int Hs, int stride, int R)
     return (int)std::min<long long>(best, 1 << 30);
 }
 
+// Rounding error of fp32 sums, as far as comparing two orders of the same sum goes: a chain of n additions of
+// random terms has an error variance of n/2 in units of one rounding of its result, and the levels of a
+// sum add up.  (A chain's additions are its products in fp32, of which an MFMA rounds each, and its MFMAs in
+// bf16, which round once.)  A kernel that takes a launch over from another one may not have the larger error: it sums
+// in groups where one chain would be too long, or stays out.  (Measured over 75 layers at N = 1 ... 160 against
+// 64 bits: the ratio of two orders' errors is within 20 % of the root of the ratio of these figures, and
+// nearer to 1 where both are small, where the result's own rounding counts: a half.  Groups aim
+// below the old figure by that much, a plan that cannot reach this is taken up to the old figure.)
+constexpr double kErrorMargin = 0.7, kOwnRounding = 0.5;
+double chain_error(double n, double group) { return group > 0 && n > group ? group / 2 + n / (2 * group) : n / 2; }
+// The largest group, in whole units of `unit` additions, with which n additions stay within `most` (the best
+// one if none does); 0 if one chain does.
+int group_within(double n, double unit, double most)
+{
+    if (n / 2 <= most) return 0;
+    const double root = most * most - n;
+    const double g = root > 0 ? (most + std::sqrt(root)) / unit : std::sqrt(n) / unit + 0.5;
+    return std::max(1, (int)g);
+}
+
 // Whether the forward and backward kernels' 32-bit byte offsets (and the 32-bit size of a buffer
 // resource) reach all of the weights; conv_create takes up to 2^31 of them, 8 GB in fp32.
 bool weights_reach(int Cb, int Kp, int R, int S) { return (double)Cb * R * S * Kp * 16 <= 4.0e9; }
@@ -420,9 +440,36 @@ IgemmPlan plan_igemm_tile(int dtype, int N, int Cb, int H, int W, int Kp, int P,
                           int stride, int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0,
                           int zero_fill, const IgemmGeo &geo);
 
+// fp32: whether the error of a plan's sums stays within `most`, with the group that sees to it (set in the
+// plan's arguments).
+bool sums_within(IgemmPlan &p, double most)
+{
+    IgemmArgs &a = p.a;
+    double n, unit, rest = a.ksplit > 1 ? a.ksplit / 2.0 : 0;
+    if (p.reg) {
+        n = 8.0 * ceil_div(a.st_per, p.v.wk);
+        unit = 8.0 * igemm_reg_depth(p.v.dtype, p.v.fk, p.v.fm, p.v.wk);
+        rest += std::log2((double)p.v.wk) / 2;
+    } else {
+        unit = 4.0 * p.v.npl * p.v.r * p.v.s;
+        n = unit * a.n_stage;
+    }
+    if (p.reg || igemm_variant_groups(p.v)) a.group = group_within(n, unit, kErrorMargin * most - rest);
+    return chain_error(n, a.group * unit) + rest <= most + kOwnRounding;
+}
+
+// (CONVMI_IGEMM_GROUP: steps or rounds that are summed apart, wherever the kernel can -- for tests)
+IgemmPlan with_group(IgemmPlan p)
+{
+    const char *env = getenv("CONVMI_IGEMM_GROUP");
+    if (env && p.ok && p.v.dtype == CONV_F32 && (p.reg ? !p.fallback : igemm_variant_groups(p.v))) p.a.group = atoi(env);
+    return p;
+}
+
+// most_error > 0: the rounding error that the plan's sums may have (fp32).
 IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S,
                      int stride, int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0,
-                     int zero_fill, const IgemmGeo &geo = IgemmGeo{}, bool may_split = false)
+                     int zero_fill, const IgemmGeo &geo = IgemmGeo{}, bool may_split = false, double most_error = 0)
 {
     IgemmPlan p;
     if (!geo.fallback)
@@ -436,9 +483,10 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
     if (p.ok ? !measured && !getenv("CONVMI_IGEMM_CAND") && igemm_stem_lds(p.v, p.a) == 0 : geo.fallback) {
         const bool scatter = zero_fill != 0;
         IgemmPlan best = p;
-        double best_us = p.ok ? 0.95 * estimate_us(p, scatter) : 1e30;
-        auto consider = [&](const IgemmPlan &c) {
-            if (!c.ok) return;
+        const bool exact_enough = p.ok && (most_error <= 0 || sums_within(best, most_error));
+        double best_us = exact_enough ? 0.95 * estimate_us(p, scatter) : 1e30;
+        auto consider = [&](IgemmPlan c) {
+            if (!c.ok || (most_error > 0 && !sums_within(c, most_error))) return;
             const double us = estimate_us(c, scatter);
             // (of two staged ones bound by memory alike, where tiles abound, the one that reads its input less often)
             if (us < best_us || (us == best_us && !c.reg && !best.reg && c.v.fk > best.v.fk && c.a.total >= 768)) {
@@ -468,9 +516,11 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
         if (sscanf(env, "%d,%d,%d,%d", &fk, &fm, &nw, &ks) >= 3 && ks >= 1 && (ks == 1 || may_split)) {
             IgemmPlan c = try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                                   zero_fill, geo, fk, fm, nw, ks);
-            if (c.ok) return c;
+            if (c.ok && most_error > 0) sums_within(c, most_error);
+            if (c.ok) return with_group(c);
         }
     }
+    p = with_group(p);
     // One channel tile: every line of the input is staged by exactly one workgroup.  Loaded
     // non-temporally it does not displace the weights in the L2 nor settle in the last-level
     // cache on its way past.  The same with two channel tiles side by side on an XCD, as long as
@@ -1413,12 +1463,44 @@ void plan_upd_general(conv_plan *p)
 // with a ring of `depth` stages each, the pixel list in `splits` parts.
 struct RingCand {
     int fc, fk, nw, depth, splits;
+    int sum;  // the kernel's summation
 };
+// Error of the sums of the update that is planned, its partial copies added in eight chains, ascending.
+double planned_upd_error(const conv_plan *p)
+{
+    const UpdArgs &a = p->ua;
+    double pixels, waves = 1;
+    if (p->upd_flat || p->upd_flat_bf16) {
+        pixels = a.rows_per_split;
+        waves = p->upd_flat ? 4 / p->upd_wb : p->urv.wp;
+    } else {
+        pixels = (double)a.rows_per_split * std::min(p->info.Q, p->upd_strips > 1 ? p->upd_strip_w : p->info.Q);
+        if (p->upd_rows) waves = p->urv.wp;
+        if (p->upd_bands) waves = p->upd_bands_layout == 0 ? 2 : p->upd_bands_layout == 1 ? 4 : 8;
+    }
+    pixels = std::min(pixels, (double)p->d.N * p->info.P * p->info.Q) / waves;
+    const int c = p->upd_copies;
+    return chain_error(pixels / (p->d.dtype == CONV_BF16 ? 16 : 1), 0) + (p->upd_rows || waves == 1 ? 0 : waves / 2) +
+           (c > 1 ? ceil_div(c, 8) / 2.0 + std::min(8, c) / 2.0 : 0);
+}
+// ... and of the ring kernel's, in the summation c.sum; sets its group.
+double ring_error(const conv_plan *p, const RingCand &c, UpdArgs &a, double most)
+{
+    const bool bf16 = p->d.dtype == CONV_BF16;
+    const int chains = a.splits <= 8 ? 1 : a.splits <= 64 ? 8 : 32;  // (see launch_upd_reduce)
+    const double n = (double)ceil_div(a.rows_per_split, c.nw) / (bf16 ? 16 : 1), unit = c.depth * (bf16 ? 1.0 : 8.0);
+    // (waves without a pixel add zeros)
+    const int waves = std::min(c.nw, ceil_div(std::min(a.rows_per_split, p->d.N * a.P * a.Q), bf16 ? 16 : 8));
+    const double rest = std::log2((double)waves) / 2 +
+                        (a.splits > 1 ? ceil_div(a.splits, chains) / 2.0 + std::log2((double)chains) / 2 : 0);
+    a.group = c.sum == 1 ? std::max(1, group_within(n, unit, kErrorMargin * most - rest)) : 0;
+    return rest + chain_error(n, c.sum == 0 ? 0 : c.sum == 1 ? a.group * unit : 8);
+}
 bool plan_ring(const conv_plan *p, const RingCand &c, UpdArgs &a)
 {
     const conv_desc_t &d = p->d;
     const conv_info_t &f = p->info;
-    if (!upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth)) return false;
+    if (!upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth, c.sum)) return false;
     const double npix = (double)d.N * f.P * f.Q;
     // exact small divisions, 24-bit products, 32-bit byte offsets
     if (npix >= 3.9e6 || (double)(d.N + 1) * std::max(f.Cb, f.Kb) >= 8.0e6 || (double)d.H * d.W >= 8.0e6 ||
@@ -1462,11 +1544,14 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
     const int tiles = d.S * c.fc * c.fk, ops = d.S * c.fc + c.fk;
     const double mfma = tiles * (bf16 ? 32.0 : 256.0);
     const double stages = ceil_div(ceil_div(a.rows_per_split, c.nw * (bf16 ? 16 : 8)), c.depth) * c.depth;
-    const double shared = std::max(mfma * q.c_mfma * c.nw / 4, ops * c.nw * 16 * q.c_load);
+    const double shared = std::max(mfma * q.c_mfma * c.nw / 4, ops * c.nw * 16 * q.c_load) *
+                          (c.sum == 0 ? 1.0 : c.sum == 1 ? 1.03 : 1.14);
     const double lone = q.fixed + stages * std::max(shared, mfma * q.c_mfma + q.stage + ops * q.per_op) + q.exch * tiles * c.nw;
     const double busy = stages * shared + q.exch * tiles * c.nw;
     // workgroups a CU holds: LDS, and registers (16 per tile, and what the operands take)
-    const int regs = 16 * tiles + (bf16 ? 4 : 3) * ops + 40;
+    int regs = 16 * tiles + (bf16 ? 4 : 3) * ops + 40;
+    if (c.sum > 0) regs += c.sum == 1 ? 16 * tiles : tiles > 1 && tiles <= 8 ? 32 : 16;
+    if (c.sum == 1 && tiles <= 3) regs = std::min(regs, 128);  // (launch bounds)
     const int resident = std::max(1, std::min((int)(kMaxLds / upd_ring_lds_bytes(d.S, c.fc, c.fk, c.nw, c.depth)),
                                               std::min(8, 512 / regs) * 4 / c.nw));
     const int per_cu = ceil_div(a.per_xcd * 8, 256), full = per_cu / resident, rest = per_cu - full * resident;
@@ -1528,9 +1613,24 @@ bool plan_upd_ring(conv_plan *p)
     UpdArgs best_a{};
     double best_us = 0;
     bool have = false;
+    const double most_error = planned_upd_error(p);
+    int force = -1, group = 0;
     auto consider = [&](RingCand c) {
         UpdArgs a;
+        c.sum = std::max(0, force);
         if (!plan_ring(p, c, a)) return;
+        double error = ring_error(p, c, a, most_error);
+        if (force < 0) {
+            // one chain where it is exact enough (summing apart costs 1 - 5 % in groups, 6 - 18 % by the stage)
+            const int apart = upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth, 1) ? 1
+                              : upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth, 2) ? 2 : 0;
+            if (apart > 0 && error > (apart == 1 ? kErrorMargin : 0.9) * most_error + kOwnRounding) {
+                c.sum = apart;
+                error = ring_error(p, c, a, most_error);
+            }
+            if (error > most_error + kOwnRounding) return;
+        }
+        if (group > 0) a.group = group;
         const double us = ring_estimate_us(p, c, a);
         if (!have || us < best_us) {
             best = c;
@@ -1539,10 +1639,12 @@ bool plan_upd_ring(conv_plan *p)
             have = true;
         }
     };
-    // (CONVMI_UPD_RING="fc,fk,waves,depth,splits": one variant wherever it exists; "0": never -- a tuning aid)
+    // (CONVMI_UPD_RING="fc,fk,waves,depth,splits[,sum[,group]]": one variant wherever it exists, in one chain unless
+    // another summation is asked for; "0": never -- a tuning aid)
     if (const char *env = getenv("CONVMI_UPD_RING")) {
         RingCand c{};
-        if (sscanf(env, "%d,%d,%d,%d,%d", &c.fc, &c.fk, &c.nw, &c.depth, &c.splits) != 5) return false;
+        force = 0;
+        if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &c.fc, &c.fk, &c.nw, &c.depth, &c.splits, &force, &group) < 5) return false;
         consider(c);
     } else if (ring_applies(p)) {
         for (const auto &k : kBlocks) {
@@ -1551,15 +1653,15 @@ bool plan_upd_ring(conv_plan *p)
             if (d.R * d.S == 1 && k[0] == 1 &&
                 (double)f.in_bytes + (double)f.out_bytes > (d.dtype == CONV_BF16 ? 64.0e6 : 100.0e6))
                 continue;
-            consider({k[0], k[1], k[2], k[3], 1});
-            consider({k[0], k[1], k[2], k[3], std::max(1, 256 / tiles)});
-            if (d.S == 3) consider({k[0], k[1], k[2], k[3], std::max(1, 512 / tiles)});
+            consider({k[0], k[1], k[2], k[3], 1, 0});
+            consider({k[0], k[1], k[2], k[3], std::max(1, 256 / tiles), 0});
+            if (d.S == 3) consider({k[0], k[1], k[2], k[3], std::max(1, 512 / tiles), 0});
         }
     }
     if (!have || (double)best_a.splits * f.dwt_bytes > std::max(2.0 * ((double)f.in_bytes + (double)f.out_bytes), 8.0e9))
         return false;
     p->ua = best_a;
-    p->urv = UpdRowsVariant{d.R, d.S, 1, best.depth, best.nw, best.fc, best.fk, 0};
+    p->urv = UpdRowsVariant{d.R, d.S, 1, best.depth, best.nw, best.fc, best.fk, best.sum};
     p->upd_lds = upd_ring_lds_bytes(d.S, best.fc, best.fk, best.nw, best.depth);
     p->upd_grid = best_a.per_xcd * 8;
     p->upd_copies = best_a.splits;
@@ -1717,8 +1819,14 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
         const IgemmPlan base = plan_igemm_tile(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride,
                                                pad_h, pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{});
         const bool few_tiles = base.ok && base.a.total <= 128 && base.a.n_stage >= 4;
+        // (what that sum's error is in the large tiles, split for 512 workgroups)
+        double most_error = 0;
+        if (few_tiles && d.dtype == CONV_F32) {
+            const int per = ceil_div(base.a.n_stage, std::min(base.a.n_stage / 2, 512 / base.a.total));
+            most_error = chain_error(4.0 * base.v.npl * d.R * d.S * per, 0) + ceil_div(base.a.n_stage, per) / 2.0;
+        }
         p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
-                            pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, few_tiles);
+                            pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, few_tiles, most_error);
         // (a filter without a staged kernel: the register-operand kernel from 1e8 flops on; below, the
         // tests of the untiled kernels expect those)
         if (!p->fwd.ok && (2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q >= 1.0e8 || getenv("CONVMI_IGEMM_REG"))) {
@@ -2043,7 +2151,7 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
     hipError_t e = hipSuccess;
     if (h->upd_ring) {
         if (a.splits == 1) a.partial = static_cast<float *>(dwt);
-        e = launch_upd_ring(h->d.dtype, h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, a, h->upd_grid, s);
+        e = launch_upd_ring(h->d.dtype, h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, h->urv.strided, a, h->upd_grid, s);
         if (a.splits == 1) return e == hipSuccess ? CONV_OK : CONV_ELAUNCH;
     } else if (h->upd_flat_bf16)
         e = launch_upd_bf16_1x1(h->urv, a, h->upd_grid, s);
@@ -2273,17 +2381,17 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         if (p->reg) {
             snprintf(buf, buflen,
                      "igemm_reg dt=%d waves=%d frags=%dx%d RS=%dx%d tiles=%d (m=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu "
-                     "steps=%d ksplit=%d launches=%d",
+                     "steps=%d group=%d ksplit=%d launches=%d",
                      p->v.dtype, p->v.wk, p->v.fk, p->v.fm, p->v.r, p->v.s, p->a.total, p->a.n_mt, p->a.n_kt,
-                     p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
+                     p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.group, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
             return CONV_OK;
         }
         snprintf(buf, buflen,
                  "igemm dt=%d waves=%dx%d frags=%dx%d npl=%d nt=%d RS=%dx%d ppt=%d TR=%d TQ=%d tiles=%d "
-                 "(m=%d q=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu stages=%d ksplit=%d launches=%d",
+                 "(m=%d q=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu stages=%d group=%d ksplit=%d launches=%d",
                  p->v.dtype, p->v.wk, p->v.wm, p->v.fk, p->v.fm, p->v.npl, p->v.nt, p->v.r, p->v.s, p->v.ppt,
                  p->a.TR, p->a.TQ, p->a.total, p->a.n_mt, p->a.n_qt, p->a.n_kt, p->a.gk, p->grid, p->lds,
-                 p->a.n_stage, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
+                 p->a.n_stage, p->a.group, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
         if (pass == 0 && h->fwd_stem_lds) {
             const size_t n = strlen(buf);
             snprintf(buf + n, buflen - n, " resident_filter_lds=%zu", h->fwd_stem_lds);
@@ -2294,11 +2402,11 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         if (!h->upd_ok) return CONV_EUNSUPPORTED;
         if (h->upd_ring) {
             snprintf(buf, buflen,
-                     "%s dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d pixels/split=%d splits=%d tiles=%dx%dx%d grid=%d "
-                     "lds=%zu launches=1",
+                     "%s dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d sum=%d group=%d pixels/split=%d splits=%d tiles=%dx%dx%d "
+                     "grid=%d lds=%zu launches=1",
                      h->d.R * h->d.S == 1 ? "upd_1x1" : "upd_rows1", (int)h->d.dtype, h->d.R, h->d.S, h->urv.wp,
-                     h->urv.wk, h->urv.fc, h->urv.fk, h->ua.rows_per_split, h->ua.splits, h->ua.n_ct, h->ua.n_kt,
-                     h->d.R, h->upd_grid, h->upd_lds);
+                     h->urv.wk, h->urv.fc, h->urv.fk, h->urv.strided, h->ua.group, h->ua.rows_per_split, h->ua.splits,
+                     h->ua.n_ct, h->ua.n_kt, h->d.R, h->upd_grid, h->upd_lds);
             return CONV_OK;
         }
         if (h->upd_flat_bf16) {

@@ -81,6 +81,8 @@ struct IgemmArgs {
     int R, S;           // filter extent (the register-operand kernel takes it at run time)
     int exact;          // register-operand kernel: taps outside the image contribute nothing, not zero times
                         // the weight (which is NaN where the weight is infinite), as on the untiled loops
+    int group;          // fp32: steps (staged kernel), or rounds of its steps in flight (register-operand
+                        // kernel), that are summed apart; 0: the whole reduction in one chain
     int no_taps;        // ... and this launch has no tap inside anywhere: a class of zeros
 };
 
@@ -119,6 +121,8 @@ struct IgemmQuadArgs {
 };
 hipError_t launch_igemm_quad(int dtype, const IgemmQuadArgs &q, size_t lds_bytes, hipStream_t stream);
 bool igemm_variant_exists(const IgemmVariant &v);
+// Whether the variant can sum its steps in groups (IgemmArgs::group).
+bool igemm_variant_groups(const IgemmVariant &v);
 // Bit p is set where the variant (default input policy) exists with p staged pixels per thread.
 unsigned igemm_variant_ppts(const IgemmVariant &v);
 // The register-operand kernel for results of few tiles (any filter extent): a tile of fk*32
@@ -203,6 +207,7 @@ struct UpdArgs {
     int live_ch;     // few-channel fp32 kernel: input channels that exist (1..4)
     int runs;        // bf16 row kernel: 8-pixel runs per output row
     int Qp;          // fp32 kernel: row pitch of the staged dO band (pixels)
+    int group;       // ring kernel: rounds of its stages that are summed apart (its summation 1)
 };
 struct UpdVariant {
     int dtype;
@@ -242,12 +247,13 @@ hipError_t launch_upd_bf16_1x1(const UpdRowsVariant &v, const UpdArgs &a, int gr
 // per split, a multiple of 32; n_ct / n_kt = tiles over input / output channels)
 size_t upd_f32_1x1_lds_bytes(int wb);
 hipError_t launch_upd_f32_1x1(int wb, bool a_is_in, const UpdArgs &a, int grid, hipStream_t stream);
-// Filters with S columns in {1, 3, 7}: blocks of fc*32 x fk*32
-// channels x one filter row, nw waves that split the pixels, a ring of `depth` stages each (UpdArgs::rows_per_split = pixels
+// Filters with S columns in {1, 3, 5, 7}: blocks of fc*32 x fk*32 channels x one filter row, nw waves
+// that split the pixels, a ring of `depth` stages each, summation `sum` (UpdArgs::rows_per_split = pixels
 // per split; one split: UpdArgs::partial is dW itself)
-bool upd_ring_exists(int dtype, int s, int fc, int fk, int nw, int depth);
+bool upd_ring_exists(int dtype, int s, int fc, int fk, int nw, int depth, int sum);
 size_t upd_ring_lds_bytes(int s, int fc, int fk, int nw, int depth);
-hipError_t launch_upd_ring(int dtype, int fc, int fk, int nw, int depth, const UpdArgs &a, int grid, hipStream_t stream);
+hipError_t launch_upd_ring(int dtype, int fc, int fk, int nw, int depth, int sum, const UpdArgs &a, int grid,
+                           hipStream_t stream);
 // at most 4 input channels: filter-row formulation, 7x7 and 3x3; fp32 tensors, or bf16
 // tensors widened on their way into LDS (then UpdArgs::Kb counts blocks of 8 channels)
 hipError_t launch_upd_c4(int dtype, int r, int s, const UpdArgs &a, size_t lds_bytes, int grid,

@@ -112,6 +112,23 @@ struct Elem<CONV_BF16> {
     }
 };
 
+// x(W0) + ... + x(W1 - 1), pairwise.
+template <int W0, int W1, class F>
+static __device__ __forceinline__ f32x4 wave_sum(F &&x)
+{
+    if constexpr (W1 - W0 == 1)
+        return x(W0);
+    else
+        return wave_sum<W0, (W0 + W1) / 2>(x) + wave_sum<(W0 + W1) / 2, W1>(x);
+}
+// sum += part in this place: the additions are not moved down to where the sum is next read, which
+// would keep the registers of every part on the way there alive.
+static __device__ __forceinline__ void add_here(f32x16 &sum, const f32x16 &part)
+{
+    sum += part;
+    asm volatile("" : "+v"(sum));
+}
+
 // NB: LDS buffers of the staging ring (2 = double buffering; more = the loads run further ahead)
 // NTI: 1 = the input tile is loaded non-temporally.  For plans with a single channel tile, where
 // every input line is read by exactly one workgroup: such lines then leave the L2 first and
@@ -120,7 +137,10 @@ struct Elem<CONV_BF16> {
 // that widen the channel count: 25 - 35 % faster).
 // (Register budget: two workgroups per CU for the four-wave tiles of at most 128 accumulator
 // registers; a 7x7 filter alone fills most of a CU's LDS, so those run one per CU anyway.)
-template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0>
+// GROUPS: IgemmArgs::group > 0 sums that many steps from zero before they are added to the sum of the steps
+// before (0: one chain); where a result of few tiles used to have its reduction split over
+// workgroups, one chain has the larger rounding error (the planner's chain_error).
+template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0, bool GROUPS = false>
 __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, unsigned char *const lds)
 {
     using E_ = Elem<DT>;
@@ -459,9 +479,42 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
         };
         read_round(0, 0, ac, bc);
         int st = 0;
-        for (; st + AHEAD < nst; ++st) step(st, std::true_type{}, std::true_type{});
-        for (; st + 1 < nst; ++st) step(st, std::true_type{}, std::false_type{});
-        step(st, std::false_type{}, std::false_type{});
+        if constexpr (GROUPS) {
+            if (a.group > 0) {
+                f32x16 sum[FK][FM];  // of the groups so far
+#pragma unroll
+                for (int i = 0; i < FK; ++i)
+#pragma unroll
+                    for (int j = 0; j < FM; ++j) sum[i][j] = f32x16{};
+                auto end_group = [&]() {
+#pragma unroll
+                    for (int i = 0; i < FK; ++i)
+#pragma unroll
+                        for (int j = 0; j < FM; ++j) {
+                            add_here(sum[i][j], acc[i][j]);
+                            acc[i][j] = f32x16{};
+                        }
+                };
+                while (st + AHEAD < nst) {
+                    for (const int end = min(nst - AHEAD, st + a.group); st < end; ++st)
+                        step(st, std::true_type{}, std::true_type{});
+                    end_group();
+                }
+                for (; st + 1 < nst; ++st) step(st, std::true_type{}, std::false_type{});
+                step(st, std::false_type{}, std::false_type{});
+                end_group();
+#pragma unroll
+                for (int i = 0; i < FK; ++i)
+#pragma unroll
+                    for (int j = 0; j < FM; ++j) acc[i][j] = sum[i][j];
+                st = nst;
+            }
+        }
+        if (!GROUPS || st < nst) {
+            for (; st + AHEAD < nst; ++st) step(st, std::true_type{}, std::true_type{});
+            for (; st + 1 < nst; ++st) step(st, std::true_type{}, std::false_type{});
+            step(st, std::false_type{}, std::false_type{});
+        }
     }
 
     // ---- epilogue: each lane owns, per fragment, one pixel and 4x4 channels.
@@ -603,12 +656,18 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
     }
 }
 
+// Variants whose steps can be summed in groups: the second set of accumulators costs the 64 x 128 tile no
+// workgroup per CU (the 128 x 128 tile, twice as large, would lose one).
+constexpr bool igemm_groups(int dt, int wk, int wm, int fk, int fm)
+{
+    return dt == CONV_F32 && wk == 2 && wm == 2 && fk == 1 && fm == 2;
+}
 
 template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0>
 __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 && R * S < 49) ? 2 : 1)) void igemm_kernel(const IgemmArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    igemm_tile<DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NTI>(a, blockIdx.x, lds);
+    igemm_tile<DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NTI, igemm_groups(DT, WK, WM, FK, FM)>(a, blockIdx.x, lds);
 }
 
 typedef void (*igemm_fn_t)(const IgemmArgs);

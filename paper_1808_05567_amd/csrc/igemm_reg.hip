@@ -5,7 +5,7 @@
 // handful of workgroups on 256 CUs, each a serial chain of up to 64 steps.  Here the chip is
 // filled from the other side: a workgroup owns a small tile (FK*32 channels x FM*32 pixels) and
 // its waves split the REDUCTION of that tile between them, each with the whole tile in
-// its accumulators.  The waves' sums meet in LDS at the end, added in wave order (one fixed
+// its accumulators.  The waves' sums meet in LDS at the end, added pairwise (one fixed
 // order), so one launch does it and no partial results go through memory.
 //
 // Operands go from memory straight into the registers the MFMAs take them from (a pixel's
@@ -64,7 +64,10 @@ __device__ __forceinline__ f32x4 sum_inside_image(const IgemmArgs &a, int n, int
 // EXACT: for layers that would else run on the untiled loops, which leave the taps outside the image
 // out.  Here such a tap multiplies a weight by zero, which an infinite or NaN weight turns into NaN; a
 // sum that is NaN is therefore formed again without them.
-template <int DT, int FK, int FM, int NW, int D, bool EXACT>
+// GROUPS (fp32): a wave's steps are summed in groups of IgemmArgs::group rounds of D, each from zero, then
+// added to the sum of the groups before.  One chain over a wave's share has the larger rounding error
+// where the same result used to have its reduction split over more chains.
+template <int DT, int FK, int FM, int NW, int D, bool EXACT, bool GROUPS>
 __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kernel(const IgemmArgs a)
 {
     using E_ = Elem<DT>;
@@ -177,36 +180,63 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
         for (int j = 0; j < FM; ++j)
 #pragma unroll
             for (int t = 0; t < 16; ++t) acc[i][j][t] = 0.0f;
+    auto multiply = [&](const u32x4(&av)[FK], const u32x4(&bv)[FM]) {
+#pragma unroll
+        for (int i = 0; i < FK; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j) E_::mma(av[i], bv[j], acc[i][j]);
+    };
 
     if (u0 < u1) {
 #pragma unroll
         for (int d = 0; d < D; ++d) load(A[d], B[d]);
         // (loads past u1 ask for nothing: their lanes are out of range)
-        int g = u0;
-        for (; g + D < u1; g += D) {
+        // rounds of D steps from g on, up to `end`: the loads of the next round go out behind each step
+        auto rounds = [&](int &g, int end) {
+            for (; g < end; g += D) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
+                for (int d = 0; d < D; ++d) {
+                    multiply(A[d], B[d]);
+                    load(A[d], B[d]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        };
+        int g = u0;
+        f32x16 sum[GROUPS ? FK : 1][GROUPS ? FM : 1];  // of the groups so far
+        auto end_group = [&]() {
+            if constexpr (GROUPS) {
 #pragma unroll
                 for (int i = 0; i < FK; ++i)
 #pragma unroll
-                    for (int j = 0; j < FM; ++j) E_::mma(A[d][i], B[d][j], acc[i][j]);
-                load(A[d], B[d]);
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int j = 0; j < FM; ++j) {
+                        add_here(sum[i][j], acc[i][j]);
+                        acc[i][j] = f32x16{};
+                    }
             }
+        };
+        if constexpr (GROUPS) {
+#pragma unroll
+            for (int i = 0; i < FK; ++i)
+#pragma unroll
+                for (int j = 0; j < FM; ++j) sum[i][j] = f32x16{};
+            for (; g + a.group * D < u1; end_group()) rounds(g, g + a.group * D);
         }
+        rounds(g, u1 - D);
         // the last 1 .. D steps, already in registers
 #pragma unroll
         for (int d = 0; d < D; ++d)
-            if (g + d < u1) {
+            if (g + d < u1) multiply(A[d], B[d]);
+        if constexpr (GROUPS) {
+            end_group();
 #pragma unroll
-                for (int i = 0; i < FK; ++i)
+            for (int i = 0; i < FK; ++i)
 #pragma unroll
-                    for (int j = 0; j < FM; ++j) E_::mma(A[d][i], B[d][j], acc[i][j]);
-            }
+                for (int j = 0; j < FM; ++j) acc[i][j] = sum[i][j];
+        }
     }
-
     // The waves' sums, G fragments per round: every wave writes its own, then each thread adds
-    // one chunk of 4 consecutive channels of one pixel over the waves, in wave order.
+    // one chunk of 4 consecutive channels of one pixel over the waves, pairwise.
     const size_t oplane = (size_t)a.OH * a.OW * 16;
     const size_t out_bytes = (size_t)a.N * a.out_kb * oplane;
     constexpr unsigned SC = (V == 8) ? 2u : 1u;  // a partial result is fp32 whatever the type
@@ -227,9 +257,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
         __syncthreads();
         const int g = tid >> 8, ch = tid & 255;  // (wave-uniform: 4 waves per fragment)
         if (g < G) {
-            f32x4 v = xch[(g * NW) * 256 + ch];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) v += xch[(g * NW + w) * 256 + ch];
+            f32x4 v = wave_sum<0, NW>([&](int w) { return xch[(g * NW + w) * 256 + ch]; });
             const int f = f0 + g, fi = f / FM, fj = f - fi * FM;
             const int krow = k0 + fi * 32 + (ch >> 6) * 8 + 4 * h;
             const int m = m0 + fj * 32 + l32;
@@ -290,10 +318,11 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
 }
 
 #define REG_ENTRY(DT, FK, FM, NW, D) \
-    {DT, FK, FM, NW, D, igemm_reg_kernel<DT, FK, FM, NW, D, false>, igemm_reg_kernel<DT, FK, FM, NW, D, true>}
+    {DT, FK, FM, NW, D, igemm_reg_kernel<DT, FK, FM, NW, D, false, false>, \
+     igemm_reg_kernel<DT, FK, FM, NW, D, true, false>, igemm_reg_kernel<DT, FK, FM, NW, D, false, DT == CONV_F32>}
 static const struct RegEntry {
     int dtype, fk, fm, nw, depth;
-    igemm_fn_t fn, exact_fn;
+    igemm_fn_t fn, exact_fn, groups_fn;
 } g_reg[] = {
     REG_ENTRY(CONV_F32, 1, 1, 4, 4),  REG_ENTRY(CONV_F32, 1, 1, 8, 3),  REG_ENTRY(CONV_F32, 2, 1, 8, 3),
     REG_ENTRY(CONV_F32, 1, 2, 4, 3),  REG_ENTRY(CONV_F32, 2, 2, 4, 3),
@@ -323,7 +352,7 @@ hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid,
     for (const RegEntry &e : g_reg) {
         if (e.dtype != v.dtype || e.fk != v.fk || e.fm != v.fm || e.nw != v.wk) continue;
         const size_t lds = igemm_reg_lds_bytes(e.fk, e.fm, e.nw);
-        const igemm_fn_t fn = a.exact ? e.exact_fn : e.fn;
+        const igemm_fn_t fn = a.exact ? e.exact_fn : a.group > 0 ? e.groups_fn : e.fn;
         if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(fn), lds); err != hipSuccess)
             return err;
         hipLaunchKernelGGL(fn, dim3(grid), dim3(e.nw * 64), lds, stream, a);

@@ -522,7 +522,7 @@ __global__ __launch_bounds__(256) void upd_bf16_kernel(const UpdArgs a)
 }
 
 // dW[e] = sum_j partial[j][e] in a fixed order: G interleaved chains over j (chain g takes
-// j = g, g+G, ...), each ascending, then chains 0..G-1 ascending.
+// j = g, g+G, ...), each ascending, then the chains pairwise.
 // Bound by the trip to memory where dW is small (a first layer: 256 copies of 36 - 100 KB), by
 // bandwidth otherwise, so a chain asks for eight copies before it adds the first, and the chains
 // are as many as leave each with one or two such groups.  (Eight chains of one load at a time:
@@ -555,10 +555,12 @@ __global__ __launch_bounds__(256) void upd_reduce_kernel(const f32x4 *__restrict
     if constexpr (G > 1) {
         __shared__ f32x4 part[G][COLS];
         part[g][colt] = s;
-        __syncthreads();
-        if (g != 0) return;
 #pragma unroll
-        for (int q = 1; q < G; ++q) s += part[q][colt];
+        for (int half = G / 2; half >= 1; half /= 2) {
+            __syncthreads();
+            if (g < half) part[g][colt] = s += part[g + half][colt];
+        }
+        if (g != 0) return;
     }
     if (idx >= n4) return;
     if constexpr (HALF) {

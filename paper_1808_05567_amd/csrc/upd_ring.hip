@@ -10,7 +10,7 @@
 // minibatch (N = 8: 25 us + 7 us for 3 us of arithmetic).  Here a workgroup owns a small block (FC*32 input
 // channels x FK*32 output channels x the S taps of ONE filter row), so that the blocks
 // themselves fill the chip, and its waves split the pixels of the block between them; their
-// sums meet in LDS, in wave order.  Few or no partial copies are left, and with one split
+// sums meet in LDS, pairwise.  Few or no partial copies are left, and with one split
 // the kernel writes dW itself.
 //
 // Operands: a stage is PXS pixels of the flat list (n, oj, oi), sixteen in bf16 (one MFMA's reduction) and
@@ -42,8 +42,14 @@
 namespace convmi {
 
 // S taps of a filter row, FC x FK accumulator tiles per tap, NW waves, a ring of D stages each.
-template <int DT, int S, int FC, int FK, int NW, int D>
-__global__ __launch_bounds__(NW * 64, 2) void upd_ring_kernel(const UpdArgs a)
+// SUM: how a wave adds up its pixels.  0: in one chain.  1: in groups of UpdArgs::group rounds of D stages,
+// each summed from zero, then added to the sum of the groups before.  2 (fp32): a stage's eight
+// pixels from zero, then added.  One chain has the larger rounding error where the wave has
+// more pixels than a wave of the kernel that this one replaces (the planner's upd_sum_error): in fp32
+// up to twice the relative error.  1 takes a second set of accumulators, 2 only one or two tiles.
+template <int DT, int S, int FC, int FK, int NW, int D, int SUM>
+__global__ __launch_bounds__(NW * 64, SUM == 1 && S * FC * FK <= 3 ? 4 : 2) void
+upd_ring_kernel(const UpdArgs a)
 {
     constexpr bool BF = DT == CONV_BF16;
     constexpr int V = BF ? 8 : 4;
@@ -146,64 +152,104 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_ring_kernel(const UpdArgs a)
     const int steps = (g1 - g0 + NW * PXS - 1) / (NW * PXS);
 #pragma unroll
     for (int d = 0; d < D; ++d) load(d);
-    // (whole groups of D stages: what lies past the range's end arrives as zeros)
-    for (int u = 0; u < steps; u += D) {
+    f32x16 sum[SUM == 1 ? NF : 1];  // of the groups so far
+    if constexpr (SUM == 1) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            // this stage's loads have landed; the D - 1 later ones may be on their way
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 1) * NO) : "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (BF) {
-                const unsigned p = lds_address(ring + d * (NO * 1024)) + (unsigned)r_lane;
-                lds_u32x2 t[2 * NO];
-                static_for<0, NO>([&](auto oc) {
-                    constexpr int o = decltype(oc)::value;
-                    t[2 * o] = lds_read_tr16_b64_untracked<o * 1024>(p);
-                    t[2 * o + 1] = lds_read_tr16_b64_untracked<o * 1024 + NB * 64>(p);
-                });
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        for (int f = 0; f < NF; ++f) sum[f] = f32x16{};
+    }
+    for (int u = 0; u < steps;) {
+        // (whole rounds of D stages: what lies past the range's end arrives as zeros)
+        for (const int end = SUM == 1 ? min(steps, u + a.group * D) : steps; u < end; u += D) {
 #pragma unroll
-                for (int o = 0; o < 2 * NO; ++o) lds_read_landed(t[o]);
+            for (int d = 0; d < D; ++d) {
+                // this stage's loads have landed; the D - 1 later ones may be on their way
                 __builtin_amdgcn_sched_barrier(0);
-                load(d);  // (the patch has been read: the stage D further on takes it)
-                auto operand = [&](int o) {
-                    const u32x4 v = {t[2 * o][0], t[2 * o][1], t[2 * o + 1][0], t[2 * o + 1][1]};
-                    return __builtin_bit_cast(bf16x8, v);
-                };
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 1) * NO) : "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (BF) {
+                    const unsigned p = lds_address(ring + d * (NO * 1024)) + (unsigned)r_lane;
+                    lds_u32x2 t[2 * NO];
+                    static_for<0, NO>([&](auto oc) {
+                        constexpr int o = decltype(oc)::value;
+                        t[2 * o] = lds_read_tr16_b64_untracked<o * 1024>(p);
+                        t[2 * o + 1] = lds_read_tr16_b64_untracked<o * 1024 + NB * 64>(p);
+                    });
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-                for (int o = 0; o < NA; ++o)
-#pragma unroll
-                    for (int j = 0; j < FK; ++j)
-                        acc[o * FK + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(operand(o), operand(NA + j),
-                                                                                  acc[o * FK + j], 0, 0, 0);
-            } else {
-                const float *p = reinterpret_cast<const float *>(ring + d * (NO * 1024) + r_lane);
-                float t[PXS / 2][NO];
-#pragma unroll
-                for (int q = 0; q < PXS / 2; ++q)
-#pragma unroll
-                    for (int o = 0; o < NO; ++o) t[q][o] = p[(o * 1024 + (q >> 1) * 512 + (q & 1) * 32) / 4];
-#pragma unroll
-                for (int q = 0; q < PXS / 2; ++q) {
-                    if (q == PXS / 2 - 1) {
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                        __builtin_amdgcn_sched_barrier(0);
-                        load(d);
-                    }
+                    for (int o = 0; o < 2 * NO; ++o) lds_read_landed(t[o]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load(d);  // (the patch has been read: the stage D further on takes it)
+                    auto operand = [&](int o) {
+                        const u32x4 v = {t[2 * o][0], t[2 * o][1], t[2 * o + 1][0], t[2 * o + 1][1]};
+                        return __builtin_bit_cast(bf16x8, v);
+                    };
 #pragma unroll
                     for (int o = 0; o < NA; ++o)
 #pragma unroll
                         for (int j = 0; j < FK; ++j)
-                            acc[o * FK + j] = __builtin_amdgcn_mfma_f32_32x32x2f32(t[q][o], t[q][NA + j],
-                                                                                   acc[o * FK + j], 0, 0, 0);
+                            acc[o * FK + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(operand(o), operand(NA + j),
+                                                                                      acc[o * FK + j], 0, 0, 0);
+                } else {
+                    const float *p = reinterpret_cast<const float *>(ring + d * (NO * 1024) + r_lane);
+                    float t[PXS / 2][NO];
+#pragma unroll
+                    for (int q = 0; q < PXS / 2; ++q)
+#pragma unroll
+                        for (int o = 0; o < NO; ++o) t[q][o] = p[(o * 1024 + (q >> 1) * 512 + (q & 1) * 32) / 4];
+                    if constexpr (SUM == 2) {
+                        // (a tile's sum is added behind the next tile's MFMAs where there are registers for two)
+                        constexpr bool LATER = NF > 1 && NF <= 8;
+                        f32x16 part[LATER ? 2 : 1];
+#pragma unroll
+                        for (int f = 0; f < NF; ++f) {
+                            f32x16 &now = part[LATER ? f & 1 : 0];
+                            now = f32x16{};
+#pragma unroll
+                            for (int q = 0; q < PXS / 2; ++q)
+                                now = __builtin_amdgcn_mfma_f32_32x32x2f32(t[q][f / FK], t[q][NA + f % FK], now, 0, 0, 0);
+                            if (f == 0) {
+                                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                                __builtin_amdgcn_sched_barrier(0);
+                                load(d);
+                            }
+                            if (LATER && f > 0) add_here(acc[f - 1], part[(f - 1) & 1]);
+                            if (!LATER || f == NF - 1) add_here(acc[f], now);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < PXS / 2; ++q) {
+                            if (q == PXS / 2 - 1) {
+                                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                                __builtin_amdgcn_sched_barrier(0);
+                                load(d);
+                            }
+#pragma unroll
+                            for (int o = 0; o < NA; ++o)
+#pragma unroll
+                                for (int j = 0; j < FK; ++j)
+                                    acc[o * FK + j] = __builtin_amdgcn_mfma_f32_32x32x2f32(t[q][o], t[q][NA + j],
+                                                                                           acc[o * FK + j], 0, 0, 0);
+                        }
+                    }
                 }
             }
         }
+        if constexpr (SUM == 1) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                add_here(sum[f], acc[f]);
+                acc[f] = f32x16{};
+            }
+        }
+    }
+    if constexpr (SUM == 1) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[f] = sum[f];
     }
     wait_all_memory();  // (the last stages' loads still write zeros into the ring)
 
-    // The waves' sums, G tiles per round, in wave order.  Rows of a tile are input channels: a
+    // The waves' sums, G tiles per round, pairwise.  Rows of a tile are input channels: a
     // chunk of four consecutive ones is 16 bytes of dW.
     const int RS = a.R * S;
     float *const dst = a.partial + (size_t)split * ((size_t)a.Cb * RS * a.Kp * V);
@@ -223,9 +269,7 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_ring_kernel(const UpdArgs a)
         __syncthreads();
         const int g = tid >> 8, ch = tid & 255, f = f0 + g;
         if (f < NF) {
-            f32x4 v = xch[(g * NW) * 256 + ch];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) v += xch[(g * NW + w) * 256 + ch];
+            const f32x4 v = wave_sum<0, NW>([&](int w) { return xch[(g * NW + w) * 256 + ch]; });
             const int o = f / FK, j = f - o * FK, s = o / FC, i = o - s * FC;
             const int c = c0 + 32 * i + (ch >> 6) * 8 + 4 * h;
             const int k = k0 + 32 * j + l32;
@@ -237,24 +281,35 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_ring_kernel(const UpdArgs a)
 }
 
 typedef void (*upd_ring_fn_t)(const UpdArgs);
-#define UPD_RING_ENTRY(DT, S, FC, FK, NW, D) {DT, S, FC, FK, NW, D, upd_ring_kernel<DT, S, FC, FK, NW, D>}
+#define UPD_RING_ENTRY(DT, S, FC, FK, NW, D, SUM) {DT, S, FC, FK, NW, D, SUM, upd_ring_kernel<DT, S, FC, FK, NW, D, SUM>}
 static const struct UpdRingEntry {
-    int dtype, s, fc, fk, nw, depth;
+    int dtype, s, fc, fk, nw, depth, sum;
     upd_ring_fn_t fn;
 } g_upd_ring[] = {
-#define BOTH(S, FC, FK, NW, D) UPD_RING_ENTRY(CONV_F32, S, FC, FK, NW, D), UPD_RING_ENTRY(CONV_BF16, S, FC, FK, NW, D)
-    BOTH(1, 1, 1, 8, 4), BOTH(1, 2, 2, 8, 2), BOTH(1, 2, 4, 8, 2),
-    BOTH(3, 1, 1, 8, 2), BOTH(3, 1, 2, 8, 2), BOTH(3, 2, 2, 8, 2), BOTH(3, 2, 2, 4, 4),
-    BOTH(5, 1, 1, 8, 2), BOTH(7, 1, 1, 8, 2),
+#define F32(S, FC, FK, NW, D, SUM) UPD_RING_ENTRY(CONV_F32, S, FC, FK, NW, D, 0), UPD_RING_ENTRY(CONV_F32, S, FC, FK, NW, D, SUM)
+#define BF16(S, FC, FK, NW, D) UPD_RING_ENTRY(CONV_BF16, S, FC, FK, NW, D, 0)
+#define BF16_SUM(S, FC, FK, NW, D) BF16(S, FC, FK, NW, D), UPD_RING_ENTRY(CONV_BF16, S, FC, FK, NW, D, 1)
+    F32(1, 1, 1, 8, 4, 1), F32(1, 2, 2, 8, 2, 1), F32(1, 2, 4, 8, 2, 2),
+    F32(3, 1, 1, 8, 2, 1), F32(3, 1, 2, 8, 2, 1), F32(3, 2, 2, 8, 2, 2), F32(3, 2, 2, 4, 4, 2),
+    F32(5, 1, 1, 8, 2, 1), F32(7, 1, 1, 8, 2, 2),
+    BF16_SUM(1, 1, 1, 8, 4), BF16_SUM(1, 2, 2, 8, 2), BF16(1, 2, 4, 8, 2),
+    BF16_SUM(3, 1, 1, 8, 2), BF16_SUM(3, 1, 2, 8, 2), BF16(3, 2, 2, 8, 2), BF16(3, 2, 2, 4, 4),
+    BF16_SUM(5, 1, 1, 8, 2), BF16(7, 1, 1, 8, 2),
 };
 
 // (dropped after measuring 38 layers at N = 8 ... 256: deeper rings where they fit, 4 x 2 and 4 x 4
 // fragments: at most 2 % ahead of these on a few layers)
-bool upd_ring_exists(int dtype, int s, int fc, int fk, int nw, int depth)
+static const UpdRingEntry *find_ring(int dtype, int s, int fc, int fk, int nw, int depth, int sum)
 {
     for (const UpdRingEntry &e : g_upd_ring)
-        if (e.dtype == dtype && e.s == s && e.fc == fc && e.fk == fk && e.nw == nw && e.depth == depth) return true;
-    return false;
+        if (e.dtype == dtype && e.s == s && e.fc == fc && e.fk == fk && e.nw == nw && e.depth == depth && e.sum == sum)
+            return &e;
+    return nullptr;
+}
+
+bool upd_ring_exists(int dtype, int s, int fc, int fk, int nw, int depth, int sum)
+{
+    return find_ring(dtype, s, fc, fk, nw, depth, sum) != nullptr;
 }
 
 size_t upd_ring_lds_bytes(int s, int fc, int fk, int nw, int depth)
@@ -263,17 +318,16 @@ size_t upd_ring_lds_bytes(int s, int fc, int fk, int nw, int depth)
     return std::max((size_t)nw / 4 * nw * 4096, (size_t)nw * depth * (s * fc + fk) * 1024);
 }
 
-hipError_t launch_upd_ring(int dtype, int fc, int fk, int nw, int depth, const UpdArgs &a, int grid, hipStream_t stream)
+hipError_t launch_upd_ring(int dtype, int fc, int fk, int nw, int depth, int sum, const UpdArgs &a, int grid,
+                           hipStream_t stream)
 {
-    for (const UpdRingEntry &e : g_upd_ring) {
-        if (e.dtype != dtype || e.s != a.S || e.fc != fc || e.fk != fk || e.nw != nw || e.depth != depth) continue;
-        const size_t lds = upd_ring_lds_bytes(e.s, fc, fk, nw, depth);
-        if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(e.fn), lds); err != hipSuccess)
-            return err;
-        hipLaunchKernelGGL(e.fn, dim3(grid), dim3(nw * 64), lds, stream, a);
-        return hipGetLastError();
-    }
-    return hipErrorInvalidDeviceFunction;
+    const UpdRingEntry *e = find_ring(dtype, a.S, fc, fk, nw, depth, sum);
+    if (!e) return hipErrorInvalidDeviceFunction;
+    const size_t lds = upd_ring_lds_bytes(e->s, fc, fk, nw, depth);
+    if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(e->fn), lds); err != hipSuccess)
+        return err;
+    hipLaunchKernelGGL(e->fn, dim3(grid), dim3(nw * 64), lds, stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace convmi
