@@ -2402,9 +2402,9 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         if (!h->upd_ok) return CONV_EUNSUPPORTED;
         if (h->upd_ring) {
             snprintf(buf, buflen,
-                     "%s dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d sum=%d group=%d pixels/split=%d splits=%d tiles=%dx%dx%d "
+                     "upd_ring dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d sum=%d group=%d pixels/split=%d splits=%d tiles=%dx%dx%d "
                      "grid=%d lds=%zu launches=1",
-                     h->d.R * h->d.S == 1 ? "upd_1x1" : "upd_rows1", (int)h->d.dtype, h->d.R, h->d.S, h->urv.wp,
+                     (int)h->d.dtype, h->d.R, h->d.S, h->urv.wp,
                      h->urv.wk, h->urv.fc, h->urv.fk, h->urv.strided, h->ua.group, h->ua.rows_per_split, h->ua.splits,
                      h->ua.n_ct, h->ua.n_kt, h->d.R, h->upd_grid, h->upd_lds);
             return CONV_OK;

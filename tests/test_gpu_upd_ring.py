@@ -49,7 +49,7 @@ def test_ring_update_matches_oracle(shape, dtype, monkeypatch):
             monkeypatch.setenv("CONVMI_UPD_RING", "%s,%d" % (v, splits))
             L = conv.ConvLayer(*shape, dtype=dtype)
             try:
-                assert " ring=" in conv.conv_describe(L.h, conv.PASS_UPD)
+                assert conv.conv_describe(L.h, conv.PASS_UPD).startswith("upd_ring ")
                 got = run_pass(L, "upd", I=I, dO=dO)
                 assert np.isfinite(L.dwt_blk.cpu().numpy()).all()  # (padded channel slots too)
             finally:
@@ -69,7 +69,7 @@ def test_ring_update_is_exact_on_integers_and_repeatable(shape, dtype, monkeypat
     ref = oracle.upd(I, dO, R, S, stride, pad)
     L = conv.ConvLayer(*shape, dtype=dtype)
     try:
-        assert " ring=" in conv.conv_describe(L.h, conv.PASS_UPD)
+        assert conv.conv_describe(L.h, conv.PASS_UPD).startswith("upd_ring ")
         for _ in range(3):
             assert np.array_equal(run_pass(L, "upd", I=I, dO=dO), ref.astype(np.float32))
     finally:

@@ -136,15 +136,20 @@ def test_kernel_families_are_chosen_where_they_apply():
     # ... below that, the four-wave kernel
     _, p = _plans((256, 64, 64, 56, 56, 1, 1, 1, 0), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd dt=0")
-    # bf16 1x1: flat pixel list at every width
-    for C, K in ((64, 64), (64, 256), (1024, 2048)):
-        _, p = _plans((256, C, K, 14, 14, 1, 1, 1, 0), conv.CONV_BF16)
+    # bf16 1x1: flat pixel list where the tensors are large, the ring kernel below
+    for C, K, H in ((64, 64, 56), (64, 256, 56), (1024, 2048, 14)):
+        _, p = _plans((256, C, K, H, H, 1, 1, 1, 0), conv.CONV_BF16)
         assert p[conv.PASS_UPD].startswith("upd_1x1 dt=1")
-    # 3x3 stride 1: band kernel (fp32), row kernel (bf16)
+    for N, C, K in ((256, 64, 64), (256, 64, 256), (16, 1024, 2048)):
+        _, p = _plans((N, C, K, 14, 14, 1, 1, 1, 0), conv.CONV_BF16)
+        assert p[conv.PASS_UPD].startswith("upd_ring dt=1")
+    # 3x3 stride 1: band kernel (fp32), ring kernel (bf16; with a large stride-2 layer still on the row kernel)
     _, p = _plans((256, 256, 256, 14, 14, 3, 3, 1, 1), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd_bands")
     _, p = _plans((256, 256, 256, 14, 14, 3, 3, 1, 1), conv.CONV_BF16)
-    assert p[conv.PASS_UPD].startswith("upd_rows")
+    assert p[conv.PASS_UPD].startswith("upd_ring dt=1")
+    _, p = _plans((256, 288, 384, 35, 35, 3, 3, 2, 0), conv.CONV_BF16)
+    assert p[conv.PASS_UPD].startswith("upd_rows dt=1")
     # one input channel block, fp32: filter-row kernel; backward: all classes in one launch
     _, p = _plans((256, 3, 64, 224, 224, 7, 7, 2, 3), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd_c4")
