@@ -502,7 +502,9 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
             }
         static const int kReg[][4] = {{1, 1, 4, 1}, {1, 1, 8, 1}, {2, 1, 8, 1}, {1, 2, 4, 1}, {2, 2, 4, 1},
                                       {1, 1, 8, 2}, {1, 1, 8, 4}};
+        const char *reg_env = getenv("CONVMI_IGEMM_REG");
         for (const auto &k : kReg) {
+            if (reg_env && strcmp(reg_env, "0") == 0) break;
             if (k[3] > 1 && (!may_split || dtype != CONV_F32)) continue;
             consider(try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                              zero_fill, geo, k[0], k[1], k[2], k[3]));
