@@ -1489,7 +1489,7 @@ double planned_upd_error(const conv_plan *p)
 double ring_error(const conv_plan *p, const RingCand &c, UpdArgs &a, double most)
 {
     const bool bf16 = p->d.dtype == CONV_BF16;
-    const int chains = a.splits <= 8 ? 1 : a.splits <= 64 ? 8 : 32;  // (see launch_upd_reduce)
+    const int chains = upd_reduce_chains(p->info.dwt_bytes / sizeof(float), a.splits);
     const double n = (double)ceil_div(a.rows_per_split, c.nw) / (bf16 ? 16 : 1), unit = c.depth * (bf16 ? 1.0 : 8.0);
     // (waves without a pixel add zeros)
     const int waves = std::min(c.nw, ceil_div(std::min(a.rows_per_split, p->d.N * a.P * a.Q), bf16 ? 16 : 8));
@@ -2361,7 +2361,13 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
     if ((pass == 0 && h->fwd_chunked) || (pass == 1 && h->bwd_chunked) || (pass == 2 && h->upd_chunked)) {
         const int n = snprintf(buf, buflen, "chunks=%d images=%d: ", h->n_chunks, h->chunk_n);
         if (n < 0 || (size_t)n >= buflen) return CONV_EINVAL;
-        return conv_describe(h->chunk, pass, buf + n, buflen - n);
+        const conv_status_t st = conv_describe(h->chunk, pass, buf + n, buflen - n);
+        if (st == CONV_OK && pass == 2) {
+            const size_t end = strlen(buf);
+            snprintf(buf + end, buflen - end, " chunk_chains=%d",
+                     upd_reduce_chains(h->info.dwt_bytes / sizeof(float), h->n_chunks));
+        }
+        return st;
     }
     if ((pass == 0 && h->fwd_direct) || (pass == 1 && h->bwd_direct) || (pass == 2 && h->upd_direct)) {
         const DirectArgs &a = h->da;

@@ -262,6 +262,8 @@ hipError_t launch_upd_c4(int dtype, int r, int s, const UpdArgs &a, size_t lds_b
 bool upd_c4_bf16_exists(int r, int s);
 hipError_t launch_upd_c4_bf16(int r, int s, const UpdArgs &a, size_t lds_bytes, int grid,
                               hipStream_t stream);
+// Chains in which the sum of `splits` copies of n_elems elements is formed.
+int upd_reduce_chains(size_t n_elems, int splits);
 hipError_t launch_upd_reduce(const float *partial, float *dwt, size_t n_elems, int splits, bool half_blocks,
                              hipStream_t stream);
 

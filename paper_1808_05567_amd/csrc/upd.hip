@@ -571,19 +571,32 @@ __global__ __launch_bounds__(256) void upd_reduce_kernel(const f32x4 *__restrict
     }
 }
 
+int upd_reduce_chains(size_t n_elems, int splits)
+{
+    // (chains of at most one group of eight loads up to 256 copies; a chain takes a thread per four
+    // elements, and a dispatch has fewer than 2^32 of them: 32 chains reach 2 GiB of dW, eight reach 8)
+    const size_t n4 = n_elems / 4;
+    int chains = splits <= 8 ? 1 : splits <= 64 ? 8 : 32;
+    while (chains > 1 && n4 * chains + 256 >= (size_t)1 << 32) chains = chains == 32 ? 8 : 1;
+    return chains;
+}
+
 template <bool HALF>
 static void launch_upd_reduce_as(const f32x4 *src, f32x4 *dst, size_t n4, int splits, hipStream_t stream)
 {
-    // (chains of at most one group of eight loads up to 256 copies)
-    if (splits <= 8)
+    switch (upd_reduce_chains(n4 * 4, splits)) {
+    case 1:
         hipLaunchKernelGGL((upd_reduce_kernel<1, HALF>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, src,
                            dst, n4, splits);
-    else if (splits <= 64)
+        break;
+    case 8:
         hipLaunchKernelGGL((upd_reduce_kernel<8, HALF>), dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, stream, src,
                            dst, n4, splits);
-    else
+        break;
+    default:
         hipLaunchKernelGGL((upd_reduce_kernel<32, HALF>), dim3((unsigned)((n4 + 7) / 8)), dim3(256), 0, stream, src,
                            dst, n4, splits);
+    }
 }
 
 typedef void (*upd_fn_t)(const UpdArgs);
