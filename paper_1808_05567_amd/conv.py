@@ -141,6 +141,15 @@ def _current_stream():
     return _raw_stream()
 
 
+def _forget_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+# (a forked child has no runtime of its own: there the public call comes first again, which says so)
+os.register_at_fork(after_in_child=_forget_stream)
+
+
 def _stream(stream):
     if stream is None:
         return _current_stream()
