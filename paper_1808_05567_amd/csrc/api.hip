@@ -383,7 +383,7 @@ double estimate_us(const IgemmPlan &p, bool scatter)
         const int occ = frags == 1 ? 8 : frags == 2 ? (bf16 ? 7 : 6) : 3;
         resident = std::max(1, occ * 4 / v.wk);
         launch = f.launch;
-        if (bf16) hbm = 3.3e6;
+        hbm = bf16 ? 3.3e6 : 3.0e6;
     } else {
         const bool small = v.fm <= 2;
         const Fit f = small ? (bf16 ? Fit{2.4, 1350, 298, 1.24, 2.65, 0.92, 800} : Fit{3.0, 245, 253, 1.03, 0.24, 1.0, 2220})
@@ -403,6 +403,8 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     const int full = per_cu / resident, rest = per_cu - full * resident;
     double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
     t = t / 2.3e3 + launch;
+    // (the register-operand kernel with three and more workgroups to a CU: 4 - 9 % over what the rest of the fit says)
+    if (p.reg && bf16 && p.grid > 768) t *= 1.08;
     const int V = vlen_of(v.dtype);
     const double out = (double)a.N * (scatter ? (double)a.OH * a.OW : (double)a.P * a.Q) * (a.Kp / V) * 16;
     if (a.ksplit > 1)  // the second launch, and the partial results there and back
@@ -411,8 +413,9 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     const double bytes = in + out + (double)a.Cb * RS * a.Kp * 16;
     // bf16, the rate at which a staged launch bound by memory moves its bytes: 128-pixel tiles, three
     // workgroups to a CU, 6.5 - 7.3 TB/s up to the last-level cache's 256 MB (64 -> 256 at 56x56, N = 64: 20 us,
-    // 30 in the large tiles) and less beyond (5.6 up to 450 MB with several channel tiles: N = 192 54 us, 83; else
-    // 4.6), not where they are one step of four planes (32 -> 328 at 23x23, N = 128: 12.5 us, 11.7) or scatter;
+    // 30 in the large tiles) and less beyond (5.6 up to 450 MB with several channel tiles: N = 192 54 us, 83; with
+    // one channel tile 4.6 from 130 MB on: 512 -> 128 at 28x28, N = 160, 42 us, 34 in the large tiles), not where
+    // they are one step of four planes (32 -> 328 at 23x23, N = 128: 12.5 us, 11.7) or scatter;
     // the large ones 4.8, or 6.2 where one channel tile lets the input pass by the caches (64 -> 80 at
     // 73x73, N = 256: 75 us, 88 in small tiles), and less where they leave CUs with one workgroup or none
     // (256 -> 64 at 56x56, N = 16: 112 tiles, 13 us; 7 in small tiles).
@@ -420,7 +423,7 @@ double estimate_us(const IgemmPlan &p, bool scatter)
         if (large)
             hbm = (a.n_kt == 1 ? 6.2e6 : 4.8e6) * std::min(1.0, a.total / (scatter ? 224.0 : 300.0));
         else if (!scatter && !(a.n_stage == 1 && v.npl == 4))
-            hbm = bytes <= 2.56e8 ? 6.5e6 : a.n_kt > 1 && bytes <= 4.5e8 ? 5.6e6 : 4.6e6;
+            hbm = bytes <= (a.n_kt > 1 ? 2.56e8 : 1.3e8) ? 6.5e6 : a.n_kt > 1 && bytes <= 4.5e8 ? 5.6e6 : 4.6e6;
     }
     return std::max(t, launch + bytes / hbm);
 }
@@ -494,7 +497,10 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
                 best_us = us;
             }
         };
-        for (int fk = 1; fk <= 2 && p.ok; ++fk)
+        // (25 taps leave a CU one workgroup of the small tiles too: not where the large ones fill the chip -- 48 -> 64
+        // 5x5 at 35x35: N = 48 0.99 of the large tiles' time, N = 96 1.18, N = 256 1.34)
+        const bool small = p.ok && !(dtype == CONV_BF16 && R * S >= 25 && p.a.total >= 256);
+        for (int fk = 1; fk <= 2 && small; ++fk)
             for (int npl = 8; npl >= 2; npl /= 2) {
                 if ((R * S == 1) != (npl > 2)) continue;
                 consider(try_igemm(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0,

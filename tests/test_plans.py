@@ -265,3 +265,13 @@ def test_checked_workspace_entry_points_refuse_a_short_buffer():
         assert lib.conv_upd_ws(None, 16, 16, 16, 16, need, None) == conv.CONV_EINVAL
     finally:
         conv.conv_destroy(h)
+
+
+def test_large_tiles_where_small_ones_are_slower():
+    # bf16 in small tiles: 5x5 from where the large tiles fill the chip (N = 96: 1.18 of their time), and one channel
+    # tile from 130 MB of tensors on (N = 160: 1.24)
+    for N, rest, small in ((16, (48, 64, 35, 35, 5, 5, 1, 2), True), (96, (48, 64, 35, 35, 5, 5, 1, 2), False),
+                           (96, (512, 128, 28, 28, 1, 1, 1, 0), True), (160, (512, 128, 28, 28, 1, 1, 1, 0), False)):
+        _, p = _plans((N,) + rest, conv.CONV_BF16)
+        assert p[conv.PASS_FWD].startswith("igemm dt=1 waves=2x2 frags=1x2" if small and rest[4] == 5 else
+                                           "igemm dt=1 waves=2x2 frags=2x2" if small else "igemm dt=1 waves=1x4 frags=2x4")
