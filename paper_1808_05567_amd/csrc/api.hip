@@ -1553,8 +1553,10 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
     const double mfma = tiles * (bf16 ? 32.0 : 256.0);
     const double stages = ceil_div(ceil_div(a.rows_per_split, c.nw * (bf16 ? 16 : 8)), c.depth) * c.depth;
     const double shared = std::max(mfma * q.c_mfma * c.nw / 4, ops * c.nw * 16 * q.c_load) *
-                          (c.sum == 0 ? 1.0 : c.sum == 1 ? 1.03 : 1.14);
-    const double lone = q.fixed + stages * std::max(shared, mfma * q.c_mfma + q.stage + ops * q.per_op) + q.exch * tiles * c.nw;
+                          (c.sum == 0 ? 1.0 : c.sum == 1 ? 1.03 : 1.18);
+    // (a run of four pixels of a strided 1x1 layer is two lines)
+    const double lines = bf16 && d.R * d.S == 1 && d.stride > 1 ? 1.7 : 1.0;
+    const double lone = q.fixed + lines * stages * std::max(shared, mfma * q.c_mfma + q.stage + ops * q.per_op) + q.exch * tiles * c.nw;
     const double busy = stages * shared + q.exch * tiles * c.nw;
     // workgroups a CU holds: LDS, and registers (16 per tile, and what the operands take)
     int regs = 16 * tiles + (bf16 ? 4 : 3) * ops + 40;
@@ -1568,48 +1570,51 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
     const double es = bf16 ? 2.0 : 4.0, out_b = (double)f.out_bytes;
     const double in_b = d.R * d.S > 1 ? (double)f.in_bytes
                                       : (double)d.N * f.Cp * f.P * f.Q * (d.stride > 1 ? 2 : 1) * es;
-    t = std::max(t, q.launch + (in_b + out_b) / (q.hbm_tb * 1e6));
-    t = std::max(t, q.launch + (in_b * a.n_kt + out_b * a.n_ct) * d.R / (q.l2_tb * 1e6));
+    // (which of the three bounds it is shades into the next: 160 -> 160 7x1 at 17x17 in 32 x 32 blocks, 196 us by the first
+    // and 190 by the last, takes 230)
+    const double bound[3] = {t, q.launch + (in_b + out_b) / (q.hbm_tb * 1e6),
+                             q.launch + (in_b * a.n_kt + out_b * a.n_ct) * d.R / (q.l2_tb * 1e6)};
+    const double most = *std::max_element(bound, bound + 3);
+    t = most * std::pow(std::pow(bound[0] / most, 6) + std::pow(bound[1] / most, 6) + std::pow(bound[2] / most, 6), 1.0 / 6);
     if (a.splits > 1) t += q.reduce + a.splits * (double)f.dwt_bytes * 2 / (q.copy_tb * 1e6);
     return t;
 }
 
-// Whether the ring kernel is the better one, both sides measured with three sets of tensors in turn (its
-// time / the other kernel's):
-//   - 1x1, bf16: up to 2e10 flops 0.5 - 0.96; beyond, the 128 x 256 blocks of the flat kernel re-read less of what no longer
-//     stays in the last-level cache (256 -> 512 stride 2 at 56x56, N = 128: 1.13, N = 256: 1.33).  Between two
-//     narrow sides (below 128 channels) the line is at 5e9 (64 -> 64 at 56x56, N = 128: 0.90, N = 256: 1.08).
-//   - 1x1, fp32: with 256 channels on a side up to 2e10 flops (0.3 - 0.86; at 2.6e10 0.9 - 1.0, and its
-//     family there is pinned by the planner's tests); else 0.2 - 0.6 everywhere, up to 2^19 pixels
-//     (pinned as well).
-//   - wider filters: everywhere (bf16 0.24 - 0.88, fp32 0.42 - 0.9), except bf16 stride 2 beyond 5e10 flops
-//     (288 -> 384 at 35x35, N = 64: 0.76, N = 128: 1.00, N = 256: 1.07) and fp32 3x3 in full 64 x 64 blocks beyond 5e10 flops
-//     (0.88 - 0.94: pinned).
-//   - rows of more than 128 pixels, which the other kernels take in column strips, and 5 columns, which they
-//     take in a launch per filter row, all from the sizes on where the planner's tests don't pin those
-//     (32 -> 64 3x3 at 147x147: bf16 N = 8 0.32, N = 32 0.52, fp32 0.53, 0.75; 48 -> 64 5x5 at 35x35: bf16 N = 8
-//     0.24, N = 256 0.51, fp32 0.37, 0.74).
-//   - 1x1 and 7 columns in bf16: up to 140 MB of tensors, which every channel tile reads again from the last-level
-//     cache (1x1 up to 135 MB 0.5 - 1.06; 80 -> 192 at 36x36, N = 256, 180 MB 1.22, 128 -> 512 at 28x28, N = 192, 193 MB
-//     1.19, 200 -> 60 at 50x50, N = 192, 250 MB 1.20; 1x7 40 -> 268 at 38x38, N = 128, 114 MB 0.92, N = 192, 171 MB
-//     1.15; 64 -> 64 at 150x150, N = 8, 46 MB 0.60, N = 64, 369 MB 1.16).
+// Whether the ring kernel is the better one: lines between its time / the other kernel's, both measured with two
+// sets of tensors in turn over 64 layers x N = 1 ... 256.
+//   - 1x1, bf16 (three sets of tensors), by what is read, half of a strided layer's input, and by what the channel
+//     tiles read again: up to 82 MB read 0.4 - 1.04 (stride 2: 512 -> 256 at 28x28, N = 160, 80 MB, 0.91); up to 140 MB where
+//     the channel tiles ask for 260 MB at most (64 -> 64 at 56x56, N = 160, 128 MB, 0.91; 288 -> 64 at 35x35, N = 160, 138 and
+//     238 MB, 0.94; but 768 -> 192 at 17x17, N = 160, 89 and 355 MB, 1.16; 128 -> 512 at 28x28, N = 128, 128 and 411 MB,
+//     1.14); beyond 140 MB mostly slower (128 -> 512, 161 MB 1.07, 64 -> 80 at 73x73, 147 MB 1.17).  By operations: up
+//     to 2.3e10 (2.2e10 0.92; 2.6e10 0.98 - 1.07; 5.3e10 1.30), between two narrow sides (below 128 channels) 5e9 (4.4e9
+//     1.04, 6.6e9 1.12).
+//   - 1x1, fp32: with 256 channels on a side, where the other kernel has eight waves and 256 channels, up to 3e10
+//     (1.3e10 0.63 - 0.98, 2.6e10 0.91 - 0.99, 3.3e10 0.96 - 1.0, 5.3e10 1.02 - 1.05); else everywhere (0.2 - 0.73).
+//   - wider filters, fp32: everywhere (0.19 - 0.97; full 64 x 64 blocks beyond 5e10 operations 0.82 - 0.97).
+//   - wider filters, bf16: everywhere (0.14 - 1.03), except stride 2 beyond 5e10 (288 -> 384 at 35x35, 2.8e10 0.91, 5.5e10 1.06,
+//     9.2e10 1.02, 1.5e11 1.07), seven columns beyond 140 MB of tensors (40 -> 268 at 38x38, 114 MB 0.92, 142 MB 1.07, 171 MB
+//     1.13) and one column beyond 82 MB (36 -> 760 7x1 at 20x21, 64 MB 0.98, 86 MB 1.07, 128 MB 1.15).
 bool ring_applies(const conv_plan *p)
 {
     const conv_desc_t &d = p->d;
     const conv_info_t &f = p->info;
     const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q;
-    const double npix = (double)d.N * f.P * f.Q, tensors = (double)f.in_bytes + (double)f.out_bytes;
     const int wide = std::max(d.C, d.K), narrow = std::min(d.C, d.K);
     if (d.R * d.S == 1) {
-        if (d.dtype == CONV_BF16) return flops <= 2.0e10 && (flops <= 5.0e9 || wide >= 128) && tensors <= 1.4e8;
-        if (wide >= 256 && narrow >= 32) return flops <= 2.0e10;
-        return npix <= 524288.0;
+        if (d.dtype == CONV_F32) return !(wide >= 256 && narrow >= 32) || flops <= 3.0e10;
+        return flops <= 2.3e10 && (flops <= 5.0e9 || wide >= 128);
     }
-    if (f.Q > 128 && npix < 65536.0) return false;
-    if (d.dtype == CONV_BF16 && d.S == 7 && tensors > 1.4e8) return false;
-    if (d.S == 5 && npix < 8192.0) return false;
-    if (d.dtype == CONV_BF16) return !(d.stride > 1 && flops > 5.0e10);
-    return !(d.R == 3 && d.S == 3 && d.stride == 1 && d.C % 64 == 0 && d.K % 64 == 0 && flops > 5.0e10);
+    if (d.dtype == CONV_F32) return true;
+    const double tensors = (double)f.in_bytes + (double)f.out_bytes;
+    if ((d.S == 7 && tensors > 1.4e8) || (d.S == 1 && tensors > 8.2e7)) return false;
+    return !(d.stride > 1 && flops > 5.0e10);
+}
+// ... and for the chosen blocks of a bf16 1x1 layer, whether what they read allows it.
+bool ring_reads_apply(const conv_plan *p, const UpdArgs &a)
+{
+    const double in = (double)p->info.in_bytes / (p->d.stride > 1 ? 2 : 1), out = (double)p->info.out_bytes;
+    return in + out <= 8.2e7 || (in + out <= 1.4e8 && in * a.n_kt + out * a.n_ct <= 2.6e8);
 }
 
 bool plan_upd_ring(conv_plan *p)
@@ -1648,24 +1653,28 @@ bool plan_upd_ring(conv_plan *p)
         }
     };
     // (CONVMI_UPD_RING="fc,fk,waves,depth,splits[,sum[,group]]": one variant wherever it exists, in one chain unless
-    // another summation is asked for; "0": never -- a tuning aid)
-    if (const char *env = getenv("CONVMI_UPD_RING")) {
+    // another summation is asked for; "0": never; "any": the planner's choice wherever there is one -- a tuning aid)
+    const char *env = getenv("CONVMI_UPD_RING");
+    const bool any = env && strcmp(env, "any") == 0;
+    if (env && !any) {
         RingCand c{};
         force = 0;
         if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &c.fc, &c.fk, &c.nw, &c.depth, &c.splits, &force, &group) < 5) return false;
         consider(c);
-    } else if (ring_applies(p)) {
+    } else if (any || ring_applies(p)) {
         for (const auto &k : kBlocks) {
             const int tiles = ceil_div(f.Cp, k[0] * 32) * ceil_div(f.Kp, k[1] * 32) * d.R;
             // (32 x 32 blocks of a 1x1 filter re-read both tensors once per 32 channels: for small ones)
             if (d.R * d.S == 1 && k[0] == 1 &&
                 (double)f.in_bytes + (double)f.out_bytes > (d.dtype == CONV_BF16 ? 64.0e6 : 100.0e6))
                 continue;
-            consider({k[0], k[1], k[2], k[3], 1, 0});
+            // (a range that one split's chains do not hold is cut for all CUs, not into as few parts as that takes)
+            if (tiles >= 256 || (double)d.N * f.P * f.Q <= (double)(k[2] << 13)) consider({k[0], k[1], k[2], k[3], 1, 0});
             consider({k[0], k[1], k[2], k[3], std::max(1, 256 / tiles), 0});
-            if (d.S == 3) consider({k[0], k[1], k[2], k[3], std::max(1, 512 / tiles), 0});
+            if (d.S == 3 || d.dtype == CONV_F32) consider({k[0], k[1], k[2], k[3], std::max(1, 512 / tiles), 0});
         }
     }
+    if (have && !env && d.dtype == CONV_BF16 && d.R * d.S == 1 && !ring_reads_apply(p, best_a)) return false;
     if (!have || (double)best_a.splits * f.dwt_bytes > std::max(2.0 * ((double)f.in_bytes + (double)f.out_bytes), 8.0e9))
         return false;
     p->ua = best_a;

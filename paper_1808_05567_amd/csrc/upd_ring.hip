@@ -289,7 +289,7 @@ static const struct UpdRingEntry {
 #define F32(S, FC, FK, NW, D, SUM) UPD_RING_ENTRY(CONV_F32, S, FC, FK, NW, D, 0), UPD_RING_ENTRY(CONV_F32, S, FC, FK, NW, D, SUM)
 #define BF16(S, FC, FK, NW, D) UPD_RING_ENTRY(CONV_BF16, S, FC, FK, NW, D, 0)
 #define BF16_SUM(S, FC, FK, NW, D) BF16(S, FC, FK, NW, D), UPD_RING_ENTRY(CONV_BF16, S, FC, FK, NW, D, 1)
-    F32(1, 1, 1, 8, 4, 1), F32(1, 2, 2, 8, 2, 1), F32(1, 2, 4, 8, 2, 2),
+    F32(1, 1, 1, 8, 4, 1), F32(1, 2, 2, 8, 2, 1), UPD_RING_ENTRY(CONV_F32, 1, 2, 4, 8, 2, 0),
     F32(3, 1, 1, 8, 2, 1), F32(3, 1, 2, 8, 2, 1), F32(3, 2, 2, 8, 2, 2), F32(3, 2, 2, 4, 4, 2),
     F32(5, 1, 1, 8, 2, 1), F32(7, 1, 1, 8, 2, 2),
     BF16_SUM(1, 1, 1, 8, 4), BF16_SUM(1, 2, 2, 8, 2), BF16(1, 2, 4, 8, 2),

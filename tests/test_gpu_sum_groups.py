@@ -56,7 +56,7 @@ def test_staged_kernel(shape, group, monkeypatch):
 
 
 # columns, type: variants with their summations apart (1: groups, 2: by the stage)
-RING = {(1, F32): ["1,1,8,4,%d,1", "2,2,8,2,%d,1", "2,4,8,2,%d,2"], (3, F32): ["1,1,8,2,%d,1", "1,2,8,2,%d,1", "2,2,8,2,%d,2", "2,2,4,4,%d,2"],
+RING = {(1, F32): ["1,1,8,4,%d,1", "2,2,8,2,%d,1"], (3, F32): ["1,1,8,2,%d,1", "1,2,8,2,%d,1", "2,2,8,2,%d,2", "2,2,4,4,%d,2"],
         (5, F32): ["1,1,8,2,%d,1"], (7, F32): ["1,1,8,2,%d,2"], (1, BF16): ["1,1,8,4,%d,1", "2,2,8,2,%d,1"],
         (3, BF16): ["1,1,8,2,%d,1", "1,2,8,2,%d,1"], (5, BF16): ["1,1,8,2,%d,1"]}
 RING_SHAPES = [(1, 32, 32, 1, 1, 1, 1, 1, 0), (3, 72, 136, 17, 15, 1, 1, 1, 0), (3, 64, 64, 14, 14, 3, 3, 1, 1), (2, 40, 100, 27, 31, 3, 3, 2, 1),

@@ -66,16 +66,23 @@ def test_inception_v3_plans_fit_the_machine(N, dt):
         assert (info.P, info.Q) == (l.P, l.Q)
 
 
-def test_update_of_tall_filters_and_wide_rows():
+def test_update_of_tall_filters_and_wide_rows(monkeypatch):
     def upd(shape, dt=conv.CONV_F32):
         return _plans(shape, dt)[1][conv.PASS_UPD]
+    shapes = [(4, 64, 64, 17, 17, 7, 1, 1, (3, 0)), (4, 64, 64, 17, 17, 1, 7, 1, (0, 3)), (4, 48, 64, 35, 35, 5, 5, 1, 2),
+              (2, 32, 64, 147, 147, 3, 3, 1, 1)]
+    for s in shapes:
+        for dt in (conv.CONV_F32, conv.CONV_BF16):
+            assert upd(s, dt).startswith("upd_ring ") and "launches=1" in upd(s, dt)
+    # without the ring kernel (images and minibatches beyond its indices)
+    monkeypatch.setenv("CONVMI_UPD_RING", "0")
     # 7x1 and 1x7: one launch; 5x5: one launch per filter row
-    assert "RS=7x1" in upd((4, 64, 64, 17, 17, 7, 1, 1, (3, 0))) and "launches=1" in upd((4, 64, 64, 17, 17, 7, 1, 1, (3, 0)))
-    assert "launches=1" in upd((4, 64, 64, 17, 17, 1, 7, 1, (0, 3)))
-    assert "RS=1x5" in upd((4, 48, 64, 35, 35, 5, 5, 1, 2)) and "launches=5" in upd((4, 48, 64, 35, 35, 5, 5, 1, 2))
+    assert "RS=7x1" in upd(shapes[0]) and "launches=1" in upd(shapes[0])
+    assert "launches=1" in upd(shapes[1])
+    assert "RS=1x5" in upd(shapes[2]) and "launches=5" in upd(shapes[2])
     # 147-wide rows: strips of output columns, one launch each
-    assert "launches=3" in upd((2, 32, 64, 147, 147, 3, 3, 1, 1))
-    assert "launches=2" in upd((2, 32, 64, 147, 147, 3, 3, 1, 1), conv.CONV_BF16)
+    assert "launches=3" in upd(shapes[3])
+    assert "launches=2" in upd(shapes[3], conv.CONV_BF16)
 
 
 @pytest.mark.parametrize("dt", [conv.CONV_F32, conv.CONV_BF16], ids=["f32", "bf16"])
@@ -127,7 +134,8 @@ def test_seeded_rectangular_sweep_plans_fit_the_machine():
     assert planned > 1000  # (tiled kernels; the rest run on the direct ones)
 
 
-def test_kernel_families_are_chosen_where_they_apply():
+def test_update_families_without_the_ring_kernel(monkeypatch):
+    monkeypatch.setenv("CONVMI_UPD_RING", "0")
     # fp32 1x1 with 256 channels on one side: eight-wave kernel on the flat pixel list
     _, p = _plans((256, 256, 1024, 14, 14, 1, 1, 1, 0), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd_1x1 dt=0") and "in x out" in p[conv.PASS_UPD]
@@ -136,20 +144,39 @@ def test_kernel_families_are_chosen_where_they_apply():
     # ... below that, the four-wave kernel
     _, p = _plans((256, 64, 64, 56, 56, 1, 1, 1, 0), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd dt=0")
-    # bf16 1x1: flat pixel list where the tensors are large, the ring kernel below
-    for C, K, H in ((64, 64, 56), (64, 256, 56), (1024, 2048, 14)):
-        _, p = _plans((256, C, K, H, H, 1, 1, 1, 0), conv.CONV_BF16)
+    # bf16 1x1: flat pixel list at every width
+    for C, K in ((64, 64), (64, 256), (1024, 2048)):
+        _, p = _plans((256, C, K, 14, 14, 1, 1, 1, 0), conv.CONV_BF16)
         assert p[conv.PASS_UPD].startswith("upd_1x1 dt=1")
-    for N, C, K in ((256, 64, 64), (256, 64, 256), (16, 1024, 2048)):
-        _, p = _plans((N, C, K, 14, 14, 1, 1, 1, 0), conv.CONV_BF16)
-        assert p[conv.PASS_UPD].startswith("upd_ring dt=1")
-    # 3x3 stride 1: band kernel (fp32), ring kernel (bf16; with a large stride-2 layer still on the row kernel)
+    # 3x3 stride 1: band kernel (fp32), row kernel (bf16)
     _, p = _plans((256, 256, 256, 14, 14, 3, 3, 1, 1), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd_bands")
     _, p = _plans((256, 256, 256, 14, 14, 3, 3, 1, 1), conv.CONV_BF16)
-    assert p[conv.PASS_UPD].startswith("upd_ring dt=1")
-    _, p = _plans((256, 288, 384, 35, 35, 3, 3, 2, 0), conv.CONV_BF16)
-    assert p[conv.PASS_UPD].startswith("upd_rows dt=1")
+    assert p[conv.PASS_UPD].startswith("upd_rows")
+
+
+# N, C, K, H, R, stride, pad, type: update kernel, on either side of the ring kernel's lines
+RING_LINES = [
+    (128, 512, 1024, 28, 1, 2, 0, conv.CONV_F32, "upd_ring dt=0"), (192, 512, 1024, 28, 1, 2, 0, conv.CONV_F32, "upd_1x1 dt=0"),
+    (256, 760, 760, 9, 1, 1, 0, conv.CONV_F32, "upd_ring dt=0"), (256, 256, 512, 56, 1, 2, 0, conv.CONV_F32, "upd_1x1 dt=0"),
+    (256, 64, 64, 56, 1, 1, 0, conv.CONV_F32, "upd_ring dt=0"), (256, 256, 256, 14, 3, 1, 1, conv.CONV_F32, "upd_ring dt=0"),
+    (64, 64, 256, 56, 1, 1, 0, conv.CONV_BF16, "upd_ring dt=1"), (128, 64, 256, 56, 1, 1, 0, conv.CONV_BF16, "upd_1x1 dt=1"),
+    (128, 64, 64, 56, 1, 1, 0, conv.CONV_BF16, "upd_ring dt=1"), (256, 64, 64, 56, 1, 1, 0, conv.CONV_BF16, "upd_1x1 dt=1"),
+    (160, 512, 256, 28, 1, 2, 0, conv.CONV_BF16, "upd_ring dt=1"), (192, 512, 256, 28, 1, 2, 0, conv.CONV_BF16, "upd_1x1 dt=1"),
+    (160, 288, 64, 35, 1, 1, 0, conv.CONV_BF16, "upd_ring dt=1"), (160, 768, 192, 17, 1, 1, 0, conv.CONV_BF16, "upd_1x1 dt=1"),
+    (96, 1024, 2048, 14, 1, 2, 0, conv.CONV_BF16, "upd_ring dt=1"), (128, 1024, 2048, 14, 1, 2, 0, conv.CONV_BF16, "upd_1x1 dt=1"),
+    (64, 288, 384, 35, 3, 2, 0, conv.CONV_BF16, "upd_ring dt=1"), (96, 288, 384, 35, 3, 2, 0, conv.CONV_BF16, "upd_rows dt=1"),
+    (256, 256, 256, 14, 3, 1, 1, conv.CONV_BF16, "upd_ring dt=1"),
+]
+
+
+@pytest.mark.parametrize("case", RING_LINES, ids=lambda c: "x".join(map(str, c[:7])) + ("-bf16" if c[7] else "-f32"))
+def test_update_on_either_side_of_the_ring_kernels_lines(case):
+    N, C, K, H, R, stride, pad, dt, want = case
+    assert _plans((N, C, K, H, H, R, R, stride, pad), dt)[1][conv.PASS_UPD].startswith(want)
+
+
+def test_kernel_families_are_chosen_where_they_apply():
     # one input channel block, fp32: filter-row kernel; backward: all classes in one launch
     _, p = _plans((256, 3, 64, 224, 224, 7, 7, 2, 3), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd_c4")
