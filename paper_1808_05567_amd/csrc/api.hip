@@ -682,9 +682,8 @@ IgemmPlan plan_igemm_tile(int dtype, int N, int Cb, int H, int W, int Kp, int P,
 //   - bf16: everywhere (0.43 - 0.88; 512 -> 512 at 14x14 up to N = 8 and 32 -> 64 at 149x149, N = 256: 1.0);
 //   - fp32: where the tiles fill the chip before their chain of K/8 steps tells, 1.25 tiles per output
 //     channel (0.62 - 0.94, up to 1.01; below: 128 -> 128 at 28x28, N = 8 1.02, 288 -> 384 at 35x35, N = 8 1.03, N = 1
-//     1.57), or the chain is short (K <= 96: 0.55 - 0.94); not where half of a tile's rows are
-//     empty (32 -> 64 at 149x149, N = 32: 1.48); and from 1024 pixels on: the planner's tests pin four
-//     launches below.
+//     1.57), or the chain is short (K <= 96: 0.55 - 0.94, from 25 pixels on; K = 128 1.02, K = 256 1.3 where the
+//     tiles are few); not where half of a tile's rows are empty (32 -> 64 at 149x149, N = 32: 1.48).
 // (128 x 128 tiles: at most 5 % ahead, on a few bf16 layers; fp32 up to twice as long.)
 void plan_bwd_quad(conv_plan *p)
 {
@@ -714,8 +713,7 @@ void plan_bwd_quad(conv_plan *p)
         off += (size_t)f.Kb * R2 * S2 * f.Cp * f.vlen * esize_of(d.dtype);
     }
     // (CONVMI_BWD_QUAD: 0 never, 1 wherever it fits -- a tuning aid)
-    bool want = d.dtype == CONV_BF16 || (f.Cp > 32 && (d.K <= 96 || tiles >= 1.25 * d.K) &&
-                                         (double)d.N * d.H * d.W >= 1024.0);
+    bool want = d.dtype == CONV_BF16 || (f.Cp > 32 && (d.K <= 96 || tiles >= 1.25 * d.K));
     if (const char *env = getenv("CONVMI_BWD_QUAD")) want = atoi(env) != 0;
     if (!want) return;
     for (int i = 0; i < 4; ++i) p->bwd[i] = cls[i];
@@ -1844,9 +1842,9 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
         }
         p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,
                             pad_w, f.P, f.Q, 1, 0, 0, 0, IgemmGeo{}, few_tiles, most_error);
-        // (a filter without a staged kernel: the register-operand kernel from 1e8 flops on; below, the
-        // tests of the untiled kernels expect those)
-        if (!p->fwd.ok && (2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q >= 1.0e8 || getenv("CONVMI_IGEMM_REG"))) {
+        // (a filter without a staged kernel: the register-operand kernel, 0.16 - 0.85 of the untiled loops' time, the
+        // same where both are a launch: 8 -> 8 channels, 1x5 at 9x9, 4.1 us)
+        if (!p->fwd.ok) {
             IgemmGeo any_filter;
             any_filter.fallback = true;
             p->fwd = plan_igemm(d.dtype, d.N, f.Cb, d.H, d.W, f.Kp, f.P, f.Q, d.R, d.S, d.stride, pad_h,

@@ -20,7 +20,7 @@ CHUNKED = [
     ((7, 32, 160, 9, 9, 1, 1, 2, 0), 3),             # 3, 3, 1: the last chunk is one image
     ((5, 3, 64, 32, 32, 7, 7, 2, 3), 2),             # first-layer kernels
     ((4, 48, 40, 8, 8, 1, 3, 1, (0, 1)), 1),         # one image per launch
-    ((6, 20, 24, 9, 11, 1, 5, 1, (0, 2)), 4),        # chunks that run on the direct kernels
+    ((6, 20, 24, 9, 11, 1, 5, 1, (0, 2)), 4),        # chunks without a staged kernel
     ((5, 24, 32, 13, 13, 3, 3, 2, 0), 2),            # strided backward: several launches per chunk
 ]
 

@@ -42,7 +42,7 @@ SMALL = [
     (2, 32, 64, 9, 9, 3, 3, 1, 1),
     (3, 32, 32, 11, 15, 3, 3, 1, 1),
     (1, 8, 16, 5, 147, 3, 3, 1, 1),       # ... in strips of 49 columns
-    (3, 40, 72, 10, 13, 7, 7, 2, 3),      # 7x7 stride 2 over many channels (fp32 forward: direct kernel)
+    (3, 40, 72, 10, 13, 7, 7, 2, 3),      # 7x7 stride 2 over many channels (fp32 forward: no staged kernel)
     # enough 256 x 256 / 128 x 512 tiles for the bf16 eight-wave variants (ragged last pixel tile)
     (25, 128, 512, 28, 28, 1, 1, 1, 0),   # 1x1 forward: 2 channel tiles x 78 pixel tiles, two steps
     (32, 512, 128, 56, 56, 1, 1, 2, 0),   # 1x1 stride 2 backward: scatter with zero fill from eight waves
@@ -100,7 +100,8 @@ RECT = [
 ]
 
 # descriptors outside the tiled kernels' tables: these run (in at least one pass) on the
-# untiled direct kernels, which take any filter, stride and per-axis pad
+# untiled direct kernels where the register-operand kernel is kept out; they take any filter, stride and
+# per-axis pad
 DIRECT = [
     (2, 64, 32, 12, 12, 7, 7, 1, 3),          # 7x7 over many channels
     (2, 20, 24, 9, 11, 1, 5, 1, (0, 2)),
@@ -120,9 +121,11 @@ def _layer(shape, dtype):
 
 @pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("shape", DIRECT, ids=lambda s: "x".join(map(str, s)).replace(" ", ""))
-def test_direct_kernels_match_oracle(shape, dtype):
+def test_direct_kernels_match_oracle(shape, dtype, monkeypatch):
     """Algorithms 1, 6 and 8 as plain loop nests over the blocked layouts, for descriptors no
-    tiled kernel fits: every pass has a kernel and matches the oracle."""
+    tiled kernel fits: every pass has a kernel and matches the oracle.  (Without the register-operand
+    kernel, which stands in for the first two.)"""
+    monkeypatch.setenv("CONVMI_IGEMM_REG", "0")
     N, C, K, H, W, R, S, stride, pad = shape
     I, Wt, dO = make_inputs(shape, dtype, layer_id=41)
     L = _layer(shape, dtype)
@@ -375,8 +378,8 @@ REPEAT = [
     (4, 32, 64, 35, 35, 3, 3, 1, 1),      # four pixel groups folded through LDS
     (2, 3, 64, 64, 64, 7, 7, 2, 3),
     (4, 96, 96, 17, 17, 7, 1, 1, (3, 0)),
-    (300, 8, 8, 5, 5, 2, 2, 1, 1),        # the untiled direct kernels: update ...
-    (8, 20, 24, 9, 11, 1, 5, 1, (0, 2)),  # ... forward and backward
+    (300, 8, 8, 5, 5, 2, 2, 1, 1),        # the untiled direct kernel: update
+    (8, 20, 24, 9, 11, 1, 5, 1, (0, 2)),  # no staged kernel for forward and backward
 ]
 
 
@@ -404,7 +407,7 @@ FUSED = [
     (2, 20, 24, 8, 8, 3, 3, 1, 1),        # padded channel slots stay zero
     (2, 48, 72, 17, 17, 1, 7, 1, (0, 3)),  # rectangular filter, padding along one axis
     (2, 32, 40, 13, 13, 3, 3, 2, 0),       # unpadded stride 2
-    (2, 20, 24, 9, 11, 1, 5, 1, (0, 2)),   # a filter only the direct kernel serves
+    (2, 20, 24, 9, 11, 1, 5, 1, (0, 2)),   # a filter without a staged kernel
     (3, 3, 64, 40, 44, 7, 7, 2, 3),        # a first layer: operators in the resident-filter kernel's store
     (2, 3, 40, 21, 19, 7, 7, 2, 3),        # ... with a ragged channel tile
 ]

@@ -181,9 +181,14 @@ def test_kernel_families_are_chosen_where_they_apply():
     _, p = _plans((256, 3, 64, 224, 224, 7, 7, 2, 3), conv.CONV_F32)
     assert p[conv.PASS_UPD].startswith("upd_c4")
     assert "launches=1" in p[conv.PASS_BWD_DATA]
-    # 3x3 stride 2 backward: one launch per residue class
-    _, p = _plans((4, 64, 64, 14, 14, 3, 3, 2, 1), conv.CONV_F32)
-    assert "launches=4" in p[conv.PASS_BWD_DATA]
+    # 3x3 stride 2 backward: the residue classes in one launch, fp32 one launch each where a long reduction over
+    # few tiles would be one chain
+    for C, dt, launches in ((64, conv.CONV_F32, 1), (256, conv.CONV_F32, 4), (256, conv.CONV_BF16, 1)):
+        _, p = _plans((4, C, C, 14, 14, 3, 3, 2, 1), dt)
+        assert "launches=%d" % launches in p[conv.PASS_BWD_DATA]
+    # a filter without a staged kernel: the register-operand kernel, whatever the size
+    _, p = _plans((1, 8, 8, 9, 9, 1, 5, 1, (0, 2)), conv.CONV_F32)
+    assert p[conv.PASS_FWD].startswith("igemm_reg ") and p[conv.PASS_BWD_DATA].startswith("igemm_reg ")
     # small minibatch, long reduction: the forward reduction is split
     _, p = _plans((1, 512, 512, 7, 7, 3, 3, 1, 1), conv.CONV_F32)
     assert _field(p[conv.PASS_FWD], "ksplit") > 1
