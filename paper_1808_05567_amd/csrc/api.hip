@@ -383,7 +383,8 @@ double estimate_us(const IgemmPlan &p, bool scatter)
         const int occ = frags == 1 ? 8 : frags == 2 ? (bf16 ? 7 : 6) : 3;
         resident = std::max(1, occ * 4 / v.wk);
         launch = f.launch;
-        hbm = bf16 ? 3.3e6 : 3.0e6;
+        // (fp32 beyond a dozen workgroups to a CU: 288 -> 64 backward at 35x35, N = 112, 96 us, 73 in staged tiles)
+        hbm = bf16 ? 3.3e6 : p.grid > 3072 ? 2.3e6 : 3.0e6;
     } else {
         const bool small = v.fm <= 2;
         const Fit f = small ? (bf16 ? Fit{2.4, 1350, 298, 1.24, 2.65, 0.92, 800} : Fit{3.0, 245, 253, 1.03, 0.24, 1.0, 2220})

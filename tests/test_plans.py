@@ -307,3 +307,9 @@ def test_large_tiles_where_small_ones_are_slower():
         _, p = _plans((N,) + rest, conv.CONV_BF16)
         assert p[conv.PASS_FWD].startswith("igemm dt=1 waves=2x2 frags=1x2" if small and rest[4] == 5 else
                                            "igemm dt=1 waves=2x2 frags=2x2" if small else "igemm dt=1 waves=1x4 frags=2x4")
+
+
+def test_fp32_small_tiles_in_registers_only_for_few_of_them():
+    # 288 -> 64 backward at 35x35: beyond a dozen workgroups to a CU (N = 112: 96 us, 73 staged) not in registers
+    for N, name in ((24, "igemm_reg "), (112, "igemm ")):
+        assert _plans((N, 288, 64, 35, 35, 1, 1, 1, 0), conv.CONV_F32)[1][conv.PASS_BWD_DATA].startswith(name)
