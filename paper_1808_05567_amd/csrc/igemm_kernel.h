@@ -183,7 +183,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
     // 1/gk of them, stays resident in its L2 for the whole launch.  The planner picks gk so
     // that the bytes fetched from beyond the L2s, gk x input + (8/gk) x weights, are least.
     // With one channel group (gk == 1) the tiles are dealt in one run, channel tile fastest, in
-    // equal shares: whole pixel tiles per XCD would give some XCDs up to n_kt tiles more than
+    // shares of per_xcd, equal ones as a rule: whole pixel tiles per XCD give some XCDs up to n_kt tiles more than
     // others, and one tile more than an XCD has CUs doubles the launch (252 tiles of the 160 -> 192
     // 7x1 layer at N = 128, fp32: 33 tiles on some XCDs, 274 us; 32 at most, 157).
     const int x = bid & 7, j = bid >> 3;

@@ -313,3 +313,12 @@ def test_fp32_small_tiles_in_registers_only_for_few_of_them():
     # 288 -> 64 backward at 35x35: beyond a dozen workgroups to a CU (N = 112: 96 us, 73 staged) not in registers
     for N, name in ((24, "igemm_reg "), (112, "igemm ")):
         assert _plans((N, 288, 64, 35, 35, 1, 1, 1, 0), conv.CONV_F32)[1][conv.PASS_BWD_DATA].startswith(name)
+
+
+def test_shares_of_the_xcds():
+    # one channel group: whole pixel tiles (21 of 8 tiles: 24 to an XCD) for bf16 1x1 where they cost no CU a tile more, else
+    # equal shares
+    for shape, dt, tiles, grid in (((24, 512, 1024, 28, 28, 1, 1, 2, 0), conv.CONV_BF16, 168, 192),
+                                   ((112, 256, 256, 14, 14, 3, 3, 1, 1), conv.CONV_BF16, 176, 176)):
+        p = _plans(shape, dt)[1][conv.PASS_FWD]
+        assert (_field(p, "tiles"), _field(p, "xcd_kgroups"), _field(p, "grid")) == (tiles, 1, grid)
