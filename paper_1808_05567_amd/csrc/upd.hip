@@ -524,10 +524,12 @@ __global__ __launch_bounds__(256) void upd_bf16_kernel(const UpdArgs a)
 // dW[e] = sum_j partial[j][e] in a fixed order: G interleaved chains over j (chain g takes
 // j = g, g+G, ...), each ascending, then the chains pairwise.
 // Bound by the trip to memory where dW is small (a first layer: 256 copies of 36 - 100 KB), by
-// bandwidth otherwise, so a chain asks for eight copies before it adds the first, and the chains
+// bandwidth otherwise, so a chain asks for eight copies (of 16 chains four) before it adds the first, and the chains
 // are as many as leave each with one or two such groups.  (Eight chains of one load at a time:
 // 11 us for the 256 copies of a first layer, 38 us for the 1024 of a 32 -> 32 3x3 layer at 149x149;
-// and seven of eight threads idle where there are two copies.)
+// and seven of eight threads idle where there are two copies.  Eight chains of eight loads at 33 to 64 copies a
+// power of two apart, which lie in the same memory channels: 63 copies of 512 KB 9.1 us, 6.2 with one load at a time and
+// in 16 chains of four; elsewhere these two are equal, 16 chains below 32 copies up to half as slow again.)
 // HALF: the copies hold the lower four channel slots of eight-slot blocks (a first layer in bf16);
 // the upper four of dW are zeros.
 template <int G, bool HALF>
@@ -535,7 +537,7 @@ __global__ __launch_bounds__(256) void upd_reduce_kernel(const f32x4 *__restrict
                                                          f32x4 *__restrict__ dwt, size_t n4,
                                                          int splits)
 {
-    constexpr int COLS = 256 / G, AHEAD = 8;
+    constexpr int COLS = 256 / G, AHEAD = G == 16 ? 4 : 8;
     const int colt = threadIdx.x % COLS;
     const int g = threadIdx.x / COLS;
     const size_t idx = (size_t)blockIdx.x * COLS + colt;
@@ -573,11 +575,11 @@ __global__ __launch_bounds__(256) void upd_reduce_kernel(const f32x4 *__restrict
 
 int upd_reduce_chains(size_t n_elems, int splits)
 {
-    // (chains of at most one group of eight loads up to 256 copies; a chain takes a thread per four
-    // elements, and a dispatch has fewer than 2^32 of them: 32 chains reach 2 GiB of dW, eight reach 8)
+    // (chains of at most one group of loads up to 256 copies; a chain takes a thread per four
+    // elements, and a dispatch has fewer than 2^32 of them: 32 chains reach 2 GiB of dW, 16 reach 4, eight 8)
     const size_t n4 = n_elems / 4;
-    int chains = splits <= 8 ? 1 : splits <= 64 ? 8 : 32;
-    while (chains > 1 && n4 * chains + 256 >= (size_t)1 << 32) chains = chains == 32 ? 8 : 1;
+    int chains = splits <= 8 ? 1 : splits < 32 ? 8 : splits <= 64 ? 16 : 32;
+    while (chains > 1 && n4 * chains + 256 >= (size_t)1 << 32) chains = chains > 8 ? chains / 2 : 1;
     return chains;
 }
 
@@ -591,6 +593,10 @@ static void launch_upd_reduce_as(const f32x4 *src, f32x4 *dst, size_t n4, int sp
         break;
     case 8:
         hipLaunchKernelGGL((upd_reduce_kernel<8, HALF>), dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, stream, src,
+                           dst, n4, splits);
+        break;
+    case 16:
+        hipLaunchKernelGGL((upd_reduce_kernel<16, HALF>), dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, stream, src,
                            dst, n4, splits);
         break;
     default:
