@@ -1588,12 +1588,12 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
 // Whether the ring kernel is the better one: lines between its time / the other kernel's, both measured with two
 // sets of tensors in turn over 64 layers x N = 1 ... 256.
 //   - 1x1, bf16 (three sets of tensors), by what is read, half of a strided layer's input, and by what the channel
-//     tiles read again: up to 82 MB read 0.4 - 1.04 (stride 2: 512 -> 256 at 28x28, N = 160, 80 MB, 0.91); up to 140 MB where
-//     the channel tiles ask for 260 MB at most (64 -> 64 at 56x56, N = 160, 128 MB, 0.91; 288 -> 64 at 35x35, N = 160, 138 and
-//     238 MB, 0.94; but 768 -> 192 at 17x17, N = 160, 89 and 355 MB, 1.16; 128 -> 512 at 28x28, N = 128, 128 and 411 MB,
-//     1.14); beyond 140 MB mostly slower (128 -> 512, 161 MB 1.07, 64 -> 80 at 73x73, 147 MB 1.17).  By operations: up
-//     to 2.3e10 (2.2e10 0.92; 2.6e10 0.98 - 1.07; 5.3e10 1.30), between two narrow sides (below 128 channels) 5e9 (4.4e9
-//     1.04, 6.6e9 1.12).
+//     tiles read again: up to 82 MB read 0.4 - 1.04 (stride 2: 512 -> 256 at 28x28, N = 160, 80 MB, 0.91; but 512 ->
+//     1024 at 28x28, N = 96, 1.02 - 1.10 from run to run); up to 140 MB where the channel tiles ask for 260 MB at most
+//     (64 -> 64 at 56x56, N = 160, 128 MB, 0.91; 288 -> 64 at 35x35, N = 160, 138 and 238 MB, 0.94; but 768 -> 192 at
+//     17x17, N = 160, 89 and 355 MB, 1.16; 128 -> 512 at 28x28, N = 128, 128 and 411 MB, 1.14); beyond 140 MB mostly
+//     slower (128 -> 512, 161 MB 1.07, 64 -> 80 at 73x73, 147 MB 1.17).  By operations: up to 2.3e10 (2.2e10 0.92;
+//     2.6e10 0.98 - 1.07; 5.3e10 1.30), between two narrow sides (below 128 channels) 5e9 (4.4e9 1.04, 6.6e9 1.12).
 //   - 1x1, fp32: with 256 channels on a side, where the other kernel has eight waves and 256 channels, up to 3e10
 //     (1.3e10 0.63 - 0.98, 2.6e10 0.91 - 0.99, 3.3e10 0.96 - 1.0, 5.3e10 1.02 - 1.05); else everywhere (0.2 - 0.73).
 //   - wider filters, fp32: everywhere (0.19 - 0.97; full 64 x 64 blocks beyond 5e10 operations 0.82 - 0.97).

@@ -30,11 +30,11 @@
 // comes from HBM is waited for by everyone who shares it, and the ring holds two stages: with
 // tensors far beyond the last-level cache the bf16 1x1 layers are better off in the large blocks (planner).
 // Measured against the kernels these layers ran on before (whole update, reduce launch included; three sets of
-// tensors in turn), fp32 / bf16: 256 -> 256 3x3 at 14x14, N = 8: 41 -> 28 / 30 -> 8 us, N = 32: 84 -> 73 /
-// 41 -> 19, N = 128: 263 -> 248 / 60 -> 40; 1024 -> 256 1x1 at 14x14, N = 32: 66 -> 38 / 17 -> 14; 288 -> 384 3x3
-// stride 2 at 35x35, N = 32: 263 -> 164 / 61 -> 41; 160 -> 192 7x1 at 17x17, N = 128: 261 -> 162 / 68 -> 37.  (A first
+// tensors in turn), fp32 / bf16: 256 -> 256 3x3 at 14x14, N = 8: 35 -> 30 / 20 -> 9 us, N = 32: 81 -> 72 /
+// 33 -> 19, N = 128: 264 -> 249 / 54 -> 38; 1024 -> 256 1x1 at 14x14, N = 32: 62 -> 37 / 16 -> 12; 288 -> 384 3x3
+// stride 2 at 35x35, N = 32: 268 -> 173 / 57 -> 45; 160 -> 192 7x1 at 17x17, N = 128: 249 -> 169 / 59 -> 37.  (A first
 // version gathered into registers -- in fp32 a float per lane, 24 clocks of the L1 for each: 296 us
-// where this one takes 248; in bf16 through LDS writes with one stage in flight: 54 us for 40.)
+// where this one takes 249; in bf16 through LDS writes with one stage in flight: 54 us for 38.)
 #include <algorithm>
 
 #include "igemm_kernel.h"
