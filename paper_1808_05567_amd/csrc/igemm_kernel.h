@@ -46,13 +46,22 @@ struct Elem<CONV_F32> {
     }
     template <int NCH>
     static constexpr int mfmas_per_operand = NCH;
-    // Load 4 consecutive channels of one pixel (zeros if byte_off is out of range).
+    // 4 consecutive channels of one pixel as they are in memory (zeros if byte_off is out of range), and
+    // widened.
+    typedef u32x4 Four;
+    static __device__ __forceinline__ Four load4(rsrc_t r, unsigned byte_off, unsigned uniform_off)
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, uniform_off, 0);
+    }
+    static __device__ __forceinline__ void widen4(const Four &v, float (&x)[4])
+    {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[t] = __uint_as_float(v[t]);
+    }
     static __device__ __forceinline__ void load4(rsrc_t r, unsigned byte_off, unsigned uniform_off,
                                                  float (&x)[4])
     {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, uniform_off, 0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = __uint_as_float(v[t]);
+        widen4(load4(r, byte_off, uniform_off), x);
     }
     // Store 4 consecutive channels of one pixel (dropped if byte_off is out of range).
     template <int POLICY = 0>
@@ -94,14 +103,22 @@ struct Elem<CONV_BF16> {
     }
     template <int NCH>
     static constexpr int mfmas_per_operand = 1;
-    static __device__ __forceinline__ void load4(rsrc_t r, unsigned byte_off, unsigned uniform_off,
-                                                 float (&x)[4])
+    typedef u32x2 Four;
+    static __device__ __forceinline__ Four load4(rsrc_t r, unsigned byte_off, unsigned uniform_off)
     {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, uniform_off, 0);
+        return __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, uniform_off, 0);
+    }
+    static __device__ __forceinline__ void widen4(const Four &v, float (&x)[4])
+    {
         x[0] = __uint_as_float(v[0] << 16);
         x[1] = __uint_as_float(v[0] & 0xFFFF0000u);
         x[2] = __uint_as_float(v[1] << 16);
         x[3] = __uint_as_float(v[1] & 0xFFFF0000u);
+    }
+    static __device__ __forceinline__ void load4(rsrc_t r, unsigned byte_off, unsigned uniform_off,
+                                                 float (&x)[4])
+    {
+        widen4(load4(r, byte_off, uniform_off), x);
     }
     template <int POLICY = 0>
     static __device__ __forceinline__ void store4(rsrc_t r, unsigned byte_off, unsigned uniform_off,
