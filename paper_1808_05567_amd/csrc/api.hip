@@ -38,6 +38,7 @@ struct IgemmPlan {
     size_t lds = 0;
     int grid = 0;
     bool reg = false;  // the register-operand kernel (v.wk waves split the reduction of a tile)
+    bool patch = false;  // ... with the pixels in LDS (reg is set too)
     bool fallback = false;  // ... because no staged tile fits (IgemmGeo::fallback)
 };
 
@@ -305,10 +306,11 @@ double igemm_waste(const IgemmPlan &p, int N, int P, int Q, int Kp)
 // ksplit > 1, that many workgroups) that split the reduction.
 IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S, int stride,
                   int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0, int zero_fill,
-                  const IgemmGeo &geo, int fk, int fm, int nw, int ksplit)
+                  const IgemmGeo &geo, int fk, int fm, int nw, int ksplit, int patch_fk = 0)
 {
     IgemmPlan pl;
-    if (igemm_reg_depth(dtype, fk, fm, nw) == 0) return pl;
+    if (patch_fk > 0) fk = patch_fk;  // (the patch kernel's plan: variants of its own)
+    else if (igemm_reg_depth(dtype, fk, fm, nw) == 0) return pl;
     const int V = vlen_of(dtype);
     // 32-bit byte offsets, exact small divisions and 24-bit products, as in try_igemm
     const double in_units = (double)N * Cb * H * W, out_units = (double)N * (Kp / V) * OH * OW;
@@ -356,6 +358,40 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
     return pl;
 }
 
+// The same with the pixels in LDS, for filters of several taps.
+IgemmPlan try_patch(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S, int stride,
+                    int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0, int zero_fill,
+                    const IgemmGeo &geo, int fk, int fm, int nw)
+{
+    IgemmPlan pl;
+    if (geo.fallback || !igemm_patch_exists(dtype, R * S, fk, fm, nw)) return pl;
+    IgemmPlan c = try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0, zero_fill,
+                          geo, 0, fm, nw, 1, fk);
+    if (!c.ok) return pl;
+    IgemmArgs &a = c.a;
+    // (the patch is a run of the flat input list: its pixels' order is that of the result's)
+    const long long HW = (long long)H * W;
+    if ((P - 1) * (long long)stride * W + (Q - 1) * (long long)a.cstride >= HW || (long long)stride * W <= (Q - 1) * (long long)a.cstride)
+        return pl;
+    // exact small divisions
+    if ((double)N * HW >= 4.0e6) return pl;
+    // the longest patch: tiles start at every multiple of the tile in turn, which repeats after P*Q of them
+    const int TM = fm * 32, PQ = P * Q;
+    auto pos = [&](long long m) { return m / PQ * HW + m % PQ / Q * stride * W + m % Q * a.cstride; };
+    long long longest = 0;
+    for (int t = 0; t < std::min(a.n_mt, PQ); ++t)
+        longest = std::max(longest, pos(std::min((long long)N * PQ, (long long)(t + 1) * TM) - 1) - pos((long long)t * TM));
+    longest += (R - 1) * W + S;
+    if (longest > 64 * kPatchLoads) return pl;
+    a.PLS = ceil_div((int)longest, 64) * 64;
+    a.inv_Hs = 1.0f / (float)HW;
+    a.fwd_wt = geo.fwd_wt ? 1 : 0;
+    c.lds = igemm_patch_lds_bytes(fk, fm, nw, a.PLS, geo.fwd_wt);
+    if (c.lds > (size_t)kMaxLds) return pl;
+    c.patch = true;
+    return c;
+}
+
 // What a plan's launch takes, in microseconds, as far as the choice between kernels and tiles goes.
 // A workgroup alone on its CU takes `lone` clocks: a fixed part (set-up, first loads, stores) and
 // its steps, each bound by what it asks of the matrix cores, of the 64 B/clk into the CU or of
@@ -366,8 +402,10 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
 // 6 - 15 %.  The plan with the lowest estimate was on average 1 % (fp32) and 2 % (bf16) behind the
 // fastest variant, and took 0.61 times as long as the large tiles that these sizes ran on before, their
 // reduction split through memory (0.55 / 0.29 times as long as those without the split).
+double estimate_patch_us(const IgemmPlan &p);
 double estimate_us(const IgemmPlan &p, bool scatter)
 {
+    if (p.patch) return estimate_patch_us(p);
     const IgemmArgs &a = p.a;
     const IgemmVariant &v = p.v;
     const bool bf16 = v.dtype == CONV_BF16;
@@ -435,9 +473,48 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     return std::max(t, launch + bytes / hbm);
 }
 
+// The same for the patch kernel: a wave's share is pairs of channel blocks, each a patch and the weights of all taps.
+// Fitted to 4 700 launches (3x3, 1x7 and 7x1 layers, N = 1 ... 256, every variant, forward / with the forward pass's
+// weights; three sets of tensors in turn): rms error 11 %, the choice 3 % behind the fastest variant.
+double estimate_patch_us(const IgemmPlan &p)
+{
+    const IgemmArgs &a = p.a;
+    const IgemmVariant &v = p.v;
+    struct Fit { double launch, fixed, frag, c_mfma, c_load, c_read, tap, pair, pos, exch, busy, four, hbm; };
+    static const Fit fits[2] = {{2.0, 3250, 132, 1.52, 0.83, 0.97, 102, 0, 1.0, 155, 1450, 1.17, 1.66e6},
+                                {1.4, 3060, 433, 1.73, 1.01, 1.84, 273, 307, 0.4, 165, 2480, 1.18, 1.85e6}};
+    const Fit &f = fits[a.fwd_wt ? 1 : 0];
+    const double taps = a.R * a.S, frags = v.fk * v.fm, waves = v.wk;
+    const double pairs = ceil_div(ceil_div(a.Cb, 2), v.wk);
+    const double shared = std::max({taps * frags * 32 * waves / 4 * f.c_mfma,
+                                    waves * (taps * v.fk + a.PLS / 32) * 16 * f.c_load,
+                                    waves * taps * v.fm * 8 * f.c_read * (a.stride > 1 ? 2 : 1)});
+    const double lone = (f.fixed + f.frag * frags + pairs * (std::max(shared, taps * f.tap + f.pair) + f.pos * a.PLS) +
+                         f.exch * frags * waves) * (v.wk == 4 ? f.four : 1.0);
+    const double busy = pairs * (shared + f.pos / 4 * a.PLS) + f.exch * frags * waves + f.busy;
+    // (waves per SIMD that the registers leave room for)
+    const int occ = frags == 1 ? 7 : v.fk == 1 && v.fm == 2 ? 4 : frags == 2 ? 5 : v.fm == 2 ? 3 : 2;
+    const int resident = std::max(1, std::min((int)(kMaxLds / p.lds), occ * 4 / v.wk));
+    const int per_cu = ceil_div(p.grid, 256), full = per_cu / resident, rest = per_cu - full * resident;
+    const double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
+    const double bytes = (double)a.N * a.Cb * a.H * a.W * 16 + (double)a.N * a.P * a.Q * a.Kp * 2 + (double)a.Cb * taps * a.Kp * 16;
+    // (8 % on top: without them the choice is 6 - 26 % behind the kernel it takes over from in 17 of 560 launches, with
+    // them in three)
+    return 1.08 * std::max(t / 2.3e3 + f.launch, f.launch + bytes / f.hbm);
+}
+
+// What the launch that transforms the weights of a backward pass takes, and what the pass loses by finding
+// them beyond the L2: 3.3 us for 0.5 MB, 3.7 for 1.2 MB, 6.4 for 4.7 MB.
+double transform_us(const IgemmPlan &p)
+{
+    return 3.0 + 0.7e-6 * (double)p.a.Cb * p.a.Kp * 16 * (p.reg ? p.a.R * p.a.S : p.v.r * p.v.s);
+}
+
 hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t stream)
 {
-    return p.reg ? launch_igemm_reg(p.v, a, p.grid, stream) : launch_igemm(p.v, a, p.lds, p.grid, stream);
+    return p.patch ? launch_igemm_patch(p.v, a, p.grid, stream)
+           : p.reg ? launch_igemm_reg(p.v, a, p.grid, stream)
+                   : launch_igemm(p.v, a, p.lds, p.grid, stream);
 }
 
 // Plan one launch of the implicit-GEMM kernel.
@@ -494,10 +571,10 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
         const bool scatter = zero_fill != 0;
         IgemmPlan best = p;
         const bool exact_enough = p.ok && (most_error <= 0 || sums_within(best, most_error));
-        double best_us = exact_enough ? 0.95 * estimate_us(p, scatter) : 1e30;
+        double best_us = exact_enough ? 0.95 * estimate_us(p, scatter) + (geo.fwd_wt ? transform_us(p) : 0) : 1e30;
         auto consider = [&](IgemmPlan c) {
             if (!c.ok || (most_error > 0 && !sums_within(c, most_error))) return;
-            const double us = estimate_us(c, scatter);
+            const double us = estimate_us(c, scatter) + (geo.fwd_wt && !c.a.fwd_wt ? transform_us(c) : 0);
             // (of two staged ones bound by memory alike, where tiles abound, the one that reads its input less often)
             if (us < best_us || (us == best_us && !c.reg && !best.reg && c.v.fk > best.v.fk && c.a.total >= 768)) {
                 best = c;
@@ -522,6 +599,12 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
             consider(try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                              zero_fill, geo, k[0], k[1], k[2], k[3]));
         }
+        static const int kPatch[][3] = {{1, 1, 8}, {2, 1, 8}, {1, 2, 8}, {1, 2, 4}, {2, 2, 4}, {2, 2, 8}, {1, 4, 4}, {2, 4, 4}, {1, 4, 8}};
+        for (const auto &k : kPatch) {
+            if (reg_env && strcmp(reg_env, "0") == 0) break;
+            consider(try_patch(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
+                               zero_fill, geo, k[0], k[1], k[2]));
+        }
         p = best;
     }
     // (CONVMI_IGEMM_REG="fk,fm,waves,ksplit": one variant of the register-operand kernel wherever it
@@ -533,6 +616,15 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
                                   zero_fill, geo, fk, fm, nw, ks);
             if (c.ok && most_error > 0) sums_within(c, most_error);
             if (c.ok) return with_group(c);
+        }
+    }
+    // (CONVMI_IGEMM_PATCH="fk,fm,waves": one variant of the patch kernel wherever it exists -- a tuning aid)
+    if (const char *env = getenv("CONVMI_IGEMM_PATCH"); env && p.ok) {
+        int fk = 0, fm = 0, nw = 0;
+        if (sscanf(env, "%d,%d,%d", &fk, &fm, &nw) == 3) {
+            IgemmPlan c = try_patch(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
+                                    zero_fill, geo, fk, fm, nw);
+            if (c.ok) return c;
         }
     }
     p = with_group(p);
@@ -748,7 +840,9 @@ void plan_bwd(conv_plan *p)
         // the entry point without a workspace: a split reduction changes nothing for its callers.
         const size_t wt_b = ((size_t)f.Kb * d.R * d.S * f.Cp * f.vlen * es + 255) / 256 * 256;
         const size_t copy_b = (size_t)d.N * f.Cp * d.H * d.W * sizeof(float);
-        for (const IgemmGeo &geo : {IgemmGeo{}, any_filter})
+        IgemmGeo staged;
+        staged.fwd_wt = true;
+        for (const IgemmGeo &geo : {staged, any_filter})
             if (!b.p.ok)
                 b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, d.H, d.W, d.R, d.S, 1, d.R - 1 - pad_h,
                                  d.S - 1 - pad_w, d.H, d.W, 1, 0, 0, 0, geo, wt_b + 4 * copy_b <= kScratchBytes);
@@ -2080,8 +2174,8 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
     if (h->bwd_mode == 0) return CONV_EUNSUPPORTED;
     if (!ws) return CONV_EWORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    // the transformed weights of all classes, up to four to a launch
-    for (int i = 0; i < h->n_bwd;) {
+    // the transformed weights of all classes, up to four to a launch (none where the kernel reads the forward pass's)
+    for (int i = 0; i < h->n_bwd && !h->bwd[0].p.a.fwd_wt;) {
         if (h->bwd[i].merged) {
             WtMergeArgs m = h->bwd[i].m;
             m.src = wt;
@@ -2115,7 +2209,7 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
     }
     for (int i = 0; i < h->n_bwd; ++i) {
         const BwdClass &b = h->bwd[i];
-        void *wt2 = static_cast<char *>(ws) + b.ws_off;
+        const void *wt2 = b.p.a.fwd_wt ? wt : static_cast<char *>(ws) + b.ws_off;
         IgemmArgs a = b.p.a;
         a.in = dout;
         a.wt = wt2;
@@ -2408,10 +2502,12 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         if (!p->ok) return CONV_EUNSUPPORTED;
         if (p->reg) {
             snprintf(buf, buflen,
-                     "igemm_reg dt=%d waves=%d frags=%dx%d RS=%dx%d tiles=%d (m=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu "
+                     "%s dt=%d waves=%d frags=%dx%d RS=%dx%d tiles=%d (m=%d k=%d) xcd_kgroups=%d grid=%d lds=%zu "
                      "steps=%d group=%d ksplit=%d launches=%d",
-                     p->v.dtype, p->v.wk, p->v.fk, p->v.fm, p->v.r, p->v.s, p->a.total, p->a.n_mt, p->a.n_kt,
+                     p->patch ? "igemm_patch" : "igemm_reg", p->v.dtype, p->v.wk, p->v.fk, p->v.fm, p->v.r, p->v.s,
+                     p->a.total, p->a.n_mt, p->a.n_kt,
                      p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.group, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
+            if (p->a.fwd_wt) strncat(buf, " forward_weights=1", buflen - strlen(buf) - 1);
             return CONV_OK;
         }
         snprintf(buf, buflen,

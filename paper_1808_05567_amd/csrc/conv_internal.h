@@ -83,6 +83,7 @@ struct IgemmArgs {
                         // the weight (which is NaN where the weight is infinite), as on the untiled loops
     int group;          // fp32: steps (staged kernel), or rounds of its steps in flight (register-operand
                         // kernel), that are summed apart; 0: the whole reduction in one chain
+    int fwd_wt;         // patch kernel: `wt` are the forward pass's weights [Kp/8][R][S][Cb*8][8], not transformed ones
     int no_taps;        // ... and this launch has no tap inside anywhere: a class of zeros
 };
 
@@ -93,6 +94,7 @@ struct IgemmGeo {
     bool fallback = false;  // no staged tile fits: the register-operand kernel, whatever the size, in its
                             // exact form
     bool no_taps = false;   // IgemmArgs::no_taps
+    bool fwd_wt = false;    // a kernel that reads the forward pass's weights may be planned (IgemmArgs::fwd_wt)
 };
 
 // Key of a kernel instantiation; the host picks one per pass at plan time.
@@ -133,6 +135,12 @@ unsigned igemm_variant_ppts(const IgemmVariant &v);
 int igemm_reg_depth(int dtype, int fk, int fm, int nw);
 size_t igemm_reg_lds_bytes(int fk, int fm, int nw);
 hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream);
+// The same with the pixels of a tile and their halo in LDS, for filters of several taps (bf16): IgemmArgs::PLS =
+// positions of a patch, at most 64 * kPatchLoads, inv_Hs = 1 / (H*W), the rest as above.
+constexpr int kPatchLoads = 4;
+bool igemm_patch_exists(int dtype, int ntap, int fk, int fm, int nw);
+size_t igemm_patch_lds_bytes(int fk, int fm, int nw, int pls, bool fwd_wt);
+hipError_t launch_igemm_patch(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream);
 // The resident-filter kernel for first layers (one channel block in, one reduction step, one
 // channel tile): LDS it needs for the plan, 0 if it does not serve it; and its launch (plain
 // store only: no fused operators).

@@ -24,7 +24,7 @@
 // at 14x14, N = 1: 25 -> 8.6 / 11 -> 5.3 us, N = 8: 29 -> 24 / 13.5 -> 6.4; 512 -> 2048 1x1 at 7x7, N = 1: 15 -> 6.1 / 8.7 -> 3.9.
 #include <algorithm>
 
-#include "igemm_kernel.h"
+#include "igemm_exchange.h"
 
 namespace convmi {
 
@@ -75,14 +75,9 @@ template <int DT, int FK, int FM, int NW, int D, bool EXACT, bool GROUPS>
 __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kernel(const IgemmArgs a)
 {
     using E_ = Elem<DT>;
-    constexpr int V = E_::V;
-    constexpr int TK = FK * 32, TM = FM * 32, NF = FK * FM, NT = NW * 64;
-    // fragments summed per round through LDS: as many as give every thread a 4-channel chunk
-    constexpr int G = (NT / 256 < NF) ? NT / 256 : NF;
-    static_assert(NF % G == 0, "whole rounds");
+    constexpr int TK = FK * 32, TM = FM * 32;
 
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    f32x4 *const xch = reinterpret_cast<f32x4 *>(lds);  // [G][NW][256] chunks of 4 channels
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -90,24 +85,8 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
     const int h = lane >> 5;
     const int l32 = lane & 31;
 
-    // Workgroup -> tile: dealt over the XCDs as in igemm_kernel.
-    const int bid = blockIdx.x;
-    const int x = bid & 7, jx = bid >> 3;
-    int sp = 0, kt, mt;
-    if (a.gk == 1) {
-        int lin = x * a.per_xcd + jx;
-        if (lin >= a.total * a.ksplit) return;
-        sp = lin / a.total;  // (copy sp of a reduction split over workgroups)
-        lin -= sp * a.total;
-        mt = lin / a.n_kt;
-        kt = lin - mt * a.n_kt;
-    } else {
-        const int kg = x % a.gk, mg = x / a.gk;
-        const int mql = jx / a.kt_per;
-        kt = kg * a.kt_per + (jx - mql * a.kt_per);
-        mt = mg * a.mq_per + mql;
-        if (kt >= a.n_kt || mql >= a.mq_per || mt >= a.n_mt) return;
-    }
+    int kt, mt, sp;
+    if (!small_tile(a, blockIdx.x, kt, mt, sp)) return;
     const int k0 = kt * TK, m0 = mt * TM;
     const int PQ = a.P * a.Q, npix = a.N * PQ, HW = a.H * a.W, RS = a.R * a.S;
     const float inv_PQ = a.inv_P, inv_Q = a.inv_TQ;  // (1 / (P*Q), 1 / Q in this kernel's plans)
@@ -239,108 +218,9 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
                 for (int j = 0; j < FM; ++j) acc[i][j] = sum[i][j];
         }
     }
-    // The waves' sums, G fragments per round: every wave writes its own, then each thread adds
-    // one chunk of 4 consecutive channels of one pixel over the waves, pairwise.
-    constexpr int NR = NF / G;
-    const size_t oplane = (size_t)a.OH * a.OW * 16;
-    const size_t out_bytes = (size_t)a.N * a.out_kb * oplane;
-    constexpr unsigned SC = (V == 8) ? 2u : 1u;  // a partial result is fp32 whatever the type
-    const rsrc_t ro = a.ksplit > 1 ? make_rsrc(static_cast<char *>(a.out) + (size_t)sp * out_bytes * SC, 0, out_bytes * SC)
-                                   : make_rsrc(a.out, 0, out_bytes);
-    const int tg = tid >> 8, ch = tid & 255;  // (wave-uniform: 4 waves per fragment)
-    // Where the thread's chunk of each round goes, and what is fused into it: the operands of all rounds are
-    // requested here, ahead of the first exchange.  (Behind it, round by round, each round waited for a trip
-    // to memory: the compiler moves no load over the stores of the round before, since the residual may be the
-    // output buffer -- a thread reads only what it will write itself.  Bottleneck block of 8 images, 1024 and 256
-    // channels at 14x14, bf16: 20.9 -> 19.7 us; 1024 -> 2048 stride 2 with a residual, N = 12: 14.6 -> 13.7.)
-    int krow[NR], nn[NR], oj[NR], oi[NR], oy[NR], ox[NR];
-    bool ok[NR];
-    unsigned pos[NR];
-    f32x4 sv[NR], bv[NR];
-    typename E_::Four res[NR];
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        const int f = q * G + tg, fi = f / FM, fj = f - fi * FM;
-        krow[q] = k0 + fi * 32 + (ch >> 6) * 8 + 4 * h;
-        const int m = m0 + fj * 32 + l32;
-        nn[q] = fast_div(m, inv_PQ);
-        const int rem = m - mul24(nn[q], PQ);
-        oj[q] = fast_div(rem, inv_Q);
-        oi[q] = rem - mul24(oj[q], a.Q);
-        ok[q] = tg < G && m < npix && krow[q] < a.Kp;
-        oy[q] = mul24(oj[q], a.ostr) + a.oy0;
-        ox[q] = mul24(oi[q], a.ostr_x) + a.ox0;
-        int kb = krow[q] / V;
-        if (a.shuffle) {  // the channel block is a position of the ostr x ostr_x cell
-            const int cy = kb / a.ostr_x;
-            oy[q] += cy;
-            ox[q] += kb - cy * a.ostr_x;
-            kb = 0;
-            ok[q] = ok[q] && oy[q] < a.OH && ox[q] < a.OW;
-        }
-        pos[q] = (unsigned)(mul24(mul24(mul24(nn[q], a.out_kb) + kb, a.OH) + oy[q], a.OW) + ox[q]) * 16u +
-                 (V == 8 ? (unsigned)(krow[q] & 4) * 2u : 0u);
-        sv[q] = f32x4{1.f, 1.f, 1.f, 1.f};
-        bv[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        res[q] = typename E_::Four{};
-        if (a.ksplit == 1) {
-            // (rows beyond Kp are out of range)
-            if (a.scale)
-                sv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      make_rsrc(a.scale, 0, (size_t)a.Kp * 4), (unsigned)krow[q] * 4u, 0, 0));
-            if (a.bias)
-                bv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      make_rsrc(a.bias, 0, (size_t)a.Kp * 4), (unsigned)krow[q] * 4u, 0, 0));
-            if (a.resid) res[q] = E_::load4(make_rsrc(a.resid, 0, out_bytes), ok[q] ? pos[q] : kOutOfRange, 0);
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        const int f0 = q * G;
-        if (f0 > 0) __syncthreads();
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const f32x16 &c = acc[(f0 + g) / FM][(f0 + g) % FM];
-#pragma unroll
-            for (int vq = 0; vq < 4; ++vq) {
-                const f32x4 v = {c[4 * vq], c[4 * vq + 1], c[4 * vq + 2], c[4 * vq + 3]};
-                xch[(g * NW + wave) * 256 + vq * 64 + lane] = v;
-            }
-        }
-        __syncthreads();
-        if (tg < G) {
-            f32x4 v = wave_sum<0, NW>([&](int w) { return xch[(tg * NW + w) * 256 + ch]; });
-            if constexpr (EXACT) {
-                if (ok[q] && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]))
-                    v = sum_inside_image<DT>(a, nn[q], oj[q], oi[q], krow[q], sbeg, sbeg + nst);
-            }
-            if (a.ksplit > 1) {
-                Elem<CONV_F32>::store4(ro, ok[q] ? pos[q] * SC : kOutOfRange, 0, v[0], v[1], v[2], v[3]);
-            } else {
-                const unsigned off = ok[q] ? pos[q] : kOutOfRange;
-                float o[4] = {v[0], v[1], v[2], v[3]};
-                if (a.scale != nullptr || a.bias != nullptr || a.resid != nullptr || a.relu != 0) {
-                    float r4[4];
-                    E_::widen4(res[q], r4);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        o[t] = o[t] * sv[q][t] + r4[t] + bv[q][t];
-                        if (a.relu) o[t] = fmaxf(o[t], 0.0f);
-                    }
-                }
-                E_::store4(ro, off, 0, o[0], o[1], o[2], o[3]);
-                if (a.zero_fill) {
-                    for (int dy = 0; dy < a.ostr; ++dy)
-                        for (int dx = 0; dx < a.ostr_x; ++dx) {
-                            if ((dy | dx) == 0) continue;
-                            const bool in = ok[q] && oy[q] + dy < a.OH && ox[q] + dx < a.OW;
-                            E_::store4(ro, in ? off + (unsigned)(dy * a.OW + dx) * 16u : kOutOfRange, 0, 0.f, 0.f,
-                                       0.f, 0.f);
-                        }
-                }
-            }
-        }
-    }
+    add_and_store<DT, FK, FM, NW, EXACT>(a, acc, lds, k0, m0, sp, [&](int n, int oj, int oi, int krow) {
+        return sum_inside_image<DT>(a, n, oj, oi, krow, sbeg, sbeg + nst);
+    });
 }
 
 #define REG_ENTRY(DT, FK, FM, NW, D) \
