@@ -212,8 +212,8 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
             LR = max_band_rows(N, P, TR, Hs, stride, R);
         }
         ppt = -1;
-        for (int cand = 1; cand <= 16 && ppt < 0; ++cand)
-            if ((have_ppt >> cand & 1) && (long long)LR * LW <= (long long)cand * NT) ppt = cand;
+        for (int cand = 0; cand <= 16 && ppt < 0; ++cand)
+            if ((have_ppt >> cand & 1) && (long long)LR * LW <= (cand == 0 ? NT / 2 : (long long)cand * NT)) ppt = cand;
         if (ppt < 0) continue;
         // the plane pitch is a whole number of wave-level (64-lane) loads
         // (a single-step reduction never touches the second buffer)

@@ -106,9 +106,11 @@ static IgemmEntry g_igemm[] = {
     IGEMM_ENTRY_NB_NT(CONV_BF16, 4, 2, 2, 4, 8, 1, 1, 1, 2, 1),
     // results of few tiles (small minibatches, small images): 64 x 128 and 128 x 128 tiles, picked
     // by the planner's time estimate (see estimate_us)
+    IGEMM_ENTRY_SMALL(CONV_F32, 4, 1, 1, 0), IGEMM_ENTRY_SMALL(CONV_F32, 8, 1, 1, 0),
     IGEMM_ENTRY_SMALL(CONV_F32, 4, 1, 1, 1), IGEMM_ENTRY_SMALL(CONV_F32, 8, 1, 1, 1),
     IGEMM_ENTRY_SMALL(CONV_F32, 2, 3, 3, 1), IGEMM_ENTRY_SMALL(CONV_F32, 2, 3, 3, 2),
     IGEMM_ENTRY_SMALL(CONV_F32, 2, 3, 3, 3),
+    IGEMM_ENTRY_SMALL(CONV_BF16, 4, 1, 1, 0), IGEMM_ENTRY_SMALL(CONV_BF16, 8, 1, 1, 0),
     IGEMM_ENTRY_SMALL(CONV_BF16, 4, 1, 1, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 8, 1, 1, 1),
     IGEMM_ENTRY_SMALL(CONV_BF16, 2, 3, 3, 1), IGEMM_ENTRY_SMALL(CONV_BF16, 2, 3, 3, 2),
     IGEMM_ENTRY_SMALL(CONV_BF16, 2, 3, 3, 3),

@@ -157,18 +157,24 @@ static __device__ __forceinline__ void add_here(f32x16 &sum, const f32x16 &part)
 // GROUPS: IgemmArgs::group > 0 sums that many steps from zero before they are added to the sum of the steps
 // before (0: one chain); where a result of few tiles used to have its reduction split over
 // workgroups, one chain has the larger rounding error (the planner's chain_error).
-template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0, bool GROUPS = false>
+// PPT: staged positions per thread of a staging group of four waves.  0: at most 128 positions, a group is two waves
+// (a 1x1 tile of 128 pixels is two wave-level loads a plane: four waves, each with its load of every plane, brought
+// every other one in twice, a third to two fifths of all that a step loads -- 1024 -> 256 at 14x14, bf16,
+// N = 70: 16.3 -> 14.5 us; 768 -> 128 at 17x17, N = 192: 21.2 -> 17.9; fp32 512 -> 1024 stride 2 at 28x28, N = 28: 56 -> 52).
+template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT_, int NB = 2, int NTI = 0, bool GROUPS = false>
 __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, unsigned char *const lds)
 {
     using E_ = Elem<DT>;
     constexpr int V = E_::V;
     constexpr int NT = WK * WM * 64;
-    // Four or eight waves.  Eight waves are two groups of four for the staging of the input
+    // Four or eight waves.  Eight waves are two groups of four (PPT 0: two waves to a group) for the staging of the input
     // tile: each group brings in its own half of a step's channel planes, with the chunk
     // bookkeeping of a four-wave workgroup.  (Two waves per SIMD inside ONE workgroup share
     // one staged tile: half the bytes pulled into LDS per flop of two four-wave workgroups.)
     static_assert(NT == 256 || NT == 512, "four or eight waves");
-    constexpr int NG = NT / 256;
+    constexpr int GW = PPT_ == 0 ? 2 : 4;  // waves of a staging group
+    constexpr int PPT = PPT_ == 0 ? 1 : PPT_;
+    constexpr int NG = NT / (GW * 64);
     static_assert(NPL % NG == 0, "every wave group stages whole planes");
     constexpr int NPLG = NPL / NG;  // planes a wave group stages per step
     constexpr int TK = WK * FK * 32;
@@ -249,8 +255,8 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
     // surplus loads repeat the last chunk group (same bytes to the same place),
     // which keeps the staging code free of branches.
     const int wave_chunk = wave * 64;
-    const int grp = wave >> 2;               // staging group of this wave
-    const int grp_chunk = (wave & 3) * 64;   // its first chunk within the group's share
+    const int grp = wave / GW;               // staging group of this wave
+    const int grp_chunk = (wave % GW) * 64;  // its first chunk within the group's share
     const size_t in_bytes = (size_t)a.N * a.Cb * HW * 16;
     const size_t wt_bytes = (size_t)a.Cb * NTAPS * a.Kp * 16;
     const rsrc_t rsrc_in = make_rsrc(a.in, 0, in_bytes);
@@ -270,7 +276,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
             const int j = l / PPT, i = l - j * PPT;
             const int pl = grp * NPLG + j;
             load_to_lds_16<NTI ? 2 : 0>(rsrc_in, g_off[i], (unsigned)(cb0 + pl) * (unsigned)HW * 16u,
-                           ib + (pl * a.PLS + min(i * 256 + grp_chunk, a.PLS - 64)) * 16);
+                           ib + (pl * a.PLS + min(i * (GW * 64) + grp_chunk, a.PLS - 64)) * 16);
         } else {
             const int i = l - NPLG * PPT;
             load_to_lds_16(rsrc_wt, w_off[i], (unsigned)cb0 * (unsigned)(NTAPS * a.Kp) * 16u,
@@ -300,7 +306,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
     }
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-        const int p = min(i * 256 + grp_chunk, a.PLS - 64) + lane;
+        const int p = min(i * (GW * 64) + grp_chunk, a.PLS - 64) + lane;
         unsigned off = kOutOfRange;
         if (p < a.LRW) {
             const int row = fast_div(p, inv_LW);

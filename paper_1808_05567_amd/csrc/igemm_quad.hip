@@ -27,6 +27,8 @@ __global__ __launch_bounds__(256, 2) void igemm_quad_kernel(const IgemmQuadArgs 
         igemm_tile<DT, 2, 2, 1, 2, 2, 2, 1, 1>(q.cls[1], bid - q.end[0], lds);
     else if (bid < q.end[2])
         igemm_tile<DT, 2, 2, 1, 2, 2, 1, 2, 1>(q.cls[2], bid - q.end[1], lds);
+    else if (q.cls[3].PLS <= 128)
+        igemm_tile<DT, 2, 2, 1, 2, 4, 1, 1, 0>(q.cls[3], bid - q.end[2], lds);
     else
         igemm_tile<DT, 2, 2, 1, 2, 4, 1, 1, 1>(q.cls[3], bid - q.end[2], lds);
 }
