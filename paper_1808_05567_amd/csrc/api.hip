@@ -327,6 +327,7 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
     a.out_kb = Kp / V;
     a.exact = geo.fallback ? 1 : 0;
     a.no_taps = geo.no_taps ? 1 : 0;
+    a.fwd_wt = geo.fwd_wt && dtype == CONV_BF16 && !geo.fallback ? 1 : 0;
     a.inv_P = 1.0f / (float)(P * Q);
     a.inv_TQ = 1.0f / (float)Q;
     a.n_qt = 1;
@@ -421,14 +422,24 @@ double estimate_us(const IgemmPlan &p, bool scatter)
         const Fit f = bf16 ? Fit{2.6, 0, 256, 0, 1.26, 284, 1480} : Fit{3.9, 0, 441, 1.22, 1.2, 0, 1300};
         const double per = ceil_div(a.st_per, v.wk);  // steps of a wave
         const double simd_waves = v.wk / 4;
+        // (the forward pass's weights through LDS: fitted to 1 930 launches, rms error 11 %, whole rounds of its ring)
+        const Fit w = {3.0, 0, 400, 1.3, 1.16, 248, 870};
+        const double rounds = ceil_div((int)per, 4) * 4;
+        const double shared = std::max({frags * mfma * w.c_mfma * simd_waves, v.wk * (v.fk + v.fm) * 16.0 * w.c_load,
+                                        v.wk * v.fk * 16.0 * 0.67});
+        if (a.fwd_wt) {
+            lone = w.fixed + rounds * std::max(shared, w.step) + w.c_read * frags * v.wk;
+            busy = rounds * shared + w.busy + 0.54 * w.c_read * frags * v.wk;
+        } else {
         lone = f.fixed + per * std::max(frags * mfma * f.c_mfma * simd_waves, f.step) + f.c_read * frags * v.wk;
         busy = per * std::max(frags * mfma * f.c_mfma * simd_waves, v.wk * (v.fk + v.fm) * 16.0 * f.c_load) + f.busy;
+        }
         // (waves per SIMD that the registers leave room for)
         const int occ = frags == 1 ? 8 : frags == 2 ? (bf16 ? 7 : 6) : 3;
         resident = std::max(1, occ * 4 / v.wk);
-        launch = f.launch;
+        launch = a.fwd_wt ? w.launch : f.launch;
         // (fp32 beyond a dozen workgroups to a CU: 288 -> 64 backward at 35x35, N = 112, 96 us, 73 in staged tiles)
-        hbm = bf16 ? 3.3e6 : p.grid > 3072 ? 2.3e6 : 3.0e6;
+        hbm = a.fwd_wt ? 2.6e6 : bf16 ? 3.3e6 : p.grid > 3072 ? 2.3e6 : 3.0e6;
     } else {
         const bool small = v.fm <= 2;
         const Fit f = small ? (bf16 ? Fit{2.4, 1350, 298, 1.24, 2.65, 0.92, 800} : Fit{3.0, 245, 253, 1.03, 0.24, 1.0, 2220})
@@ -449,7 +460,7 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
     t = t / 2.3e3 + launch;
     // (the register-operand kernel with three and more workgroups to a CU: 4 - 9 % over what the rest of the fit says)
-    if (p.reg && bf16 && p.grid > 768) t *= 1.08;
+    if (p.reg && bf16 && p.grid > 768 && !a.fwd_wt) t *= 1.08;
     const int V = vlen_of(v.dtype);
     const double out = (double)a.N * (scatter ? (double)a.OH * a.OW : (double)a.P * a.Q) * (a.Kp / V) * 16;
     if (a.ksplit > 1)  // the second launch, and the partial results there and back
@@ -470,6 +481,8 @@ double estimate_us(const IgemmPlan &p, bool scatter)
         else if (!scatter && !(a.n_stage == 1 && v.npl == 4))
             hbm = bytes <= (a.n_kt > 1 ? 2.56e8 : 1.3e8) ? 6.5e6 : a.n_kt > 1 && bytes <= 4.5e8 ? 5.6e6 : 4.6e6;
     }
+    // (10 % on top: without them 13 of 280 1x1 passes are 3 % and more behind the kernel it takes over from, with them 7)
+    if (a.fwd_wt) return 1.1 * (scatter ? 1.17 : 1.0) * std::max(t, launch + bytes / hbm);
     return std::max(t, launch + bytes / hbm);
 }
 
@@ -860,8 +873,10 @@ void plan_bwd(conv_plan *p)
     }
     if (d.R == 1 && d.S == 1 && pad_h == 0 && pad_w == 0) {
         BwdClass &b = p->bwd[0];
+        IgemmGeo geo;
+        geo.fwd_wt = true;
         b.p = plan_igemm(d.dtype, d.N, f.Kb, f.P, f.Q, f.Cp, f.P, f.Q, 1, 1, 1, 0, 0, d.H, d.W,
-                         d.stride, 0, 0, 1);
+                         d.stride, 0, 0, 1, geo);
         b.x = WtXformArgs{nullptr, nullptr, f.Cb, f.Kb, f.Cp, f.Kp, 1, 1, 1, 1, 1, 0, 0, 1, 1};
         b.ws_off = 0;
         if (b.p.ok) {

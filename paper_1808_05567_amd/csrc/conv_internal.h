@@ -83,7 +83,7 @@ struct IgemmArgs {
                         // the weight (which is NaN where the weight is infinite), as on the untiled loops
     int group;          // fp32: steps (staged kernel), or rounds of its steps in flight (register-operand
                         // kernel), that are summed apart; 0: the whole reduction in one chain
-    int fwd_wt;         // patch kernel: `wt` are the forward pass's weights [Kp/8][R][S][Cb*8][8], not transformed ones
+    int fwd_wt;         // register-operand and patch kernel: `wt` are the forward pass's weights [Kp/8][R][S][Cb*8][8], not transformed ones
     int no_taps;        // ... and this launch has no tap inside anywhere: a class of zeros
 };
 

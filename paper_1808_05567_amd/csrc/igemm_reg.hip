@@ -71,7 +71,9 @@ __device__ __forceinline__ f32x4 sum_inside_image(const IgemmArgs &a, int n, int
 // added to the sum of the groups before.  One chain over a wave's share has the larger rounding error
 // where the same result used to have its reduction split over more chains.  (It costs 1 - 14 %: 128 -> 128 3x3 at 28x28,
 // N = 28, 68.5 us for 66.8; 512 -> 2048 1x1 at 7x7, N = 1, 6.4 for 6.0; 256 -> 1024 1x1 at 14x14, N = 15, 22.9 for 19.6.)
-template <int DT, int FK, int FM, int NW, int D, bool EXACT, bool GROUPS>
+// FWD_WT (bf16, backward by data): the weights as the forward pass has them, through a ring of LDS of the wave's own and
+// transposing reads, the tap flipped (as in igemm_patch.hip): no launch that transforms them first.
+template <int DT, int FK, int FM, int NW, int D, bool EXACT, bool GROUPS, bool FWD_WT = false>
 __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kernel(const IgemmArgs a)
 {
     using E_ = Elem<DT>;
@@ -113,11 +115,20 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
         ih0[j] = m < npix ? y - a.pad_h : 0x40000000;
         iw0[j] = x - a.pad_w;
     }
+    // (the forward pass's weights: the lane's block of dI and channel of dO, in the order of the LDS)
+    const int wquad = lane >> 4, wblk = (lane >> 2) & 3;
+    const int kf = a.Cb * 8;  // ... and their rows
 #pragma unroll
     for (int i = 0; i < FK; ++i) {
-        const int k = k0 + i * 32 + l32;
-        a_off[i] = k < a.Kp ? (unsigned)(mul24(h, RS * a.Kp) + k) * 16u : kOutOfRange;
+        if constexpr (FWD_WT) {
+            const int blk = (k0 >> 3) + 4 * i + wblk;
+            a_off[i] = blk < a.Kp >> 3 ? ((unsigned)blk * (unsigned)(RS * kf) + 4 * wquad + (lane & 3)) * 16u : kOutOfRange;
+        } else {
+            const int k = k0 + i * 32 + l32;
+            a_off[i] = k < a.Kp ? (unsigned)(mul24(h, RS * a.Kp) + k) * 16u : kOutOfRange;
+        }
     }
+    unsigned char *const ring = lds + wave * (D * FK * 1024);
 
     // This wave's share of the reduction: steps [u0, u1), step u = (channel-block pair, r, s);
     // the lane halves take the two blocks of the pair.
@@ -132,8 +143,8 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
     int s = tap - r * a.S;
     int u = u0;  // next step to load
 
-    u32x4 A[D][FK], B[D][FM];
-    auto load = [&](u32x4(&av)[FK], u32x4(&bv)[FM]) {
+    u32x4 A[FWD_WT ? 1 : D][FK], B[D][FM];
+    auto load = [&](u32x4(&av)[FK], u32x4(&bv)[FM], int slot) {
         // (past the wave's share, and the upper half of an odd last pair: zeros on both sides)
         const bool live = u < u1 && 2 * cp + h < a.Cb;
         const unsigned sa = (unsigned)(2 * cp * RS + r * a.S + s) * (unsigned)a.Kp * 16u;
@@ -143,9 +154,17 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
             const bool in = live && (unsigned)(ih0[j] + r) < (unsigned)a.H && (unsigned)(iw0[j] + s) < (unsigned)a.W;
             bv[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_in, in ? b_off[j] : kOutOfRange, u < u1 ? sb : 0u, 0);
         }
+        if constexpr (FWD_WT) {
+            const bool mine = u < u1 && 2 * cp + (wquad >> 1) < a.Cb;
+            const unsigned sf = (unsigned)((RS - 1 - r * a.S - s) * kf + 16 * cp) * 16u;
 #pragma unroll
-        for (int i = 0; i < FK; ++i)
-            av[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_wt, live ? a_off[i] : kOutOfRange, u < u1 ? sa : 0u, 0);
+            for (int i = 0; i < FK; ++i)
+                load_to_lds_16(rsrc_wt, mine ? a_off[i] : kOutOfRange, u < u1 ? sf : 0u, ring + (slot * FK + i) * 1024);
+        } else {
+#pragma unroll
+            for (int i = 0; i < FK; ++i)
+                av[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_wt, live ? a_off[i] : kOutOfRange, u < u1 ? sa : 0u, 0);
+        }
         ++u;
         if (++s == a.S) {
             s = 0;
@@ -170,9 +189,60 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
             for (int j = 0; j < FM; ++j) E_::mma(av[i], bv[j], acc[i][j]);
     };
 
+    if constexpr (FWD_WT) {
+        static_assert(D >= 3 && DT == CONV_BF16, "a step's weights are read while the one before multiplies");
+        // transposing reads: lanes 4*j + q of a group of 16 address 4 channels of dI of channel j of dO and receive
+        // channels 0..3 of dO of their own channel; two reads make the 8 of a lane half
+        const int q4 = lane & 3;
+        const unsigned read_at = lds_address(ring) +
+            (unsigned)(((8 * h + 2 * ((lane >> 4) & 1) + (q4 >> 1)) * 4 + ((lane >> 2) & 3)) * 16 + (q4 & 1) * 8);
+        lds_u32x2 an[2 * FK];
+        auto read_weights = [&](auto sc) {
+            constexpr int slot = decltype(sc)::value;
+            static_for<0, FK>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                an[2 * i] = lds_read_tr16_b64_untracked<(slot * FK + i) * 1024>(read_at);
+                an[2 * i + 1] = lds_read_tr16_b64_untracked<(slot * FK + i) * 1024 + 256>(read_at);
+            });
+        };
+        auto weights_landed = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            lds_reads_pending<0>();
+#pragma unroll
+            for (int o = 0; o < 2 * FK; ++o) lds_read_landed(an[o]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < FK; ++i) A[0][i] = u32x4{an[2 * i][0], an[2 * i][1], an[2 * i + 1][0], an[2 * i + 1][1]};
+        };
+        if (u0 < u1) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                load(A[0], B[d], d);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 1) * (FK + FM)) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            read_weights(std::integral_constant<int, 0>{});
+            weights_landed();
+            for (int g = u0; g < u1; g += D)
+                static_for<0, D>([&](auto dc) {
+                    constexpr int d = decltype(dc)::value;
+                    // (a step past the share: zeros on both sides) the loads of the step after this one have landed
+                    __builtin_amdgcn_sched_barrier(0);
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * (FK + FM)) : "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_weights(std::integral_constant<int, (d + 1) % D>{});
+                    multiply(A[0], B[d]);
+                    weights_landed();
+                    load(A[0], B[d], d);
+                });
+        }
+        wait_all_memory();  // (the rings are done with before the sums take their place)
+        __syncthreads();
+    } else
     if (u0 < u1) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) load(A[d], B[d]);
+        for (int d = 0; d < D; ++d) load(A[d], B[d], d);
         // (loads past u1 ask for nothing: their lanes are out of range)
         // rounds of D steps from g on, up to `end`: the loads of the next round go out behind each step
         auto rounds = [&](int &g, int end) {
@@ -180,7 +250,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
                     multiply(A[d], B[d]);
-                    load(A[d], B[d]);
+                    load(A[d], B[d], d);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -223,12 +293,19 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
     });
 }
 
+constexpr int kWeightRing = 4;  // steps of the ring of the forward pass's weights
+template <int DT, int FK, int FM, int NW>
+constexpr igemm_fn_t fwd_wt_kernel()
+{
+    if constexpr (DT == CONV_BF16) return igemm_reg_kernel<DT, FK, FM, NW, kWeightRing, false, false, true>;
+    else return nullptr;
+}
 #define REG_ENTRY(DT, FK, FM, NW, D) \
     {DT, FK, FM, NW, D, igemm_reg_kernel<DT, FK, FM, NW, D, false, false>, \
-     igemm_reg_kernel<DT, FK, FM, NW, D, true, false>, igemm_reg_kernel<DT, FK, FM, NW, D, false, DT == CONV_F32>}
+     igemm_reg_kernel<DT, FK, FM, NW, D, true, false>, igemm_reg_kernel<DT, FK, FM, NW, D, false, DT == CONV_F32>, fwd_wt_kernel<DT, FK, FM, NW>()}
 static const struct RegEntry {
     int dtype, fk, fm, nw, depth;
-    igemm_fn_t fn, exact_fn, groups_fn;
+    igemm_fn_t fn, exact_fn, groups_fn, fwd_wt_fn;
 } g_reg[] = {
     REG_ENTRY(CONV_F32, 1, 1, 4, 4),  REG_ENTRY(CONV_F32, 1, 1, 8, 3),  REG_ENTRY(CONV_F32, 2, 1, 8, 3),
     REG_ENTRY(CONV_F32, 1, 2, 4, 3),  REG_ENTRY(CONV_F32, 2, 2, 4, 3),
@@ -257,8 +334,9 @@ hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid,
 {
     for (const RegEntry &e : g_reg) {
         if (e.dtype != v.dtype || e.fk != v.fk || e.fm != v.fm || e.nw != v.wk) continue;
-        const size_t lds = igemm_reg_lds_bytes(e.fk, e.fm, e.nw);
-        const igemm_fn_t fn = a.exact ? e.exact_fn : a.group > 0 ? e.groups_fn : e.fn;
+        const size_t lds = std::max(igemm_reg_lds_bytes(e.fk, e.fm, e.nw), a.fwd_wt ? (size_t)e.nw * kWeightRing * e.fk * 1024 : 0);
+        const igemm_fn_t fn = a.fwd_wt ? e.fwd_wt_fn : a.exact ? e.exact_fn : a.group > 0 ? e.groups_fn : e.fn;
+        if (!fn) return hipErrorInvalidDeviceFunction;
         if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(fn), lds); err != hipSuccess)
             return err;
         hipLaunchKernelGGL(fn, dim3(grid), dim3(e.nw * 64), lds, stream, a);
