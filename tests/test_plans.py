@@ -322,3 +322,20 @@ def test_shares_of_the_xcds():
                                    ((112, 256, 256, 14, 14, 3, 3, 1, 1), conv.CONV_BF16, 176, 176)):
         p = _plans(shape, dt)[1][conv.PASS_FWD]
         assert (_field(p, "tiles"), _field(p, "xcd_kgroups"), _field(p, "grid")) == (tiles, 1, grid)
+
+
+def test_fp32_1x1_takes_small_tiles_where_large_ones_leave_a_round_part_empty():
+    """Either side of the lines: 896 and 448 large tiles (of 512 that run at once) behind 32 steps and 64-row tiles
+    in one to two rounds on the small tile, 1 792 and 224 large tiles and four rounds on the large one."""
+    def tile(shape, which):
+        L = conv.conv_create(*shape[:7], shape[7], (0, 0), conv.CONV_F32)
+        try:
+            return "frags=1x2" in conv.conv_describe(L, which)
+        finally:
+            conv.conv_destroy(L)
+    assert tile((256, 512, 2048, 7, 7, 1, 1, 1), conv.PASS_FWD)
+    assert tile((256, 512, 256, 28, 28, 1, 1, 2), conv.PASS_FWD)
+    assert tile((96, 64, 64, 56, 56, 1, 1, 1), conv.PASS_FWD)
+    assert not tile((256, 512, 1024, 28, 28, 1, 1, 2), conv.PASS_FWD)
+    assert not tile((256, 2048, 512, 7, 7, 1, 1, 1), conv.PASS_FWD)
+    assert not tile((256, 192, 64, 35, 35, 1, 1, 1), conv.PASS_BWD_DATA)
