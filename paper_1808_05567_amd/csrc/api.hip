@@ -81,6 +81,7 @@ struct conv_plan {
     int upd_wb = 0;         //   its waves along the narrower tensor's channels
     bool upd_a_is_in = false; //   whether the wider tensor is the input
     UpdRowsVariant urv{};
+    bool upd_window = false;  // ... with one window of the input for all taps (bf16)
     bool upd_ring = false;  // small blocks of dW, the waves split the pixels (fragments: urv.fc, urv.fk)
     int upd_copies = 0;    // partial dW copies the reduce kernel sums
     UpdVariant uv{};
@@ -1604,7 +1605,21 @@ void plan_upd_general(conv_plan *p)
 struct RingCand {
     int fc, fk, nw, depth, splits;
     int sum;  // the kernel's summation
+    bool window = false;  // one window of the input for all taps of a filter row
 };
+bool ring_exists(const conv_plan *p, const RingCand &c, int sum)
+{
+    const conv_desc_t &d = p->d;
+    if (c.window)
+        return d.dtype == CONV_BF16 && p->pad_w <= 4 && upd_window_exists(d.S, d.stride, c.fc, c.fk, c.nw, c.depth, sum);
+    return upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth, sum);
+}
+int window_pitch(const conv_plan *p);
+size_t ring_lds_bytes(const conv_plan *p, const RingCand &c)
+{
+    return c.window ? upd_window_lds_bytes(p->d.stride, c.fc, c.fk, c.nw, c.depth)
+                    : upd_ring_lds_bytes(p->d.S, c.fc, c.fk, c.nw, c.depth);
+}
 // Error of the sums of the update that is planned, its partial copies added in eight chains, ascending.
 double planned_upd_error(const conv_plan *p)
 {
@@ -1640,8 +1655,10 @@ bool plan_ring(const conv_plan *p, const RingCand &c, UpdArgs &a)
 {
     const conv_desc_t &d = p->d;
     const conv_info_t &f = p->info;
-    if (!upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth, c.sum)) return false;
-    const double npix = (double)d.N * f.P * f.Q;
+    if (!ring_exists(p, c, c.sum)) return false;
+    // (a window's list: rows of as many slots as the input columns that a row reads need)
+    const int pitch = c.window ? window_pitch(p) : f.Q;
+    const double npix = (double)d.N * f.P * pitch;
     // exact small divisions, 24-bit products, 32-bit byte offsets
     if (npix >= 3.9e6 || (double)(d.N + 1) * std::max(f.Cb, f.Kb) >= 8.0e6 || (double)d.H * d.W >= 8.0e6 ||
         (double)f.in_bytes + ((double)p->pad_h + d.R) * d.W * 16 >= 4.0e9 || (double)f.out_bytes >= 4.0e9)
@@ -1651,6 +1668,7 @@ bool plan_ring(const conv_plan *p, const RingCand &c, UpdArgs &a)
     memset(&a, 0, sizeof(a));
     a.N = d.N; a.Cb = f.Cb; a.H = d.H; a.W = d.W; a.Kb = f.Kb; a.Kp = f.Kp; a.P = f.P; a.Q = f.Q;
     a.R = d.R; a.S = d.S; a.stride = d.stride; a.pad = p->pad_h; a.pad_w = p->pad_w;
+    a.Qpitch = pitch;
     a.n_ct = ceil_div(f.Cp, c.fc * 32);
     a.n_kt = ceil_div(f.Kp, c.fk * 32);
     // (a wave's chain of additions is an nw-th of a split: at most 2^13 pixels)
@@ -1694,7 +1712,7 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
     int regs = 16 * tiles + (bf16 ? 4 : 3) * ops + 40;
     if (c.sum > 0) regs += c.sum == 1 ? 16 * tiles : tiles > 1 && tiles <= 8 ? 32 : 16;
     if (c.sum == 1 && tiles <= 3) regs = std::min(regs, 128);  // (launch bounds)
-    const int resident = std::max(1, std::min((int)(kMaxLds / upd_ring_lds_bytes(d.S, c.fc, c.fk, c.nw, c.depth)),
+    const int resident = std::max(1, std::min((int)(kMaxLds / ring_lds_bytes(p, c)),
                                               std::min(8, 512 / regs) * 4 / c.nw));
     const int per_cu = ceil_div(a.per_xcd * 8, 256), full = per_cu / resident, rest = per_cu - full * resident;
     double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
@@ -1710,6 +1728,37 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
     t = most * std::pow(std::pow(bound[0] / most, 6) + std::pow(bound[1] / most, 6) + std::pow(bound[2] / most, 6), 1.0 / 6);
     if (a.splits > 1) t += q.reduce + a.splits * (double)f.dwt_bytes * 2 / (q.copy_tb * 1e6);
     return t;
+}
+
+// Slots of an output row of a window's list: as many as the input columns that the row reads need.
+int window_pitch(const conv_plan *p)
+{
+    const conv_desc_t &d = p->d;
+    return std::max(p->info.Q, ceil_div(std::min(d.W, d.stride * (p->info.Q - 1) - p->pad_w + d.S), d.stride));
+}
+// Whether a strided 3x3 layer's update runs with one window of the input for all taps: time of that / of the ring kernel,
+// 13 layers at N = 8 ... 200, two sets of tensors in turn (where the ring kernel's lines leave a layer to the row kernel,
+// beyond 5e10 operations, it stays there; measured there too, 0.65 - 0.81 of that kernel's time):
+//   - from 1e10 operations, more than 96 channels on both sides and few dead slots: 0.75 - 0.96 (288 -> 384 at 35x35, N = 32,
+//     1.8e10, 45.7 -> 42.9 us; 400 -> 400 at 20x20, N = 64, 61 -> 46), 1.00 where an image is narrow and dW wide (200 ->
+//     600 at 30x28, N = 32);
+//   - below: 0.87 - 1.12 from 7e9, slower under 4e9; 64 and 96 channels 1.08 - 1.3; one slot in nine dead (192 -> 320 at
+//     17x17) 1.05 and more.  With stride 1, where a tap's pixels are neighbours, the ring kernel's own loads share
+//     their cache lines and the addresses cost more than they save: 1.00 - 1.28, but 0.92 - 0.98 for 512 -> 512 at 7x7.
+bool ring_applies(const conv_plan *p);
+bool window_applies(const conv_plan *p)
+{
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q;
+    return d.dtype == CONV_BF16 && d.stride == 2 && d.S == 3 && std::min(d.C, d.K) > 96 && flops >= 1.0e10 &&
+           ring_applies(p) && 16 * window_pitch(p) <= 17 * f.Q;
+}
+// What such an update takes, in microseconds, as far as the choice of its splits goes.
+double window_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
+{
+    const double stages = (double)a.rows_per_split / (c.nw * 16);
+    return ceil_div(a.total, 256) * (0.62 * stages + 4) + (a.splits > 1 ? 3.5 + a.splits * (double)p->info.dwt_bytes * 2 / 4.0e6 : 0);
 }
 
 // Whether the ring kernel is the better one: lines between its time / the other kernel's, both measured with two
@@ -1767,8 +1816,7 @@ bool plan_upd_ring(conv_plan *p)
         double error = ring_error(p, c, a, most_error);
         if (force < 0) {
             // one chain where it is exact enough (summing apart costs 1 - 5 % in groups, 6 - 18 % by the stage)
-            const int apart = upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth, 1) ? 1
-                              : upd_ring_exists(d.dtype, d.S, c.fc, c.fk, c.nw, c.depth, 2) ? 2 : 0;
+            const int apart = ring_exists(p, c, 1) ? 1 : ring_exists(p, c, 2) ? 2 : 0;
             if (apart > 0 && error > (apart == 1 ? kErrorMargin : 0.9) * most_error + kOwnRounding) {
                 c.sum = apart;
                 error = ring_error(p, c, a, most_error);
@@ -1776,7 +1824,7 @@ bool plan_upd_ring(conv_plan *p)
             if (error > most_error + kOwnRounding) return;
         }
         if (group > 0) a.group = group;
-        const double us = ring_estimate_us(p, c, a);
+        const double us = c.window ? window_us(p, c, a) : ring_estimate_us(p, c, a);
         if (!have || us < best_us) {
             best = c;
             best_a = a;
@@ -1786,14 +1834,22 @@ bool plan_upd_ring(conv_plan *p)
     };
     // (CONVMI_UPD_RING="fc,fk,waves,depth,splits[,sum[,group]]": one variant wherever it exists, in one chain unless
     // another summation is asked for; "0": never; "any": the planner's choice wherever there is one -- a tuning aid)
-    const char *env = getenv("CONVMI_UPD_RING");
+    const char *env = getenv("CONVMI_UPD_RING"), *window_env = getenv("CONVMI_UPD_WINDOW");
     const bool any = env && strcmp(env, "any") == 0;
-    if (env && !any) {
+    if ((env && !any) || window_env) {
         RingCand c{};
+        if (window_env) {
+            env = window_env;
+            c.window = true;
+        }
         force = 0;
         if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &c.fc, &c.fk, &c.nw, &c.depth, &c.splits, &force, &group) < 5) return false;
         consider(c);
-    } else if (any || ring_applies(p)) {
+    } else if (!any && window_applies(p)) {
+        const int tiles = ceil_div(f.Cp, 64) * ceil_div(f.Kp, 64) * d.R;
+        for (const int splits : {1, std::max(1, 256 / tiles), std::max(1, 512 / tiles)}) consider({2, 2, 8, 3, splits, 0, true});
+    }
+    if (!have && !((env && !any) || window_env) && (any || ring_applies(p))) {
         for (const auto &k : kBlocks) {
             const int tiles = ceil_div(f.Cp, k[0] * 32) * ceil_div(f.Kp, k[1] * 32) * d.R;
             // (32 x 32 blocks of a 1x1 filter re-read both tensors once per 32 channels: for small ones)
@@ -1811,13 +1867,14 @@ bool plan_upd_ring(conv_plan *p)
         return false;
     p->ua = best_a;
     p->urv = UpdRowsVariant{d.R, d.S, 1, best.depth, best.nw, best.fc, best.fk, best.sum};
-    p->upd_lds = upd_ring_lds_bytes(d.S, best.fc, best.fk, best.nw, best.depth);
+    p->upd_lds = ring_lds_bytes(p, best);
     p->upd_grid = best_a.per_xcd * 8;
     p->upd_copies = best_a.splits;
     p->upd_ws = (size_t)p->upd_copies * f.dwt_bytes;  // (one split writes dW itself; the caller brings it all the same)
     p->upd_flat = p->upd_flat_bf16 = p->upd_rows = p->upd_bands = false;
     p->upd_row_launches = p->upd_strips = 1;
     p->upd_ring = true;
+    p->upd_window = best.window;
     p->upd_ok = true;
     return true;
 }
@@ -1835,6 +1892,7 @@ void plan_upd(conv_plan *p)
     p->upd_rows = false;
     p->upd_bands = false;
     p->upd_ring = false;
+    p->upd_window = false;
     // the kernels written for a family of layers first, each declining what it does not fit
     const bool few = plan_upd_c4_bf16(p) || plan_upd_c4(p);
     if (!(few || plan_upd_flat_f32(p) || plan_upd_flat_bf16(p) || plan_upd_rows(p) || plan_upd_bands(p)))
@@ -2300,7 +2358,9 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
     hipError_t e = hipSuccess;
     if (h->upd_ring) {
         if (a.splits == 1) a.partial = static_cast<float *>(dwt);
-        e = launch_upd_ring(h->d.dtype, h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, h->urv.strided, a, h->upd_grid, s);
+        e = h->upd_window ? launch_upd_window(h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, h->urv.strided, a, h->upd_grid, s)
+                          : launch_upd_ring(h->d.dtype, h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, h->urv.strided, a,
+                                            h->upd_grid, s);
         if (a.splits == 1) return e == hipSuccess ? CONV_OK : CONV_ELAUNCH;
     } else if (h->upd_flat_bf16)
         e = launch_upd_bf16_1x1(h->urv, a, h->upd_grid, s);
@@ -2560,10 +2620,10 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         if (h->upd_ring) {
             snprintf(buf, buflen,
                      "upd_ring dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d sum=%d group=%d pixels/split=%d splits=%d tiles=%dx%dx%d "
-                     "grid=%d lds=%zu launches=1",
+                     "grid=%d lds=%zu launches=1 window=%d",
                      (int)h->d.dtype, h->d.R, h->d.S, h->urv.wp,
                      h->urv.wk, h->urv.fc, h->urv.fk, h->urv.strided, h->ua.group, h->ua.rows_per_split, h->ua.splits,
-                     h->ua.n_ct, h->ua.n_kt, h->d.R, h->upd_grid, h->upd_lds);
+                     h->ua.n_ct, h->ua.n_kt, h->d.R, h->upd_grid, h->upd_lds, h->upd_window ? h->ua.Qpitch : 0);
             return CONV_OK;
         }
         if (h->upd_flat_bf16) {
