@@ -158,6 +158,17 @@ int group_within(double n, double unit, double most)
 // resource) reach all of the weights; conv_create takes up to 2^31 of them, 8 GB in fp32.
 bool weights_reach(int Cb, int Kp, int R, int S) { return (double)Cb * R * S * Kp * 16 <= 4.0e9; }
 
+// The launch reads the forward pass's weights: a filter of `taps` taps, of which its tap (0, 0) is tap0, dr and ds taps
+// up from those of the next row and column.
+void forward_weights(IgemmArgs &a, int taps, int tap0, int dr, int ds)
+{
+    a.fwd_wt = 1;
+    a.wt_taps = taps;
+    a.wt_tap0 = tap0;
+    a.wt_dr = dr;
+    a.wt_ds = ds;
+}
+
 // One candidate plan of the implicit-GEMM kernel: `wk` waves along channels,
 // dynamic LDS at most `lds_cap` bytes.  Returns ok=false if nothing fits.
 IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S,
@@ -281,6 +292,14 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
         if (sscanf(env, "%d,%d", &rk, &rm) == 2 && rk >= 0 && rm >= 0) { a.rot_k = rk; a.rot_m = rm; }
     }
     pl.v = IgemmVariant{dtype, wk, wm, fk, fm, npl, R, S, ppt, nb};
+    if (geo.fwd_wt) {
+        IgemmVariant w = pl.v;
+        w.fw = 1;
+        if (igemm_variant_exists(w)) {
+            pl.v = w;
+            forward_weights(a, R * S, R * S - 1, S, 1);
+        }
+    }
     pl.lds = (a.n_stage > 1 ? nb : 1) * ((size_t)nent * TK * 16 + (size_t)npl * a.PLS * 16);
     pl.grid = a.per_xcd * 8;
     // 32-bit index guards (offsets are kept in 16-byte units / elements)
@@ -483,7 +502,7 @@ double estimate_us(const IgemmPlan &p, bool scatter)
             hbm = bytes <= (a.n_kt > 1 ? 2.56e8 : 1.3e8) ? 6.5e6 : a.n_kt > 1 && bytes <= 4.5e8 ? 5.6e6 : 4.6e6;
     }
     // (10 % on top: without them 13 of 280 1x1 passes are 3 % and more behind the kernel it takes over from, with them 7)
-    if (a.fwd_wt) return 1.1 * (scatter ? 1.17 : 1.0) * std::max(t, launch + bytes / hbm);
+    if (p.reg && a.fwd_wt) return 1.1 * std::max(t, launch + bytes / hbm);
     return std::max(t, launch + bytes / hbm);
 }
 
@@ -521,6 +540,9 @@ double estimate_patch_us(const IgemmPlan &p)
 // them beyond the L2: 3.3 us for 0.5 MB, 3.7 for 1.2 MB, 6.4 for 4.7 MB.
 double transform_us(const IgemmPlan &p)
 {
+    // (fp32: not counted, which leaves the lines between staged tiles and operands in registers, measured with the launch
+    // on both sides, where they are: counted, 128 -> 128 3x3 at 28x28, N = 48, takes 102 us for 95)
+    if (p.v.dtype == CONV_F32) return 0;
     return 3.0 + 0.7e-6 * (double)p.a.Cb * p.a.Kp * 16 * (p.reg ? p.a.R * p.a.S : p.v.r * p.v.s);
 }
 
@@ -585,7 +607,7 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
         const bool scatter = zero_fill != 0;
         IgemmPlan best = p;
         const bool exact_enough = p.ok && (most_error <= 0 || sums_within(best, most_error));
-        double best_us = exact_enough ? 0.95 * estimate_us(p, scatter) + (geo.fwd_wt ? transform_us(p) : 0) : 1e30;
+        double best_us = exact_enough ? 0.95 * estimate_us(p, scatter) + (geo.fwd_wt && !p.a.fwd_wt ? transform_us(p) : 0) : 1e30;
         auto consider = [&](IgemmPlan c) {
             if (!c.ok || (most_error > 0 && !sums_within(c, most_error))) return;
             const double us = estimate_us(c, scatter) + (geo.fwd_wt && !c.a.fwd_wt ? transform_us(c) : 0);
@@ -677,7 +699,7 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
     if (p.ok && want && !p.reg) {
         IgemmVariant v = p.v;
         v.nt = 1;
-        if (igemm_variant_exists(v)) p.v = v;
+        if (igemm_variant_exists(v)) p.v = v;  // (with the weights it has)
     }
     return p;
 }
@@ -838,6 +860,8 @@ void plan_bwd_quad(conv_plan *p)
                              a.oy0, a.ox0, 0, IgemmGeo{}, 2, 2, 1, 2, (size_t)kMaxLds, 2, R2 * S2 == 1 ? 4 : 2, 1);
         if (!cls[i].p.ok) return;
         tiles += cls[i].p.a.total;
+        const int off_r = cls[i].x.r_off, off_s = cls[i].x.s_off;
+        forward_weights(cls[i].p.a, 9, (off_r + 2 * (R2 - 1)) * 3 + off_s + 2 * (S2 - 1), 6, 2);
         cls[i].x.R2 = R2;
         cls[i].x.S2 = S2;
         cls[i].ws_off = off;
@@ -2291,7 +2315,7 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
             const BwdClass &b = h->bwd[i];
             q.cls[i] = b.p.a;
             q.cls[i].in = dout;
-            q.cls[i].wt = static_cast<const char *>(ws) + b.ws_off;
+            q.cls[i].wt = wt;
             q.cls[i].out = din;
             q.end[i] = grid += b.p.grid;
             lds = std::max(lds, b.p.lds);
@@ -2609,6 +2633,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
                  p->v.dtype, p->v.wk, p->v.wm, p->v.fk, p->v.fm, p->v.npl, p->v.nt, p->v.r, p->v.s, p->v.ppt,
                  p->a.TR, p->a.TQ, p->a.total, p->a.n_mt, p->a.n_qt, p->a.n_kt, p->a.gk, p->grid, p->lds,
                  p->a.n_stage, p->a.group, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
+        if (p->a.fwd_wt) strncat(buf, " forward_weights=1", buflen - strlen(buf) - 1);
         if (pass == 0 && h->fwd_stem_lds) {
             const size_t n = strlen(buf);
             snprintf(buf + n, buflen - n, " resident_filter_lds=%zu", h->fwd_stem_lds);

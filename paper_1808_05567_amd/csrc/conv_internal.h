@@ -83,7 +83,10 @@ struct IgemmArgs {
                         // the weight (which is NaN where the weight is infinite), as on the untiled loops
     int group;          // fp32: steps (staged kernel), or rounds of its steps in flight (register-operand
                         // kernel), that are summed apart; 0: the whole reduction in one chain
-    int fwd_wt;         // register-operand and patch kernel: `wt` are the forward pass's weights [Kp/8][R][S][Cb*8][8], not transformed ones
+    int fwd_wt;         // backward pass: `wt` are the forward pass's weights [Kp/V][taps][Cb*V][V], not transformed ones
+    // ... staged kernel: their taps, which of them tap (0, 0) of this launch is, and how far apart those of
+    // consecutive rows and columns lie (downwards)
+    int wt_taps, wt_tap0, wt_dr, wt_ds;
     int no_taps;        // ... and this launch has no tap inside anywhere: a class of zeros
 };
 
@@ -107,6 +110,7 @@ struct IgemmVariant {
     int ppt;     // staged input pixels per thread
     int nb = 2;  // LDS buffers of the staging ring
     int nt = 0;  // 1: the input tile is loaded non-temporally (plans with one channel tile)
+    int fw = 0;  // 1: the forward pass's weights (IgemmArgs::fwd_wt)
 };
 
 // Raise a kernel's dynamic-LDS limit to at least `bytes` (once per kernel and size; safe to

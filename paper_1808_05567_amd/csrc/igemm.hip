@@ -124,7 +124,7 @@ static IgemmEntry *find_in(IgemmEntry *tab, int n, const IgemmVariant &v)
     for (int i = 0; i < n; ++i) {
         const IgemmVariant &w = tab[i].v;
         if (w.dtype == v.dtype && w.wk == v.wk && w.wm == v.wm && w.fk == v.fk && w.fm == v.fm &&
-            w.npl == v.npl && w.r == v.r && w.s == v.s && w.ppt == v.ppt && w.nb == v.nb && w.nt == v.nt)
+            w.npl == v.npl && w.r == v.r && w.s == v.s && w.ppt == v.ppt && w.nb == v.nb && w.nt == v.nt && w.fw == v.fw)
             return &tab[i];
     }
     return nullptr;
@@ -132,6 +132,11 @@ static IgemmEntry *find_in(IgemmEntry *tab, int n, const IgemmVariant &v)
 
 static IgemmEntry *find_igemm(const IgemmVariant &v)
 {
+    if (v.fw) {
+        int n = 0;
+        IgemmEntry *tab = igemm_fwd_wt_entries(&n);
+        return find_in(tab, n, v);
+    }
     if (IgemmEntry *e = find_in(g_igemm, (int)(sizeof(g_igemm) / sizeof(g_igemm[0])), v)) return e;
     int n = 0;
     IgemmEntry *rect = igemm_rect_entries(&n);

@@ -161,7 +161,11 @@ static __device__ __forceinline__ void add_here(f32x16 &sum, const f32x16 &part)
 // (a 1x1 tile of 128 pixels is two wave-level loads a plane: four waves, each with its load of every plane, brought
 // every other one in twice, a third to two fifths of all that a step loads -- 1024 -> 256 at 14x14, bf16,
 // N = 70: 16.3 -> 14.5 us; 768 -> 128 at 17x17, N = 192: 21.2 -> 17.9; fp32 512 -> 1024 stride 2 at 28x28, N = 28: 56 -> 52).
-template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT_, int NB = 2, int NTI = 0, bool GROUPS = false>
+// FWD_WT (backward by data): the weights as the forward pass has them, [channel block of dI][tap][channel of dO][V].  A
+// fragment of a round, 32 channels of dI by two blocks of dO, is 64 chunks of V channels of dI each; they are staged in
+// an order from which the operands can be read transposed -- bf16 with the transposing reads, fp32 a float at a time --
+// and the launch that would transform all weights first is left out (3.3 us and more of every backward pass).
+template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT_, int NB = 2, int NTI = 0, bool GROUPS = false, bool FWD_WT = false>
 __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, unsigned char *const lds)
 {
     using E_ = Elem<DT>;
@@ -258,7 +262,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
     const int grp = wave / GW;               // staging group of this wave
     const int grp_chunk = (wave % GW) * 64;  // its first chunk within the group's share
     const size_t in_bytes = (size_t)a.N * a.Cb * HW * 16;
-    const size_t wt_bytes = (size_t)a.Cb * NTAPS * a.Kp * 16;
+    const size_t wt_bytes = (size_t)a.Cb * (FWD_WT ? a.wt_taps : NTAPS) * a.Kp * 16;
     const rsrc_t rsrc_in = make_rsrc(a.in, 0, in_bytes);
     const rsrc_t rsrc_wt = make_rsrc(a.wt, 0, wt_bytes);
     unsigned g_off[PPT];  // per-thread source byte offsets of the staged input pixels (plane 0)
@@ -279,7 +283,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
                            ib + (pl * a.PLS + min(i * (GW * 64) + grp_chunk, a.PLS - 64)) * 16);
         } else {
             const int i = l - NPLG * PPT;
-            load_to_lds_16(rsrc_wt, w_off[i], (unsigned)cb0 * (unsigned)(NTAPS * a.Kp) * 16u,
+            load_to_lds_16(rsrc_wt, w_off[i], (unsigned)cb0 * (unsigned)(FWD_WT ? V : NTAPS * a.Kp) * 16u,
                            wb + min(i * NT + wave_chunk, WCH - 64) * 16);
         }
     };
@@ -295,12 +299,23 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
     for (int i = 0; i < WPT; ++i) {
         const int w = min(i * NT + wave_chunk, WCH - 64) + lane;
         unsigned off = kOutOfRange;
-        const int e = w / TK;
-        const int k = w - e * TK;
-        const int tap = e / NPL;
-        const int pl = e - tap * NPL;
-        if (tap < NTAPS && k0 + k < a.Kp)
-            off = (unsigned)(mul24(pl * NTAPS + tap, a.Kp) + k0 + k) * 16u;
+        if constexpr (FWD_WT) {
+            // chunk u of round q's fragment f: bf16 quads of four channels of dO, the quad's four blocks of dI side by
+            // side; fp32 the eight channels of dO of a block of dI, swapped so that eight blocks' reads spread over the banks
+            const int q = w / (2 * TK), rest_w = w - q * (2 * TK), f = rest_w >> 6, u = rest_w & 63;
+            const int tap = q / (NPL / 2), pp = q - tap * (NPL / 2), tr = tap / S, ts = tap - tr * S;
+            const int blk = k0 / V + f * (32 / V) + (V == 8 ? (u >> 2) & 3 : u >> 3);
+            const int ch = pp * 2 * V + (V == 8 ? (u >> 4) * 4 + (u & 3) : (u & 7) ^ (u >> 3));
+            if (blk < a.Kp / V)
+                off = ((unsigned)(blk * a.wt_taps + a.wt_tap0 - tr * a.wt_dr - ts * a.wt_ds) * (unsigned)(a.Cb * V) + (unsigned)ch) * 16u;
+        } else {
+            const int e = w / TK;
+            const int k = w - e * TK;
+            const int tap = e / NPL;
+            const int pl = e - tap * NPL;
+            if (tap < NTAPS && k0 + k < a.Kp)
+                off = (unsigned)(mul24(pl * NTAPS + tap, a.Kp) + k0 + k) * 16u;
+        }
         w_off[i] = off;
         fetch_one(0, NPLG * PPT + i);
     }
@@ -378,6 +393,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
     __syncthreads();
 
     if constexpr (NPL == 1) {
+        static_assert(!FWD_WT, "a fragment is two channel blocks");
         static_assert(NB == 2, "the one-plane path is double buffered");
         // One channel block per step: the two lane halves take two taps.
         for (int st = 0; st < nst; ++st) {
@@ -439,17 +455,60 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
         constexpr int NQ = NTAPS * (NPL / 2);
         static_assert(NQ >= 2, "a step needs two MFMA rounds");
         u32x4 ac[FK], bc[FM];
-        auto read_round = [&](int buf, int q, u32x4(&af)[FK], u32x4(&bf)[FM]) {
+        // (FWD_WT: what the transposing reads, which the compiler does not track, have under way; the lane's address
+        // in a fragment: bf16, lanes 4*j + q of a group of 16 address 4 channels of dI of channel j of dO and receive
+        // channels 0..3 of dO of their own; fp32, its channel of dI of channel t of its lane half's block of dO)
+        lds_u32x2 tr[FWD_WT && V == 8 ? 2 * FK : 1];
+        unsigned tr_lane[FWD_WT ? (V == 8 ? 1 : 4) : 1];
+        if constexpr (FWD_WT) {
+            if constexpr (V == 8)
+                tr_lane[0] = (unsigned)(wave_k * FK * 1024 + ((8 * h + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 4 + ((lane >> 2) & 3)) * 16 +
+                                        (lane & 1) * 8);
+            else
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    tr_lane[t] = (unsigned)(wave_k * FK * 1024 + (l32 >> 2) * 128 + (((4 * h + t) ^ (l32 >> 2)) & 7) * 16 + (l32 & 3) * 4);
+        }
+        auto read_round = [&](int buf, auto qc, u32x4(&af)[FK], u32x4(&bf)[FM]) {
+            constexpr int q = decltype(qc)::value;
             const unsigned char *wb = lds + buf * bufbytes;
             const unsigned char *ib = wb + WBYTES;
-            const int tap = q / (NPL / 2), pp = q - tap * (NPL / 2);
+            constexpr int tap = q / (NPL / 2), pp = q - tap * (NPL / 2);
             const int toff = ((tap / S) * a.LW + (tap % S) + 2 * pp * a.PLS) * 16;
+            if constexpr (FWD_WT && V == 8) {
+                const unsigned at = lds_address(wb) + tr_lane[0];
+                static_for<0, FK>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    tr[2 * i] = lds_read_tr16_b64_untracked<2 * q * TK * 16 + i * 1024>(at);
+                    tr[2 * i + 1] = lds_read_tr16_b64_untracked<2 * q * TK * 16 + i * 1024 + 256>(at);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            } else if constexpr (FWD_WT) {
 #pragma unroll
-            for (int i = 0; i < FK; ++i)
-                af[i] = *reinterpret_cast<const u32x4 *>(wb + a_base + (2 * q * TK + 32 * i) * 16);
+                for (int i = 0; i < FK; ++i)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        af[i][t] = *reinterpret_cast<const unsigned *>(wb + tr_lane[t] + 2 * q * TK * 16 + i * 1024);
+            } else {
+#pragma unroll
+                for (int i = 0; i < FK; ++i)
+                    af[i] = *reinterpret_cast<const u32x4 *>(wb + a_base + (2 * q * TK + 32 * i) * 16);
+            }
 #pragma unroll
             for (int j = 0; j < FM; ++j)
                 bf[j] = *reinterpret_cast<const u32x4 *>(ib + bpos[j] + toff);
+        };
+        // The transposing reads of a round have landed in its operands.
+        auto weights_landed = [&](u32x4(&af)[FK]) {
+            if constexpr (FWD_WT && V == 8) {
+                __builtin_amdgcn_sched_barrier(0);
+                lds_reads_pending<0>();
+#pragma unroll
+                for (int o = 0; o < 2 * FK; ++o) lds_read_landed(tr[o]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < FK; ++i) af[i] = u32x4{tr[2 * i][0], tr[2 * i][1], tr[2 * i + 1][0], tr[2 * i + 1][1]};
+            }
         };
         // With NB > 2 buffers the loads of step st+NB-1 issue during step st and a
         // step waits only for the loads of the step that follows it: a wave's
@@ -463,13 +522,13 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
         auto step = [&](int st, auto more_tag, auto issue_tag) {
             constexpr bool MORE = decltype(more_tag)::value;    // a step follows
             constexpr bool ISSUE = decltype(issue_tag)::value;  // step st+AHEAD exists
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
+            static_for<0, NQ>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
                 u32x4 an[FK], bn[FM];
-                if (q + 1 < NQ)
-                    read_round(st % NB, q + 1, an, bn);
-                else if (MORE)
-                    read_round((st + 1) % NB, 0, an, bn);
+                if constexpr (q + 1 < NQ)
+                    read_round(st % NB, std::integral_constant<int, q + 1>{}, an, bn);
+                else if constexpr (MORE)
+                    read_round((st + 1) % NB, std::integral_constant<int, 0>{}, an, bn);
                 if (ISSUE && q == 0) fetch(st + AHEAD);
 #pragma unroll
                 for (int i = 0; i < FK; ++i)
@@ -485,6 +544,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
                     __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);  // staging loads
                 }
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (q + 1 < NQ || MORE) weights_landed(an);
                 if (MORE && q == NQ - 2) {
                     if (ISSUE && NB > 2)
                         __builtin_amdgcn_s_waitcnt(WAIT_PARTIAL);
@@ -498,9 +558,10 @@ __device__ __forceinline__ void igemm_tile(const IgemmArgs &a, const int bid, un
 #pragma unroll
                     for (int j = 0; j < FM; ++j) bc[j] = bn[j];
                 }
-            }
+            });
         };
-        read_round(0, 0, ac, bc);
+        read_round(0, std::integral_constant<int, 0>{}, ac, bc);
+        weights_landed(ac);
         int st = 0;
         if constexpr (GROUPS) {
             if (a.group > 0) {
@@ -686,11 +747,11 @@ constexpr bool igemm_groups(int dt, int wk, int wm, int fk, int fm)
     return dt == CONV_F32 && wk == 2 && wm == 2 && fk == 1 && fm == 2;
 }
 
-template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0>
+template <int DT, int WK, int WM, int FK, int FM, int NPL, int R, int S, int PPT, int NB = 2, int NTI = 0, bool FWD_WT = false>
 __global__ __launch_bounds__(WK *WM * 64, ((WK * WM == 4 && FK * FM * 16 <= 128 && R * S < 49) ? 2 : 1)) void igemm_kernel(const IgemmArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    igemm_tile<DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NTI, igemm_groups(DT, WK, WM, FK, FM)>(a, blockIdx.x, lds);
+    igemm_tile<DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NTI, !FWD_WT && igemm_groups(DT, WK, WM, FK, FM), FWD_WT>(a, blockIdx.x, lds);
 }
 
 typedef void (*igemm_fn_t)(const IgemmArgs);
@@ -713,7 +774,14 @@ struct IgemmEntry {
     IGEMM_ENTRY(DT, 2, 2, 1, 2, NPL, R, S, PPT), IGEMM_ENTRY(DT, 2, 2, 2, 2, NPL, R, S, PPT)
 
 
-// Entries of the rectangular-filter translation unit.
+#define IGEMM_ENTRY_WT(DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NT)          \
+    {                                                                            \
+        {DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NT, 1},                         \
+            igemm_kernel<DT, WK, WM, FK, FM, NPL, R, S, PPT, NB, NT, true>       \
+    }
+
+// Entries of the rectangular-filter translation unit, and of the one for the forward pass's weights.
 IgemmEntry *igemm_rect_entries(int *count);
+IgemmEntry *igemm_fwd_wt_entries(int *count);
 
 }  // namespace convmi

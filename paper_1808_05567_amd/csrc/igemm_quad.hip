@@ -16,21 +16,27 @@
 
 namespace convmi {
 
+template <int DT, int NPL, int R, int S, int PPT>
+static __device__ __forceinline__ void quad_tile(const IgemmArgs &a, int bid, unsigned char *lds)
+{
+    igemm_tile<DT, 2, 2, 1, 2, NPL, R, S, PPT, 2, 0, false, true>(a, bid, lds);
+}
+
 template <int DT>
 __global__ __launch_bounds__(256, 2) void igemm_quad_kernel(const IgemmQuadArgs q)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int bid = blockIdx.x;  // (every class's grid is a multiple of 8: its XCDs stay bid mod 8)
     if (bid < q.end[0])
-        igemm_tile<DT, 2, 2, 1, 2, 2, 2, 2, 1>(q.cls[0], bid, lds);
+        quad_tile<DT, 2, 2, 2, 1>(q.cls[0], bid, lds);
     else if (bid < q.end[1])
-        igemm_tile<DT, 2, 2, 1, 2, 2, 2, 1, 1>(q.cls[1], bid - q.end[0], lds);
+        quad_tile<DT, 2, 2, 1, 1>(q.cls[1], bid - q.end[0], lds);
     else if (bid < q.end[2])
-        igemm_tile<DT, 2, 2, 1, 2, 2, 1, 2, 1>(q.cls[2], bid - q.end[1], lds);
+        quad_tile<DT, 2, 1, 2, 1>(q.cls[2], bid - q.end[1], lds);
     else if (q.cls[3].PLS <= 128)
-        igemm_tile<DT, 2, 2, 1, 2, 4, 1, 1, 0>(q.cls[3], bid - q.end[2], lds);
+        quad_tile<DT, 4, 1, 1, 0>(q.cls[3], bid - q.end[2], lds);
     else
-        igemm_tile<DT, 2, 2, 1, 2, 4, 1, 1, 1>(q.cls[3], bid - q.end[2], lds);
+        quad_tile<DT, 4, 1, 1, 1>(q.cls[3], bid - q.end[2], lds);
 }
 
 hipError_t launch_igemm_quad(int dtype, const IgemmQuadArgs &q, size_t lds_bytes, hipStream_t stream)
