@@ -196,7 +196,8 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
  *   - A plan whose backward pass needs more scratch returns CONV_ESCRATCH before anything
  *     is launched (all layers of Table I fit: at most 9.4 MB, layer 18 in fp32).
  *   - The array keeps the previous call's contents; nothing has to start at zero, because
- *     the weight transform writes every byte the convolution kernel then reads.
+ *     the weight transform writes every byte the convolution kernel then reads (a kernel that
+ *     takes the forward pass's weights reads none of it; the size asked for is the same).
  *   - All calls on one GPU share the one array: calls that may overlap on a GPU (different
  *     streams, different host threads) race on it.  Serialise them, or use conv_bwd_data
  *     with a workspace per stream.

@@ -11,7 +11,9 @@
 // Bound by the operand reads from LDS in bf16 (three reads to two MFMAs), by the MFMAs in fp32.  Measured against
 // one launch per class and per transform of its weights: 288 -> 384 at 35x35, N = 32, bf16 58 -> 39 us
 // (fp32 202 -> 176); 64 -> 64 at 56x56, N = 8, 19 -> 8 (24 -> 15); 512 -> 512 at 14x14, N = 128, 81 -> 51
-// (293 -> 233).
+// (293 -> 233).  All classes read the forward pass's weights (FWD_WT in igemm_kernel.h), which leaves out the launch that
+// transformed them: 288 -> 384 at 35x35, N = 32, bf16 40 -> 36; 42 passes at N = 2 ... 192, 0.80 of the time in bf16 (0.61 ... 1.04),
+// 0.96 in fp32 (0.87 ... 1.03).
 #include "igemm_kernel.h"
 
 namespace convmi {

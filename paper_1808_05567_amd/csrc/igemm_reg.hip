@@ -22,6 +22,8 @@
 //
 // Measured against the staged kernel with the reduction split over workgroups (forward, fp32 / bf16): 256 -> 256 3x3
 // at 14x14, N = 1: 25 -> 8.6 / 11 -> 5.3 us, N = 8: 29 -> 24 / 13.5 -> 6.4; 512 -> 2048 1x1 at 7x7, N = 1: 15 -> 6.1 / 8.7 -> 3.9.
+// (bf16 filters of seven and nine taps run on igemm_patch.hip, which reads their pixels once for all taps, where that is
+// the faster one by estimate.)
 #include <algorithm>
 
 #include "igemm_exchange.h"
@@ -72,7 +74,8 @@ __device__ __forceinline__ f32x4 sum_inside_image(const IgemmArgs &a, int n, int
 // where the same result used to have its reduction split over more chains.  (It costs 1 - 14 %: 128 -> 128 3x3 at 28x28,
 // N = 28, 68.5 us for 66.8; 512 -> 2048 1x1 at 7x7, N = 1, 6.4 for 6.0; 256 -> 1024 1x1 at 14x14, N = 15, 22.9 for 19.6.)
 // FWD_WT (bf16, backward by data): the weights as the forward pass has them, through a ring of LDS of the wave's own and
-// transposing reads, the tap flipped (as in igemm_patch.hip): no launch that transforms them first.
+// transposing reads, the tap flipped (as in igemm_patch.hip): no launch that transforms them first.  (1x1 backward passes on
+// this kernel, N = 2 ... 192, three sets of tensors in turn: 0.90 of the time with the launch.)
 template <int DT, int FK, int FM, int NW, int D, bool EXACT, bool GROUPS, bool FWD_WT = false>
 __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kernel(const IgemmArgs a)
 {
