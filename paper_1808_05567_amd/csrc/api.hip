@@ -503,7 +503,12 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     }
     // (10 % on top: without them 13 of 280 1x1 passes are 3 % and more behind the kernel it takes over from, with them 7)
     if (p.reg && a.fwd_wt) return 1.1 * std::max(t, launch + bytes / hbm);
-    return std::max(t, launch + bytes / hbm);
+    // (bf16 staged tiles that scatter, four stores for every one the fit has seen, and read the forward pass's weights: six
+    // layers, N = 2 ... 64, take 1.23, 1.34, 1.45 and 1.64 of the estimate.  With it 23 of 104 backward passes of those six and
+    // seven other layers, N = 2 ... 192, run on another kernel, in 0.83 of the time (0.51 ... 1.03): 512 -> 1024 stride 2 at
+    // 28x28, N = 24, 21.7 -> 16.5 us, 64 -> 256 at 56x56, N = 96, 26.4 -> 16.1, 1024 -> 512 at 14x14, N = 48, 16.1 -> 12.7)
+    const double scattered = !bf16 || !scatter || p.reg ? 1.0 : large ? 1.6 : v.fk == 2 ? 1.45 : v.npl == 8 ? 1.23 : 1.34;
+    return scattered * std::max(t, launch + bytes / hbm);
 }
 
 // The same for the patch kernel: a wave's share is pairs of channel blocks, each a patch and the weights of all taps.
