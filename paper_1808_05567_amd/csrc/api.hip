@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <unordered_map>
 
 #include "conv_internal.h"
@@ -396,15 +397,14 @@ IgemmPlan try_patch(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
         return pl;
     // exact small divisions
     if ((double)N * HW >= 4.0e6) return pl;
-    // the longest patch: tiles start at every multiple of the tile in turn, which repeats after P*Q of them
-    const int TM = fm * 32, PQ = P * Q;
-    auto pos = [&](long long m) { return m / PQ * HW + m % PQ / Q * stride * W + m % Q * a.cstride; };
-    long long longest = 0;
-    for (int t = 0; t < std::min(a.n_mt, PQ); ++t)
-        longest = std::max(longest, pos(std::min((long long)N * PQ, (long long)(t + 1) * TM) - 1) - pos((long long)t * TM));
-    longest += (R - 1) * W + S;
-    if (longest > 64 * kPatchLoads) return pl;
-    a.PLS = ceil_div((int)longest, 64) * 64;
+    // the longest patch: tiles start at every multiple of the tile in turn, which repeats after P*Q / gcd(P*Q, tile) of them
+    const int TM = fm * 32, PQ = P * Q, npix = N * PQ, most = 64 * kPatchLoads - ((R - 1) * W + S);
+    auto pos = [&](int m) { return m / PQ * (int)HW + m % PQ / Q * stride * W + m % Q * a.cstride; };
+    int longest = 0;
+    for (int t = 0, end = std::min(a.n_mt, PQ / std::gcd(PQ, TM)); t < end && longest <= most; ++t)
+        longest = std::max(longest, pos(std::min(npix, (t + 1) * TM) - 1) - pos(t * TM));
+    if (longest > most) return pl;
+    a.PLS = ceil_div(longest + (R - 1) * W + S, 64) * 64;
     a.inv_Hs = 1.0f / (float)HW;
     a.fwd_wt = geo.fwd_wt ? 1 : 0;
     c.lds = igemm_patch_lds_bytes(fk, fm, nw, a.PLS, geo.fwd_wt);
