@@ -451,8 +451,8 @@ double estimate_us(const IgemmPlan &p, bool scatter)
             lone = w.fixed + rounds * std::max(shared, w.step) + w.c_read * frags * v.wk;
             busy = rounds * shared + w.busy + 0.54 * w.c_read * frags * v.wk;
         } else {
-        lone = f.fixed + per * std::max(frags * mfma * f.c_mfma * simd_waves, f.step) + f.c_read * frags * v.wk;
-        busy = per * std::max(frags * mfma * f.c_mfma * simd_waves, v.wk * (v.fk + v.fm) * 16.0 * f.c_load) + f.busy;
+            lone = f.fixed + per * std::max(frags * mfma * f.c_mfma * simd_waves, f.step) + f.c_read * frags * v.wk;
+            busy = per * std::max(frags * mfma * f.c_mfma * simd_waves, v.wk * (v.fk + v.fm) * 16.0 * f.c_load) + f.busy;
         }
         // (waves per SIMD that the registers leave room for)
         const int occ = frags == 1 ? 8 : frags == 2 ? (bf16 ? 7 : 6) : 3;

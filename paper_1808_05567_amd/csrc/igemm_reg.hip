@@ -242,8 +242,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
         }
         wait_all_memory();  // (the rings are done with before the sums take their place)
         __syncthreads();
-    } else
-    if (u0 < u1) {
+    } else if (u0 < u1) {
 #pragma unroll
         for (int d = 0; d < D; ++d) load(A[d], B[d], d);
         // (loads past u1 ask for nothing: their lanes are out of range)
