@@ -160,14 +160,17 @@ int group_within(double n, double unit, double most)
 bool weights_reach(int Cb, int Kp, int R, int S) { return (double)Cb * R * S * Kp * 16 <= 4.0e9; }
 
 // The launch reads the forward pass's weights: a filter of `taps` taps, of which its tap (0, 0) is tap0, dr and ds taps
-// up from those of the next row and column.
-void forward_weights(IgemmArgs &a, int taps, int tap0, int dr, int ds)
+// up from those of the next row and column.  False, and nothing is set, if they are out of reach: a residue class of a
+// strided pass addresses all taps, though its own sub-filter has at most four of nine.
+bool forward_weights(IgemmArgs &a, int taps, int tap0, int dr, int ds)
 {
+    if (!weights_reach(a.Cb, a.Kp, taps, 1)) return false;
     a.fwd_wt = 1;
     a.wt_taps = taps;
     a.wt_tap0 = tap0;
     a.wt_dr = dr;
     a.wt_ds = ds;
+    return true;
 }
 
 // One candidate plan of the implicit-GEMM kernel: `wk` waves along channels,
@@ -296,10 +299,7 @@ IgemmPlan try_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
     if (geo.fwd_wt) {
         IgemmVariant w = pl.v;
         w.fw = 1;
-        if (igemm_variant_exists(w)) {
-            pl.v = w;
-            forward_weights(a, R * S, R * S - 1, S, 1);
-        }
+        if (igemm_variant_exists(w) && forward_weights(a, R * S, R * S - 1, S, 1)) pl.v = w;
     }
     pl.lds = (a.n_stage > 1 ? nb : 1) * ((size_t)nent * TK * 16 + (size_t)npl * a.PLS * 16);
     pl.grid = a.per_xcd * 8;
@@ -866,7 +866,7 @@ void plan_bwd_quad(conv_plan *p)
         if (!cls[i].p.ok) return;
         tiles += cls[i].p.a.total;
         const int off_r = cls[i].x.r_off, off_s = cls[i].x.s_off;
-        forward_weights(cls[i].p.a, 9, (off_r + 2 * (R2 - 1)) * 3 + off_s + 2 * (S2 - 1), 6, 2);
+        if (!forward_weights(cls[i].p.a, 9, (off_r + 2 * (R2 - 1)) * 3 + off_s + 2 * (S2 - 1), 6, 2)) return;
         cls[i].x.R2 = R2;
         cls[i].x.S2 = S2;
         cls[i].ws_off = off;

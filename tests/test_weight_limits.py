@@ -37,6 +37,7 @@ def test_weights_beyond_32_bit_offsets_run_untiled(shape):
     wt_bytes, (fwd, bwd) = _describe(shape)
     assert wt_bytes > 4.0e9
     assert fwd.startswith("direct "), fwd
+    assert "forward_weights=1" not in bwd, bwd
     if shape[7] == 1:  # (a strided pass transforms the weights into one sub-filter per residue class)
         assert bwd.startswith("direct "), bwd
 
@@ -46,3 +47,28 @@ def test_weights_just_within_them_keep_their_tiled_kernels(shape):
     wt_bytes, plans = _describe(shape)
     assert 3.8e9 < wt_bytes <= 4.0e9
     assert all(p.startswith("igemm") for p in plans), plans
+
+
+@pytest.mark.parametrize("shape", [
+    (16, 12000, 12000, 28, 28, 3, 3, 2, 1, F32),          # 5.2 GB
+    (8, 24000, 6000, 28, 28, 3, 3, 2, 1, F32),
+    (8, 40000, 4000, 14, 14, 3, 3, 2, 1, F32),
+    (8, 10800, 10400, 14, 14, 3, 3, 2, 1, F32),           # 4.04 GB
+    (8, 15200, 15200, 14, 14, 3, 3, 2, 1, BF16),          # 4.2 GB
+], ids=lambda s: "x".join(map(str, s)))
+def test_strided_backward_of_such_weights_transforms_them(shape):
+    """Each residue class is in reach, the whole filter is not: a launch per class, on the class's own weights."""
+    wt_bytes, (fwd, bwd) = _describe(shape)
+    assert wt_bytes > 4.0e9
+    assert fwd.startswith("direct "), fwd
+    assert bwd.startswith("igemm") and "launches=4" in bwd and "forward_weights=1" not in bwd, bwd
+
+
+@pytest.mark.parametrize("shape", [(8, 10400, 10400, 14, 14, 3, 3, 2, 1, F32), (8, 14880, 14880, 14, 14, 3, 3, 2, 1, BF16)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_strided_backward_of_weights_just_within_reach_does_not(shape):
+    wt_bytes, (fwd, bwd) = _describe(shape)
+    assert 3.8e9 < wt_bytes <= 4.0e9
+    assert fwd.startswith("igemm"), fwd
+    if shape[-1] == BF16:  # (fp32: a chain of this length is better off in a launch per class)
+        assert "launches=1" in bwd and "forward_weights=1" in bwd, bwd
