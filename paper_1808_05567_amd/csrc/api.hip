@@ -380,6 +380,32 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
     return pl;
 }
 
+// The most input positions from the first to the last of `tile` consecutive pixels of an N x P x Q result whose rows lie
+// `row` positions apart, whose columns `col` and whose images HW.  Stops once it is beyond `most`.
+// Tiles start at every multiple of the tile in turn, which repeats after P*Q / gcd(P*Q, tile) of them.  Of two tiles, what
+// differs is whether they cross one row and one image more, so the walk over the starts ends where one has both that add
+// (231 x 165 pixels under 1x7, N = 64: conv_create took 4 ms to divide its way through 36 000 starts for each variant, 0.1 now).
+long long longest_run(int N, int P, int Q, long long row, long long col, long long HW, int tile, long long most)
+{
+    const int PQ = P * Q, npix = N * PQ, tiles = ceil_div(npix, tile);
+    const int period = std::min(tiles, PQ / std::gcd(PQ, tile)), whole = std::min(period, npix / tile);
+    const int n = (tile - 1) / PQ, rest = (tile - 1) % PQ, a = (tile - 1) / Q, b = (tile - 1) % Q;
+    const long long least = a * row + n * (HW - P * row) + b * col, by_row = row - Q * col, by_image = HW - P * row;
+    const long long bound = least + (b > 0 ? std::max(by_row, 0LL) : 0) + (rest > 0 ? std::max(by_image, 0LL) : 0);
+    long long longest = 0;
+    const int step_x = tile % PQ, step_c = tile % Q;
+    for (int t = 0, x = 0, c = 0; t < whole && longest < bound && longest <= most; ++t) {
+        longest = std::max(longest, least + (c + b >= Q ? by_row : 0) + (x + rest >= PQ ? by_image : 0));
+        if ((x += step_x) >= PQ) x -= PQ;
+        if ((c += step_c) >= Q) c -= Q;
+    }
+    if (whole < period) {  // (the last one, which is not whole)
+        auto pos = [&](int m) { return m / PQ * HW + m % PQ / Q * row + m % Q * col; };
+        longest = std::max(longest, pos(npix - 1) - pos(whole * tile));
+    }
+    return longest;
+}
+
 // The same with the pixels in LDS, for filters of several taps.
 IgemmPlan try_patch(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, int R, int S, int stride,
                     int pad_h, int pad_w, int OH, int OW, int ostr, int oy0, int ox0, int zero_fill,
@@ -397,14 +423,11 @@ IgemmPlan try_patch(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
         return pl;
     // exact small divisions
     if ((double)N * HW >= 4.0e6) return pl;
-    // the longest patch: tiles start at every multiple of the tile in turn, which repeats after P*Q / gcd(P*Q, tile) of them
-    const int TM = fm * 32, PQ = P * Q, npix = N * PQ, most = 64 * kPatchLoads - ((R - 1) * W + S);
-    auto pos = [&](int m) { return m / PQ * (int)HW + m % PQ / Q * stride * W + m % Q * a.cstride; };
-    int longest = 0;
-    for (int t = 0, end = std::min(a.n_mt, PQ / std::gcd(PQ, TM)); t < end && longest <= most; ++t)
-        longest = std::max(longest, pos(std::min(npix, (t + 1) * TM) - 1) - pos(t * TM));
+    // the longest patch
+    const int most = 64 * kPatchLoads - ((R - 1) * W + S);
+    const long long longest = longest_run(N, P, Q, (long long)stride * W, a.cstride, HW, fm * 32, most);
     if (longest > most) return pl;
-    a.PLS = ceil_div(longest + (R - 1) * W + S, 64) * 64;
+    a.PLS = ceil_div((int)longest + (R - 1) * W + S, 64) * 64;
     a.inv_Hs = 1.0f / (float)HW;
     a.fwd_wt = geo.fwd_wt ? 1 : 0;
     c.lds = igemm_patch_lds_bytes(fk, fm, nw, a.PLS, geo.fwd_wt);
