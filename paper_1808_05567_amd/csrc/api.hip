@@ -636,11 +636,15 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
         IgemmPlan best = p;
         const bool exact_enough = p.ok && (most_error <= 0 || sums_within(best, most_error));
         double best_us = exact_enough ? 0.95 * estimate_us(p, scatter) + (geo.fwd_wt && !p.a.fwd_wt ? transform_us(p) : 0) : 1e30;
+        auto transforms = [&](const IgemmPlan &c) { return geo.fwd_wt && dtype == CONV_BF16 && !c.a.fwd_wt; };
         auto consider = [&](IgemmPlan c) {
             if (!c.ok || (most_error > 0 && !sums_within(c, most_error))) return;
             const double us = estimate_us(c, scatter) + (geo.fwd_wt && !c.a.fwd_wt ? transform_us(c) : 0);
-            // (of two staged ones bound by memory alike, where tiles abound, the one that reads its input less often)
-            if (us < best_us || (us == best_us && !c.reg && !best.reg && c.v.fk > best.v.fk && c.a.total >= 768)) {
+            // (of two bound by memory alike: staged ones, where tiles abound, the one that reads its input less often; on
+            // transformed weights in registers the larger tile -- 264 -> 256 stride 2 at 45x48, N = 86, 46 us, 59 in the smaller)
+            const bool larger = c.reg && best.reg ? transforms(c) && transforms(best) && c.v.fk * c.v.fm > best.v.fk * best.v.fm
+                                                  : !c.reg && !best.reg && c.v.fk > best.v.fk && c.a.total >= 768;
+            if (us < best_us || (us == best_us && larger)) {
                 best = c;
                 best_us = us;
             }
@@ -656,12 +660,19 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
             }
         static const int kReg[][4] = {{1, 1, 4, 1}, {1, 1, 8, 1}, {2, 1, 8, 1}, {1, 2, 4, 1}, {2, 2, 4, 1},
                                       {1, 1, 8, 2}, {1, 1, 8, 4}};
+        IgemmGeo transformed = geo;
+        transformed.fwd_wt = false;
         const char *reg_env = getenv("CONVMI_IGEMM_REG");
         for (const auto &k : kReg) {
             if (reg_env && strcmp(reg_env, "0") == 0) break;
             if (k[3] > 1 && (!may_split || dtype != CONV_F32)) continue;
             consider(try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                              zero_fill, geo, k[0], k[1], k[2], k[3]));
+            // (bf16 backward passes: on transformed weights too, which many tiles repay -- 344 <- 216 1x1 at 19x21, N = 98, 27 us, 30 in
+            // the staged tile of one channel block that is next; 48 -> 256 at 35x35, N = 8, 8.1 and 8.9)
+            if (geo.fwd_wt && dtype == CONV_BF16)
+                consider(try_reg(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
+                                 zero_fill, transformed, k[0], k[1], k[2], k[3]));
         }
         static const int kPatch[][3] = {{1, 1, 8}, {2, 1, 8}, {1, 2, 8}, {1, 2, 4}, {2, 2, 4}, {2, 2, 8}, {1, 4, 4}, {2, 4, 4}, {1, 4, 8}};
         for (const auto &k : kPatch) {
