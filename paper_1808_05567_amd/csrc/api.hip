@@ -530,7 +530,10 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     // layers, N = 2 ... 64, take 1.23, 1.34, 1.45 and 1.64 of the estimate.  With it 23 of 104 backward passes of those six and
     // seven other layers, N = 2 ... 192, run on another kernel, in 0.83 of the time (0.51 ... 1.03): 512 -> 1024 stride 2 at
     // 28x28, N = 24, 21.7 -> 16.5 us, 64 -> 256 at 56x56, N = 96, 26.4 -> 16.1, 1024 -> 512 at 14x14, N = 48, 16.1 -> 12.7)
-    const double scattered = !bf16 || !scatter || p.reg ? 1.0 : large ? 1.6 : v.fk == 2 ? 1.45 : v.npl == 8 ? 1.23 : 1.34;
+    // (... and in one round of short reductions the stores tell most: 1.1 - 1.5 of that, up to eight steps on 32 to 224 tiles;
+    // 256 <- 256 stride 2 at 15x16, N = 53, 8.3 us where the register-operand kernel takes 7.3)
+    const double few = !large && a.total <= 256 && a.n_stage <= 8 ? 1.2 : 1.0;
+    const double scattered = !bf16 || !scatter || p.reg ? 1.0 : few * (large ? 1.6 : v.fk == 2 ? 1.45 : v.npl == 8 ? 1.23 : 1.34);
     return scattered * std::max(t, launch + bytes / hbm);
 }
 

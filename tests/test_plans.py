@@ -388,3 +388,10 @@ def test_bf16_backward_on_transformed_weights_where_the_kernels_on_the_forward_o
         assert p.startswith("igemm_reg ") and "frags=2x2" in p and "forward_weights=1" not in p, p
     p = _plans((8, 1024, 256, 14, 14, 1, 1, 1, 0), conv.CONV_BF16)[1][conv.PASS_BWD_DATA]
     assert "forward_weights=1" in p, p
+
+
+def test_bf16_strided_1x1_backward_of_few_tiles_is_not_staged():
+    # (8.3 and 8.6 us in the staged tile, 7.3 and 7.4 in registers)
+    for shape in ((53, 248, 256, 15, 16, 1, 1, 2, 0), (9, 512, 256, 28, 28, 1, 1, 2, 0)):
+        p = _plans(shape, conv.CONV_BF16)[1][conv.PASS_BWD_DATA]
+        assert p.startswith("igemm_reg ") and "forward_weights=1" in p, p
