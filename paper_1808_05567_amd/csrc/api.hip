@@ -685,17 +685,21 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
         }
         p = best;
         // fp32 1x1: the 64 x 128 tile where the large ones leave a last round of workgroups part empty (512 run at once),
-        // which the estimate is too coarse to see.  Time of the small / the large tile, 50 layers at N = 48 ... 256:
-        //   - 128-row tiles filling 0.83 - 0.92 of one round, or 0.72 - 0.92 of two, behind at least 8 steps: 0.91 - 0.98 (512 ->
-        //     2048 at 7x7, N = 256, 219 -> 202 us; 512 -> 1024 stride 2 at 28x28, N = 256, backward 482 -> 438); at 0.65 of two
-        //     0.97 - 1.09, in the third round and later 0.99 - 1.14;
-        //   - 64-row tiles, 0.82 - 2.3 rounds behind at most 12 steps: 0.77 - 0.98 (64 -> 64 at 56x56, N = 96, 40 -> 33); 16 steps
-        //     0.97 - 1.05, 4.4 rounds 1.01 - 1.09.
+        // which the estimate is too coarse to see.  Time of the small / the large tile, 900 passes of 40 layers, N = 8 ... 256:
+        //   - 128-row tiles filling 0.83 - 0.88 of one round behind at least 8 steps (32 where input or result are strided): 0.90 -
+        //     1.03, 0.97 on average (512 -> 256 stride 2 at 28x28, N = 252, 123 -> 115 us), strided and shorter 0.95 - 1.05; from
+        //     there to 0.92 0.92 - 1.13, up to one round 0.91 - 1.13;
+        //   - 1.5 - 1.83 rounds: 0.88 - 1.02 (512 -> 2048 at 7x7, N = 256, 219 -> 202; 512 -> 1024 stride 2 at 28x28, N = 256,
+        //     backward 482 -> 438); 1.44 - 1.5 0.99 - 1.13, 1.83 - 2.05 0.92 - 1.13, in the third round and later 0.93 - 1.14;
+        //   - 64-row tiles, 0.82 - 2.3 rounds behind at most 12 steps: 0.78 - 1.02 (64 -> 64 at 56x56, N = 96, 40 -> 33), 0.84 at
+        //     2.5; longer 0.85 - 1.05.  Where half of the rows are empty 0.94 - 1.05 up to 1.12 rounds, 0.85 - 0.98 beyond.
         if (p.ok && !p.reg && dtype == CONV_F32 && R * S == 1 && p.v.fm == 7 && p.a.sampled && Cb % 8 == 0) {
             const double filled = p.a.total / 512.0;
+            const bool strided = stride > 1 || ostr > 1;
             const bool rounds = p.v.wk == 4 && p.a.n_stage >= 8 &&
-                                ((filled >= 0.83 && filled <= 0.92) || (filled >= 1.44 && filled <= 1.84));
-            const bool narrow = p.v.wk == 2 && Kp <= 64 && p.a.n_stage <= 12 && filled >= 0.82 && filled <= 2.3;
+                                ((filled >= 0.83 && filled <= 0.88 && (!strided || p.a.n_stage >= 32)) ||
+                                 (filled >= 1.5 && filled <= 1.83));
+            const bool narrow = p.v.wk == 2 && Kp <= 64 && p.a.n_stage <= 12 && filled >= (Kp <= 32 ? 1.12 : 0.82) && filled <= 2.3;
             if (rounds || narrow) {
                 IgemmPlan c = try_igemm(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                                         zero_fill, geo, 2, 2, 1, 2, (size_t)kMaxLds, 2, 8);

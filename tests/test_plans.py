@@ -395,3 +395,20 @@ def test_bf16_strided_1x1_backward_of_few_tiles_is_not_staged():
     for shape in ((53, 248, 256, 15, 16, 1, 1, 2, 0), (9, 512, 256, 28, 28, 1, 1, 2, 0)):
         p = _plans(shape, conv.CONV_BF16)[1][conv.PASS_BWD_DATA]
         assert p.startswith("igemm_reg ") and "forward_weights=1" in p, p
+
+
+def test_fp32_1x1_keeps_large_tiles_where_small_ones_are_slower():
+    """Beside the lines of the test above (time of the small tile / the large one): 464 and 462 large tiles 1.05,
+    744 tiles 1.06, 940 tiles 1.04, a short strided reduction over 442 tiles 1.05, half-empty tiles in one round 1.04."""
+    def small(shape, which):
+        return "frags=1x2" in _plans(shape, conv.CONV_F32)[1][which]
+    assert not small((33, 128, 512, 28, 28, 1, 1, 1, 0), conv.PASS_FWD)
+    assert not small((132, 512, 128, 28, 28, 1, 1, 1, 0), conv.PASS_FWD)
+    assert not small((53, 128, 512, 28, 28, 1, 1, 1, 0), conv.PASS_FWD)
+    assert not small((67, 128, 512, 28, 28, 1, 1, 1, 0), conv.PASS_FWD)
+    assert not small((63, 256, 128, 56, 56, 1, 1, 2, 0), conv.PASS_BWD_DATA)
+    assert not small((160, 192, 32, 35, 35, 1, 1, 1, 0), conv.PASS_FWD)
+    # within them: 0.90, 0.91, 0.85
+    assert small((61, 128, 256, 28, 28, 1, 1, 1, 0), conv.PASS_FWD)
+    assert small((94, 320, 640, 20, 20, 1, 1, 1, 0), conv.PASS_FWD)
+    assert small((211, 192, 32, 35, 35, 1, 1, 1, 0), conv.PASS_FWD)
