@@ -1807,22 +1807,28 @@ int window_pitch(const conv_plan *p)
     return std::max(p->info.Q, ceil_div(std::min(d.W, d.stride * (p->info.Q - 1) - p->pad_w + d.S), d.stride));
 }
 // Whether a strided 3x3 layer's update runs with one window of the input for all taps: time of that / of the ring kernel,
-// 13 layers at N = 8 ... 200, two sets of tensors in turn (where the ring kernel's lines leave a layer to the row kernel,
-// beyond 5e10 operations, it stays there; measured there too, 0.65 - 0.81 of that kernel's time):
-//   - from 1e10 operations, more than 96 channels on both sides and few dead slots: 0.75 - 0.96 (288 -> 384 at 35x35, N = 32,
-//     1.8e10, 45.7 -> 42.9 us; 400 -> 400 at 20x20, N = 64, 61 -> 46), 1.00 where an image is narrow and dW wide (200 ->
-//     600 at 30x28, N = 32);
-//   - below: 0.87 - 1.12 from 7e9, slower under 4e9; 64 and 96 channels 1.08 - 1.3; one slot in nine dead (192 -> 320 at
-//     17x17) 1.05 and more.  With stride 1, where a tap's pixels are neighbours, the ring kernel's own loads share
-//     their cache lines and the addresses cost more than they save: 1.00 - 1.28, but 0.92 - 0.98 for 512 -> 512 at 7x7.
+// 16 layers at 5e9 ... 5e10 operations, three sets of tensors in turn (where the ring kernel's lines leave a layer to the row
+// kernel, beyond 5e10 operations, it stays there; measured there too, 0.65 - 0.81 of that kernel's time), more than 96
+// channels on both sides and few dead slots:
+//   - blocks of dW that fill half of the CUs with one split: from 1e10 operations 0.73 - 0.99 (400 -> 400 at 20x20, N = 62, 61
+//     -> 45 us); below 0.85 - 1.14;
+//   - fewer: from 1.6e10 0.75 - 1.00 (288 -> 384 at 35x35, N = 31, 1.8e10, 42 -> 41; N = 43 57 -> 52); 1e10 - 1.6e10 0.83 - 1.13;
+//   - ... and one side at least twice the other: from 3.3e10 0.77 - 0.96; 1e10 - 1.6e10 0.93 - 1.25, up to 2.3e10 0.91 - 1.07, up to
+//     3.3e10 0.75 - 1.04 (128 -> 256 at 56x56, N = 39, 32 -> 34; N = 87 73 -> 64);
+//   - 64 and 96 channels 1.08 - 1.3; one slot in nine dead (192 -> 320 at 17x17) 1.05 and more.  With stride 1, where a tap's
+//     pixels are neighbours, the ring kernel's own loads share their cache lines and the addresses cost more than they
+//     save: 1.00 - 1.28, but 0.92 - 0.98 for 512 -> 512 at 7x7.
 bool ring_applies(const conv_plan *p);
 bool window_applies(const conv_plan *p)
 {
     const conv_desc_t &d = p->d;
     const conv_info_t &f = p->info;
     const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q;
-    return d.dtype == CONV_BF16 && d.stride == 2 && d.S == 3 && std::min(d.C, d.K) > 96 && flops >= 1.0e10 &&
-           ring_applies(p) && 16 * window_pitch(p) <= 17 * f.Q;
+    const int wide = std::max(d.C, d.K), narrow = std::min(d.C, d.K);
+    const long long blocks = (long long)ceil_div(f.Cp, 64) * ceil_div(f.Kp, 64) * d.R;
+    const double from = blocks >= 128 ? 1.0e10 : wide < 2 * narrow ? 1.6e10 : 3.3e10;
+    return d.dtype == CONV_BF16 && d.stride == 2 && d.S == 3 && narrow > 96 && flops >= from && ring_applies(p) &&
+           16 * window_pitch(p) <= 17 * f.Q;
 }
 // What such an update takes, in microseconds, as far as the choice of its splits goes.
 double window_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)

@@ -20,8 +20,8 @@
 // quad are stored with neighbours swapped.
 //
 // What bounds it now: vector instructions, 138 a stage (addresses of the next chunk and of the taps) next to 12 MFMAs, 45 of
-// the 85 thousand clocks that a CU is busy; MFMAs 29.  288 -> 384 at 35x35, no padding, N = 32 / 64: 45.7 -> 42.9 /
-// 80 -> 71 us with the reduce launch, 512 -> 512 at 14x14, N = 64: 35 -> 29.  (The same kernel for stride 1 and for 5 and
+// the 85 thousand clocks that a CU is busy; MFMAs 29.  288 -> 384 at 35x35, no padding, N = 37 / 70: 50 -> 47 /
+// 87 -> 79 us with the reduce launch, 512 -> 512 at 14x14, N = 61: 33 -> 28.  (The same kernel for stride 1 and for 5 and
 // 7 columns was built and measured: the lines at window_applies.)
 #include <algorithm>
 

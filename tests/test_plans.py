@@ -412,3 +412,18 @@ def test_fp32_1x1_keeps_large_tiles_where_small_ones_are_slower():
     assert small((61, 128, 256, 28, 28, 1, 1, 1, 0), conv.PASS_FWD)
     assert small((94, 320, 640, 20, 20, 1, 1, 1, 0), conv.PASS_FWD)
     assert small((211, 192, 32, 35, 35, 1, 1, 1, 0), conv.PASS_FWD)
+
+
+def test_window_update_from_where_it_is_faster():
+    """Time of the window kernel / the ring kernel beside each; both print as upd_ring."""
+    for (N, C, K, H, W, pad), want in (((44, 512, 512, 14, 14, 1), True),       # 0.88
+                                       ((35, 400, 400, 20, 20, 1), True),       # 0.85
+                                       ((21, 288, 384, 35, 35, 0), False),      # 1.07
+                                       ((37, 288, 384, 35, 35, 0), True),       # 0.93
+                                       ((52, 128, 128, 56, 56, 1), False),      # 1.06
+                                       ((78, 128, 128, 56, 56, 1), True),       # 0.97
+                                       ((39, 128, 256, 56, 56, 1), False),      # 1.07
+                                       ((87, 128, 256, 56, 56, 1), True),       # 0.89
+                                       ((21, 740, 180, 30, 31, 1), False)):     # 1.18
+        p = _plans((N, C, K, H, W, 3, 3, 2, pad), conv.CONV_BF16)[1][conv.PASS_UPD]
+        assert p.startswith("upd_ring ") and (_field(p, "window") > 0) == want, (N, C, K, p)
