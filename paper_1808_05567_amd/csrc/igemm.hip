@@ -145,7 +145,7 @@ static IgemmEntry *find_igemm(const IgemmVariant &v)
 
 bool igemm_variant_exists(const IgemmVariant &v) { return find_igemm(v) != nullptr; }
 
-bool igemm_variant_groups(const IgemmVariant &v) { return igemm_groups(v.dtype, v.wk, v.wm, v.fk, v.fm); }
+bool igemm_variant_groups(const IgemmVariant &v) { return !v.fw && igemm_groups(v.dtype, v.wk, v.wm, v.fk, v.fm); }
 
 unsigned igemm_variant_ppts(const IgemmVariant &v)
 {

@@ -427,3 +427,13 @@ def test_window_update_from_where_it_is_faster():
                                        ((21, 740, 180, 30, 31, 1), False)):     # 1.18
         p = _plans((N, C, K, H, W, 3, 3, 2, pad), conv.CONV_BF16)[1][conv.PASS_UPD]
         assert p.startswith("upd_ring ") and (_field(p, "window") > 0) == want, (N, C, K, p)
+
+
+def test_group_is_what_the_kernel_sums(monkeypatch):
+    """The staged kernel on the forward pass's weights sums in one chain; the plan must not say otherwise."""
+    monkeypatch.setenv("CONVMI_IGEMM_REG", "0")
+    monkeypatch.setenv("CONVMI_IGEMM_CAND", "2,2,1,2,2,4")
+    monkeypatch.setenv("CONVMI_IGEMM_GROUP", "2")
+    p = _plans((4, 128, 128, 28, 28, 1, 1, 1, 0), conv.CONV_F32)[1]
+    assert p[conv.PASS_FWD].startswith("igemm ") and _field(p[conv.PASS_FWD], "group") == 2
+    assert "forward_weights=1" in p[conv.PASS_BWD_DATA] and _field(p[conv.PASS_BWD_DATA], "group") == 0
