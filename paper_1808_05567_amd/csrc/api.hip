@@ -372,7 +372,7 @@ IgemmPlan try_reg(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q, 
     a.mq_per = ceil_div(a.n_mt, 8 / a.gk);
     a.per_xcd = a.gk == 1 ? ceil_div(a.total * a.ksplit, 8) : a.kt_per * a.mq_per;
     pl.v = IgemmVariant{dtype, nw, 1, fk, fm, 2, R, S, 0};
-    pl.lds = igemm_reg_lds_bytes(fk, fm, nw);
+    pl.lds = igemm_reg_lds_bytes(fk, fm, nw, a.fwd_wt != 0);
     pl.grid = a.per_xcd * 8;
     pl.reg = true;
     pl.fallback = geo.fallback;

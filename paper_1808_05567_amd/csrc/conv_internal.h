@@ -137,7 +137,7 @@ unsigned igemm_variant_ppts(const IgemmVariant &v);
 // reduction step is one tap of one pair of channel blocks.
 // (steps a wave keeps in flight; 0: no such variant)
 int igemm_reg_depth(int dtype, int fk, int fm, int nw);
-size_t igemm_reg_lds_bytes(int fk, int fm, int nw);
+size_t igemm_reg_lds_bytes(int fk, int fm, int nw, bool fwd_wt);
 hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream);
 // The same with the pixels of a tile and their halo in LDS, for filters of several taps (bf16): IgemmArgs::PLS =
 // positions of a patch, at most 64 * kPatchLoads, inv_Hs = 1 / (H*W), the rest as above.

@@ -307,7 +307,7 @@ bool igemm_patch_exists(int dtype, int ntap, int fk, int fm, int nw) { return fi
 size_t igemm_patch_lds_bytes(int fk, int fm, int nw, int pls, bool fwd_wt)
 {
     return std::max((size_t)nw * (2 * (2 * (size_t)pls * 16 + 16) + (fwd_wt ? kPatchRing * fk * 1024 : 0)),
-                    igemm_reg_lds_bytes(fk, fm, nw));
+                    igemm_reg_lds_bytes(fk, fm, nw, false));
 }
 
 hipError_t launch_igemm_patch(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream)

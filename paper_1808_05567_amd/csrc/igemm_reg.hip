@@ -326,17 +326,17 @@ int igemm_reg_depth(int dtype, int fk, int fm, int nw)
     return 0;
 }
 
-size_t igemm_reg_lds_bytes(int fk, int fm, int nw)
+size_t igemm_reg_lds_bytes(int fk, int fm, int nw, bool fwd_wt)
 {
     const int per_round = std::min(nw / 4, fk * fm);
-    return (size_t)per_round * nw * 4096;
+    return std::max((size_t)per_round * nw * 4096, fwd_wt ? (size_t)nw * kWeightRing * fk * 1024 : 0);
 }
 
 hipError_t launch_igemm_reg(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream)
 {
     for (const RegEntry &e : g_reg) {
         if (e.dtype != v.dtype || e.fk != v.fk || e.fm != v.fm || e.nw != v.wk) continue;
-        const size_t lds = std::max(igemm_reg_lds_bytes(e.fk, e.fm, e.nw), a.fwd_wt ? (size_t)e.nw * kWeightRing * e.fk * 1024 : 0);
+        const size_t lds = igemm_reg_lds_bytes(e.fk, e.fm, e.nw, a.fwd_wt != 0);
         const igemm_fn_t fn = a.fwd_wt ? e.fwd_wt_fn : a.exact ? e.exact_fn : a.group > 0 ? e.groups_fn : e.fn;
         if (!fn) return hipErrorInvalidDeviceFunction;
         if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(fn), lds); err != hipSuccess)

@@ -437,3 +437,12 @@ def test_group_is_what_the_kernel_sums(monkeypatch):
     p = _plans((4, 128, 128, 28, 28, 1, 1, 1, 0), conv.CONV_F32)[1]
     assert p[conv.PASS_FWD].startswith("igemm ") and _field(p[conv.PASS_FWD], "group") == 2
     assert "forward_weights=1" in p[conv.PASS_BWD_DATA] and _field(p[conv.PASS_BWD_DATA], "group") == 0
+
+
+def test_lds_of_the_register_operand_kernel_counts_its_ring_of_weights(monkeypatch):
+    """Four steps of 1 KiB a wave and channel fragment, where that is more than the exchange of the sums."""
+    for variant, fwd, bwd in (("2,2,4", 16384, 32768), ("1,1,8", 32768, 32768), ("2,1,8", 65536, 65536)):
+        monkeypatch.setenv("CONVMI_IGEMM_REG", variant)
+        p = _plans((4, 128, 128, 28, 28, 1, 1, 1, 0), conv.CONV_BF16)[1]
+        assert "forward_weights=1" in p[conv.PASS_BWD_DATA]
+        assert (_field(p[conv.PASS_FWD], "lds"), _field(p[conv.PASS_BWD_DATA], "lds")) == (fwd, bwd), (variant, p)
