@@ -95,3 +95,26 @@ def test_patch_kernel_keeps_images_apart(monkeypatch):
         for n in (0, 2):
             assert_close(got[n], ref[n], conv.CONV_BF16, "image %d, variant %s" % (n, v))
         assert np.isnan(got[1]).all()
+
+
+@pytest.mark.parametrize("shape", [(4, 3, 64, 30, 31, 5, 5, 2, 2),      # classes as the rows of one 3x3 filter
+                                   (3, 8, 40, 18, 20, 5, 5, 2, 2),
+                                   (2, 24, 40, 22, 23, 7, 7, 3, 3)],    # a launch per class, most of them 2x2 and 3x3 taps
+                         ids=lambda s: "x".join(map(str, s)))
+def test_residue_classes_of_strided_backward_passes(shape, monkeypatch):
+    N, C, K, H, W, R, S, stride, pad = shape
+    _, Wt, dO = make_inputs(shape, conv.CONV_BF16, layer_id=9)
+    ref = oracle.bwd_data(dO, Wt, H, W, stride, pad)
+    ran = 0
+    for v in VARIANTS:
+        monkeypatch.setenv("CONVMI_IGEMM_PATCH", v)
+        L = conv.ConvLayer(*shape, dtype=conv.CONV_BF16)
+        try:
+            text = conv.conv_describe(L.h, conv.PASS_BWD_DATA)
+            if text.startswith("igemm_patch "):
+                assert "forward_weights=1" not in text
+                ran += 1
+                assert_close(run_pass(L, "bwd", Wt=Wt, dO=dO), ref, conv.CONV_BF16, v)
+        finally:
+            L.close()
+    assert ran >= 2
