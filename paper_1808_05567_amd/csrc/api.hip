@@ -908,9 +908,6 @@ void plan_bwd_quad(conv_plan *p)
         tiles += cls[i].p.a.total;
         const int off_r = cls[i].x.r_off, off_s = cls[i].x.s_off;
         if (!forward_weights(cls[i].p.a, 9, (off_r + 2 * (R2 - 1)) * 3 + off_s + 2 * (S2 - 1), 6, 2)) return;
-        cls[i].x.R2 = R2;
-        cls[i].x.S2 = S2;
-        cls[i].ws_off = off;
         off += (size_t)f.Kb * R2 * S2 * f.Cp * f.vlen * esize_of(d.dtype);
     }
     // (CONVMI_BWD_QUAD: 0 never, 1 wherever it fits -- a tuning aid)
@@ -1687,8 +1684,7 @@ bool ring_exists(const conv_plan *p, const RingCand &c, int sum)
 int window_pitch(const conv_plan *p);
 size_t ring_lds_bytes(const conv_plan *p, const RingCand &c)
 {
-    return c.window ? upd_window_lds_bytes(p->d.stride, c.fc, c.fk, c.nw, c.depth)
-                    : upd_ring_lds_bytes(p->d.S, c.fc, c.fk, c.nw, c.depth);
+    return c.window ? upd_window_lds_bytes() : upd_ring_lds_bytes(p->d.S, c.fc, c.fk, c.nw, c.depth);
 }
 // Error of the sums of the update that is planned, its partial copies added in eight chains, ascending.
 double planned_upd_error(const conv_plan *p)
@@ -2434,7 +2430,7 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
     hipError_t e = hipSuccess;
     if (h->upd_ring) {
         if (a.splits == 1) a.partial = static_cast<float *>(dwt);
-        e = h->upd_window ? launch_upd_window(h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, h->urv.strided, a, h->upd_grid, s)
+        e = h->upd_window ? launch_upd_window(a, h->upd_grid, s)
                           : launch_upd_ring(h->d.dtype, h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, h->urv.strided, a,
                                             h->upd_grid, s);
         if (a.splits == 1) return e == hipSuccess ? CONV_OK : CONV_ELAUNCH;

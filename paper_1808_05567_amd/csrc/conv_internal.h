@@ -269,8 +269,8 @@ hipError_t launch_upd_ring(int dtype, int fc, int fk, int nw, int depth, int sum
 // bf16, three columns, stride 2, pad_w <= 4: the same with one window of the input for all taps of the
 // filter row (UpdArgs::Qpitch = slots of an output row, rows_per_split = slots per split)
 bool upd_window_exists(int s, int stride, int fc, int fk, int nw, int depth, int sum);
-size_t upd_window_lds_bytes(int stride, int fc, int fk, int nw, int depth);
-hipError_t launch_upd_window(int fc, int fk, int nw, int depth, int sum, const UpdArgs &a, int grid, hipStream_t stream);
+size_t upd_window_lds_bytes();
+hipError_t launch_upd_window(const UpdArgs &a, int grid, hipStream_t stream);
 // at most 4 input channels: filter-row formulation, 7x7 and 3x3; fp32 tensors, or bf16
 // tensors widened on their way into LDS (then UpdArgs::Kb counts blocks of 8 channels)
 hipError_t launch_upd_c4(int dtype, int r, int s, const UpdArgs &a, size_t lds_bytes, int grid,

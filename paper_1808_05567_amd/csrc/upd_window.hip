@@ -29,9 +29,10 @@
 
 namespace convmi {
 
-// S taps of a filter row, stride ST (1 or 2), FC x FK accumulator tiles per tap, NW waves, a ring of NS chunks each; SUM
-// as in upd_ring_kernel: 0 one chain, 1 groups of UpdArgs::group rounds of NS stages.
-template <int S, int ST, int FC, int FK, int NW, int NS, int SUM>
+// The one form that is built: S taps of a filter row, stride ST, FC x FK accumulator tiles per tap, NW waves, a ring
+// of NS chunks each, one chain of sums per wave.
+constexpr int S = 3, ST = 2, FC = 2, FK = 2, NW = 8, NS = 3;
+
 __global__ __launch_bounds__(NW * 64, 2) void upd_window_kernel(const UpdArgs a)
 {
     constexpr int V = 8, NB = 4;              // channels of a block, blocks of a fragment
@@ -94,12 +95,12 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_window_kernel(const UpdArgs a)
 #pragma unroll
         for (int l = 0; l < ST; ++l) {
             const int quad = 4 * l + lquad;
-            const int off = 4 * quad + (ST == 2 ? lpx ^ (quad & 1) : lpx) - AHEAD;
+            const int off = 4 * quad + (lpx ^ (quad & 1)) - AHEAD;
             // (counted from a row before the first: the dividend is not negative)
-            const int t = tl + (off >> (ST - 1)) + Lp;  // slot, and which of its ST positions
+            const int t = tl + (off >> 1) + Lp;  // slot, and which of its two positions
             const int row1 = fast_div(t, inv_Lp);
             const int row = row1 - 1;
-            const int x = ST * (t - mul24(row1, Lp)) + (ST == 2 ? off & 1 : 0);
+            const int x = ST * (t - mul24(row1, Lp)) + (off & 1);
             const int n = fast_div(max(row, 0), inv_P);
             const int y = ST * (row - mul24(n, a.P)) + r - a.pad;
             const bool in = (unsigned)row < (unsigned)rows && (unsigned)y < (unsigned)a.H && x < a.W;
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_window_kernel(const UpdArgs a)
     for (int s = 0; s < S; ++s) {
         const int p = ST * (8 * h + j4) + s - a.pad_w + AHEAD;
         const int quad = p >> 2;
-        in_addr[s] = ring_addr + (unsigned)(quad * 256 + ((ST == 2 ? (p & 3) ^ (quad & 1) : p & 3) * 16) + part);
+        in_addr[s] = ring_addr + (unsigned)(quad * 256 + ((p & 3) ^ (quad & 1)) * 16 + part);
         wraps |= (quad >= 4 * ST ? 1u : 0u) << (2 * s) | (quad + ST >= 4 * ST ? 2u : 0u) << (2 * s);
     }
     // Column of the lane's two slots, and its window's first column; a tap outside [0, W) reads zeros.
@@ -159,11 +160,6 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_window_kernel(const UpdArgs a)
         for (int d = 0; d < NS; ++d) load(d);
     }
     __syncthreads();  // (the zeros are written)
-    f32x16 sum[SUM == 1 ? NF : 1];  // of the groups so far
-    if constexpr (SUM == 1) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) sum[f] = f32x16{};
-    }
     auto stage = [&](auto dc) {
         constexpr int d = decltype(dc)::value;
         // this chunk's loads and the next one's have landed; the NS - 2 later ones may be on their way
@@ -224,28 +220,12 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_window_kernel(const UpdArgs a)
                         acc[(s * FC + i) * FK + j], 0, 0, 0);
         });
     };
-    for (int u = 0; u < steps;) {
-        const int end = SUM == 1 ? min(steps, u + a.group * NS) : steps;
-        for (; u + NS <= end; u += NS) static_for<0, NS>(stage);
-        // (the last stages of the run)
-        if (u < end) {
-            static_for<0, NS - 1>([&](auto dc) {
-                if (u + decltype(dc)::value < end) stage(dc);
-            });
-            u = end;
-        }
-        if constexpr (SUM == 1) {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                add_here(sum[f], acc[f]);
-                acc[f] = f32x16{};
-            }
-        }
-    }
-    if constexpr (SUM == 1) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) acc[f] = sum[f];
-    }
+    int u = 0;
+    for (; u + NS <= steps; u += NS) static_for<0, NS>(stage);
+    // (the last stages of the run)
+    static_for<0, NS - 1>([&](auto dc) {
+        if (u + decltype(dc)::value < steps) stage(dc);
+    });
     wait_all_memory();  // (the last chunks' loads still write into the ring)
 
     // The waves' sums, G tiles per round, pairwise.  Rows of a tile are input channels: a
@@ -279,41 +259,23 @@ __global__ __launch_bounds__(NW * 64, 2) void upd_window_kernel(const UpdArgs a)
     }
 }
 
-typedef void (*upd_window_fn_t)(const UpdArgs);
-static const struct UpdWindowEntry {
-    int s, st, fc, fk, nw, depth, sum;
-    upd_window_fn_t fn;
-} g_upd_window[] = {
-#define ENTRY(S, ST, FC, FK, NW, NS, SUM) {S, ST, FC, FK, NW, NS, SUM, upd_window_kernel<S, ST, FC, FK, NW, NS, SUM>}
-    ENTRY(3, 2, 2, 2, 8, 3, 0),
-};
-
-static const UpdWindowEntry *find_window(int s, int st, int fc, int fk, int nw, int depth, int sum)
-{
-    for (const UpdWindowEntry &e : g_upd_window)
-        if (e.s == s && e.st == st && e.fc == fc && e.fk == fk && e.nw == nw && e.depth == depth && e.sum == sum) return &e;
-    return nullptr;
-}
-
 bool upd_window_exists(int s, int stride, int fc, int fk, int nw, int depth, int sum)
 {
-    return find_window(s, stride, fc, fk, nw, depth, sum) != nullptr;
+    return s == S && stride == ST && fc == FC && fk == FK && nw == NW && depth == NS && sum == 0;
 }
 
-size_t upd_window_lds_bytes(int stride, int fc, int fk, int nw, int depth)
+size_t upd_window_lds_bytes()
 {
-    // (the exchange holds nw/4 tiles of every wave)
-    return std::max((size_t)nw / 4 * nw * 4096, ((size_t)nw * (stride * fc + fk) + stride * fc) * depth * 1024);
+    // (the exchange holds NW/4 tiles of every wave)
+    return std::max((size_t)NW / 4 * NW * 4096, ((size_t)NW * (ST * FC + FK) + ST * FC) * NS * 1024);
 }
 
-hipError_t launch_upd_window(int fc, int fk, int nw, int depth, int sum, const UpdArgs &a, int grid, hipStream_t stream)
+hipError_t launch_upd_window(const UpdArgs &a, int grid, hipStream_t stream)
 {
-    const UpdWindowEntry *e = find_window(a.S, a.stride, fc, fk, nw, depth, sum);
-    if (!e) return hipErrorInvalidDeviceFunction;
-    const size_t lds = upd_window_lds_bytes(a.stride, fc, fk, nw, depth);
-    if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(e->fn), lds); err != hipSuccess)
+    const size_t lds = upd_window_lds_bytes();
+    if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(upd_window_kernel), lds); err != hipSuccess)
         return err;
-    hipLaunchKernelGGL(e->fn, dim3(grid), dim3(nw * 64), lds, stream, a);
+    hipLaunchKernelGGL(upd_window_kernel, dim3(grid), dim3(NW * 64), lds, stream, a);
     return hipGetLastError();
 }
 
