@@ -89,57 +89,60 @@ static __device__ __forceinline__ void add_and_store(const IgemmArgs &a, const f
     // round by round, each round waited for a trip to memory: the compiler moves no load over the stores of the
     // round before, since the residual may be the output buffer -- a thread reads only what it will write
     // itself.  Bottleneck block of 8 images, 1024 and 256 channels at 14x14, bf16: 20.9 -> 19.7 us; 1024 -> 2048
-    // stride 2 with a residual, N = 12: 14.6 -> 13.7.)
+    // stride 2 with a residual, N = 12: 14.6 -> 13.7.)  A launch with nothing fused takes a path without those operands: with
+    // one path for both it took 1.01 of the time of one that had none (bf16, 90 passes of 3.5 - 40 us), now 1.00, and
+    // fused bf16 launches beyond 6 us 0.98 of what they took.
     const bool fused = a.ksplit == 1 && (a.scale != nullptr || a.bias != nullptr || a.resid != nullptr || a.relu != 0);
-    f32x4 sv[NR], bv[NR];
-    typename E_::Four res[NR];
+    auto rounds = [&](auto fused_tag) {
+        constexpr bool FUSED = decltype(fused_tag)::value;
+        constexpr int NO = FUSED ? NR : 1;
+        f32x4 sv[NO], bv[NO];
+        typename E_::Four res[NO];
+        if constexpr (FUSED) {
 #pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        sv[q] = f32x4{1.f, 1.f, 1.f, 1.f};
-        bv[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        res[q] = typename E_::Four{};
-    }
-    if (fused) {
+            for (int q = 0; q < NR; ++q) {
+                sv[q] = f32x4{1.f, 1.f, 1.f, 1.f};
+                bv[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                res[q] = typename E_::Four{};
+                const Place p = place(q);
+                // (rows beyond Kp are out of range)
+                if (a.scale)
+                    sv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                          make_rsrc(a.scale, 0, (size_t)a.Kp * 4), (unsigned)p.krow * 4u, 0, 0));
+                if (a.bias)
+                    bv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                          make_rsrc(a.bias, 0, (size_t)a.Kp * 4), (unsigned)p.krow * 4u, 0, 0));
+                if (a.resid) res[q] = E_::load4(make_rsrc(a.resid, 0, out_bytes), p.ok ? p.pos : kOutOfRange, 0);
+            }
+        }
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
-            const Place p = place(q);
-            // (rows beyond Kp are out of range)
-            if (a.scale)
-                sv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      make_rsrc(a.scale, 0, (size_t)a.Kp * 4), (unsigned)p.krow * 4u, 0, 0));
-            if (a.bias)
-                bv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      make_rsrc(a.bias, 0, (size_t)a.Kp * 4), (unsigned)p.krow * 4u, 0, 0));
-            if (a.resid) res[q] = E_::load4(make_rsrc(a.resid, 0, out_bytes), p.ok ? p.pos : kOutOfRange, 0);
-        }
-    }
+            const int f0 = q * G;
+            if (f0 > 0) __syncthreads();
 #pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        const int f0 = q * G;
-        if (f0 > 0) __syncthreads();
+            for (int g = 0; g < G; ++g) {
+                const f32x16 &c = acc[(f0 + g) / FM][(f0 + g) % FM];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const f32x16 &c = acc[(f0 + g) / FM][(f0 + g) % FM];
-#pragma unroll
-            for (int vq = 0; vq < 4; ++vq) {
-                const f32x4 v = {c[4 * vq], c[4 * vq + 1], c[4 * vq + 2], c[4 * vq + 3]};
-                xch[(g * NW + wave) * 256 + vq * 64 + lane] = v;
+                for (int vq = 0; vq < 4; ++vq) {
+                    const f32x4 v = {c[4 * vq], c[4 * vq + 1], c[4 * vq + 2], c[4 * vq + 3]};
+                    xch[(g * NW + wave) * 256 + vq * 64 + lane] = v;
+                }
             }
-        }
-        __syncthreads();
-        if (tg < G) {
-            f32x4 v = wave_sum<0, NW>([&](int w) { return xch[(tg * NW + w) * 256 + ch]; });
-            const Place p = place(q);
-            if constexpr (EXACT) {
-                if (p.ok && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]))
-                    v = again(p.n, p.oj, p.oi, p.krow);
-            }
-            if (a.ksplit > 1) {
-                Elem<CONV_F32>::store4(ro, p.ok ? p.pos * SC : kOutOfRange, 0, v[0], v[1], v[2], v[3]);
-            } else {
+            __syncthreads();
+            if (tg < G) {
+                f32x4 v = wave_sum<0, NW>([&](int w) { return xch[(tg * NW + w) * 256 + ch]; });
+                const Place p = place(q);
+                if constexpr (EXACT) {
+                    if (p.ok && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]))
+                        v = again(p.n, p.oj, p.oi, p.krow);
+                }
+                if (!FUSED && a.ksplit > 1) {
+                    Elem<CONV_F32>::store4(ro, p.ok ? p.pos * SC : kOutOfRange, 0, v[0], v[1], v[2], v[3]);
+                    continue;
+                }
                 const unsigned off = p.ok ? p.pos : kOutOfRange;
                 float o[4] = {v[0], v[1], v[2], v[3]};
-                if (fused) {
+                if constexpr (FUSED) {
                     float r4[4];
                     E_::widen4(res[q], r4);
 #pragma unroll
@@ -160,7 +163,9 @@ static __device__ __forceinline__ void add_and_store(const IgemmArgs &a, const f
                 }
             }
         }
-    }
+    };
+    if (fused) rounds(std::true_type{});
+    else rounds(std::false_type{});
 }
 
 }  // namespace convmi
