@@ -1,8 +1,11 @@
-"""Backward by data reading the forward pass's weights in the staged kernel (every tile it is built in), in the residue
+"""Backward by data reading the forward pass's weights in the staged kernel (every instantiation: a host test holds the
+shapes here against the list of them), in the residue
 classes of a strided pass and in the register-operand kernel, against the oracle at the edges: ragged channels both
 ways (an odd number of channel blocks), one pixel, images smaller than a tile, tiles
 that cross images, padding other than "same", the scattering store.  The workspace holds NaN patterns: nothing may be
 read from it.  Bars: gpu_util.assert_close."""
+import re
+
 import pytest
 
 import oracle
@@ -30,7 +33,26 @@ SHAPES = [
     (1, 20, 80, 30, 29, 3, 3, 1, (0, 1)),
     (3, 72, 48, 17, 16, 1, 7, 1, (0, 3)),
     (3, 40, 96, 9, 11, 7, 1, 1, (3, 0)),
+    # two, three and more staged positions per thread: long rows, many small images to a tile, tall narrow images
+    (2, 40, 64, 5, 64, 3, 3, 1, 1),
+    (70, 40, 64, 1, 2, 3, 3, 1, 1),
+    (3, 72, 48, 60, 5, 3, 3, 1, 1),
+    (3, 40, 64, 7, 8, 7, 1, 1, (3, 0)),
+    (1, 40, 64, 7, 40, 7, 1, 1, (3, 0)),
 ]
+
+
+def tiles(shape, dtype):
+    return (TILES_1X1 if shape[5] * shape[6] == 1 else TILES)[dtype]
+
+
+def staged_variant(tile, text):
+    """The instantiation that a plan for `tile` runs on (type, waves, fragments, channel blocks, filter, positions per
+    thread, buffers, input policy); None if it is another tile or transforms the weights."""
+    wk, wm, fk, fm, nb, npl = tile.split(",")
+    m = re.match(r"igemm dt=(\d) waves=%sx%s frags=%sx%s npl=(\d+) nt=(\d) RS=(\S+) ppt=(\d+) .*forward_weights=1"
+                 % (wk, wm, fk, fm), text)
+    return m and (int(m[1]), wk + "x" + wm, fk + "x" + fm, int(m[2]), m[4], int(m[5]), int(nb), int(m[3]))
 
 
 @pytest.mark.parametrize("dtype", [conv.CONV_F32, conv.CONV_BF16], ids=["f32", "bf16"])
@@ -41,18 +63,19 @@ def test_staged_tiles_match_oracle(shape, dtype, monkeypatch):
     ref = oracle.bwd_data(dO, Wt, H, W, stride, pad)
     monkeypatch.setenv("CONVMI_IGEMM_REG", "0")
     ran = set()
-    for tile in (TILES_1X1 if R * S == 1 else TILES)[dtype]:
-        monkeypatch.setenv("CONVMI_IGEMM_CAND", tile)
-        L = conv.ConvLayer(*shape, dtype=dtype)
-        try:
-            text = conv.conv_describe(L.h, conv.PASS_BWD_DATA)
-            if "forward_weights=1" in text and "waves=%s frags=%s " % tuple(
-                    "x".join(tile.split(",")[i:i + 2]) for i in (0, 2)) in text:
-                ran.add(tile)
-                L.ws.fill_(0xFF)
-                assert_close(run_pass(L, "bwd", Wt=Wt, dO=dO), ref, dtype, tile)
-        finally:
-            L.close()
+    for tile in tiles(shape, dtype):
+        for nt in ("0", "1"):  # (the input non-temporally, where that is built)
+            monkeypatch.setenv("CONVMI_IGEMM_CAND", tile)
+            monkeypatch.setenv("CONVMI_IGEMM_NT", nt)
+            L = conv.ConvLayer(*shape, dtype=dtype)
+            try:
+                v = staged_variant(tile, conv.conv_describe(L.h, conv.PASS_BWD_DATA))
+                if v and v not in ran:
+                    ran.add(v)
+                    L.ws.fill_(0xFF)
+                    assert_close(run_pass(L, "bwd", Wt=Wt, dO=dO), ref, dtype, tile)
+            finally:
+                L.close()
     assert len(ran) >= 2, ran
 
 

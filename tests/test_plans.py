@@ -446,3 +446,47 @@ def test_lds_of_the_register_operand_kernel_counts_its_ring_of_weights(monkeypat
         p = _plans((4, 128, 128, 28, 28, 1, 1, 1, 0), conv.CONV_BF16)[1]
         assert "forward_weights=1" in p[conv.PASS_BWD_DATA]
         assert (_field(p[conv.PASS_FWD], "lds"), _field(p[conv.PASS_BWD_DATA], "lds")) == (fwd, bwd), (variant, p)
+
+
+def test_every_tile_on_forward_weights_is_reached_by_the_test_that_runs_them(monkeypatch):
+    """The instantiations of the staged kernel that read the forward pass's weights, against what the shapes, tiles and
+    input policies of test_gpu_forward_weights.py plan."""
+    from test_gpu_forward_weights import SHAPES, staged_variant, tiles
+    want = set()
+
+    def built(dtype, waves, frags, npl, rs, ppt, nb=2, policies=(0,)):
+        want.update((dtype, waves, frags, npl, rs, ppt, nb, nt) for nt in policies)
+    F32, BF16 = conv.CONV_F32, conv.CONV_BF16
+    for dtype in (F32, BF16):
+        for frags in ("1x2", "2x2"):
+            for npl, rs, ppt in ((4, "1x1", 0), (8, "1x1", 0), (2, "3x3", 1), (2, "3x3", 2), (2, "3x3", 3), (2, "1x7", 1),
+                                 (2, "7x1", 1), (2, "7x1", 2)):
+                built(dtype, "2x2", frags, npl, rs, ppt)
+    for nb in (2, 3):
+        built(BF16, "4x1", "1x7", 4, "1x1", 1, nb, (0, 1))
+        built(BF16, "2x2", "1x7", 4, "1x1", 2, nb, (0, 1))
+    built(BF16, "4x2", "2x4", 8, "1x1", 1, 2, (0, 1))
+    built(BF16, "2x2", "2x4", 4, "1x1", 1)
+    built(BF16, "4x1", "1x7", 8, "1x1", 1)
+    built(F32, "4x1", "1x7", 4, "1x1", 1, 2, (0, 1))
+    built(F32, "2x2", "1x7", 4, "1x1", 2, 2, (0, 1))
+    for waves in ("1x4", "2x4"):
+        for ppt in (3, 4):
+            built(BF16, waves, "2x4", 2, "3x3", ppt)
+    built(BF16, "1x4", "2x4", 2, "1x7", 3)
+    built(BF16, "1x4", "2x4", 2, "7x1", 3)
+    built(F32, "4x1", "1x7", 2, "3x3", 2)
+    built(F32, "2x2", "1x7", 2, "3x3", 3)
+    for ppt in (5, 6):
+        built(F32, "1x4", "1x7", 2, "3x3", ppt)
+    assert len(want) == 58
+    monkeypatch.setenv("CONVMI_IGEMM_REG", "0")
+    got = set()
+    for shape in SHAPES:
+        for dtype in (F32, BF16):
+            for tile in tiles(shape, dtype):
+                for nt in ("0", "1"):
+                    monkeypatch.setenv("CONVMI_IGEMM_CAND", tile)
+                    monkeypatch.setenv("CONVMI_IGEMM_NT", nt)
+                    got.add(staged_variant(tile, _plans(shape, dtype)[1][conv.PASS_BWD_DATA]))
+    assert got - {None} == want
