@@ -876,13 +876,14 @@ IgemmPlan plan_igemm_tile(int dtype, int N, int Cb, int H, int W, int Kp, int P,
 }
 
 // The four residue classes of a 3x3 stride-2 backward pass in one launch of 64 x 128 tiles, where that is
-// faster than one launch each of what plan_igemm picks (time of the one launch / of the four, 11 layers at
-// N = 1 ... 256, both with the weights of all classes transformed in one launch):
-//   - bf16: everywhere (0.43 - 0.88; 512 -> 512 at 14x14 up to N = 8 and 32 -> 64 at 149x149, N = 256: 1.0);
-//   - fp32: where the tiles fill the chip before their chain of K/8 steps tells, 1.25 tiles per output
-//     channel (0.62 - 0.94, up to 1.01; below: 128 -> 128 at 28x28, N = 8 1.02, 288 -> 384 at 35x35, N = 8 1.03, N = 1
-//     1.57), or the chain is short (K <= 96: 0.55 - 0.94, from 25 pixels on; K = 128 1.02, K = 256 1.3 where the
-//     tiles are few); not where half of a tile's rows are empty (32 -> 64 at 149x149, N = 32: 1.48).
+// faster than one launch each of what plan_igemm picks.  Time of the one launch, which reads the forward pass's weights, / of
+// the four and the launch that transforms theirs, 15 layers at N = 1 ... 256:
+//   - bf16: everywhere (0.27 - 0.88);
+//   - fp32: where the tiles fill the chip before their chain of K/8 steps tells, 1.25 tiles per output channel, or the
+//     chain is short (K <= 96), but not where half of a tile's rows are empty (32 -> 64 at 149x149, N = 8 up: 1.1 - 1.65): 0.46 -
+//     1.02.  Elsewhere 0.69 - 1.65: 0.7 - 0.95 from about half a tile per output channel on (256 -> 256 at 28x28, N = 8, 41 us
+//     and 35), where the one launch sums each result in one chain and the four split it over waves; 1.06 - 1.4 below
+//     (288 -> 384 at 35x35, N = 1 36.7 and 49.7).
 // (128 x 128 tiles: at most 5 % ahead, on a few bf16 layers; fp32 up to twice as long.)
 void plan_bwd_quad(conv_plan *p)
 {
