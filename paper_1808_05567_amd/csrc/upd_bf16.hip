@@ -378,6 +378,12 @@ __global__ __launch_bounds__(WC *WK *WP * 64) void upd_rows_bf16_kernel(const Up
                     t += WP;
                     if (2 * t >= nruns) break;
                 }
+                // The reads for the pair behind the last one are awaited too, though nothing takes them: to the compiler
+                // their registers are free from here on, and what it puts there (the addresses of the next band's
+                // loads) would be overwritten when they land.
+                __builtin_amdgcn_sched_barrier(0);
+                lds_reads_pending<0>();
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             u32x2 w0[R][FC][PER_ROW];
