@@ -569,12 +569,13 @@ double estimate_patch_us(const IgemmPlan &p)
 
 // What the launch that transforms the weights of a backward pass takes, and what the pass loses by finding
 // them beyond the L2: 3.3 us for 0.5 MB, 3.7 for 1.2 MB, 6.4 for 4.7 MB.
+double transform_launch_us(double weight_bytes) { return 3.0 + 0.7e-6 * weight_bytes; }
 double transform_us(const IgemmPlan &p)
 {
     // (fp32: not counted, which leaves the lines between staged tiles and operands in registers, measured with the launch
     // on both sides, where they are: counted, 128 -> 128 3x3 at 28x28, N = 48, takes 102 us for 95)
     if (p.v.dtype == CONV_F32) return 0;
-    return 3.0 + 0.7e-6 * (double)p.a.Cb * p.a.Kp * 16 * (p.reg ? p.a.R * p.a.S : p.v.r * p.v.s);
+    return transform_launch_us((double)p.a.Cb * p.a.Kp * 16 * (p.reg ? p.a.R * p.a.S : p.v.r * p.v.s));
 }
 
 hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t stream)
@@ -582,6 +583,21 @@ hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t strea
     return p.patch ? launch_igemm_patch(p.v, a, p.grid, stream)
            : p.reg ? launch_igemm_reg(p.v, a, p.grid, stream)
                    : launch_igemm(p.v, a, p.lds, p.grid, stream);
+}
+
+// fp32: whether a staged backward launch of `us` microseconds takes the forward pass's weights.  It saves a launch and costs four
+// 4-byte reads of LDS for one of 16, next to as many MFMAs as pixel fragments share the operand.  403 passes of 70 layers,
+// N = 4 ... 256, in both forms: the reads cost 1 % of the launch under 1x1 in tiles of two pixel fragments and 1x7, less
+// under 3x3 in seven fragments, 3 - 4 % else (up to 8), so that they are slower from about 150 us on (64 <- 640 7x1 at
+// 30x30, N = 28, 140 -> 146 us; 512 <- 2048 1x1 at 7x7, N = 256, 232 -> 242; one launch for the classes of 84 <- 736 3x3
+// stride 2 at 59x57, N = 28, 327 -> 336).  With this line the passes take 0.94 of the time with the transform, as without it,
+// at most 1.03 (1.04 without), and 1.001 of the better form's.
+// (CONVMI_FORWARD_WEIGHTS: 0 never, 1 wherever such a tile is built, in fp32 -- a tuning aid)
+bool forward_weights_pay(int taps, int columns, int fm, double us, double weight_bytes)
+{
+    if (const char *env = getenv("CONVMI_FORWARD_WEIGHTS")) return atoi(env) != 0;
+    const bool cheap = taps == 1 ? fm == 2 : columns == 7 || (taps == 9 && fm == 7);
+    return (cheap ? 0.01 : 0.03) * us < transform_launch_us(weight_bytes);
 }
 
 // Plan one launch of the implicit-GEMM kernel.
@@ -706,6 +722,11 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
                 if (c.ok && (most_error <= 0 || sums_within(c, most_error))) p = c;
             }
         }
+    }
+    if (p.ok && !p.reg && dtype == CONV_F32 && p.v.fw &&
+        !forward_weights_pay(R * S, S, p.v.fm, estimate_us(p, zero_fill != 0), (double)Cb * R * S * Kp * 16)) {
+        p.v.fw = 0;
+        p.a.fwd_wt = 0;
     }
     // (CONVMI_IGEMM_REG="fk,fm,waves,ksplit": one variant of the register-operand kernel wherever it
     // exists; "0": never -- a tuning aid)
@@ -895,6 +916,7 @@ void plan_bwd_quad(conv_plan *p)
     BwdClass cls[4];
     size_t off = 0;
     int tiles = 0;
+    bool forward = true;
     for (int i = 0; i < 4; ++i) {
         const int R2 = i < 2 ? 2 : 1, S2 = i == 0 || i == 2 ? 2 : 1;
         const BwdClass *b = nullptr;
@@ -908,14 +930,27 @@ void plan_bwd_quad(conv_plan *p)
         if (!cls[i].p.ok) return;
         tiles += cls[i].p.a.total;
         const int off_r = cls[i].x.r_off, off_s = cls[i].x.s_off;
-        if (!forward_weights(cls[i].p.a, 9, (off_r + 2 * (R2 - 1)) * 3 + off_s + 2 * (S2 - 1), 6, 2)) return;
+        forward = forward_weights(cls[i].p.a, 9, (off_r + 2 * (R2 - 1)) * 3 + off_s + 2 * (S2 - 1), 6, 2);
+        cls[i].x.R2 = R2;
+        cls[i].x.S2 = S2;
+        cls[i].ws_off = off;
         off += (size_t)f.Kb * R2 * S2 * f.Cp * f.vlen * esize_of(d.dtype);
     }
     // (CONVMI_BWD_QUAD: 0 never, 1 wherever it fits -- a tuning aid)
     bool want = d.dtype == CONV_BF16 || (f.Cp > 32 && (d.K <= 96 || tiles >= 1.25 * d.K));
     if (const char *env = getenv("CONVMI_BWD_QUAD")) want = atoi(env) != 0;
-    if (!want) return;
-    for (int i = 0; i < 4; ++i) p->bwd[i] = cls[i];
+    // (bf16 has no form of the kernel that reads transformed weights)
+    if (!want || (!forward && d.dtype == CONV_BF16)) return;
+    if (d.dtype == CONV_F32) {
+        // (one launch: the classes' estimates without theirs, which are together 1.14 of what it takes beyond 100 us)
+        double us = 0;
+        for (const BwdClass &c : cls) us += estimate_us(c.p, true) - 3.0;
+        forward = forward && forward_weights_pay(9, 3, 2, 0.88 * us, (double)off);
+    }
+    for (int i = 0; i < 4; ++i) {
+        cls[i].p.a.fwd_wt = forward ? 1 : 0;
+        p->bwd[i] = cls[i];
+    }
     p->bwd_ws = off;
     p->bwd_quad = true;
 }
@@ -2364,7 +2399,7 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
             const BwdClass &b = h->bwd[i];
             q.cls[i] = b.p.a;
             q.cls[i].in = dout;
-            q.cls[i].wt = wt;
+            q.cls[i].wt = b.p.a.fwd_wt ? wt : static_cast<char *>(ws) + b.ws_off;
             q.cls[i].out = din;
             q.end[i] = grid += b.p.grid;
             lds = std::max(lds, b.p.lds);

@@ -18,32 +18,34 @@
 
 namespace convmi {
 
-template <int DT, int NPL, int R, int S, int PPT>
+template <int DT, bool FWD_WT, int NPL, int R, int S, int PPT>
 static __device__ __forceinline__ void quad_tile(const IgemmArgs &a, int bid, unsigned char *lds)
 {
-    igemm_tile<DT, 2, 2, 1, 2, NPL, R, S, PPT, 2, 0, false, true>(a, bid, lds);
+    igemm_tile<DT, 2, 2, 1, 2, NPL, R, S, PPT, 2, 0, false, FWD_WT>(a, bid, lds);
 }
 
-template <int DT>
+template <int DT, bool FWD_WT>
 __global__ __launch_bounds__(256, 2) void igemm_quad_kernel(const IgemmQuadArgs q)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int bid = blockIdx.x;  // (every class's grid is a multiple of 8: its XCDs stay bid mod 8)
     if (bid < q.end[0])
-        quad_tile<DT, 2, 2, 2, 1>(q.cls[0], bid, lds);
+        quad_tile<DT, FWD_WT, 2, 2, 2, 1>(q.cls[0], bid, lds);
     else if (bid < q.end[1])
-        quad_tile<DT, 2, 2, 1, 1>(q.cls[1], bid - q.end[0], lds);
+        quad_tile<DT, FWD_WT, 2, 2, 1, 1>(q.cls[1], bid - q.end[0], lds);
     else if (bid < q.end[2])
-        quad_tile<DT, 2, 1, 2, 1>(q.cls[2], bid - q.end[1], lds);
+        quad_tile<DT, FWD_WT, 2, 1, 2, 1>(q.cls[2], bid - q.end[1], lds);
     else if (q.cls[3].PLS <= 128)
-        quad_tile<DT, 4, 1, 1, 0>(q.cls[3], bid - q.end[2], lds);
+        quad_tile<DT, FWD_WT, 4, 1, 1, 0>(q.cls[3], bid - q.end[2], lds);
     else
-        quad_tile<DT, 4, 1, 1, 1>(q.cls[3], bid - q.end[2], lds);
+        quad_tile<DT, FWD_WT, 4, 1, 1, 1>(q.cls[3], bid - q.end[2], lds);
 }
 
 hipError_t launch_igemm_quad(int dtype, const IgemmQuadArgs &q, size_t lds_bytes, hipStream_t stream)
 {
-    void (*const fn)(const IgemmQuadArgs) = dtype == CONV_BF16 ? igemm_quad_kernel<CONV_BF16> : igemm_quad_kernel<CONV_F32>;
+    void (*const fn)(const IgemmQuadArgs) = dtype == CONV_BF16    ? igemm_quad_kernel<CONV_BF16, true>
+                                            : q.cls[0].fwd_wt ? igemm_quad_kernel<CONV_F32, true>
+                                                              : igemm_quad_kernel<CONV_F32, false>;
     if (hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void *>(fn), lds_bytes); err != hipSuccess)
         return err;
     hipLaunchKernelGGL(fn, dim3(q.end[3]), dim3(256), lds_bytes, stream, q);

@@ -79,6 +79,33 @@ def test_staged_tiles_match_oracle(shape, dtype, monkeypatch):
     assert len(ran) >= 2, ran
 
 
+@pytest.mark.parametrize("shape,env", [
+    ((5, 36, 48, 7, 8, 3, 3, 2, 0), ("CONVMI_BWD_QUAD", "1")),
+    ((3, 100, 48, 13, 11, 3, 3, 2, 1), ("CONVMI_BWD_QUAD", "1")),
+    ((3, 264, 160, 13, 11, 1, 1, 1, 0), ("CONVMI_IGEMM_CAND", "4,1,1,7,2,4")),
+    ((3, 40, 192, 9, 10, 1, 1, 2, 0), ("CONVMI_IGEMM_CAND", "2,2,2,2,2,8")),
+    ((3, 40, 96, 9, 11, 7, 1, 1, (3, 0)), ("CONVMI_IGEMM_CAND", "2,2,1,2,2,2")),
+], ids=str)
+def test_fp32_passes_in_both_forms_are_the_same(shape, env, monkeypatch):
+    """Long launches transform the weights after all: the same sums, in the same order."""
+    N, C, K, H, W, R, S, stride, pad = shape
+    _, Wt, dO = make_inputs(shape, conv.CONV_F32, layer_id=11)
+    monkeypatch.setenv("CONVMI_IGEMM_REG", "0")
+    monkeypatch.setenv(*env)
+    got = []
+    for form in ("0", "1"):
+        monkeypatch.setenv("CONVMI_FORWARD_WEIGHTS", form)
+        L = conv.ConvLayer(*shape, dtype=conv.CONV_F32)
+        try:
+            assert ("forward_weights=1" in conv.conv_describe(L.h, conv.PASS_BWD_DATA)) == (form == "1")
+            L.ws.fill_(0xFF)
+            got.append(run_pass(L, "bwd", Wt=Wt, dO=dO))
+        finally:
+            L.close()
+    assert_close(got[0], oracle.bwd_data(dO, Wt, H, W, stride, pad), conv.CONV_F32, str(env))
+    assert (got[0] == got[1]).all()
+
+
 @pytest.mark.parametrize("shape,dtype,env", [
     ((3, 264, 136, 5, 7, 1, 1, 1, 0), conv.CONV_BF16, ("CONVMI_IGEMM_REG", "1,1,8")),
     ((3, 264, 136, 5, 7, 1, 1, 1, 0), conv.CONV_BF16, ("CONVMI_IGEMM_REG", "2,1,8")),

@@ -490,3 +490,15 @@ def test_every_tile_on_forward_weights_is_reached_by_the_test_that_runs_them(mon
                     monkeypatch.setenv("CONVMI_IGEMM_NT", nt)
                     got.add(staged_variant(tile, _plans(shape, dtype)[1][conv.PASS_BWD_DATA]))
     assert got - {None} == want
+
+
+def test_fp32_backward_transforms_the_weights_where_the_launch_is_long():
+    """Time on the forward pass's weights / with the transform beside each."""
+    for shape, forward in (((28, 84, 736, 59, 57, 3, 3, 2, 1), False),       # 1.03
+                           ((64, 64, 64, 56, 56, 3, 3, 2, 1), True),         # 0.97
+                           ((64, 64, 640, 30, 30, 7, 1, 1, (3, 0)), False),  # 1.03
+                           ((256, 512, 2048, 7, 7, 1, 1, 1, 0), False),      # 1.04
+                           ((256, 512, 1024, 28, 28, 1, 1, 2, 0), True),     # 0.99: two pixel fragments
+                           ((8, 1024, 256, 14, 14, 1, 1, 1, 0), True)):
+        p = _plans(shape, conv.CONV_F32)[1][conv.PASS_BWD_DATA]
+        assert ("forward_weights=1" in p) == forward, (shape, p)

@@ -57,11 +57,13 @@ def test_weights_just_within_them_keep_their_tiled_kernels(shape):
     (8, 15200, 15200, 14, 14, 3, 3, 2, 1, BF16),          # 4.2 GB
 ], ids=lambda s: "x".join(map(str, s)))
 def test_strided_backward_of_such_weights_transforms_them(shape):
-    """Each residue class is in reach, the whole filter is not: a launch per class, on the class's own weights."""
+    """Each residue class is in reach, the whole filter is not: the classes run on their own, transformed weights."""
     wt_bytes, (fwd, bwd) = _describe(shape)
     assert wt_bytes > 4.0e9
     assert fwd.startswith("direct "), fwd
-    assert bwd.startswith("igemm") and "launches=4" in bwd and "forward_weights=1" not in bwd, bwd
+    assert bwd.startswith("igemm") and "forward_weights=1" not in bwd, bwd
+    if shape[-1] == BF16:  # (no kernel for the classes in one launch reads transformed weights)
+        assert "launches=4" in bwd, bwd
 
 
 @pytest.mark.parametrize("shape", [(8, 10400, 10400, 14, 14, 3, 3, 2, 1, F32), (8, 14880, 14880, 14, 14, 3, 3, 2, 1, BF16)],
@@ -70,5 +72,5 @@ def test_strided_backward_of_weights_just_within_reach_does_not(shape):
     wt_bytes, (fwd, bwd) = _describe(shape)
     assert 3.8e9 < wt_bytes <= 4.0e9
     assert fwd.startswith("igemm"), fwd
-    if shape[-1] == BF16:  # (fp32: a chain of this length is better off in a launch per class)
+    if shape[-1] == BF16:  # (fp32: a launch of this length repays the transform)
         assert "launches=1" in bwd and "forward_weights=1" in bwd, bwd
