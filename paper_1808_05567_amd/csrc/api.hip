@@ -526,6 +526,10 @@ double estimate_us(const IgemmPlan &p, bool scatter)
     }
     // (10 % on top: without them 13 of 280 1x1 passes are 3 % and more behind the kernel it takes over from, with them 7)
     if (p.reg && a.fwd_wt) return 1.1 * std::max(t, launch + bytes / hbm);
+    // (in registers on transformed weights, scattering: 3 % on top, and 3.0 TB/s where memory bounds it.  226 passes of odd channel
+    // blocks, N = 8 ... 256, all candidates timed: without, 13 of them are 3 % and more slower than the next one down the list,
+    // 168 <- 52 at 32x35, N = 196, 31 us for 24; with it two, of 12 us)
+    if (p.reg && bf16 && scatter) return std::max(1.03 * t, launch + bytes / (bytes > 6.0e7 ? std::min(hbm, 3.0e6) : hbm));
     // (bf16 staged tiles that scatter, four stores for every one the fit has seen, and read the forward pass's weights: six
     // layers, N = 2 ... 64, take 1.23, 1.34, 1.45 and 1.64 of the estimate.  With it 23 of 104 backward passes of those six and
     // seven other layers, N = 2 ... 192, run on another kernel, in 0.83 of the time (0.51 ... 1.03): 512 -> 1024 stride 2 at
@@ -660,7 +664,7 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
             if (!c.ok || (most_error > 0 && !sums_within(c, most_error))) return;
             const double us = estimate_us(c, scatter) + (geo.fwd_wt && !c.a.fwd_wt ? transform_us(c) : 0);
             // (of two bound by memory alike: staged ones, where tiles abound, the one that reads its input less often; on
-            // transformed weights in registers the larger tile -- 264 -> 256 stride 2 at 45x48, N = 86, 46 us, 59 in the smaller)
+            // transformed weights in registers the larger tile -- 324 <- 456 stride 2 at 55x55, N = 81, 57 us, 89 in the smaller)
             const bool larger = c.reg && best.reg ? transforms(c) && transforms(best) && c.v.fk * c.v.fm > best.v.fk * best.v.fm
                                                   : !c.reg && !best.reg && c.v.fk > best.v.fk && c.a.total >= 768;
             if (us < best_us || (us == best_us && larger)) {
@@ -708,14 +712,15 @@ IgemmPlan plan_igemm(int dtype, int N, int Cb, int H, int W, int Kp, int P, int 
         //   - 1.5 - 1.83 rounds: 0.88 - 1.02 (512 -> 2048 at 7x7, N = 256, 219 -> 202; 512 -> 1024 stride 2 at 28x28, N = 256,
         //     backward 482 -> 438); 1.44 - 1.5 0.99 - 1.13, 1.83 - 2.05 0.92 - 1.13, in the third round and later 0.93 - 1.14;
         //   - 64-row tiles, 0.82 - 2.3 rounds behind at most 12 steps: 0.78 - 1.02 (64 -> 64 at 56x56, N = 96, 40 -> 33), 0.84 at
-        //     2.5; longer 0.85 - 1.05.  Where half of the rows are empty 0.94 - 1.05 up to 1.12 rounds, 0.85 - 0.98 beyond.
+        //     2.5; longer 0.85 - 1.05.  Where half of the rows are empty 0.94 up to 0.865, 1.04 up to 1.12, 0.85 - 0.98 beyond.
         if (p.ok && !p.reg && dtype == CONV_F32 && R * S == 1 && p.v.fm == 7 && p.a.sampled && Cb % 8 == 0) {
             const double filled = p.a.total / 512.0;
             const bool strided = stride > 1 || ostr > 1;
             const bool rounds = p.v.wk == 4 && p.a.n_stage >= 8 &&
                                 ((filled >= 0.83 && filled <= 0.88 && (!strided || p.a.n_stage >= 32)) ||
                                  (filled >= 1.5 && filled <= 1.83));
-            const bool narrow = p.v.wk == 2 && Kp <= 64 && p.a.n_stage <= 12 && filled >= (Kp <= 32 ? 1.12 : 0.82) && filled <= 2.3;
+            const bool narrow = p.v.wk == 2 && Kp <= 64 && p.a.n_stage <= 12 && filled >= 0.82 && filled <= 2.3 &&
+                                (Kp > 32 || filled <= 0.865 || filled >= 1.12);
             if (rounds || narrow) {
                 IgemmPlan c = try_igemm(dtype, N, Cb, H, W, Kp, P, Q, R, S, stride, pad_h, pad_w, OH, OW, ostr, oy0, ox0,
                                         zero_fill, geo, 2, 2, 1, 2, (size_t)kMaxLds, 2, 8);

@@ -383,11 +383,14 @@ def test_bf16_backward_on_transformed_weights_where_the_kernels_on_the_forward_o
     """The register-operand kernel behind a transform: channel blocks that only the one-block tile takes else, and many
     tiles; of two tiles that memory bounds alike, the larger."""
     for shape in ((8, 256, 48, 35, 35, 1, 1, 1, 0), (98, 344, 216, 19, 21, 1, 1, 1, 0), (12, 360, 360, 46, 47, 7, 1, 1, (3, 0)),
-                  (86, 256, 264, 45, 48, 1, 1, 2, 0)):
+                  (81, 324, 456, 55, 55, 1, 1, 2, 0), (190, 204, 296, 23, 26, 1, 1, 2, 0)):
         p = _plans(shape, conv.CONV_BF16)[1][conv.PASS_BWD_DATA]
         assert p.startswith("igemm_reg ") and "frags=2x2" in p and "forward_weights=1" not in p, p
     p = _plans((8, 1024, 256, 14, 14, 1, 1, 1, 0), conv.CONV_BF16)[1][conv.PASS_BWD_DATA]
     assert "forward_weights=1" in p, p
+    # scattering and bound by memory: 31 us where the staged tile of one channel block takes 24
+    p = _plans((196, 168, 52, 32, 35, 1, 1, 2, 0), conv.CONV_BF16)[1][conv.PASS_BWD_DATA]
+    assert p.startswith("igemm ") and "npl=1" in p, p
 
 
 def test_bf16_strided_1x1_backward_of_few_tiles_is_not_staged():
