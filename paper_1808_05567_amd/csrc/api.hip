@@ -1843,29 +1843,33 @@ int window_pitch(const conv_plan *p)
     const conv_desc_t &d = p->d;
     return std::max(p->info.Q, ceil_div(std::min(d.W, d.stride * (p->info.Q - 1) - p->pad_w + d.S), d.stride));
 }
-// Whether a strided 3x3 layer's update runs with one window of the input for all taps: time of that / of the ring kernel,
-// 16 layers at 5e9 ... 5e10 operations, three sets of tensors in turn (where the ring kernel's lines leave a layer to the row
-// kernel, beyond 5e10 operations, it stays there; measured there too, 0.65 - 0.81 of that kernel's time), more than 96
-// channels on both sides and few dead slots:
-//   - blocks of dW that fill half of the CUs with one split: from 1e10 operations 0.73 - 0.99 (400 -> 400 at 20x20, N = 62, 61
-//     -> 45 us); below 0.85 - 1.14;
-//   - fewer: from 1.6e10 0.75 - 1.00 (288 -> 384 at 35x35, N = 31, 1.8e10, 42 -> 41; N = 43 57 -> 52); 1e10 - 1.6e10 0.83 - 1.13;
-//   - ... and one side at least twice the other: from 3.3e10 0.77 - 0.96; 1e10 - 1.6e10 0.93 - 1.25, up to 2.3e10 0.91 - 1.07, up to
-//     3.3e10 0.75 - 1.04 (128 -> 256 at 56x56, N = 39, 32 -> 34; N = 87 73 -> 64);
+// Whether a strided 3x3 layer's update may run with one window of the input for all taps, and whether it does beside what
+// the ring kernel would run as: time of the window / of the ring kernel, 569 layers of 7e9 ... 5e10 operations, three sets
+// of tensors in turn (beyond 5e10 operations the ring kernel's lines leave a layer to the row kernel and it stays there;
+// measured there too, 0.65 - 0.81 of that kernel's time):
+//   - where the ring kernel takes the window's 64 x 64 blocks: from 1e10 operations 0.71 - 1.11, in the mean 0.92 (400 -> 400
+//     at 20x20, N = 62, 61 -> 45 us; 128 -> 308 at 30x33, N = 121, 33 -> 37); 7e9 - 1e10 0.88 - 1.10;
+//   - where it takes half a block, for fewer splits or none, what counts is how full the last round of workgroups is.  The
+//     window's grid at least a tenth fuller: from 1e10 0.67 - 1.09, in the mean 0.92 (440 -> 256 at 13x14, N = 172, 168 half
+//     blocks or three splits of 84, 50 -> 33 us); below 0.70 - 1.32;
+//   - ... and not: 0.86 - 1.53, in the mean 1.10 (512 -> 320 at 55x54, N = 5, 240 or 120, 21 -> 31 us; 672 -> 232 at 39x38,
+//     N = 20, 252 or 396, 34 -> 51), below 1e10 1.00 - 1.61;
 //   - 64 and 96 channels 1.08 - 1.3; one slot in nine dead (192 -> 320 at 17x17) 1.05 and more.  With stride 1, where a tap's
 //     pixels are neighbours, the ring kernel's own loads share their cache lines and the addresses cost more than they
 //     save: 1.00 - 1.28, but 0.92 - 0.98 for 512 -> 512 at 7x7.
+// Over all of them this costs 1.010 of the better kernel's time, the window from 1e10 on 1.015, never 1.07.
 bool ring_applies(const conv_plan *p);
 bool window_applies(const conv_plan *p)
 {
     const conv_desc_t &d = p->d;
-    const conv_info_t &f = p->info;
-    const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)f.P * f.Q;
-    const int wide = std::max(d.C, d.K), narrow = std::min(d.C, d.K);
-    const long long blocks = (long long)ceil_div(f.Cp, 64) * ceil_div(f.Kp, 64) * d.R;
-    const double from = blocks >= 128 ? 1.0e10 : wide < 2 * narrow ? 1.6e10 : 3.3e10;
-    return d.dtype == CONV_BF16 && d.stride == 2 && d.S == 3 && narrow > 96 && flops >= from && ring_applies(p) &&
-           16 * window_pitch(p) <= 17 * f.Q;
+    const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)p->info.P * p->info.Q;
+    return d.dtype == CONV_BF16 && d.stride == 2 && d.S == 3 && std::min(d.C, d.K) > 96 && flops >= 1.0e10 &&
+           ring_applies(p) && 16 * window_pitch(p) <= 17 * p->info.Q;
+}
+bool window_beats(const RingCand &ring, const UpdArgs &ring_a, const UpdArgs &window_a)
+{
+    auto filled = [](const UpdArgs &a) { return (double)a.total / (ceil_div(a.total, 256) * 256); };
+    return ring.fc * ring.fk >= 4 || filled(window_a) >= 1.1 * filled(ring_a);
 }
 // What such an update takes, in microseconds, as far as the choice of its splits goes.
 double window_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
@@ -1958,11 +1962,7 @@ bool plan_upd_ring(conv_plan *p)
         force = 0;
         if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &c.fc, &c.fk, &c.nw, &c.depth, &c.splits, &force, &group) < 5) return false;
         consider(c);
-    } else if (!any && window_applies(p)) {
-        const int tiles = ceil_div(f.Cp, 64) * ceil_div(f.Kp, 64) * d.R;
-        for (const int splits : {1, std::max(1, 256 / tiles), std::max(1, 512 / tiles)}) consider({2, 2, 8, 3, splits, 0, true});
-    }
-    if (!have && !((env && !any) || window_env) && (any || ring_applies(p))) {
+    } else if (any || ring_applies(p)) {
         for (const auto &k : kBlocks) {
             const int tiles = ceil_div(f.Cp, k[0] * 32) * ceil_div(f.Kp, k[1] * 32) * d.R;
             // (32 x 32 blocks of a 1x1 filter re-read both tensors once per 32 channels: for small ones)
@@ -1973,6 +1973,19 @@ bool plan_upd_ring(conv_plan *p)
             if (tiles >= 256 || (double)d.N * f.P * f.Q <= (double)(k[2] << 13)) consider({k[0], k[1], k[2], k[3], 1, 0});
             consider({k[0], k[1], k[2], k[3], std::max(1, 256 / tiles), 0});
             if (d.S == 3 || d.dtype == CONV_F32) consider({k[0], k[1], k[2], k[3], std::max(1, 512 / tiles), 0});
+        }
+        if (!any && window_applies(p)) {
+            const RingCand ring = best;
+            const UpdArgs ring_a = best_a;
+            const bool have_ring = have;
+            const int tiles = ceil_div(f.Cp, 64) * ceil_div(f.Kp, 64) * d.R;
+            have = false;
+            for (const int splits : {1, std::max(1, 256 / tiles), std::max(1, 512 / tiles)}) consider({2, 2, 8, 3, splits, 0, true});
+            if (have_ring && !(have && window_beats(ring, ring_a, best_a))) {
+                best = ring;
+                best_a = ring_a;
+                have = true;
+            }
         }
     }
     if (have && !env && d.dtype == CONV_BF16 && d.R * d.S == 1 && !ring_reads_apply(p, best_a)) return false;

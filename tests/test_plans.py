@@ -419,15 +419,17 @@ def test_fp32_1x1_keeps_large_tiles_where_small_ones_are_slower():
 
 def test_window_update_from_where_it_is_faster():
     """Time of the window kernel / the ring kernel beside each; both print as upd_ring."""
-    for (N, C, K, H, W, pad), want in (((44, 512, 512, 14, 14, 1), True),       # 0.88
+    for (N, C, K, H, W, pad), want in (((30, 400, 400, 20, 20, 1), False),      # 0.90, below 1e10 operations
                                        ((35, 400, 400, 20, 20, 1), True),       # 0.85
-                                       ((21, 288, 384, 35, 35, 0), False),      # 1.07
                                        ((37, 288, 384, 35, 35, 0), True),       # 0.93
-                                       ((52, 128, 128, 56, 56, 1), False),      # 1.06
                                        ((78, 128, 128, 56, 56, 1), True),       # 0.97
-                                       ((39, 128, 256, 56, 56, 1), False),      # 1.07
                                        ((87, 128, 256, 56, 56, 1), True),       # 0.89
-                                       ((21, 740, 180, 30, 31, 1), False)):     # 1.18
+                                       ((5, 512, 320, 55, 54, 1), False),       # 1.43: 240 half blocks, or 120
+                                       ((21, 740, 180, 30, 31, 1), False),      # 1.18: 216, or two splits of 108
+                                       ((20, 672, 232, 39, 38, 0), False),      # 1.53: 252, or three splits of 132
+                                       ((21, 716, 240, 36, 36, 0), True),       # 0.83: 276, or three splits of 144
+                                       ((25, 732, 128, 30, 33, 1), True),       # 0.85: 138, or three splits of 72
+                                       ((172, 440, 256, 13, 14, 1), True)):     # 0.67: 168, or three splits of 84
         p = _plans((N, C, K, H, W, 3, 3, 2, pad), conv.CONV_BF16)[1][conv.PASS_UPD]
         assert p.startswith("upd_ring ") and (_field(p, "window") > 0) == want, (N, C, K, p)
 
