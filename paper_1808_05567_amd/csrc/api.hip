@@ -32,6 +32,16 @@ hipError_t ensure_dynamic_lds(const void *kernel, size_t bytes)
 
 namespace {
 
+// fp32 on the bf16 matrix instructions (igemm_split.hip), in the place of an IgemmPlan's kernel.
+struct SplitPlan {
+    bool ok = false;
+    IgemmSplitVariant v{};
+    int fk = 0, fm = 0, nw = 0;  // nw > 0: the register-operand kernel's form of it
+    IgemmArgs a{};
+    size_t lds = 0;
+    int grid = 0;
+};
+
 struct IgemmPlan {
     bool ok = false;
     IgemmVariant v{};
@@ -41,6 +51,15 @@ struct IgemmPlan {
     bool reg = false;  // the register-operand kernel (v.wk waves split the reduction of a tile)
     bool patch = false;  // ... with the pixels in LDS (reg is set too)
     bool fallback = false;  // ... because no staged tile fits (IgemmGeo::fallback)
+    SplitPlan split;
+};
+
+// The residue classes of a strided backward pass in one launch on the bf16 instructions.
+struct SplitClassesPlan {
+    bool ok = false;
+    IgemmSplitVariant v{};
+    IgemmSplitClasses c{};
+    size_t lds = 0;
 };
 
 struct BwdClass {  // one stride-parity class of the generic backward pass
@@ -66,6 +85,7 @@ struct conv_plan {
     int n_bwd = 0;
     bool bwd_quad = false;  // four classes (2x2, 2x1, 1x2, 1x1 taps, in this order) in one launch
     BwdClass bwd[16];
+    SplitClassesPlan bwd_classes;  // runs in the place of all that
     size_t bwd_ws = 0;
     // (a backward pass that would run untiled but for the register-operand kernel, which takes a
     // workspace: a caller that brings none still gets the untiled kernel)
@@ -447,6 +467,7 @@ IgemmPlan try_patch(int dtype, int N, int Cb, int H, int W, int Kp, int P, int Q
 // fastest variant, and took 0.61 times as long as the large tiles that these sizes ran on before, their
 // reduction split through memory (0.55 / 0.29 times as long as those without the split).
 double estimate_patch_us(const IgemmPlan &p);
+double sums_error(const IgemmPlan &p);
 double estimate_us(const IgemmPlan &p, bool scatter)
 {
     if (p.patch) return estimate_patch_us(p);
@@ -582,8 +603,253 @@ double transform_us(const IgemmPlan &p)
     return transform_launch_us((double)p.a.Cb * p.a.Kp * 16 * (p.reg ? p.a.R * p.a.S : p.v.r * p.v.s));
 }
 
+// Where a launch may read the forward pass's weights (the arguments of forward_weights); taps 0: nowhere.
+struct FwdWeights {
+    int taps = 0, tap0 = 0, dr = 0, ds = 0;
+};
+
+// Channel groups over the XCDs, as in try_igemm: `image` pixels read per image.
+void share_over_xcds(IgemmArgs &a, double image, int taps)
+{
+    const double in_b = (double)a.N * a.Cb * image * 16.0, wt_b = (double)a.Cb * taps * a.Kp * 16.0;
+    double best = 0;
+    a.gk = 1;
+    for (int gk = 1; gk <= 8 && gk <= a.n_kt && a.ksplit == 1; gk *= 2) {
+        if (a.n_kt % gk != 0) continue;
+        double cost = gk * in_b + (8.0 / gk) * wt_b;
+        if (wt_b / gk > 2.0e6) cost += 8.0 * in_b;
+        if (gk == 1 || cost < best) { best = cost; a.gk = gk; }
+    }
+    a.kt_per = ceil_div(a.n_kt, a.gk);
+    a.mq_per = ceil_div(a.n_mt, 8 / a.gk);
+    a.per_xcd = a.gk == 1 ? ceil_div(a.total * a.ksplit, 8) : a.kt_per * a.mq_per;
+}
+
+// A plan of the split kernel for the launch that `p` plans, R x S taps.
+SplitPlan try_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, int wk, int wm, int fm, int kw, int g, int strips,
+                    int least_ni = 0)
+{
+    SplitPlan s;
+    const IgemmArgs &b = p.a;
+    // (a launch with a staged plan: its tensors are within 32-bit offsets)
+    if (!p.ok || b.no_taps || b.shuffle || b.cstride != b.stride || b.ostr_x != b.ostr) return s;
+    IgemmArgs &a = s.a;
+    a = b;
+    a.R = R;
+    a.S = S;
+    a.fwd_wt = a.group = 0;
+    if (fw.taps > 0 && !forward_weights(a, fw.taps, fw.tap0, fw.dr, fw.ds)) return s;
+    a.ksplit = 1;
+    a.sampled = R * S == 1 && a.pad_h == 0 && a.pad_w == 0 && (a.P - 1) * (long long)a.stride < a.H &&
+                (a.Q - 1) * (long long)a.stride < a.W;
+    if (a.sampled && strips > 1) return s;
+    const int TK = wk * 32, TM = wm * fm * 32;
+    a.n_qt = strips;
+    a.TQ = ceil_div(a.Q, strips);
+    if ((strips - 1) * a.TQ >= a.Q) return s;
+    a.TR = 0;
+    if (a.sampled) {
+        a.Hs = a.P;
+        a.LW = a.TQ;
+        a.LRW = TM;
+    } else {
+        // rows of an image: those its pixels read, without the rows of zeros below it that stand for the next image's above it too
+        const int rows = (a.P - 1) * a.stride + R;
+        a.Hs = rows - std::max(0, std::min(rows - a.pad_h - a.H, a.pad_h));
+        a.LW = (a.TQ - 1) * a.stride + S;
+        const long long touched = std::min<long long>((TM - 2) / a.TQ + 2, (long long)a.N * a.P);
+        const long long crossings = std::min<long long>(a.N - 1, ceil_div((int)touched - 1, a.P));
+        const long long LR = (touched - 1) * a.stride + crossings * std::max(0, a.Hs - a.P * a.stride) + R;
+        if (LR * a.LW > 4096) return s;
+        a.LRW = (int)LR * a.LW;
+    }
+    a.PLS = a.LRW;
+    const int ni = std::max(ceil_div(2 * g * ceil_div(a.LRW, 64), 4), least_ni);
+    s.v = IgemmSplitVariant{wk, wm, fm, kw, g, ni, a.fwd_wt};
+    if (!igemm_split_exists(s.v)) return s;
+    s.lds = igemm_split_lds_bytes(s.v, a.PLS);
+    if (s.lds > (size_t)kMaxLds) return s;
+    a.inv_P = 1.0f / (float)a.P;
+    a.inv_Hs = 1.0f / (float)a.Hs;
+    a.inv_LW = 1.0f / (float)a.LW;
+    a.inv_TQ = 1.0f / (float)a.TQ;
+    const long long tiles = (((long long)a.N * a.P * a.TQ + TM - 1) / TM) * strips;
+    if ((long long)a.N * a.P * a.TQ >= (1LL << 30) || tiles * ceil_div(a.Kp, TK) >= (1 << 24)) return s;
+    a.n_mt = (int)tiles;
+    a.n_kt = ceil_div(a.Kp, TK);
+    a.n_stage = ceil_div(a.Cb, 4 * g);
+    a.st_per = a.n_stage;
+    a.total = a.n_mt * a.n_kt;
+    share_over_xcds(a, a.sampled ? (double)a.P * a.Q : (double)a.H * a.W, R * S);
+    a.rot_k = a.rot_m = 1;
+    s.grid = a.per_xcd * 8;
+    s.ok = true;
+    return s;
+}
+
+// The register-operand kernel's form.  (A reduction split over workgroups: as many of them as `p` has, whose workspace it uses.)
+SplitPlan try_reg_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, int fk, int fm, int nw)
+{
+    SplitPlan s;
+    const IgemmArgs &b = p.a;
+    if (!p.ok || b.no_taps || b.shuffle || b.cstride != b.stride || b.ostr_x != b.ostr || !igemm_reg_split_exists(fk, fm, nw)) return s;
+    // 32-bit byte offsets, exact small divisions and 24-bit products, as in try_reg
+    const double shift = (double)std::max(0, b.pad_h) * b.W + std::max(0, b.pad_w);
+    if (((double)b.N * b.Cb * b.H * b.W + shift) * 16 > 4.0e9 || b.pad_h < 0 || b.pad_w < 0) return s;
+    if ((double)b.N * b.P * b.Q + fm * 32 >= 4.0e6 || (double)R * S * b.Kp >= 4.0e6) return s;
+    if ((double)(b.N + 1) * std::max(b.Cb + 3, b.out_kb) * std::max(b.H, b.OH) >= 8.0e6) return s;
+    IgemmArgs &a = s.a;
+    a = b;
+    a.R = R;
+    a.S = S;
+    a.fwd_wt = a.group = 0;
+    if (fw.taps > 0 && !forward_weights(a, fw.taps, fw.tap0, fw.dr, fw.ds)) return s;
+    a.inv_P = 1.0f / (float)(a.P * a.Q);
+    a.inv_TQ = 1.0f / (float)a.Q;
+    a.n_qt = 1;
+    a.n_mt = ceil_div(a.N * a.P * a.Q, fm * 32);
+    a.n_kt = ceil_div(a.Kp, fk * 32);
+    a.total = a.n_mt * a.n_kt;
+    a.n_stage = ceil_div(a.Cb, 4) * R * S;
+    a.st_per = ceil_div(a.n_stage, b.ksplit);
+    a.ksplit = ceil_div(a.n_stage, a.st_per);
+    if (a.ksplit != b.ksplit) return s;
+    share_over_xcds(a, R * S == 1 ? (double)a.P * a.Q : (double)a.H * a.W, R * S);
+    s.lds = igemm_reg_split_lds_bytes(fk, fm, nw, a.fwd_wt != 0);
+    s.fk = fk;
+    s.fm = fm;
+    s.nw = nw;
+    s.grid = a.per_xcd * 8;
+    s.ok = true;
+    return s;
+}
+
+static const int kSplitTiles[][4] = {{4, 1, 4, 1}, {4, 1, 2, 1}, {2, 2, 4, 1}, {2, 2, 2, 1}, {4, 1, 4, 2}, {4, 1, 2, 2}, {2, 2, 4, 2}, {2, 2, 2, 2}};
+static const int kRegSplitTiles[][3] = {{1, 1, 4}, {1, 1, 8}, {1, 1, 16}, {2, 1, 4}, {2, 1, 8}, {1, 2, 4}, {2, 2, 4}, {2, 2, 8}};
+
+// Error of its sums in the same units (chain_error): an MFMA rounds the sum of the large products once for sixteen channels; what
+// the small ones add to it is nothing beside that.
+double split_error(const SplitPlan &s)
+{
+    const IgemmArgs &a = s.a;
+    if (s.nw > 0) return ceil_div(a.st_per, s.nw) / 2.0 + std::log2((double)s.nw) / 2 + (a.ksplit > 1 ? a.ksplit / 2.0 : 0) + 0.5;
+    return ceil_div(a.n_stage, s.v.kw) * s.v.g * a.R * a.S / 2.0 + (s.v.kw - 1) / 2.0 + 0.5;
+}
+
+// What a launch on the bf16 instructions takes, in microseconds, without the launch that transforms a backward pass's weights: the form of
+// estimate_us.  Fitted to 49 000 launches, 650 drawn layers of ResNet-50, Inception-v3 and odd sizes, N = 1 ... 256, every
+// variant, three sets of tensors in turn: rms error 8 % (in registers 14 %); the choice is 3 % behind the fastest.
+struct SplitTimes {
+    double lone, busy;  // clocks of a workgroup alone on its CU, and of one among others
+    int resident;
+};
+SplitTimes split_times(const SplitPlan &s, bool scatter)
+{
+    const IgemmArgs &a = s.a;
+    const double fw = a.fwd_wt ? 1 : 0;
+    SplitTimes t;
+    if (s.nw > 0) {
+        const int type = s.fk * s.fm == 4 ? 3 : s.fk * s.fm == 1 ? 0 : s.fk == 2 ? 1 : 2, frags = s.fk * s.fm;
+        static const double lone[4] = {711, 1192, 1508, 2272}, busy[4] = {498, 847, 945, 1339};
+        const double per = ceil_div(a.st_per, s.nw), simd = s.nw / 4.0;
+        const double loads = s.nw * (s.fk + s.fm) * 32.0, shared = std::max((busy[type] + fw * 92 * s.fk) * simd, loads);
+        const double k = scatter ? 1.22 : 1.0;
+        t.busy = k * (per * shared + 605 + 1.79 * 123 * frags * s.nw);
+        t.lone = k * (3724 + per * std::max(lone[type] + fw * 111 * s.fk, shared) + 123.0 * frags * s.nw);
+        t.resident = std::max(1, (frags == 1 ? 4 : frags == 2 ? 3 : 2) * 4 / s.nw);
+        return t;
+    }
+    const IgemmSplitVariant &v = s.v;
+    const bool wide = v.fm == 4;
+    const double steps = ceil_div(a.n_stage, v.kw), rounds = v.g * a.R * a.S, k = scatter ? 2.06 : 1.0;
+    t.busy = v.kw * steps * (rounds * ((wide ? 814 : 560) + fw * 161) + v.ni * 225 + 120) + 1417 * v.fm * v.kw * k;
+    t.lone = std::max(t.busy, (7244 + 775 * v.fm) * k + steps * (rounds * ((wide ? 952 : 702) + fw * 253) + v.ni * 262 + 281));
+    t.resident = std::max(1, std::min((int)(kMaxLds / s.lds), v.kw == 2 ? 1 : wide ? 2 : 3));
+    return t;
+}
+double tensor_bytes(const IgemmArgs &a, bool scatter)
+{
+    const int taps = a.R * a.S;
+    return (double)a.N * a.Cb * 16 * (taps == 1 ? (double)a.P * a.Q : (double)a.H * a.W) +
+           (double)a.N * a.Kp * 4 * (scatter ? (double)a.OH * a.OW : (double)a.P * a.Q) + (double)a.Cb * taps * a.Kp * 16;
+}
+double split_us(const SplitPlan &s, bool scatter)
+{
+    const IgemmArgs &a = s.a;
+    const SplitTimes w = split_times(s, scatter);
+    const int per_cu = ceil_div(s.grid, 256), full = per_cu / w.resident, rest = per_cu - full * w.resident;
+    const double t = full * std::max(w.lone, w.resident * w.busy) + (rest > 0 ? std::max(w.lone, rest * w.busy) : 0.0);
+    const double launch = s.nw > 0 ? 2.4 : 1.2, hbm = s.nw > 0 ? 3.2e6 : 3.7e6;
+    double us = std::max(t / (s.nw > 0 ? 2.2e3 : 2.1e3) + launch, launch + tensor_bytes(a, scatter) / hbm);
+    if (a.ksplit > 1)  // the second launch, and the partial results there and back
+        us += 1.7 + a.ksplit * (double)a.N * a.P * a.Q * a.Kp * 4 * 2 / 4.0e6;
+    return us;
+}
+
+// Whether the launch that `p` plans runs on the bf16 instructions: where the estimate says that this is at least 4 % faster, and the
+// sums are no less exact.  fw: where the forward pass's weights may be read.
+// (CONVMI_IGEMM_SPLIT="wk,wm,fm,kw,g,strips,fw" or "r,fk,fm,waves,fw": one variant wherever it fits, fw 1: on the forward pass's
+// weights; 0: never -- a tuning aid, as are those that ask for a variant on the fp32 instructions)
+bool fp32_variant_asked_for()
+{
+    for (const char *name : {"CONVMI_IGEMM_CAND", "CONVMI_IGEMM_REG", "CONVMI_IGEMM_GROUP", "CONVMI_IGEMM_NT", "CONVMI_IGEMM_GK",
+                             "CONVMI_IGEMM_ROT", "CONVMI_BWD_QUAD", "CONVMI_FORWARD_WEIGHTS", "CONVMI_STEM"})
+        if (getenv(name)) return true;
+    return false;
+}
+constexpr double kSplitMargin = 0.96;
+SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, bool backward)
+{
+    SplitPlan best;
+    if (!p.ok || p.v.dtype != CONV_F32) return best;
+    if (const char *env = getenv("CONVMI_IGEMM_SPLIT")) {
+        int wk = 0, wm = 0, fm = 0, kw = 0, g = 0, strips = 1, f = 0;
+        if (sscanf(env, "r,%d,%d,%d,%d", &wk, &fm, &kw, &f) >= 3)
+            return f && fw.taps == 0 ? best : try_reg_split(p, R, S, f ? fw : FwdWeights{}, wk, fm, kw);
+        if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &wk, &wm, &fm, &kw, &g, &strips, &f) < 5 || strips < 1) return best;
+        return f && fw.taps == 0 ? best : try_split(p, R, S, f ? fw : FwdWeights{}, wk, wm, fm, kw, g, strips);
+    }
+    if (fp32_variant_asked_for()) return best;
+    const bool scatter = p.a.zero_fill != 0;
+    const double transform = backward ? transform_launch_us((double)p.a.Cb * R * S * p.a.Kp * 16) : 0;
+    double best_us = kSplitMargin * (estimate_us(p, scatter) + (p.a.fwd_wt ? 0 : transform));
+    const double most_error = sums_error(p) + kOwnRounding;
+    auto consider = [&](const SplitPlan &c) {
+        if (!c.ok || split_error(c) > most_error) return;
+        // (staged: half a microsecond on top, which the estimate is off where a launch is short)
+        const double us = split_us(c, scatter) + (c.nw > 0 ? 0 : 0.5) + (c.a.fwd_wt ? 0 : transform);
+        if (us < best_us) {
+            best = c;
+            best_us = us;
+        }
+    };
+    for (const FwdWeights &w : {FwdWeights{}, fw}) {
+        for (const auto &t : kSplitTiles) {
+            for (int g = 1; g <= 2; ++g) {
+                if (g > 1 && R * S > 1) continue;
+                for (int strips = 1; strips <= 4; ++strips) consider(try_split(p, R, S, w, t[0], t[1], t[2], t[3], g, strips));
+            }
+        }
+        for (const auto &t : kRegSplitTiles) consider(try_reg_split(p, R, S, w, t[0], t[1], t[2]));
+        if (fw.taps == 0) break;
+    }
+    return best;
+}
+
 hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t stream)
 {
+    if (p.split.ok) {
+        IgemmArgs s = p.split.a;
+        s.in = a.in;
+        s.wt = a.wt;
+        s.out = a.out;
+        s.scale = a.scale;
+        s.bias = a.bias;
+        s.resid = a.resid;
+        s.relu = a.relu;
+        if (p.split.nw > 0) return launch_igemm_reg_split(p.split.fk, p.split.fm, p.split.nw, s, p.split.grid, stream);
+        return launch_igemm_split(p.split.v, s, p.split.lds, p.split.grid, stream);
+    }
     return p.patch ? launch_igemm_patch(p.v, a, p.grid, stream)
            : p.reg ? launch_igemm_reg(p.v, a, p.grid, stream)
                    : launch_igemm(p.v, a, p.lds, p.grid, stream);
@@ -630,6 +896,15 @@ bool sums_within(IgemmPlan &p, double most)
     }
     if (p.reg || igemm_variant_groups(p.v)) a.group = group_within(n, unit, kErrorMargin * most - rest);
     return chain_error(n, a.group * unit) + rest <= most + kOwnRounding;
+}
+
+// ... and that error as the plan is.
+double sums_error(const IgemmPlan &p)
+{
+    const IgemmArgs &a = p.a;
+    const double unit = p.reg ? 8.0 * igemm_reg_depth(p.v.dtype, p.v.fk, p.v.fm, p.v.wk) : 4.0 * p.v.npl * p.v.r * p.v.s;
+    const double n = p.reg ? 8.0 * ceil_div(a.st_per, p.v.wk) : unit * a.n_stage;
+    return chain_error(n, a.group * unit) + (a.ksplit > 1 ? a.ksplit / 2.0 : 0) + (p.reg ? std::log2((double)p.v.wk) / 2 : 0);
 }
 
 // (CONVMI_IGEMM_GROUP: steps or rounds that are summed apart, wherever the kernel can -- for tests)
@@ -1126,6 +1401,117 @@ void plan_bwd(conv_plan *p)
     p->n_bwd = n;
     p->bwd_ws = off;
     if (!fallback) plan_bwd_quad(p);
+}
+
+// Where launch i of a backward pass may read the forward pass's weights.
+FwdWeights class_weights(const conv_plan *p, int i)
+{
+    const WtXformArgs &x = p->bwd[i].x;
+    const int st = p->bwd_mode == 2 ? p->d.stride : 1;
+    if (x.R2 != x.Rsub || x.S2 != x.Ssub || x.Rsub < 1 || x.Ssub < 1) return FwdWeights{};
+    return FwdWeights{p->d.R * p->d.S, (x.r_off + st * (x.R2 - 1)) * p->d.S + x.s_off + st * (x.S2 - 1), st * p->d.S, st};
+}
+
+// The classes in one launch of one variant, those of most taps first.
+SplitClassesPlan try_split_classes(const conv_plan *p, int wk, int wm, int fm, int kw, int g, int strips)
+{
+    SplitClassesPlan s;
+    if (p->bwd_mode != 2 || p->n_bwd < 1 || p->n_bwd > 4) return s;
+    int order[4] = {0, 1, 2, 3};
+    auto taps = [&](int i) { return p->bwd[i].x.R2 * p->bwd[i].x.S2; };
+    std::stable_sort(order, order + p->n_bwd, [&](int i, int j) { return taps(i) > taps(j); });
+    // (a variant's shares are those of the class that needs most)
+    int ni = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        int grid = 0, most = 0;
+        s.lds = 0;
+        for (int k = 0; k < 4; ++k) {
+            if (k >= p->n_bwd) {
+                s.c.end[k] = grid;
+                continue;
+            }
+            const int i = order[k];
+            const FwdWeights fw = class_weights(p, i);
+            if (fw.taps == 0) return SplitClassesPlan{};
+            const SplitPlan c = try_split(p->bwd[i].p, p->bwd[i].x.R2, p->bwd[i].x.S2, fw, wk, wm, fm, kw, g, strips, ni);
+            if (!c.ok) return SplitClassesPlan{};
+            s.c.cls[k] = c.a;
+            s.c.end[k] = grid += c.grid;
+            s.lds = std::max(s.lds, c.lds);
+            s.v = c.v;
+            most = std::max(most, c.v.ni);
+        }
+        ni = most;
+    }
+    s.ok = igemm_split_classes_exist(s.v);
+    return s;
+}
+
+double classes_error(const conv_plan *p, const SplitClassesPlan &s)
+{
+    double most = 0;
+    for (int k = 0; k < p->n_bwd; ++k) {
+        SplitPlan c;
+        c.a = s.c.cls[k];
+        c.v = s.v;
+        most = std::max(most, split_error(c));
+    }
+    return most;
+}
+// What the one launch takes: the workgroups of all classes share the CUs, and none is done before its own tile is.
+double classes_us(const conv_plan *p, const SplitClassesPlan &s)
+{
+    double busy = 0, lone = 0, bytes = 0;
+    for (int k = 0; k < p->n_bwd; ++k) {
+        SplitPlan c;
+        c.a = s.c.cls[k];
+        c.v = s.v;
+        c.lds = s.lds;
+        const SplitTimes t = split_times(c, true);
+        busy += t.busy * c.a.total;
+        lone = std::max(lone, t.lone);
+        bytes += tensor_bytes(c.a, false);
+    }
+    const double launch = 1.2;
+    return std::max(std::max(lone, busy / 256 + 0.5 * lone) / 2.1e3 + launch, launch + bytes / 3.7e6);
+}
+
+// The backward pass on the bf16 instructions.
+void plan_bwd_split(conv_plan *p)
+{
+    p->bwd_classes = SplitClassesPlan{};
+    if (p->d.dtype != CONV_F32 || p->bwd_mode == 0 || p->bwd_mode == 3) return;
+    if (p->bwd_mode == 2) {
+        if (const char *env = getenv("CONVMI_IGEMM_SPLIT")) {
+            int wk = 0, wm = 0, fm = 0, kw = 0, g = 0, strips = 1;
+            if (sscanf(env, "%d,%d,%d,%d,%d,%d", &wk, &wm, &fm, &kw, &g, &strips) >= 5 && strips > 0)
+                p->bwd_classes = try_split_classes(p, wk, wm, fm, kw, g, strips);
+            return;
+        }
+        if (fp32_variant_asked_for()) return;
+        // (one launch for the classes, or one each and the launch that transforms their weights)
+        double old_us = 0, weights = 0, most_error = 0;
+        for (int i = 0; i < p->n_bwd; ++i) {
+            const BwdClass &b = p->bwd[i];
+            old_us += p->bwd_quad ? 0.88 * (estimate_us(b.p, true) - 3.0) : estimate_us(b.p, true);
+            weights += (double)b.x.Kb * b.x.R2 * b.x.S2 * b.x.Cp * 16;
+            most_error = std::max(most_error, sums_error(b.p));
+        }
+        old_us += (p->bwd_quad ? 3.0 : 0.0) + (p->bwd[0].p.a.fwd_wt ? 0 : transform_launch_us(weights));
+        double best_us = kSplitMargin * old_us;
+        for (const auto &t : kSplitTiles)
+            for (int strips = 1; strips <= 4; ++strips) {
+                const SplitClassesPlan c = try_split_classes(p, t[0], t[1], t[2], t[3], 1, strips);
+                if (!c.ok || classes_error(p, c) > most_error + kOwnRounding) continue;
+                const double us = classes_us(p, c);
+                if (us < best_us) {
+                    p->bwd_classes = c;
+                    best_us = us;
+                }
+            }
+        return;
+    }
+    p->bwd[0].p.split = plan_split(p->bwd[0].p, p->bwd[0].x.R2, p->bwd[0].x.S2, class_weights(p, 0), true);
 }
 
 // Weight update, bf16, at most 4 input channels: (tap, channel) rows on the bf16 MFMA.
@@ -2183,7 +2569,9 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
             // workgroup several tiles to walk: for tests of that path)
             if (const char *cap = getenv("CONVMI_STEM_WG"); cap && atoi(cap) > 0) p->fwd.a.jstep = atoi(cap);
         }
+        if (p->fwd_stem_lds == 0) p->fwd.split = plan_split(p->fwd, d.R, d.S, FwdWeights{}, false);
         plan_bwd(p);
+        plan_bwd_split(p);
         p->bwd_ws_optional = p->bwd_mode != 0 && p->bwd[0].p.fallback;
         plan_upd(p);
     }
@@ -2331,8 +2719,9 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     }
     if (!h->fwd.ok) return CONV_EUNSUPPORTED;
     IgemmArgs a = h->fwd.a;
-    const bool split = a.ksplit > 1;
-    if (split && !ws) return CONV_EWORKSPACE;
+    // (a workspace is asked for by the plan on the fp32 instructions, whatever runs in its place)
+    if (a.ksplit > 1 && !ws) return CONV_EWORKSPACE;
+    const bool split = a.ksplit > 1 && (!h->fwd.split.ok || h->fwd.split.a.ksplit > 1);
     a.in = in;
     a.wt = wt;
     a.out = split ? ws : out;
@@ -2346,7 +2735,7 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     // long there, and the residual's round trips do not fit into them -- 0.49 ms against 0.38
     // on the general kernel for layer 1 of Table I; in fp32 it is 0.64 against 0.89)
     const bool fused_ops = scale || bias || residual || relu;
-    if (h->fwd_stem_lds && !(fused_ops && h->d.dtype == CONV_BF16))
+    if (h->fwd_stem_lds && !h->fwd.split.ok && !(fused_ops && h->d.dtype == CONV_BF16))
         e = launch_igemm_stem(h->fwd.v, a, h->fwd_stem_lds, (hipStream_t)stream);
     else
         e = launch_plan(h->fwd, a, (hipStream_t)stream);
@@ -2391,8 +2780,18 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
     if (h->bwd_mode == 0) return CONV_EUNSUPPORTED;
     if (!ws) return CONV_EWORKSPACE;
     hipStream_t s = (hipStream_t)stream;
+    if (h->bwd_classes.ok) {
+        IgemmSplitClasses c = h->bwd_classes.c;
+        for (IgemmArgs &a : c.cls) {
+            a.in = dout;
+            a.wt = wt;
+            a.out = din;
+        }
+        return launch_igemm_split_classes(h->bwd_classes.v, c, h->bwd_classes.lds, s) == hipSuccess ? CONV_OK : CONV_ELAUNCH;
+    }
     // the transformed weights of all classes, up to four to a launch (none where the kernel reads the forward pass's)
-    for (int i = 0; i < h->n_bwd && !h->bwd[0].p.a.fwd_wt;) {
+    const bool forward = (h->bwd[0].p.split.ok ? h->bwd[0].p.split.a : h->bwd[0].p.a).fwd_wt != 0;
+    for (int i = 0; i < h->n_bwd && !forward;) {
         if (h->bwd[i].merged) {
             WtMergeArgs m = h->bwd[i].m;
             m.src = wt;
@@ -2426,11 +2825,11 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
     }
     for (int i = 0; i < h->n_bwd; ++i) {
         const BwdClass &b = h->bwd[i];
-        const void *wt2 = b.p.a.fwd_wt ? wt : static_cast<char *>(ws) + b.ws_off;
+        const void *wt2 = forward ? wt : static_cast<char *>(ws) + b.ws_off;
         IgemmArgs a = b.p.a;
         a.in = dout;
         a.wt = wt2;
-        void *part = a.ksplit > 1 ? static_cast<char *>(ws) + b.part_off : nullptr;
+        void *part = a.ksplit > 1 && (!b.p.split.ok || b.p.split.a.ksplit > 1) ? static_cast<char *>(ws) + b.part_off : nullptr;
         a.out = part ? part : din;
         if (launch_plan(b.p, a, s) != hipSuccess) return CONV_ELAUNCH;
         if (part && launch_split_reduce(h->d.dtype, static_cast<const float *>(part), din,
@@ -2687,6 +3086,25 @@ conv_status_t conv_unpack_dwt(conv_handle_t h, const void *blk_f32, void *kcrs_f
                             (hipStream_t)stream) == hipSuccess ? CONV_OK : CONV_ELAUNCH;
 }
 
+// What runs in the place of the plan on the fp32 instructions that stands before it.
+static void describe_split(const SplitPlan &s, char *buf, size_t buflen)
+{
+    if (!s.ok) return;
+    const size_t n = strlen(buf);
+    if (s.nw > 0)
+        snprintf(buf + n, buflen - n, " on_bf16x3=igemm_reg_split,%dx%d,waves%d,fw%d,tiles%d,lds%zu", s.fk, s.fm,
+                 s.nw, s.a.fwd_wt, s.a.total, s.lds);
+    else
+        snprintf(buf + n, buflen - n, " on_bf16x3=igemm_split,%dx%d,fm%d,sets%d,groups%d,shares%d,strips%d,fw%d,tiles%d,lds%zu",
+                 s.v.wk, s.v.wm, s.v.fm, s.v.kw, s.v.g, s.v.ni, s.a.n_qt, s.a.fwd_wt, s.a.total, s.lds);
+}
+static void describe_classes(const SplitClassesPlan &s, char *buf, size_t buflen)
+{
+    if (!s.ok) return;
+    const size_t n = strlen(buf);
+    snprintf(buf + n, buflen - n, " on_bf16x3=igemm_split_classes,%dx%d,fm%d,sets%d,groups%d,shares%d,strips%d,workgroups%d,lds%zu", s.v.wk, s.v.wm,
+             s.v.fm, s.v.kw, s.v.g, s.v.ni, s.c.cls[0].n_qt, s.c.end[3], s.lds);
+}
 conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buflen)
 {
     if (!h || !buf || buflen == 0) return CONV_EINVAL;
@@ -2727,6 +3145,8 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
                      p->a.total, p->a.n_mt, p->a.n_kt,
                      p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.group, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
             if (p->a.fwd_wt) strncat(buf, " forward_weights=1", buflen - strlen(buf) - 1);
+            describe_split(p->split, buf, buflen);
+            if (pass == 1) describe_classes(h->bwd_classes, buf, buflen);
             return CONV_OK;
         }
         snprintf(buf, buflen,
@@ -2740,6 +3160,8 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
             const size_t n = strlen(buf);
             snprintf(buf + n, buflen - n, " resident_filter_lds=%zu", h->fwd_stem_lds);
         }
+        describe_split(p->split, buf, buflen);
+        if (pass == 1) describe_classes(h->bwd_classes, buf, buflen);
         return CONV_OK;
     }
     if (pass == 2) {

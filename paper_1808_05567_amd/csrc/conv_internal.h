@@ -145,6 +145,30 @@ constexpr int kPatchLoads = 4;
 bool igemm_patch_exists(int dtype, int ntap, int fk, int fm, int nw);
 size_t igemm_patch_lds_bytes(int fk, int fm, int nw, int pls, bool fwd_wt);
 hipError_t launch_igemm_patch(const IgemmVariant &v, const IgemmArgs &a, int grid, hipStream_t stream);
+// fp32 tensors on the bf16 matrix instructions: wk x wm waves, fm pixel fragments each, kw such sets that split the channels,
+// g groups of 16 channels a step, ni shares of the input tile per wave and step.  IgemmArgs: n_mt counts pixel tiles of all
+// strips, n_stage steps of 16 * g channels; TQ is a strip's width, Hs, LW, LRW, PLS the staged tile's rows per image,
+// width, positions and the pitch of a plane in positions.
+struct IgemmSplitVariant {
+    int wk, wm, fm, kw, g, ni;
+    int fw = 0;  // 1: on the forward pass's weights (IgemmArgs::fwd_wt)
+};
+bool igemm_split_exists(const IgemmSplitVariant &v);
+size_t igemm_split_lds_bytes(const IgemmSplitVariant &v, int pls);
+// Up to four such launches in one, one variant for all, on the forward pass's weights: class i has the workgroups end[i-1] .. end[i]
+// (whole multiples of eight).
+struct IgemmSplitClasses {
+    IgemmArgs cls[4];
+    int end[4];
+};
+bool igemm_split_classes_exist(const IgemmSplitVariant &v);
+hipError_t launch_igemm_split_classes(const IgemmSplitVariant &v, const IgemmSplitClasses &c, size_t lds_bytes, hipStream_t stream);
+// The register-operand kernel in that form: fk x fm fragments, nw waves that split the reduction; a step is one tap of four
+// channel blocks, the rest of the arguments as for igemm_reg.
+bool igemm_reg_split_exists(int fk, int fm, int nw);
+size_t igemm_reg_split_lds_bytes(int fk, int fm, int nw, bool fwd_wt);
+hipError_t launch_igemm_reg_split(int fk, int fm, int nw, const IgemmArgs &a, int grid, hipStream_t stream);
+hipError_t launch_igemm_split(const IgemmSplitVariant &v, const IgemmArgs &a, size_t lds_bytes, int grid, hipStream_t stream);
 // The resident-filter kernel for first layers (one channel block in, one reduction step, one
 // channel tile): LDS it needs for the plan, 0 if it does not serve it; and its launch (plain
 // store only: no fused operators).

@@ -30,41 +30,6 @@
 
 namespace convmi {
 
-template <int DT>
-__device__ __forceinline__ float widened(const void *base, size_t i)
-{
-    if constexpr (DT == CONV_BF16)
-        return __builtin_bit_cast(float, (unsigned)static_cast<const unsigned short *>(base)[i] << 16);
-    else
-        return static_cast<const float *>(base)[i];
-}
-
-// Four consecutive channels of one pixel, krow .. krow + 3 at (n, oj, oi), summed over steps [u0, u1) one
-// product at a time, taps outside the image left out (EXACT kernels, where the MFMAs' sum is NaN).
-template <int DT>
-__device__ __forceinline__ f32x4 sum_inside_image(const IgemmArgs &a, int n, int oj, int oi, int krow, int u0, int u1)
-{
-    constexpr int V = Elem<DT>::V;
-    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-    if (a.no_taps) return sum;
-    const int RS = a.R * a.S;
-    for (int u = u0; u < u1; ++u) {
-        const int cp = u / RS, tap = u - cp * RS, r = tap / a.S, s = tap - r * a.S;
-        const int y = oj * a.stride - a.pad_h + r, x = oi * a.cstride - a.pad_w + s;
-        if (y < 0 || y >= a.H || x < 0 || x >= a.W) continue;
-        for (int cb = 2 * cp; cb < min(2 * cp + 2, a.Cb); ++cb) {
-            const size_t in = ((size_t)n * a.Cb + cb) * a.H * a.W + (size_t)y * a.W + x;
-            const size_t wt = ((size_t)cb * RS + tap) * a.Kp + krow;
-            for (int c = 0; c < V; ++c) {
-                const float v = widened<DT>(a.in, in * V + c);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) sum[t] = fmaf(v, widened<DT>(a.wt, (wt + t) * V + c), sum[t]);
-            }
-        }
-    }
-    return sum;
-}
-
 // FK x FM accumulator tiles per wave, NW waves that split the reduction, D steps in flight.
 // EXACT: for layers that would else run on the untiled loops, which leave the taps outside the image
 // out.  Here such a tap multiplies a weight by zero, which an infinite or NaN weight turns into NaN; a
@@ -290,8 +255,8 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
                 for (int j = 0; j < FM; ++j) acc[i][j] = sum[i][j];
         }
     }
-    add_and_store<DT, FK, FM, NW, EXACT>(a, acc, lds, k0, m0, sp, [&](int n, int oj, int oi, int krow) {
-        return sum_inside_image<DT>(a, n, oj, oi, krow, sbeg, sbeg + nst);
+    add_and_store<DT, FK, FM, NW, EXACT ? SUMS_NAN_AGAIN : SUMS_AS_THEY_ARE>(a, acc, lds, k0, m0, sp, [&](int n, int oj, int oi, int krow) {
+        return sum_one_by_one<DT, 2>(a, n, oj, oi, krow, sbeg, sbeg + nst, true);
     });
 }
 

@@ -1,0 +1,125 @@
+// fp32 operands as sums of three bf16 numbers, for products of fp32 tensors on the bf16 matrix instructions.
+//
+// x = h + m + l: h is x rounded to 8 significant bits, x - h has at most 16 of them, m takes the upper 8 and l what is
+// left, so the sum is exact.  Of the nine products of two such numbers six are formed, h*h, h*m, m*h, m*m, h*l, l*h; the other
+// three are below 2^-25 of the product, and of random sign.  Six bf16 MFMAs of 16 reduction indices take 192 clocks where
+// fp32 ones take 512.  The sums are no less exact for it: an fp32 MFMA rounds the sum once per product, a bf16 one once
+// per 16 (at most), and the five small products go into a sum of their own.  Measured against 64 bits, one chain of n
+// products, uniform * normal values, error of the fp32 MFMAs / of this: n = 16 7.4e-8 / 3.1e-8, 256 2.9e-7 / 8.6e-8, 4608
+// 1.2e-6 / 4.1e-7, 36864 3.5e-6 / 1.2e-6 (all six in one sum: 3.3e-8, 2.3e-7, 1.1e-6, 3.2e-6).
+//
+// What three bf16 numbers do not hold: infinities (x - h is NaN), values that round to infinity, and the last bits of values
+// below 2^-109.  All of the first two make a sum infinite or NaN; such sums, and
+// tiny ones, are formed again in fp32 (sum_needs_fp32).
+#pragma once
+#include "igemm_exchange.h"
+
+namespace convmi {
+
+struct Bf16x3 {
+    u32x4 h, m, l;  // eight numbers
+};
+
+// Eight numbers, in eight pieces of five or six instructions that stand between MFMAs: pieces 2*p and 2*p + 1 make pair p, the
+// first of it in the lower half of h, m, l.  `rest` carries x - h from one to the other.
+constexpr int kSplitPieces = 8;
+template <int I>
+static __device__ __forceinline__ void split_piece(const u32x4 (&raw)[2], Bf16x3 &s, float (&rest)[2])
+{
+    constexpr int p = I / 2;
+    if constexpr (I % 2 == 0) {
+        const float a = __uint_as_float(raw[p / 2][p % 2 * 2]), b = __uint_as_float(raw[p / 2][p % 2 * 2 + 1]);
+        unsigned h = pack_bf16x2(a, b);
+        asm volatile("" : "+v"(h));  // (else the halves are rounded again one by one)
+        rest[0] = a - __uint_as_float(h << 16);
+        rest[1] = b - __uint_as_float(h & 0xFFFF0000u);
+        asm volatile("" : "+v"(rest[0]), "+v"(rest[1]));  // (here, not where it is used)
+        s.h[p] = h;
+    } else {
+        const unsigned a = __float_as_uint(rest[0]), b = __float_as_uint(rest[1]);
+        const float la = rest[0] - __uint_as_float(a & 0xFFFF0000u), lb = rest[1] - __uint_as_float(b & 0xFFFF0000u);
+        unsigned m = __builtin_amdgcn_perm(b, a, 0x07060302), l = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302);
+        asm volatile("" : "+v"(m), "+v"(l));
+        s.m[p] = m;
+        s.l[p] = l;
+    }
+}
+static __device__ __forceinline__ Bf16x3 split8(const u32x4 (&raw)[2])
+{
+    Bf16x3 s;
+    float rest[2];
+    static_for<0, kSplitPieces>([&](auto i) { split_piece<decltype(i)::value>(raw, s, rest); });
+    return s;
+}
+static __device__ __forceinline__ void mma_bf16(const u32x4 &a, const u32x4 &b, f32x16 &c)
+{
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// big += h*h, small += the five others: product I of the six
+template <int I>
+static __device__ __forceinline__ void mma_split(const Bf16x3 &a, const Bf16x3 &b, f32x16 &big, f32x16 &small)
+{
+    if constexpr (I == 0) mma_bf16(a.l, b.h, small);
+    if constexpr (I == 1) mma_bf16(a.h, b.h, big);
+    if constexpr (I == 2) mma_bf16(a.h, b.l, small);
+    if constexpr (I == 3) mma_bf16(a.m, b.m, small);
+    if constexpr (I == 4) mma_bf16(a.m, b.h, small);
+    if constexpr (I == 5) mma_bf16(a.h, b.m, small);
+}
+
+// The weights of a backward pass as the forward pass has them, [channel block of dI][tap][channel of dO][4]: 32 channels of dI by
+// 16 of dO are 128 chunks of 4 channels of dI, lane's chunk i (of two) in channel block 4*i + wt_block(lane) and channel
+// wt_channel(lane) of dO.  Converted, they go to a wave's own 3 KiB of LDS, from where transposing reads bring each lane
+// eight channels of dO of its own channel of dI.
+constexpr int kWtBytes = 3072;
+static __device__ __forceinline__ int wt_block(int lane) { return (lane >> 2) & 3; }
+static __device__ __forceinline__ int wt_channel(int lane) { return (lane >> 4) * 4 + (lane & 3); }
+static __device__ __forceinline__ void put_weights(unsigned char *area, int lane, const Bf16x3 &s)
+{
+    unsigned char *const at = area + (wt_channel(lane) * 8 + wt_block(lane)) * 8;
+    *reinterpret_cast<u32x2 *>(at) = u32x2{s.h[0], s.h[1]};
+    *reinterpret_cast<u32x2 *>(at + 32) = u32x2{s.h[2], s.h[3]};
+    *reinterpret_cast<u32x2 *>(at + 1024) = u32x2{s.m[0], s.m[1]};
+    *reinterpret_cast<u32x2 *>(at + 1056) = u32x2{s.m[2], s.m[3]};
+    *reinterpret_cast<u32x2 *>(at + 2048) = u32x2{s.l[0], s.l[1]};
+    *reinterpret_cast<u32x2 *>(at + 2080) = u32x2{s.l[2], s.l[3]};
+}
+// Four of the eight channels of dO of piece P (h, m, l), the first or second half.
+template <int P, int HALF>
+static __device__ __forceinline__ u32x2 get_weights(const unsigned char *area, int lane)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
+    // lanes 4*j + q of a group of 16 address 4 channels of dI, block q of the group's four, of channel j of dO
+    const int q = lane & 3, rows = (lane >> 4) & 1, h = lane >> 5;
+    const unsigned char *const at = area + P * 1024 + ((8 * h + 4 * HALF + ((lane & 15) >> 2)) * 8 + 4 * rows + q) * 8;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)const_cast<unsigned char *>(at)));
+}
+
+static __device__ __forceinline__ Bf16x3 get_weights(const unsigned char *area, int lane)
+{
+    const u32x2 h0 = get_weights<0, 0>(area, lane), h1 = get_weights<0, 1>(area, lane), m0 = get_weights<1, 0>(area, lane),
+                m1 = get_weights<1, 1>(area, lane), l0 = get_weights<2, 0>(area, lane), l1 = get_weights<2, 1>(area, lane);
+    return Bf16x3{u32x4{h0[0], h0[1], h1[0], h1[1]}, u32x4{m0[0], m0[1], m1[0], m1[1]}, u32x4{l0[0], l0[1], l1[0], l1[1]}};
+}
+
+// Largest magnitude, NaN if one is.
+static __device__ __forceinline__ float max_magnitude(float t, const f32x16 &v)
+{
+#pragma unroll
+    for (int i = 0; i < 16; i += 2)
+        t = __builtin_elementwise_maximum(__builtin_elementwise_maximum(t, __builtin_fabsf(v[i])), __builtin_fabsf(v[i + 1]));
+    return t;
+}
+// Whether a wave whose lanes' largest results are t forms them again.
+static __device__ __forceinline__ bool sums_need_fp32(float t) { return __any(sum_needs_fp32(t)) != 0; }
+
+// Barrier of the workgroup behind which the waves' LDS operations are done; loads into registers stay in flight.
+static __device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+}  // namespace convmi

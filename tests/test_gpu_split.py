@@ -1,0 +1,167 @@
+"""fp32 passes on the bf16 matrix instructions (each value as three bf16 numbers): every tile and block size against the oracle at
+the edges of its tiles, what is fused into the store, and the values that three bf16 numbers do not hold.  Bars:
+gpu_util.assert_close; where the fp32 instructions give an infinity or a NaN, the same one."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1808_05567_amd import conv
+
+from gpu_util import assert_close, make_inputs, rel_l2, run_pass
+
+pytestmark = pytest.mark.gpu
+
+F32 = conv.CONV_F32
+# "channel waves, pixel waves, fragments, sets, groups of 16 channels, strips" and "r, fragments, waves"
+STAGED = ["4,1,4,1", "4,1,2,1", "2,2,4,1", "2,2,2,1", "4,1,4,2", "4,1,2,2", "2,2,4,2", "2,2,2,2"]
+IN_REGISTERS = ["r,1,1,4", "r,1,1,8", "r,1,1,16", "r,2,1,4", "r,2,1,8", "r,1,2,4", "r,2,2,4", "r,2,2,8"]
+SHAPES = [  # N, C, K, H, W, R, S, stride, pad: ragged channel blocks, images smaller than a tile, wide rows, strides, few taps
+    (3, 72, 40, 13, 15, 3, 3, 1, 1), (2, 20, 136, 9, 11, 1, 1, 1, 0), (3, 36, 52, 15, 13, 1, 1, 2, 0), (5, 32, 32, 7, 7, 3, 3, 1, 1),
+    (3, 64, 80, 17, 17, 1, 7, 1, (0, 3)), (2, 48, 64, 21, 19, 7, 1, 1, (3, 0)), (3, 64, 64, 15, 17, 3, 3, 2, 1), (2, 36, 24, 15, 17, 3, 3, 2, 0),
+    (1, 16, 32, 30, 149, 3, 3, 1, 1), (2, 32, 48, 12, 12, 5, 5, 1, 2), (2, 24, 40, 11, 12, 3, 3, 1, 0), (1, 100, 60, 3, 2, 1, 1, 1, 0),
+]
+IDS = dict(ids=lambda s: "x".join(map(str, s)).replace(" ", ""))
+
+
+def _variants(shape, which):
+    out = []
+    for v in STAGED:
+        for g, strips in ((1, 1), (2, 1), (1, 2)):
+            out += ["%s,%d,%d,%d" % (v, g, strips, fw) for fw in ((0, 1) if which == "bwd" else (0,))]
+    return out + ["%s,%d" % (v, fw) for v in IN_REGISTERS for fw in ((0, 1) if which == "bwd" else (0,))]
+
+
+def _layer(shape, **env):
+    with pytest.MonkeyPatch.context() as mp:
+        for k, v in env.items():
+            mp.setenv(k, v)
+        return conv.ConvLayer(*shape, dtype=F32)
+
+
+@pytest.mark.parametrize("which", ["fwd", "bwd"])
+@pytest.mark.parametrize("shape", SHAPES, **IDS)
+def test_forward_and_backward_match_oracle(shape, which):
+    N, C, K, H, W, R, S, stride, pad = shape
+    I, Wt, dO = make_inputs(shape, F32, layer_id=51)
+    ref = oracle.fwd(I, Wt, stride, pad) if which == "fwd" else oracle.bwd_data(dO, Wt, H, W, stride, pad)
+    kw = dict(I=I, Wt=Wt) if which == "fwd" else dict(dO=dO, Wt=Wt)
+    seen = set()
+    for v in _variants(shape, which):
+        L = _layer(shape, CONVMI_IGEMM_SPLIT=v)
+        try:
+            text = conv.conv_describe(L.h, conv.PASS_FWD if which == "fwd" else conv.PASS_BWD_DATA)
+            on = text.partition(" on_bf16x3=")[2]
+            if not on or on in seen:  # (the tile does not fit the LDS, or is the same without the last digits)
+                continue
+            seen.add(on)
+            assert_close(run_pass(L, which, **kw), ref, F32, "%s variant %s" % (which, v))
+        finally:
+            L.close()
+    strided_classes = which == "bwd" and R * S > 1 and stride > 1
+    assert len(seen) >= (3 if strided_classes else 14 if which == "fwd" else 24), sorted(seen)
+
+
+@pytest.mark.parametrize("variant", ["4,1,4,1,1", "2,2,2,2,1", "r,2,1,8"])
+def test_fused_operators(variant):
+    """Scale, bias, residual (the output buffer itself) and ReLU."""
+    shape = (2, 72, 40, 7, 5, 3, 3, 1, 1)
+    N, C, K, H, W, R, S, stride, pad = shape
+    I, Wt, res = make_inputs(shape, F32, layer_id=53)
+    rng = np.random.default_rng(5)
+    scale, bias = rng.uniform(0.5, 1.5, K).astype(np.float32), rng.normal(0, 0.2, K).astype(np.float32)
+    ref = np.maximum(oracle.fwd(I, Wt, stride, pad).astype(np.float64) * scale[:, None, None] + bias[:, None, None] + res, 0)
+    L = _layer(shape, CONVMI_IGEMM_SPLIT=variant)
+    try:
+        assert " on_bf16x3=" in conv.conv_describe(L.h, conv.PASS_FWD)
+        L.set_input(I)
+        L.set_weights(Wt)
+        L.set_outgrad(res)  # (the residual sits in the output buffer)
+        per_channel = [torch.nn.functional.pad(torch.from_numpy(a), (0, L.info.Kp - K)).to(L.device) for a in (scale, bias)]
+        L.fwd_fused(bias=per_channel[1], residual=L.out_blk, relu=True, scale=per_channel[0])
+        assert_close(L.get_output().cpu().numpy(), ref, F32, variant)
+    finally:
+        L.close()
+
+
+# which pass, fp32 variant's switch, variants
+SPECIAL = [("fwd", "CONVMI_IGEMM_SPLIT", ["4,1,4,1,1", "2,2,2,2,1", "r,1,1,8", "r,2,2,4"]),
+           ("bwd", "CONVMI_IGEMM_SPLIT", ["4,1,2,1,1,1,0", "4,1,2,1,1,1,1", "r,1,1,4,0", "r,2,1,8,1"])]
+
+
+@pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd"])
+def test_infinities_and_nan_as_on_the_fp32_instructions(which, switch, variants):
+    """... and values that round to infinity in bf16, of either sign."""
+    shape = (2, 40, 48, 12, 13, 3, 3, 1, 1)
+    I, Wt, dO = make_inputs(shape, F32, layer_id=54)
+    rng = np.random.default_rng(8)
+    for t in (I, Wt, dO):
+        flat = t.reshape(-1)
+        at = rng.choice(flat.size, 5, replace=False)
+        flat[at] = [np.inf, -np.inf, np.nan, 3.4e38, -3.4e38] if t is not Wt else [np.inf, np.nan, 3.4e38, 1e-3, 1e-3]
+    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt)}[which]
+    got = []
+    for v in ["0"] + variants:
+        L = _layer(shape, **{switch: v})
+        try:
+            on = " on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1}[which])
+            assert on == (v != "0"), v
+            got.append(run_pass(L, which, **kw).astype(np.float64))
+        finally:
+            L.close()
+    fine = np.isfinite(got[0])
+    assert 0.05 < fine.mean() < 1 and np.isinf(got[0]).any() and np.isnan(got[0]).any()
+    for g, v in zip(got[1:], variants):
+        assert np.array_equal(np.isfinite(g), fine), v
+        assert np.array_equal(g[~fine], got[0][~fine], equal_nan=True), v
+        small = fine & (np.abs(got[0]) < 1e30)
+        assert_close(np.where(small, g, 0), np.where(small, got[0], 0), F32, v)
+
+
+@pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd"])
+@pytest.mark.parametrize("exponents", [(-60, -50), (-108, 0), (-118, 10), (100, -20)], ids=str)
+def test_scale_does_not_matter(which, switch, variants, exponents):
+    """Results near and below the smallest bf16 numbers: powers of two times the operands give the same error (the fp32
+    instructions round a product of 2^-110 and less to fewer bits too, so not below that)."""
+    shape = (2, 40, 48, 12, 13, 3, 3, 1, 1)
+    I, Wt, dO = make_inputs(shape, F32, layer_id=55)
+    a, b = {"fwd": (I, Wt), "bwd": (dO, Wt)}[which]
+    refs = {"fwd": lambda: oracle.fwd(I, Wt, 1, 1), "bwd": lambda: oracle.bwd_data(dO, Wt, 12, 13, 1, 1)}
+    ref = refs[which]()
+    a *= np.float32(2.0 ** exponents[0])
+    b *= np.float32(2.0 ** exponents[1])
+    scale = 2.0 ** -(exponents[0] + exponents[1])
+    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt)}[which]
+    for v in variants:
+        L = _layer(shape, **{switch: v})
+        try:
+            assert rel_l2(run_pass(L, which, **kw).astype(np.float64) * scale, ref) < 1e-6, v
+        finally:
+            L.close()
+
+
+# Layer, pass: relative error (2-norm) against 64 bits of what the planner picks, no larger than on the fp32 instructions
+EXACT = [((28, 128, 128, 28, 28, 3, 3, 1, 1), "fwd"), ((16, 512, 512, 7, 7, 3, 3, 1, 1), "bwd"), ((8, 1024, 256, 14, 14, 1, 1, 1, 0), "fwd"),
+         ((32, 192, 192, 17, 17, 1, 7, 1, (0, 3)), "bwd"), ((16, 256, 256, 28, 28, 3, 3, 2, 1), "bwd")]
+
+
+@pytest.mark.parametrize("shape,which", EXACT, ids=lambda s: s if isinstance(s, str) else "x".join(map(str, s)).replace(" ", ""))
+def test_no_less_exact_than_the_fp32_instructions(shape, which):
+    N, C, K, H, W, R, S, stride, pad = shape
+    pads = pad if isinstance(pad, tuple) else (pad, pad)
+    I, Wt, dO = make_inputs(shape, F32, layer_id=56)
+    x, w, g = (torch.from_numpy(t).double() for t in (I, Wt, dO))
+    if which == "fwd":
+        ref = torch.nn.functional.conv2d(x, w, stride=stride, padding=pads)
+    else:
+        ref = torch.nn.grad.conv2d_input(x.shape, w, g, stride=stride, padding=pads)
+    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt)}[which]
+    err = []
+    for env in (dict(CONVMI_IGEMM_SPLIT="0"), {}):
+        L = _layer(shape, **env)
+        try:
+            assert (" on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1}[which])) == (not env)
+            err.append(rel_l2(run_pass(L, which, **kw), ref.numpy()))
+        finally:
+            L.close()
+    assert err[1] <= 1.1 * err[0], err  # (the spread between inputs)
