@@ -54,6 +54,14 @@ struct IgemmPlan {
     SplitPlan split;
 };
 
+// The same for a weight update (upd_split.hip).
+struct UpdSplitPlan {
+    bool ok = false;
+    UpdSplitVariant v{};
+    UpdArgs a{};
+    int grid = 0;
+};
+
 // The residue classes of a strided backward pass in one launch on the bf16 instructions.
 struct SplitClassesPlan {
     bool ok = false;
@@ -110,6 +118,8 @@ struct conv_plan {
     int upd_strips = 1;        // general kernels: strips of output columns, one launch each
     int upd_strip_w = 0;       // ... their width (the last may be narrower)
     UpdArgs ua{};
+    double upd_ring_us = 0;  // what the ring kernel's plan takes by estimate
+    UpdSplitPlan upd_split;  // runs in the place of all that
     size_t upd_lds = 0;
     int upd_grid = 0;
     size_t upd_ws = 0;
@@ -2377,6 +2387,7 @@ bool plan_upd_ring(conv_plan *p)
     if (have && !env && d.dtype == CONV_BF16 && d.R * d.S == 1 && !ring_reads_apply(p, best_a)) return false;
     if (!have || (double)best_a.splits * f.dwt_bytes > std::max(2.0 * ((double)f.in_bytes + (double)f.out_bytes), 8.0e9))
         return false;
+    p->upd_ring_us = best_us;
     p->ua = best_a;
     p->urv = UpdRowsVariant{d.R, d.S, 1, best.depth, best.nw, best.fc, best.fk, best.sum};
     p->upd_lds = ring_lds_bytes(p, best);
@@ -2389,6 +2400,126 @@ bool plan_upd_ring(conv_plan *p)
     p->upd_window = best.window;
     p->upd_ok = true;
     return true;
+}
+
+// A plan of the update on the bf16 instructions, `splits` ranges of pixels.
+UpdSplitPlan try_upd_split(const conv_plan *p, const UpdSplitVariant &v, int splits)
+{
+    UpdSplitPlan s;
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    if (!upd_split_exists(v) || splits < 1 || (v.t == 1 ? v.pi != v.sp : false)) return s;
+    const double npix = (double)d.N * f.P * f.Q;
+    // exact small divisions, 24-bit products, 32-bit byte offsets
+    if (npix >= 3.9e6 || (double)(d.N + 1) * f.P >= 3.9e6 || (double)d.H * d.W >= 8.0e6 || (double)f.in_bytes >= 4.0e9 ||
+        (double)f.out_bytes >= 4.0e9 || (double)f.dwt_bytes >= 4.0e9)
+        return s;
+    if (v.t > 1) {  // the positions under a stage
+        const long long crossings = (v.sp - 2) / f.Q + 1, gap = std::max(0, v.t - d.stride);
+        if ((v.sp - 1LL) * d.stride + v.t + crossings * gap > v.pi) return s;
+    }
+    UpdArgs &a = s.a;
+    memset(&a, 0, sizeof(a));
+    const int np = (int)npix;
+    a.N = d.N; a.Cb = f.Cb; a.H = d.H; a.W = d.W; a.Kb = f.Kb; a.Kp = f.Kp; a.P = f.P; a.Q = f.Q;
+    a.R = d.R; a.S = d.S; a.stride = d.stride; a.pad = p->pad_h; a.pad_w = p->pad_w;
+    a.n_ct = ceil_div(f.Cp, v.wc * v.fc * 32);
+    a.n_kt = ceil_div(f.Kp, v.wk * v.fk * 32);
+    // (a wave's chain of additions, one for 16 pixels: at most 2^16 pixels)
+    splits = std::max(splits, ceil_div(np, 1 << 16));
+    a.rows_per_split = ceil_div(ceil_div(np, splits), v.sp) * v.sp;
+    a.splits = ceil_div(np, a.rows_per_split);
+    const double total = (double)a.n_ct * a.n_kt * d.R * ceil_div(d.S, v.t) * a.splits;
+    if (total >= 1.0e8 || (double)a.splits * f.dwt_bytes > std::max(2.0 * ((double)f.in_bytes + (double)f.out_bytes), 8.0e9)) return s;
+    a.total = (int)total;
+    a.per_xcd = ceil_div(a.total, 8);
+    s.v = v;
+    s.grid = a.per_xcd * 8;
+    s.ok = true;
+    return s;
+}
+
+// Error of its sums in the units of planned_upd_error: an MFMA rounds the sum of the large products once for sixteen pixels.
+double upd_split_error(const conv_plan *p, const UpdArgs &a)
+{
+    const int chains = upd_reduce_chains(p->info.dwt_bytes / sizeof(float), a.splits);
+    return std::min((double)a.rows_per_split, (double)p->d.N * a.P * a.Q) / 32 + 0.5 +
+           (a.splits > 1 ? ceil_div(a.splits, chains) / 2.0 + std::log2((double)chains) / 2 : 0);
+}
+
+// What such an update takes, in microseconds, the reduce launch included: the form of ring_estimate_us.  Fitted to 14 700 launches
+// (250 drawn layers, every variant, 192 ... 1024 workgroups; three sets of tensors in turn): rms error 10 %, the choice 2 % behind the
+// fastest.
+double upd_split_us(const conv_plan *p, const UpdSplitPlan &s)
+{
+    const UpdSplitVariant &v = s.v;
+    const UpdArgs &a = s.a;
+    const conv_info_t &f = p->info;
+    const int waves = v.wc * v.wk, frags = v.t * v.fc * v.fk, q = v.sp / 16;
+    const double simd = waves / 4.0, mfma = q * frags * 192.0, reads = q * (v.t * v.fc + v.fk) * 6.0;
+    const double items = ceil_div(v.wc * v.fc * 4 * v.pi, waves * 64) + ceil_div(v.wk * v.fk * 4 * v.sp, waves * 64);
+    const double stages = ceil_div(a.rows_per_split, v.sp);
+    const double shared = (0.25 * mfma + 116 * items + 8.35 * reads + 47) * simd;
+    const double busy = stages * shared + 399.0 * frags * simd;
+    const double lone = std::max(busy, 4056 + 262.0 * frags + stages * std::max(0.94 * mfma + 23.8 * reads + 806, shared));
+    // (waves per SIMD that the registers leave room for)
+    const int occ = v.t > 1 || frags == 4 ? 2 : frags == 1 && v.sp == 32 ? 4 : 3;
+    const int resident = std::max(1, std::min((int)(kMaxLds / upd_split_lds_bytes(v)), occ * 4 / waves));
+    const int per_cu = ceil_div(s.grid, 256), full = per_cu / resident, rest = per_cu - full * resident;
+    const double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
+    const double out_b = (double)f.out_bytes, in_b = p->d.R * p->d.S > 1 ? (double)f.in_bytes : (double)p->d.N * f.Cp * f.P * f.Q * 4;
+    const double again = p->d.R * ceil_div(p->d.S, v.t), launch = 2.8;
+    const double bound[3] = {t / 2.1e3 + launch, launch + (in_b * a.n_kt + out_b * a.n_ct) * again / 14.6e6, launch + (in_b + out_b) / 4.0e6};
+    const double most = *std::max_element(bound, bound + 3);
+    double us = most * std::pow(std::pow(bound[0] / most, 6) + std::pow(bound[1] / most, 6) + std::pow(bound[2] / most, 6), 1.0 / 6);
+    if (a.splits > 1) us += 2.9 + a.splits * (double)f.dwt_bytes * 2 / 4.84e6;
+    return us;
+}
+static const UpdSplitVariant kUpdSplit[] = {
+    {1, 2, 2, 2, 2, 16, 16}, {1, 2, 2, 4, 2, 16, 16}, {1, 2, 1, 2, 4, 32, 32}, {1, 2, 1, 2, 2, 32, 32}, {1, 1, 2, 2, 2, 32, 32},
+    {1, 1, 1, 2, 2, 32, 32}, {1, 1, 1, 2, 2, 64, 64}, {1, 2, 1, 4, 2, 16, 16}, {1, 1, 1, 4, 2, 32, 32},
+    {3, 1, 1, 2, 2, 32, 64}, {3, 1, 1, 2, 4, 32, 64}, {3, 1, 1, 2, 2, 16, 32}, {3, 1, 1, 2, 2, 16, 64}, {3, 1, 1, 2, 4, 16, 64},
+    {3, 1, 1, 2, 4, 16, 32}, {3, 1, 1, 1, 4, 32, 64}, {3, 1, 1, 4, 2, 16, 32},
+    {4, 1, 1, 2, 2, 32, 64}, {4, 1, 1, 2, 4, 32, 64}, {4, 1, 1, 2, 2, 16, 32}, {5, 1, 1, 2, 2, 16, 32}};
+
+// Whether the update runs on the bf16 instructions: where the estimate says that this is at least 4 % faster than `fp32_us`, and the
+// sums are no less exact.
+// (CONVMI_UPD_SPLIT="t,fc,fk,wc,wk,sp,pi,splits": one variant wherever it fits; 0: never -- a tuning aid, as are those that ask for
+// a variant on the fp32 instructions)
+void plan_upd_split(conv_plan *p, double fp32_us)
+{
+    p->upd_split = UpdSplitPlan{};
+    if (p->d.dtype != CONV_F32) return;
+    if (const char *env = getenv("CONVMI_UPD_SPLIT")) {
+        UpdSplitVariant v{};
+        int splits = 1;
+        if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d,%d", &v.t, &v.fc, &v.fk, &v.wc, &v.wk, &v.sp, &v.pi, &splits) < 7) return;
+        p->upd_split = try_upd_split(p, v, splits);
+    } else if (!getenv("CONVMI_UPD_RING") && !getenv("CONVMI_UPD_WINDOW")) {
+        const double most_error = planned_upd_error(p) + kOwnRounding;
+        // (and by 1.5 us: below 20 us the estimates are as far apart as that)
+        double best_us = kSplitMargin * fp32_us - 1.5;
+        for (const UpdSplitVariant &v : kUpdSplit) {
+            const int blocks = ceil_div(p->info.Cp, v.wc * v.fc * 32) * ceil_div(p->info.Kp, v.wk * v.fk * 32) * p->d.R * ceil_div(p->d.S, v.t);
+            int last = 0;
+            for (const int target : {192, 256, 384, 512, 768, 1024}) {
+                const int splits = std::max(1, target / blocks);
+                if (splits == last) continue;
+                last = splits;
+                const UpdSplitPlan c = try_upd_split(p, v, splits);
+                if (!c.ok || upd_split_error(p, c.a) > most_error) continue;
+                const double us = upd_split_us(p, c);
+                if (us < best_us) {
+                    p->upd_split = c;
+                    best_us = us;
+                }
+            }
+        }
+    }
+    if (p->upd_split.ok) {
+        p->upd_copies = p->upd_split.a.splits;
+        p->upd_ws = (size_t)p->upd_copies * p->info.dwt_bytes;  // (one split writes dW itself; the caller brings it all the same)
+    }
 }
 
 void plan_upd(conv_plan *p)
@@ -2420,7 +2551,13 @@ void plan_upd(conv_plan *p)
     // ... and over all but a first layer's, the ring kernel where it is the better one.  (Not where the
     // update is left to the untiled loop: that leaves the taps outside the image out, where the tiled
     // kernels multiply dO by zero, and an infinite dO would make the difference a NaN.)
-    if (!few && p->upd_ok) plan_upd_ring(p);
+    const bool ring = !few && p->upd_ok && plan_upd_ring(p);
+    // ... and on the bf16 instructions, with the same exception
+    // (the kernels of eight waves with 256 channels, beyond the ring kernel's line: 110 - 135 TFLOP/s)
+    if (!few && p->upd_ok) {
+        const double flops = 2.0 * p->d.N * p->d.K * p->d.C * p->d.R * p->d.S * (double)p->info.P * p->info.Q;
+        plan_upd_split(p, ring ? p->upd_ring_us : flops / 1.35e8);
+    }
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -2881,7 +3018,14 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
     a.dout = dout;
     a.partial = static_cast<float *>(ws);
     hipError_t e = hipSuccess;
-    if (h->upd_ring) {
+    if (h->upd_split.ok) {
+        UpdArgs b = h->upd_split.a;
+        b.in = in;
+        b.dout = dout;
+        b.partial = b.splits == 1 ? static_cast<float *>(dwt) : static_cast<float *>(ws);
+        e = launch_upd_split(h->upd_split.v, b, h->upd_split.grid, s);
+        if (b.splits == 1) return e == hipSuccess ? CONV_OK : CONV_ELAUNCH;
+    } else if (h->upd_ring) {
         if (a.splits == 1) a.partial = static_cast<float *>(dwt);
         e = h->upd_window ? launch_upd_window(a, h->upd_grid, s)
                           : launch_upd_ring(h->d.dtype, h->urv.fc, h->urv.fk, h->urv.wp, h->urv.wk, h->urv.strided, a,
@@ -3105,6 +3249,69 @@ static void describe_classes(const SplitClassesPlan &s, char *buf, size_t buflen
     snprintf(buf + n, buflen - n, " on_bf16x3=igemm_split_classes,%dx%d,fm%d,sets%d,groups%d,shares%d,strips%d,workgroups%d,lds%zu", s.v.wk, s.v.wm,
              s.v.fm, s.v.kw, s.v.g, s.v.ni, s.c.cls[0].n_qt, s.c.end[3], s.lds);
 }
+static conv_status_t describe_fp32_update(conv_handle_t h, char *buf, size_t buflen)
+{
+    if (h->upd_ring) {
+        snprintf(buf, buflen,
+                 "upd_ring dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d sum=%d group=%d pixels/split=%d splits=%d tiles=%dx%dx%d "
+                 "grid=%d lds=%zu launches=1 window=%d",
+                 (int)h->d.dtype, h->d.R, h->d.S, h->urv.wp,
+                 h->urv.wk, h->urv.fc, h->urv.fk, h->urv.strided, h->ua.group, h->ua.rows_per_split, h->ua.splits,
+                 h->ua.n_ct, h->ua.n_kt, h->d.R, h->upd_grid, h->upd_lds, h->upd_window ? h->ua.Qpitch : 0);
+        return CONV_OK;
+    }
+    if (h->upd_flat_bf16) {
+        snprintf(buf, buflen,
+                 "upd_1x1 dt=1 waves=%dx%dx%d frags=%dx%d pixels/split=%d splits=%d tiles=%dx%d "
+                 "grid=%d lds=%zu",
+                 h->urv.wc, h->urv.wk, h->urv.wp, h->urv.fc, h->urv.fk, h->ua.rows_per_split,
+                 h->ua.splits, h->ua.n_ct, h->ua.n_kt, h->upd_grid, h->upd_lds);
+        return CONV_OK;
+    }
+    if (h->upd_flat) {
+        snprintf(buf, buflen,
+                 "upd_1x1 dt=0 waves=2x%dx%d tile=256x%d (%s) pixels/split=%d splits=%d tiles=%dx%d "
+                 "grid=%d lds=%zu",
+                 h->upd_wb, 4 / h->upd_wb, 64 * h->upd_wb, h->upd_a_is_in ? "in x out" : "out x in",
+                 h->ua.rows_per_split, h->ua.splits, h->ua.n_ct, h->ua.n_kt, h->upd_grid,
+                 h->upd_lds);
+        return CONV_OK;
+    }
+    if (h->upd_c4 || h->upd_c4_bf16) {
+        snprintf(buf, buflen,
+                 "upd_c4 dt=%d mfma=%s RS=%dx%d waves=%s TR=%d splits=%d rows/split=%d ktiles=%d grid=%d lds=%zu",
+                 (int)h->d.dtype, h->upd_c4_bf16 ? "bf16" : "f32", h->d.R, h->d.S,
+                 h->info.Kp <= 32 ? "1x8" : "2x4", h->ua.TR, h->ua.splits, h->ua.rows_per_split, h->ua.n_kt,
+                 h->upd_grid, h->upd_lds);
+        return CONV_OK;
+    }
+    if (h->upd_rows) {
+        snprintf(buf, buflen,
+                 "upd_rows dt=1 RS=%dx%d waves=%dx%dx%d frags=%dx%d TR=%d runs=%d splits=%d "
+                 "rows/split=%d tiles=%dx%d grid=%d lds=%zu launches=%d",
+                 h->d.R, h->d.S, h->urv.wc, h->urv.wk, h->urv.wp, h->urv.fc, h->urv.fk, h->ua.TR,
+                 h->ua.runs, h->ua.splits, h->ua.rows_per_split, h->ua.n_ct, h->ua.n_kt,
+                 h->upd_grid, h->upd_lds, h->upd_strips * h->upd_row_launches);
+        return CONV_OK;
+    }
+    if (h->upd_bands) {
+        snprintf(buf, buflen,
+                 "upd_bands dt=0 RS=%dx%d waves=%s frags=1x1 TR=%d splits=%d rows/split=%d "
+                 "tiles=%dx%d grid=%d lds=%zu launches=%d",
+                 h->d.R, h->d.S,
+                 h->upd_bands_layout == 0 ? "2x2x2" : h->upd_bands_layout == 1 ? "1x2x4" : "1x1x8",
+                 h->ua.TR, h->ua.splits, h->ua.rows_per_split, h->ua.n_ct,
+                 h->ua.n_kt, h->upd_grid, h->upd_lds, h->upd_strips);
+        return CONV_OK;
+    }
+    snprintf(buf, buflen,
+             "upd dt=%d RS=%dx%d waves=%dx%d frags=%dx%d TR=%d splits=%d rows/split=%d "
+             "tiles=%dx%d grid=%d lds=%zu launches=%d",
+             h->uv.dtype, h->uv.r, h->uv.s, h->uv.wc, h->uv.wk, h->uv.fc, h->uv.fk, h->ua.TR,
+             h->ua.splits, h->ua.rows_per_split, h->ua.n_ct, h->ua.n_kt, h->upd_grid,
+             h->upd_lds, h->upd_row_launches * h->upd_strips);
+    return CONV_OK;
+}
 conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buflen)
 {
     if (!h || !buf || buflen == 0) return CONV_EINVAL;
@@ -3164,68 +3371,18 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         if (pass == 1) describe_classes(h->bwd_classes, buf, buflen);
         return CONV_OK;
     }
+    if (pass == 2 && h->upd_split.ok) {
+        // (the plan on the fp32 instructions, then what runs in its place)
+        describe_fp32_update(h, buf, buflen);
+        const UpdSplitVariant &v = h->upd_split.v;
+        const size_t n = strlen(buf);
+        snprintf(buf + n, buflen - n, " on_bf16x3=upd_split,taps%d,%dx%d,waves_%dx%d,stage%d,positions%d,copies%d,workgroups%d", v.t, v.fc, v.fk,
+                 v.wc, v.wk, v.sp, v.pi, h->upd_split.a.splits, h->upd_split.a.total);
+        return CONV_OK;
+    }
     if (pass == 2) {
         if (!h->upd_ok) return CONV_EUNSUPPORTED;
-        if (h->upd_ring) {
-            snprintf(buf, buflen,
-                     "upd_ring dt=%d RS=%dx%d waves=1x1x%d ring=%d frags=%dx%d sum=%d group=%d pixels/split=%d splits=%d tiles=%dx%dx%d "
-                     "grid=%d lds=%zu launches=1 window=%d",
-                     (int)h->d.dtype, h->d.R, h->d.S, h->urv.wp,
-                     h->urv.wk, h->urv.fc, h->urv.fk, h->urv.strided, h->ua.group, h->ua.rows_per_split, h->ua.splits,
-                     h->ua.n_ct, h->ua.n_kt, h->d.R, h->upd_grid, h->upd_lds, h->upd_window ? h->ua.Qpitch : 0);
-            return CONV_OK;
-        }
-        if (h->upd_flat_bf16) {
-            snprintf(buf, buflen,
-                     "upd_1x1 dt=1 waves=%dx%dx%d frags=%dx%d pixels/split=%d splits=%d tiles=%dx%d "
-                     "grid=%d lds=%zu",
-                     h->urv.wc, h->urv.wk, h->urv.wp, h->urv.fc, h->urv.fk, h->ua.rows_per_split,
-                     h->ua.splits, h->ua.n_ct, h->ua.n_kt, h->upd_grid, h->upd_lds);
-            return CONV_OK;
-        }
-        if (h->upd_flat) {
-            snprintf(buf, buflen,
-                     "upd_1x1 dt=0 waves=2x%dx%d tile=256x%d (%s) pixels/split=%d splits=%d tiles=%dx%d "
-                     "grid=%d lds=%zu",
-                     h->upd_wb, 4 / h->upd_wb, 64 * h->upd_wb, h->upd_a_is_in ? "in x out" : "out x in",
-                     h->ua.rows_per_split, h->ua.splits, h->ua.n_ct, h->ua.n_kt, h->upd_grid,
-                     h->upd_lds);
-            return CONV_OK;
-        }
-        if (h->upd_c4 || h->upd_c4_bf16) {
-            snprintf(buf, buflen,
-                     "upd_c4 dt=%d mfma=%s RS=%dx%d waves=%s TR=%d splits=%d rows/split=%d ktiles=%d grid=%d lds=%zu",
-                     (int)h->d.dtype, h->upd_c4_bf16 ? "bf16" : "f32", h->d.R, h->d.S,
-                     h->info.Kp <= 32 ? "1x8" : "2x4", h->ua.TR, h->ua.splits, h->ua.rows_per_split, h->ua.n_kt,
-                     h->upd_grid, h->upd_lds);
-            return CONV_OK;
-        }
-        if (h->upd_rows) {
-            snprintf(buf, buflen,
-                     "upd_rows dt=1 RS=%dx%d waves=%dx%dx%d frags=%dx%d TR=%d runs=%d splits=%d "
-                     "rows/split=%d tiles=%dx%d grid=%d lds=%zu launches=%d",
-                     h->d.R, h->d.S, h->urv.wc, h->urv.wk, h->urv.wp, h->urv.fc, h->urv.fk, h->ua.TR,
-                     h->ua.runs, h->ua.splits, h->ua.rows_per_split, h->ua.n_ct, h->ua.n_kt,
-                     h->upd_grid, h->upd_lds, h->upd_strips * h->upd_row_launches);
-            return CONV_OK;
-        }
-        if (h->upd_bands) {
-            snprintf(buf, buflen,
-                     "upd_bands dt=0 RS=%dx%d waves=%s frags=1x1 TR=%d splits=%d rows/split=%d "
-                     "tiles=%dx%d grid=%d lds=%zu launches=%d",
-                     h->d.R, h->d.S,
-                     h->upd_bands_layout == 0 ? "2x2x2" : h->upd_bands_layout == 1 ? "1x2x4" : "1x1x8",
-                     h->ua.TR, h->ua.splits, h->ua.rows_per_split, h->ua.n_ct,
-                     h->ua.n_kt, h->upd_grid, h->upd_lds, h->upd_strips);
-            return CONV_OK;
-        }
-        snprintf(buf, buflen,
-                 "upd dt=%d RS=%dx%d waves=%dx%d frags=%dx%d TR=%d splits=%d rows/split=%d "
-                 "tiles=%dx%d grid=%d lds=%zu launches=%d",
-                 h->uv.dtype, h->uv.r, h->uv.s, h->uv.wc, h->uv.wk, h->uv.fc, h->uv.fk, h->ua.TR,
-                 h->ua.splits, h->ua.rows_per_split, h->ua.n_ct, h->ua.n_kt, h->upd_grid,
-                 h->upd_lds, h->upd_row_launches * h->upd_strips);
-        return CONV_OK;
+        return describe_fp32_update(h, buf, buflen);
     }
     return CONV_EINVAL;
 }

@@ -295,6 +295,14 @@ hipError_t launch_upd_ring(int dtype, int fc, int fk, int nw, int depth, int sum
 bool upd_window_exists(int s, int stride, int fc, int fk, int nw, int depth, int sum);
 size_t upd_window_lds_bytes();
 hipError_t launch_upd_window(const UpdArgs &a, int grid, hipStream_t stream);
+// fp32 tensors on the bf16 matrix instructions: wc*fc*32 x wk*fk*32 blocks under t taps of a filter row, stages of sp pixels and at
+// most pi positions of the input (UpdArgs::rows_per_split = pixels per split; one split: UpdArgs::partial is dW itself)
+struct UpdSplitVariant {
+    int t, fc, fk, wc, wk, sp, pi;
+};
+bool upd_split_exists(const UpdSplitVariant &v);
+size_t upd_split_lds_bytes(const UpdSplitVariant &v);
+hipError_t launch_upd_split(const UpdSplitVariant &v, const UpdArgs &a, int grid, hipStream_t stream);
 // at most 4 input channels: filter-row formulation, 7x7 and 3x3; fp32 tensors, or bf16
 // tensors widened on their way into LDS (then UpdArgs::Kb counts blocks of 8 channels)
 hipError_t launch_upd_c4(int dtype, int r, int s, const UpdArgs &a, size_t lds_bytes, int grid,

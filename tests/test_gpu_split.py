@@ -62,6 +62,32 @@ def test_forward_and_backward_match_oracle(shape, which):
     assert len(seen) >= (3 if strided_classes else 14 if which == "fwd" else 24), sorted(seen)
 
 
+UPD = ["1,2,2,2,2,16,16", "1,2,2,4,2,16,16", "1,2,1,2,4,32,32", "1,2,1,2,2,32,32", "1,1,2,2,2,32,32", "1,1,1,2,2,32,32", "1,1,1,2,2,64,64",
+       "1,2,1,4,2,16,16", "1,1,1,4,2,32,32", "3,1,1,2,2,32,64", "3,1,1,2,4,32,64", "3,1,1,2,2,16,32", "3,1,1,2,2,16,64", "3,1,1,2,4,16,64",
+       "3,1,1,2,4,16,32", "3,1,1,1,4,32,64", "3,1,1,4,2,16,32", "4,1,1,2,2,32,64", "4,1,1,2,4,32,64", "4,1,1,2,2,16,32", "5,1,1,2,2,16,32"]
+
+
+@pytest.mark.parametrize("shape", SHAPES, **IDS)
+def test_update_matches_oracle(shape):
+    N, C, K, H, W, R, S, stride, pad = shape
+    I, _, dO = make_inputs(shape, F32, layer_id=52)
+    ref = oracle.upd(I, dO, R, S, stride, pad)
+    ran = 0
+    for v in UPD:
+        for splits in (1, 3):
+            L = _layer(shape, CONVMI_UPD_SPLIT="%s,%d" % (v, splits))
+            try:
+                if " on_bf16x3=upd_split," not in conv.conv_describe(L.h, conv.PASS_UPD):
+                    assert not v.startswith("1,"), v  # (one tap fits everywhere)
+                    continue
+                ran += 1
+                assert_close(run_pass(L, "upd", I=I, dO=dO), ref, F32, "%s splits %d" % (v, splits))
+                assert np.isfinite(L.dwt_blk.cpu().numpy()).all()
+            finally:
+                L.close()
+    assert ran >= 18, ran
+
+
 @pytest.mark.parametrize("variant", ["4,1,4,1,1", "2,2,2,2,1", "r,2,1,8"])
 def test_fused_operators(variant):
     """Scale, bias, residual (the output buffer itself) and ReLU."""
@@ -86,10 +112,11 @@ def test_fused_operators(variant):
 
 # which pass, fp32 variant's switch, variants
 SPECIAL = [("fwd", "CONVMI_IGEMM_SPLIT", ["4,1,4,1,1", "2,2,2,2,1", "r,1,1,8", "r,2,2,4"]),
-           ("bwd", "CONVMI_IGEMM_SPLIT", ["4,1,2,1,1,1,0", "4,1,2,1,1,1,1", "r,1,1,4,0", "r,2,1,8,1"])]
+           ("bwd", "CONVMI_IGEMM_SPLIT", ["4,1,2,1,1,1,0", "4,1,2,1,1,1,1", "r,1,1,4,0", "r,2,1,8,1"]),
+           ("upd", "CONVMI_UPD_SPLIT", ["1,2,2,2,2,16,16", "3,1,1,2,2,32,64"])]
 
 
-@pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd"])
+@pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd", "upd"])
 def test_infinities_and_nan_as_on_the_fp32_instructions(which, switch, variants):
     """... and values that round to infinity in bf16, of either sign."""
     shape = (2, 40, 48, 12, 13, 3, 3, 1, 1)
@@ -99,12 +126,12 @@ def test_infinities_and_nan_as_on_the_fp32_instructions(which, switch, variants)
         flat = t.reshape(-1)
         at = rng.choice(flat.size, 5, replace=False)
         flat[at] = [np.inf, -np.inf, np.nan, 3.4e38, -3.4e38] if t is not Wt else [np.inf, np.nan, 3.4e38, 1e-3, 1e-3]
-    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt)}[which]
+    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt), "upd": dict(I=I, dO=dO)}[which]
     got = []
     for v in ["0"] + variants:
         L = _layer(shape, **{switch: v})
         try:
-            on = " on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1}[which])
+            on = " on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1, "upd": 2}[which])
             assert on == (v != "0"), v
             got.append(run_pass(L, which, **kw).astype(np.float64))
         finally:
@@ -118,20 +145,20 @@ def test_infinities_and_nan_as_on_the_fp32_instructions(which, switch, variants)
         assert_close(np.where(small, g, 0), np.where(small, got[0], 0), F32, v)
 
 
-@pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd"])
+@pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd", "upd"])
 @pytest.mark.parametrize("exponents", [(-60, -50), (-108, 0), (-118, 10), (100, -20)], ids=str)
 def test_scale_does_not_matter(which, switch, variants, exponents):
     """Results near and below the smallest bf16 numbers: powers of two times the operands give the same error (the fp32
     instructions round a product of 2^-110 and less to fewer bits too, so not below that)."""
     shape = (2, 40, 48, 12, 13, 3, 3, 1, 1)
     I, Wt, dO = make_inputs(shape, F32, layer_id=55)
-    a, b = {"fwd": (I, Wt), "bwd": (dO, Wt)}[which]
-    refs = {"fwd": lambda: oracle.fwd(I, Wt, 1, 1), "bwd": lambda: oracle.bwd_data(dO, Wt, 12, 13, 1, 1)}
+    a, b = {"fwd": (I, Wt), "bwd": (dO, Wt), "upd": (I, dO)}[which]
+    refs = {"fwd": lambda: oracle.fwd(I, Wt, 1, 1), "bwd": lambda: oracle.bwd_data(dO, Wt, 12, 13, 1, 1), "upd": lambda: oracle.upd(I, dO, 3, 3, 1, 1)}
     ref = refs[which]()
     a *= np.float32(2.0 ** exponents[0])
     b *= np.float32(2.0 ** exponents[1])
     scale = 2.0 ** -(exponents[0] + exponents[1])
-    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt)}[which]
+    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt), "upd": dict(I=I, dO=dO)}[which]
     for v in variants:
         L = _layer(shape, **{switch: v})
         try:
@@ -142,6 +169,7 @@ def test_scale_does_not_matter(which, switch, variants, exponents):
 
 # Layer, pass: relative error (2-norm) against 64 bits of what the planner picks, no larger than on the fp32 instructions
 EXACT = [((28, 128, 128, 28, 28, 3, 3, 1, 1), "fwd"), ((16, 512, 512, 7, 7, 3, 3, 1, 1), "bwd"), ((8, 1024, 256, 14, 14, 1, 1, 1, 0), "fwd"),
+         ((28, 128, 128, 28, 28, 3, 3, 1, 1), "upd"), ((16, 256, 512, 28, 28, 1, 1, 2, 0), "upd"), ((32, 64, 64, 56, 56, 3, 3, 1, 1), "upd"),
          ((32, 192, 192, 17, 17, 1, 7, 1, (0, 3)), "bwd"), ((16, 256, 256, 28, 28, 3, 3, 2, 1), "bwd")]
 
 
@@ -153,14 +181,16 @@ def test_no_less_exact_than_the_fp32_instructions(shape, which):
     x, w, g = (torch.from_numpy(t).double() for t in (I, Wt, dO))
     if which == "fwd":
         ref = torch.nn.functional.conv2d(x, w, stride=stride, padding=pads)
-    else:
+    elif which == "bwd":
         ref = torch.nn.grad.conv2d_input(x.shape, w, g, stride=stride, padding=pads)
-    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt)}[which]
+    else:
+        ref = torch.nn.grad.conv2d_weight(x, w.shape, g, stride=stride, padding=pads)
+    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt), "upd": dict(I=I, dO=dO)}[which]
     err = []
-    for env in (dict(CONVMI_IGEMM_SPLIT="0"), {}):
+    for env in (dict(CONVMI_IGEMM_SPLIT="0", CONVMI_UPD_SPLIT="0"), {}):
         L = _layer(shape, **env)
         try:
-            assert (" on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1}[which])) == (not env)
+            assert (" on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1, "upd": 2}[which])) == (not env)
             err.append(rel_l2(run_pass(L, which, **kw), ref.numpy()))
         finally:
             L.close()
