@@ -62,6 +62,14 @@ struct UpdSplitPlan {
     int grid = 0;
 };
 
+// ... and of bf16 tensors (upd_shared.hip).
+struct UpdSharedPlan {
+    bool ok = false;
+    UpdSharedVariant v{};
+    UpdArgs a{};
+    int grid = 0;
+};
+
 // The residue classes of a strided backward pass in one launch on the bf16 instructions.
 struct SplitClassesPlan {
     bool ok = false;
@@ -119,7 +127,8 @@ struct conv_plan {
     int upd_strip_w = 0;       // ... their width (the last may be narrower)
     UpdArgs ua{};
     double upd_ring_us = 0;  // what the ring kernel's plan takes by estimate
-    UpdSplitPlan upd_split;  // runs in the place of all that
+    UpdSplitPlan upd_split;    // runs in the place of all that (fp32)
+    UpdSharedPlan upd_shared;  // ... (bf16)
     size_t upd_lds = 0;
     int upd_grid = 0;
     size_t upd_ws = 0;
@@ -2522,6 +2531,145 @@ void plan_upd_split(conv_plan *p, double fp32_us)
     }
 }
 
+// A plan of the update with both operands staged for all waves, `splits` ranges of pixels.
+UpdSharedPlan try_upd_shared(const conv_plan *p, const UpdSharedVariant &v, int splits)
+{
+    UpdSharedPlan s;
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    if (!upd_shared_exists(v) || splits < 1 || upd_shared_lds_bytes(v) > (size_t)kMaxLds) return s;
+    if (v.t > 1 && v.st != d.stride) return s;
+    const double npix = (double)d.N * f.P * f.Q;
+    // exact small divisions, 24-bit products, 32-bit byte offsets
+    if (npix >= 3.9e6 || (double)(d.N + 1) * f.P >= 3.9e6 || (double)d.H * d.W >= 8.0e6 || (double)f.in_bytes >= 4.0e9 ||
+        (double)f.out_bytes >= 4.0e9 || (double)f.dwt_bytes >= 4.0e9)
+        return s;
+    if (v.t > 1) {  // the positions under a stage (stride 2: of each parity)
+        const long long crossings = (v.sp - 2) / f.Q + 1;
+        const long long most = v.st == 1 ? v.sp - 1LL + v.t + crossings * (v.t - 1) : v.sp - 1LL + (v.t + 1) / 2 + crossings * ((v.t + 1) / 2 - 1);
+        if (most > (v.st == 1 ? v.pi : v.pi / 2)) return s;
+    }
+    UpdArgs &a = s.a;
+    memset(&a, 0, sizeof(a));
+    const int np = (int)npix;
+    a.N = d.N; a.Cb = f.Cb; a.H = d.H; a.W = d.W; a.Kb = f.Kb; a.Kp = f.Kp; a.P = f.P; a.Q = f.Q;
+    a.R = d.R; a.S = d.S; a.stride = d.stride; a.pad = p->pad_h; a.pad_w = p->pad_w;
+    a.n_ct = ceil_div(f.Cp, v.wc * v.fc * 32);
+    a.n_kt = ceil_div(f.Kp, v.wk * v.fk * 32);
+    // (a wave's chain of additions, one for 16 pixels: at most 2^14 pixels)
+    splits = std::max(splits, ceil_div(np, v.wp << 14));
+    a.rows_per_split = ceil_div(ceil_div(np, splits), v.sp) * v.sp;
+    a.splits = ceil_div(np, a.rows_per_split);
+    const double total = (double)a.n_ct * a.n_kt * d.R * ceil_div(d.S, v.t) * a.splits;
+    if (total >= 1.0e8 || (double)a.splits * f.dwt_bytes > std::max(2.0 * ((double)f.in_bytes + (double)f.out_bytes), 8.0e9)) return s;
+    a.total = (int)total;
+    a.per_xcd = ceil_div(a.total, 8);
+    s.v = v;
+    s.grid = a.per_xcd * 8;
+    s.ok = true;
+    return s;
+}
+
+// Error of its sums in the units of planned_upd_error: an addition for sixteen pixels.
+double upd_shared_error(const conv_plan *p, const UpdSharedPlan &s)
+{
+    const UpdArgs &a = s.a;
+    const int chains = upd_reduce_chains(p->info.dwt_bytes / sizeof(float), a.splits);
+    return std::min((double)a.rows_per_split, (double)p->d.N * a.P * a.Q) / s.v.wp / 32 + std::log2((double)s.v.wp) / 2 +
+           (a.splits > 1 ? ceil_div(a.splits, chains) / 2.0 + std::log2((double)chains) / 2 : 0);
+}
+
+// What such an update takes, in microseconds, the reduce launch included: the form of ring_estimate_us.  Fitted to 12 000 launches
+// (220 drawn layers, every variant, 128 ... 768 workgroups; three sets of tensors in turn): rms error 9 %, the choice 1.3 % behind
+// the fastest.
+double upd_shared_us(const conv_plan *p, const UpdSharedPlan &s)
+{
+    const UpdSharedVariant &v = s.v;
+    const UpdArgs &a = s.a;
+    const conv_info_t &f = p->info;
+    const int waves = v.wc * v.wk * v.wp, frags = v.t * v.fc * v.fk, q = v.sp / 16 / v.wp, po = ceil_div(v.sp, 64) * 64;
+    const double simd = waves / 4.0, mfma = q * frags * 32.0, loads = (v.wc * v.fc * 4 * v.pi + v.wk * v.fk * 4 * po) / 64.0;
+    const double stages = (double)a.rows_per_split / v.sp;
+    const double shared = (0.83 * mfma + 27.5 * q + 60) * simd + 12.5 * loads, exch = 413.0 * frags * simd * (v.wp > 1 ? 1.0 : 0.38);
+    const double busy = stages * shared + exch;
+    const double lone = std::max(busy, 1600 + exch + stages * std::max(shared, 521 + 0.12 * mfma + 27.0 * 2 * q * (v.t * v.fc + v.fk)));
+    // (waves per SIMD that the registers leave room for)
+    const int regs = ceil_div(16 * frags + 8 * (v.fc + v.fk) + 30, 8) * 8;
+    const int resident = std::max(1, std::min((int)(kMaxLds / upd_shared_lds_bytes(v)), std::min(8, 512 / regs) * 4 / waves));
+    const int per_cu = ceil_div(s.grid, 256), full = per_cu / resident, rest = per_cu - full * resident;
+    const double t = full * std::max(lone, resident * busy) + (rest > 0 ? std::max(lone, rest * busy) : 0.0);
+    // (a run of four pixels of a strided 1x1 layer is two lines)
+    const double out_b = (double)f.out_bytes, in_b = (double)f.in_bytes / (p->d.R * p->d.S == 1 ? p->d.stride : 1);
+    const double again = p->d.R * ceil_div(p->d.S, v.t), launch = 2.85;
+    const double bound[3] = {t / 2.1e3 + launch, launch + (in_b * a.n_kt + out_b * a.n_ct) * again / 18.0e6, launch + (in_b + out_b) / 5.84e6};
+    const double most = *std::max_element(bound, bound + 3);
+    double us = most * std::pow(std::pow(bound[0] / most, 6) + std::pow(bound[1] / most, 6) + std::pow(bound[2] / most, 6), 1.0 / 6);
+    if (a.splits > 1) us += 2.4 + a.splits * (double)f.dwt_bytes * 2 / 5.24e6;
+    return us;
+}
+
+// Whether both operands are staged for all waves, and up to which estimate: lines between its time / the other kernel's, both
+// measured in turn over 500 drawn layers and 500 of these families (C, K = 96 ... 720, N = 16 ... 256, three sets of tensors):
+//   - seven rows or columns: in the row kernel's place everywhere (57 layers, 0.59 - 1.0, in the mean 0.79, one 1.11; 632 -> 40 7x1
+//     at 59x60, N = 18, 113 -> 89 us; 504 -> 284 1x7 at 23x21, N = 27, 57 -> 41); in the ring kernel's place up to 0.87 of its
+//     estimate (0.45 - 0.95, one 1.08; beyond, 0.88 - 1.22);
+//   - 3x3 with stride 2 from 1e10 operations (below, 0.8 - 1.6 whatever the estimates say): up to 1.15 times the window kernel's
+//     estimate (0.81 - 1.01, in the mean 0.91, 288 -> 384 at 35x35, N = 32, 42 -> 36; beyond, 0.92 - 1.22); up to 0.74 times the ring
+//     kernel's for 64 x 64 blocks (0.70 - 0.95; beyond, 0.77 - 1.27); and in the row kernel's place where its runs of eight pixels
+//     fill a row badly, or the row is long (0.66 - 0.98, in the mean 0.84; 288 -> 384 at 35x35, N = 92, 113 -> 89; else 0.9 - 1.16);
+//   - other filters: 1x1 0.85 - 1.19, 3x3 with stride 1 0.9 - 1.5, 5x5 1.15: not built for them.
+double shared_line_us(const conv_plan *p, double ring_us)
+{
+    const conv_desc_t &d = p->d;
+    const double everywhere = 1.0e9;
+    if (d.R * d.S == 7) return p->upd_ring ? 0.87 * ring_us : p->upd_rows ? everywhere : 0;
+    const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)p->info.P * p->info.Q;
+    if (d.R != 3 || d.S != 3 || d.stride != 2 || flops < 1.0e10) return 0;
+    if (p->upd_ring) return p->upd_window ? 1.15 * ring_us : p->urv.fc * p->urv.fk >= 4 ? 0.74 * ring_us : 0;
+    const int Q = p->info.Q;
+    return p->upd_rows && (Q >= 29 || ceil_div(Q, 8) * 8 >= 1.14 * Q) ? everywhere : 0;
+}
+// (CONVMI_UPD_SHARED="t,st,fc,fk,wc,wk,wp,sp,pi,nb,splits": one variant wherever it fits; 0: never -- a tuning aid, as are those that
+// ask for another kernel)
+void plan_upd_shared(conv_plan *p, double ring_us)
+{
+    p->upd_shared = UpdSharedPlan{};
+    if (p->d.dtype != CONV_BF16) return;
+    const char *env = getenv("CONVMI_UPD_SHARED");
+    const bool any = env && strcmp(env, "any") == 0;
+    if (env && !any) {
+        UpdSharedVariant v{};
+        int splits = 1;
+        if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &v.t, &v.st, &v.fc, &v.fk, &v.wc, &v.wk, &v.wp, &v.sp, &v.pi, &v.nb, &splits) < 10) return;
+        p->upd_shared = try_upd_shared(p, v, splits);
+    } else if (!getenv("CONVMI_UPD_RING") && !getenv("CONVMI_UPD_WINDOW")) {
+        const double most_error = planned_upd_error(p) + kOwnRounding;
+        double best_us = shared_line_us(p, ring_us);
+        if (any) best_us = 1e9;
+        for (int i = 0; const UpdSharedVariant *v = upd_shared_variant(i); ++i) {
+            if ((v->t == 1) != (p->d.S == 1)) continue;
+            const int blocks = ceil_div(p->info.Cp, v->wc * v->fc * 32) * ceil_div(p->info.Kp, v->wk * v->fk * 32) * p->d.R * ceil_div(p->d.S, v->t);
+            int last = 0;
+            for (const int target : {128, 192, 256, 384, 512, 768}) {
+                const int splits = std::max(1, target / blocks);
+                if (splits == last) continue;
+                last = splits;
+                const UpdSharedPlan c = try_upd_shared(p, *v, splits);
+                if (!c.ok || upd_shared_error(p, c) > most_error) continue;
+                const double us = upd_shared_us(p, c);
+                if (us < best_us) {
+                    p->upd_shared = c;
+                    best_us = us;
+                }
+            }
+        }
+    }
+    if (p->upd_shared.ok) {
+        p->upd_copies = p->upd_shared.a.splits;
+        p->upd_ws = (size_t)p->upd_copies * p->info.dwt_bytes;  // (one split writes dW itself; the caller brings it all the same)
+    }
+}
+
 void plan_upd(conv_plan *p)
 {
     p->upd_ok = false;
@@ -2557,6 +2705,7 @@ void plan_upd(conv_plan *p)
     if (!few && p->upd_ok) {
         const double flops = 2.0 * p->d.N * p->d.K * p->d.C * p->d.R * p->d.S * (double)p->info.P * p->info.Q;
         plan_upd_split(p, ring ? p->upd_ring_us : flops / 1.35e8);
+        plan_upd_shared(p, p->upd_ring_us);
     }
 }
 
@@ -3025,6 +3174,13 @@ conv_status_t conv_upd(conv_handle_t h, const void *in, const void *dout, void *
         b.partial = b.splits == 1 ? static_cast<float *>(dwt) : static_cast<float *>(ws);
         e = launch_upd_split(h->upd_split.v, b, h->upd_split.grid, s);
         if (b.splits == 1) return e == hipSuccess ? CONV_OK : CONV_ELAUNCH;
+    } else if (h->upd_shared.ok) {
+        UpdArgs b = h->upd_shared.a;
+        b.in = in;
+        b.dout = dout;
+        b.partial = b.splits == 1 ? static_cast<float *>(dwt) : static_cast<float *>(ws);
+        e = launch_upd_shared(h->upd_shared.v, b, h->upd_shared.grid, s);
+        if (b.splits == 1) return e == hipSuccess ? CONV_OK : CONV_ELAUNCH;
     } else if (h->upd_ring) {
         if (a.splits == 1) a.partial = static_cast<float *>(dwt);
         e = h->upd_window ? launch_upd_window(a, h->upd_grid, s)
@@ -3378,6 +3534,15 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
         const size_t n = strlen(buf);
         snprintf(buf + n, buflen - n, " on_bf16x3=upd_split,taps%d,%dx%d,waves_%dx%d,stage%d,positions%d,copies%d,workgroups%d", v.t, v.fc, v.fk,
                  v.wc, v.wk, v.sp, v.pi, h->upd_split.a.splits, h->upd_split.a.total);
+        return CONV_OK;
+    }
+    if (pass == 2 && h->upd_shared.ok) {
+        // (the plan without the kernel that stages for all waves, then that kernel's)
+        describe_fp32_update(h, buf, buflen);
+        const UpdSharedVariant &v = h->upd_shared.v;
+        const size_t n = strlen(buf);
+        snprintf(buf + n, buflen - n, " instead=upd_shared,taps%d,stride%d,%dx%d,waves_%dx%dx%d,stage%d,positions%d,buffers%d,copies%d,workgroups%d",
+                 v.t, v.st, v.fc, v.fk, v.wc, v.wk, v.wp, v.sp, v.pi, v.nb, h->upd_shared.a.splits, h->upd_shared.a.total);
         return CONV_OK;
     }
     if (pass == 2) {

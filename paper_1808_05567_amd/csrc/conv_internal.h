@@ -303,6 +303,16 @@ struct UpdSplitVariant {
 bool upd_split_exists(const UpdSplitVariant &v);
 size_t upd_split_lds_bytes(const UpdSplitVariant &v);
 hipError_t launch_upd_split(const UpdSplitVariant &v, const UpdArgs &a, int grid, hipStream_t stream);
+// bf16: (wc*fc*32) x (wk*fk*32) blocks under t taps of a filter row, both operands staged for all waves; st: 2 for more taps than one
+// under stride 2; wp groups of waves share a stage of sp pixels and at most pi positions of the input; nb buffers.  (UpdArgs as for
+// the kernel above.)
+struct UpdSharedVariant {
+    int t, st, fc, fk, wc, wk, wp, sp, pi, nb;
+};
+bool upd_shared_exists(const UpdSharedVariant &v);
+const UpdSharedVariant *upd_shared_variant(int i);  // the i-th, null behind the last
+size_t upd_shared_lds_bytes(const UpdSharedVariant &v);
+hipError_t launch_upd_shared(const UpdSharedVariant &v, const UpdArgs &a, int grid, hipStream_t stream);
 // at most 4 input channels: filter-row formulation, 7x7 and 3x3; fp32 tensors, or bf16
 // tensors widened on their way into LDS (then UpdArgs::Kb counts blocks of 8 channels)
 hipError_t launch_upd_c4(int dtype, int r, int s, const UpdArgs &a, size_t lds_bytes, int grid,
