@@ -51,7 +51,6 @@ struct IgemmPlan {
     bool reg = false;  // the register-operand kernel (v.wk waves split the reduction of a tile)
     bool patch = false;  // ... with the pixels in LDS (reg is set too)
     bool fallback = false;  // ... because no staged tile fits (IgemmGeo::fallback)
-    SplitPlan split;
 };
 
 // The same for a weight update (upd_split.hip).
@@ -95,12 +94,14 @@ struct conv_plan {
     conv_info_t info;
     IgemmPlan fwd;
     size_t fwd_ws = 0;  // bytes of fp32 partial results if the forward reduction is split
+    SplitPlan fwd_split;      // runs in the place of fwd (fp32)
     size_t fwd_stem_lds = 0;  // > 0: the plain forward pass runs on the resident-filter kernel (its LDS)
     // backward by data
     int bwd_mode = 0;  // 0 unsupported, 1 one launch (duality), 2 parity classes
     int n_bwd = 0;
     bool bwd_quad = false;  // four classes (2x2, 2x1, 1x2, 1x1 taps, in this order) in one launch
     BwdClass bwd[16];
+    SplitPlan bwd_split;  // runs in the place of a single launch's plan (fp32)
     SplitClassesPlan bwd_classes;  // runs in the place of all that
     size_t bwd_ws = 0;
     // (a backward pass that would run untiled but for the register-operand kernel, which takes a
@@ -855,10 +856,10 @@ SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, boo
     return best;
 }
 
-hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t stream)
+hipError_t launch_plan(const IgemmPlan &p, const SplitPlan &split, const IgemmArgs &a, hipStream_t stream)
 {
-    if (p.split.ok) {
-        IgemmArgs s = p.split.a;
+    if (split.ok) {
+        IgemmArgs s = split.a;
         s.in = a.in;
         s.wt = a.wt;
         s.out = a.out;
@@ -866,8 +867,8 @@ hipError_t launch_plan(const IgemmPlan &p, const IgemmArgs &a, hipStream_t strea
         s.bias = a.bias;
         s.resid = a.resid;
         s.relu = a.relu;
-        if (p.split.nw > 0) return launch_igemm_reg_split(p.split.fk, p.split.fm, p.split.nw, s, p.split.grid, stream);
-        return launch_igemm_split(p.split.v, s, p.split.lds, p.split.grid, stream);
+        if (split.nw > 0) return launch_igemm_reg_split(split.fk, split.fm, split.nw, s, split.grid, stream);
+        return launch_igemm_split(split.v, s, split.lds, split.grid, stream);
     }
     return p.patch ? launch_igemm_patch(p.v, a, p.grid, stream)
            : p.reg ? launch_igemm_reg(p.v, a, p.grid, stream)
@@ -1499,6 +1500,7 @@ double classes_us(const conv_plan *p, const SplitClassesPlan &s)
 void plan_bwd_split(conv_plan *p)
 {
     p->bwd_classes = SplitClassesPlan{};
+    p->bwd_split = SplitPlan{};
     if (p->d.dtype != CONV_F32 || p->bwd_mode == 0 || p->bwd_mode == 3) return;
     if (p->bwd_mode == 2) {
         if (const char *env = getenv("CONVMI_IGEMM_SPLIT")) {
@@ -1530,7 +1532,7 @@ void plan_bwd_split(conv_plan *p)
             }
         return;
     }
-    p->bwd[0].p.split = plan_split(p->bwd[0].p, p->bwd[0].x.R2, p->bwd[0].x.S2, class_weights(p, 0), true);
+    p->bwd_split = plan_split(p->bwd[0].p, p->bwd[0].x.R2, p->bwd[0].x.S2, class_weights(p, 0), true);
 }
 
 // Weight update, bf16, at most 4 input channels: (tap, channel) rows on the bf16 MFMA.
@@ -2194,6 +2196,14 @@ bool plan_ring(const conv_plan *p, const RingCand &c, UpdArgs &a)
     return true;
 }
 
+// The largest of three bounds, each of which shades into the next: the sixth root of the sum of their sixth powers.
+double shaded(const double (&bound)[3])
+{
+    double sum = 0;
+    for (const double b : bound) sum += b * b * b * b * b * b;
+    return std::sqrt(std::cbrt(sum));
+}
+
 // What such an update takes, in microseconds, as far as the choice of its block and splits goes: as
 // estimate_us, with the exchange of the waves' sums, the bytes that the blocks of a pixel range
 // re-read, and the reduce launch.  Fitted to 5 000 launches (38 layers x N = 8 ... 256, three sets of
@@ -2236,8 +2246,7 @@ double ring_estimate_us(const conv_plan *p, const RingCand &c, const UpdArgs &a)
     // and 190 by the last, takes 230)
     const double bound[3] = {t, q.launch + (in_b + out_b) / (q.hbm_tb * 1e6),
                              q.launch + (in_b * a.n_kt + out_b * a.n_ct) * d.R / (q.l2_tb * 1e6)};
-    const double most = *std::max_element(bound, bound + 3);
-    t = most * std::pow(std::pow(bound[0] / most, 6) + std::pow(bound[1] / most, 6) + std::pow(bound[2] / most, 6), 1.0 / 6);
+    t = shaded(bound);
     if (a.splits > 1) t += q.reduce + a.splits * (double)f.dwt_bytes * 2 / (q.copy_tb * 1e6);
     return t;
 }
@@ -2479,8 +2488,7 @@ double upd_split_us(const conv_plan *p, const UpdSplitPlan &s)
     const double out_b = (double)f.out_bytes, in_b = p->d.R * p->d.S > 1 ? (double)f.in_bytes : (double)p->d.N * f.Cp * f.P * f.Q * 4;
     const double again = p->d.R * ceil_div(p->d.S, v.t), launch = 2.8;
     const double bound[3] = {t / 2.1e3 + launch, launch + (in_b * a.n_kt + out_b * a.n_ct) * again / 14.6e6, launch + (in_b + out_b) / 4.0e6};
-    const double most = *std::max_element(bound, bound + 3);
-    double us = most * std::pow(std::pow(bound[0] / most, 6) + std::pow(bound[1] / most, 6) + std::pow(bound[2] / most, 6), 1.0 / 6);
+    double us = shaded(bound);
     if (a.splits > 1) us += 2.9 + a.splits * (double)f.dwt_bytes * 2 / 4.84e6;
     return us;
 }
@@ -2602,8 +2610,7 @@ double upd_shared_us(const conv_plan *p, const UpdSharedPlan &s)
     const double out_b = (double)f.out_bytes, in_b = (double)f.in_bytes / (p->d.R * p->d.S == 1 ? p->d.stride : 1);
     const double again = p->d.R * ceil_div(p->d.S, v.t), launch = 2.85;
     const double bound[3] = {t / 2.1e3 + launch, launch + (in_b * a.n_kt + out_b * a.n_ct) * again / 18.0e6, launch + (in_b + out_b) / 5.84e6};
-    const double most = *std::max_element(bound, bound + 3);
-    double us = most * std::pow(std::pow(bound[0] / most, 6) + std::pow(bound[1] / most, 6) + std::pow(bound[2] / most, 6), 1.0 / 6);
+    double us = shaded(bound);
     if (a.splits > 1) us += 2.4 + a.splits * (double)f.dwt_bytes * 2 / 5.24e6;
     return us;
 }
@@ -2855,7 +2862,7 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
             // workgroup several tiles to walk: for tests of that path)
             if (const char *cap = getenv("CONVMI_STEM_WG"); cap && atoi(cap) > 0) p->fwd.a.jstep = atoi(cap);
         }
-        if (p->fwd_stem_lds == 0) p->fwd.split = plan_split(p->fwd, d.R, d.S, FwdWeights{}, false);
+        if (p->fwd_stem_lds == 0) p->fwd_split = plan_split(p->fwd, d.R, d.S, FwdWeights{}, false);
         plan_bwd(p);
         plan_bwd_split(p);
         p->bwd_ws_optional = p->bwd_mode != 0 && p->bwd[0].p.fallback;
@@ -3007,7 +3014,7 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     IgemmArgs a = h->fwd.a;
     // (a workspace is asked for by the plan on the fp32 instructions, whatever runs in its place)
     if (a.ksplit > 1 && !ws) return CONV_EWORKSPACE;
-    const bool split = a.ksplit > 1 && (!h->fwd.split.ok || h->fwd.split.a.ksplit > 1);
+    const bool split = a.ksplit > 1 && (!h->fwd_split.ok || h->fwd_split.a.ksplit > 1);
     a.in = in;
     a.wt = wt;
     a.out = split ? ws : out;
@@ -3021,10 +3028,10 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     // long there, and the residual's round trips do not fit into them -- 0.49 ms against 0.38
     // on the general kernel for layer 1 of Table I; in fp32 it is 0.64 against 0.89)
     const bool fused_ops = scale || bias || residual || relu;
-    if (h->fwd_stem_lds && !h->fwd.split.ok && !(fused_ops && h->d.dtype == CONV_BF16))
+    if (h->fwd_stem_lds && !h->fwd_split.ok && !(fused_ops && h->d.dtype == CONV_BF16))
         e = launch_igemm_stem(h->fwd.v, a, h->fwd_stem_lds, (hipStream_t)stream);
     else
-        e = launch_plan(h->fwd, a, (hipStream_t)stream);
+        e = launch_plan(h->fwd, h->fwd_split, a, (hipStream_t)stream);
     if (e == hipSuccess && split)
         e = launch_split_reduce(h->d.dtype, static_cast<const float *>(ws), out,
                                 (size_t)h->d.N * h->info.Kp * h->info.P * h->info.Q, a.ksplit, scale,
@@ -3076,7 +3083,7 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
         return launch_igemm_split_classes(h->bwd_classes.v, c, h->bwd_classes.lds, s) == hipSuccess ? CONV_OK : CONV_ELAUNCH;
     }
     // the transformed weights of all classes, up to four to a launch (none where the kernel reads the forward pass's)
-    const bool forward = (h->bwd[0].p.split.ok ? h->bwd[0].p.split.a : h->bwd[0].p.a).fwd_wt != 0;
+    const bool forward = (h->bwd_split.ok ? h->bwd_split.a : h->bwd[0].p.a).fwd_wt != 0;
     for (int i = 0; i < h->n_bwd && !forward;) {
         if (h->bwd[i].merged) {
             WtMergeArgs m = h->bwd[i].m;
@@ -3115,9 +3122,9 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
         IgemmArgs a = b.p.a;
         a.in = dout;
         a.wt = wt2;
-        void *part = a.ksplit > 1 && (!b.p.split.ok || b.p.split.a.ksplit > 1) ? static_cast<char *>(ws) + b.part_off : nullptr;
+        void *part = a.ksplit > 1 && (!h->bwd_split.ok || h->bwd_split.a.ksplit > 1) ? static_cast<char *>(ws) + b.part_off : nullptr;
         a.out = part ? part : din;
-        if (launch_plan(b.p, a, s) != hipSuccess) return CONV_ELAUNCH;
+        if (launch_plan(b.p, h->bwd_split, a, s) != hipSuccess) return CONV_ELAUNCH;
         if (part && launch_split_reduce(h->d.dtype, static_cast<const float *>(part), din,
                                         (size_t)h->d.N * h->info.Cp * h->d.H * h->d.W, a.ksplit, nullptr, nullptr,
                                         nullptr, 0, h->d.H * h->d.W, h->info.Cb, s) != hipSuccess)
@@ -3508,7 +3515,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
                      p->a.total, p->a.n_mt, p->a.n_kt,
                      p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.group, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
             if (p->a.fwd_wt) strncat(buf, " forward_weights=1", buflen - strlen(buf) - 1);
-            describe_split(p->split, buf, buflen);
+            describe_split(pass == 0 ? h->fwd_split : h->bwd_split, buf, buflen);
             if (pass == 1) describe_classes(h->bwd_classes, buf, buflen);
             return CONV_OK;
         }
@@ -3523,7 +3530,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
             const size_t n = strlen(buf);
             snprintf(buf + n, buflen - n, " resident_filter_lds=%zu", h->fwd_stem_lds);
         }
-        describe_split(p->split, buf, buflen);
+        describe_split(pass == 0 ? h->fwd_split : h->bwd_split, buf, buflen);
         if (pass == 1) describe_classes(h->bwd_classes, buf, buflen);
         return CONV_OK;
     }
