@@ -101,6 +101,7 @@ struct conv_plan {
     int n_bwd = 0;
     bool bwd_quad = false;  // four classes (2x2, 2x1, 1x2, 1x1 taps, in this order) in one launch
     BwdClass bwd[16];
+    IgemmStreamPlan fwd_stream, bwd_stream;  // ... (bf16, nothing fused)
     SplitPlan bwd_split;  // runs in the place of a single launch's plan (fp32)
     SplitClassesPlan bwd_classes;  // runs in the place of all that
     size_t bwd_ws = 0;
@@ -810,10 +811,10 @@ double split_us(const SplitPlan &s, bool scatter)
 // sums are no less exact.  fw: where the forward pass's weights may be read.
 // (CONVMI_IGEMM_SPLIT="wk,wm,fm,kw,g,strips,fw" or "r,fk,fm,waves,fw": one variant wherever it fits, fw 1: on the forward pass's
 // weights; 0: never -- a tuning aid, as are those that ask for a variant on the fp32 instructions)
-bool fp32_variant_asked_for()
+bool variant_asked_for()
 {
     for (const char *name : {"CONVMI_IGEMM_CAND", "CONVMI_IGEMM_REG", "CONVMI_IGEMM_GROUP", "CONVMI_IGEMM_NT", "CONVMI_IGEMM_GK",
-                             "CONVMI_IGEMM_ROT", "CONVMI_BWD_QUAD", "CONVMI_FORWARD_WEIGHTS", "CONVMI_STEM"})
+                             "CONVMI_IGEMM_ROT", "CONVMI_IGEMM_PATCH", "CONVMI_BWD_QUAD", "CONVMI_FORWARD_WEIGHTS", "CONVMI_STEM"})
         if (getenv(name)) return true;
     return false;
 }
@@ -829,7 +830,7 @@ SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, boo
         if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &wk, &wm, &fm, &kw, &g, &strips, &f) < 5 || strips < 1) return best;
         return f && fw.taps == 0 ? best : try_split(p, R, S, f ? fw : FwdWeights{}, wk, wm, fm, kw, g, strips);
     }
-    if (fp32_variant_asked_for()) return best;
+    if (variant_asked_for()) return best;
     const bool scatter = p.a.zero_fill != 0;
     const double transform = backward ? transform_launch_us((double)p.a.Cb * R * S * p.a.Kp * 16) : 0;
     double best_us = kSplitMargin * (estimate_us(p, scatter) + (p.a.fwd_wt ? 0 : transform));
@@ -1509,7 +1510,7 @@ void plan_bwd_split(conv_plan *p)
                 p->bwd_classes = try_split_classes(p, wk, wm, fm, kw, g, strips);
             return;
         }
-        if (fp32_variant_asked_for()) return;
+        if (variant_asked_for()) return;
         // (one launch for the classes, or one each and the launch that transforms their weights)
         double old_us = 0, weights = 0, most_error = 0;
         for (int i = 0; i < p->n_bwd; ++i) {
@@ -1533,6 +1534,80 @@ void plan_bwd_split(conv_plan *p)
         return;
     }
     p->bwd_split = plan_split(p->bwd[0].p, p->bwd[0].x.R2, p->bwd[0].x.S2, class_weights(p, 0), true);
+}
+
+// The largest of three bounds, each of which shades into the next: the sixth root of the sum of their sixth powers.
+double shaded(const double (&bound)[3])
+{
+    double sum = 0;
+    for (const double b : bound) sum += b * b * b * b * b * b;
+    return std::sqrt(std::cbrt(sum));
+}
+
+// A plan of the kernel that keeps the weights in registers, for N images of Cb blocks of H x W pixels and a result of Kp channels.
+IgemmStreamPlan try_stream(const conv_desc_t &d, int pad_h, int pad_w, int Cb, int Kp, int fk)
+{
+    IgemmStreamPlan s;
+    if (d.dtype != CONV_BF16 || d.R != 3 || d.S != 3 || d.stride != 1 || pad_h != 1 || pad_w != 1) return s;
+    s.cs = std::max(2, ceil_div(Cb, 2));
+    s.fk = fk;
+    const double pixels = (double)d.N * d.H * d.W;
+    // exact small divisions, 24-bit products, 32-bit byte offsets
+    if (!igemm_stream_exists(s.cs, fk) || d.W > igemm_stream_widest() || pixels >= 3.9e6 || pixels * std::max(Cb, Kp / 8) * 16 >= 4.0e9) return s;
+    IgemmStreamArgs &a = s.a;
+    a.N = d.N; a.Cb = Cb; a.H = d.H; a.W = d.W; a.Kp = Kp; a.out_kb = Kp / 8;
+    a.n_kt = ceil_div(Kp, fk * 32);
+    // one workgroup per CU, one round
+    const int units = ceil_div((int)pixels, 128);
+    a.steps = ceil_div(units, std::max(1, 256 / a.n_kt));
+    a.total = ceil_div(units, a.steps) * a.n_kt;
+    a.per_xcd = ceil_div(a.total, 8);
+    if (igemm_stream_lds_bytes(s) > (size_t)kMaxLds) return s;
+    s.ok = true;
+    return s;
+}
+// What it takes, in microseconds, in the form of estimate_us.  Fitted to 480 launches (170 drawn layers of 16 ... 200 channels, N = 8 ...
+// 256, both passes, three sets of tensors in turn): rms error 5 %.
+double stream_us(const IgemmStreamPlan &s)
+{
+    const IgemmStreamArgs &a = s.a;
+    const double pixels = (double)a.N * a.H * a.W, in_b = pixels * a.Cb * 16, out_b = pixels * a.Kp * 2;
+    const double fixed = 2.8 + 0.27 * s.cs * s.fk;
+    const double bound[3] = {fixed + a.steps * std::max(0.224 * s.cs * s.fk + 0.28, 0.74), fixed + (in_b * a.n_kt + out_b) / 7.28e6,
+                             fixed + (in_b + out_b) / 5.23e6};
+    return shaded(bound);
+}
+// Whether a pass keeps the weights in registers: up to 0.88 of what estimate_us says of the other plan.  Time / the other kernel's by the
+// quotient of the estimates, 269 passes: below 0.75 0.62 - 0.88, in the mean 0.73 (32 -> 64 at 147x147, N = 64, backward 83 -> 61 us;
+// 60 -> 28 at 147x147, N = 32, 49 -> 31; 32 -> 24 at 28x31, N = 222, 13 -> 8); 0.75 - 0.88 0.64 - 1.03, mean 0.82; 0.88 - 1 0.76 - 1.16,
+// mean 0.97; beyond 0.78 - 1.53, mean 1.07 (64 -> 64 at 56x56, N = 70, 18.4 -> 21.0; N = 256 61 and 61, where both wait for memory).
+// (CONVMI_STREAM: 0 never, 1 or 2: with so many groups of 32 result channels wherever it fits -- a tuning aid, as are those that
+// ask for another kernel)
+void plan_stream(conv_plan *p)
+{
+    p->fwd_stream = p->bwd_stream = IgemmStreamPlan{};
+    const conv_info_t &f = p->info;
+    const char *env = getenv("CONVMI_STREAM");
+    if (p->d.dtype != CONV_BF16 || (env ? atoi(env) == 0 : variant_asked_for())) return;
+    auto plan = [&](const IgemmPlan &other, int Cb, int Kp, double transform) {
+        if (env) return try_stream(p->d, p->pad_h, p->pad_w, Cb, Kp, atoi(env));
+        IgemmStreamPlan best;
+        double best_us = 0.88 * (estimate_us(other, false) + transform);
+        for (int fk = 1; fk <= 2; ++fk) {
+            const IgemmStreamPlan c = try_stream(p->d, p->pad_h, p->pad_w, Cb, Kp, fk);
+            const double us = c.ok ? stream_us(c) : 0;
+            if (!c.ok || us >= best_us) continue;
+            best = c;
+            best_us = us;
+        }
+        return best;
+    };
+    if (p->fwd.ok && !p->fwd.fallback && p->fwd.a.ksplit == 1) p->fwd_stream = plan(p->fwd, f.Cb, f.Kp, 0);
+    if (p->bwd_mode == 1 && !p->bwd[0].p.fallback) {
+        const IgemmPlan &b = p->bwd[0].p;
+        p->bwd_stream = plan(b, f.Kb, f.Cp, b.a.fwd_wt ? 0 : transform_launch_us((double)f.Kb * 9 * f.Cp * 16));
+        p->bwd_stream.a.fwd_wt = 1;
+    }
 }
 
 // Weight update, bf16, at most 4 input channels: (tap, channel) rows on the bf16 MFMA.
@@ -2196,14 +2271,6 @@ bool plan_ring(const conv_plan *p, const RingCand &c, UpdArgs &a)
     return true;
 }
 
-// The largest of three bounds, each of which shades into the next: the sixth root of the sum of their sixth powers.
-double shaded(const double (&bound)[3])
-{
-    double sum = 0;
-    for (const double b : bound) sum += b * b * b * b * b * b;
-    return std::sqrt(std::cbrt(sum));
-}
-
 // What such an update takes, in microseconds, as far as the choice of its block and splits goes: as
 // estimate_us, with the exchange of the waves' sums, the bytes that the blocks of a pixel range
 // re-read, and the reduce launch.  Fitted to 5 000 launches (38 layers x N = 8 ... 256, three sets of
@@ -2865,6 +2932,7 @@ conv_status_t create_plan(const conv_desc_t *desc, int32_t pad_h, int32_t pad_w,
         if (p->fwd_stem_lds == 0) p->fwd_split = plan_split(p->fwd, d.R, d.S, FwdWeights{}, false);
         plan_bwd(p);
         plan_bwd_split(p);
+        plan_stream(p);
         p->bwd_ws_optional = p->bwd_mode != 0 && p->bwd[0].p.fallback;
         plan_upd(p);
     }
@@ -3024,6 +3092,13 @@ conv_status_t conv_fwd_fused_norm(conv_handle_t h, const void *in, const void *w
     a.resid = split ? nullptr : residual;
     a.relu = split ? 0 : (relu != 0);
     hipError_t e;
+    if (h->fwd_stream.ok && !(scale || bias || residual || relu)) {
+        IgemmStreamArgs b = h->fwd_stream.a;
+        b.in = in;
+        b.wt = wt;
+        b.out = out;
+        return launch_igemm_stream(h->fwd_stream, b, (hipStream_t)stream) == hipSuccess ? CONV_OK : CONV_ELAUNCH;
+    }
     // (bf16 with fused operators: the resident-filter kernel's phases are a few microseconds
     // long there, and the residual's round trips do not fit into them -- 0.49 ms against 0.38
     // on the general kernel for layer 1 of Table I; in fp32 it is 0.64 against 0.89)
@@ -3081,6 +3156,13 @@ conv_status_t conv_bwd_data(conv_handle_t h, const void *dout, const void *wt, v
             a.out = din;
         }
         return launch_igemm_split_classes(h->bwd_classes.v, c, h->bwd_classes.lds, s) == hipSuccess ? CONV_OK : CONV_ELAUNCH;
+    }
+    if (h->bwd_stream.ok) {
+        IgemmStreamArgs b = h->bwd_stream.a;
+        b.in = dout;
+        b.wt = wt;
+        b.out = din;
+        return launch_igemm_stream(h->bwd_stream, b, s) == hipSuccess ? CONV_OK : CONV_ELAUNCH;
     }
     // the transformed weights of all classes, up to four to a launch (none where the kernel reads the forward pass's)
     const bool forward = (h->bwd_split.ok ? h->bwd_split.a : h->bwd[0].p.a).fwd_wt != 0;
@@ -3394,7 +3476,14 @@ conv_status_t conv_unpack_dwt(conv_handle_t h, const void *blk_f32, void *kcrs_f
 }
 
 // What runs in the place of the plan on the fp32 instructions that stands before it.
-static void describe_split(const SplitPlan &s, char *buf, size_t buflen)
+static void describe_stream(const IgemmStreamPlan &p, char *buf, size_t buflen)
+{
+    if (!p.ok) return;
+    const size_t n = strlen(buf);
+    snprintf(buf + n, buflen - n, " instead=igemm_stream,channels%d,rows%d,steps%d,workgroups%d,lds%zu", p.cs * 16, p.fk * 32, p.a.steps, p.a.total,
+             igemm_stream_lds_bytes(p));
+}
+void describe_split(const SplitPlan &s, char *buf, size_t buflen)
 {
     if (!s.ok) return;
     const size_t n = strlen(buf);
@@ -3516,6 +3605,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
                      p->a.gk, p->grid, p->lds, p->a.n_stage, p->a.group, p->a.ksplit, pass == 0 || h->bwd_quad ? 1 : h->n_bwd);
             if (p->a.fwd_wt) strncat(buf, " forward_weights=1", buflen - strlen(buf) - 1);
             describe_split(pass == 0 ? h->fwd_split : h->bwd_split, buf, buflen);
+            describe_stream(pass == 0 ? h->fwd_stream : h->bwd_stream, buf, buflen);
             if (pass == 1) describe_classes(h->bwd_classes, buf, buflen);
             return CONV_OK;
         }
@@ -3531,6 +3621,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
             snprintf(buf + n, buflen - n, " resident_filter_lds=%zu", h->fwd_stem_lds);
         }
         describe_split(pass == 0 ? h->fwd_split : h->bwd_split, buf, buflen);
+        describe_stream(pass == 0 ? h->fwd_stream : h->bwd_stream, buf, buflen);
         if (pass == 1) describe_classes(h->bwd_classes, buf, buflen);
         return CONV_OK;
     }

@@ -126,6 +126,24 @@ struct IgemmQuadArgs {
     int end[4];
 };
 hipError_t launch_igemm_quad(int dtype, const IgemmQuadArgs &q, size_t lds_bytes, hipStream_t stream);
+// bf16 3x3 stride 1, the result as large as the input, weights in registers (cs groups of 16 input channels, fk of 32 result channels)
+struct IgemmStreamArgs {
+    const void *in, *wt;
+    void *out;
+    int N, Cb, H, W, Kp, out_kb;  // as IgemmArgs'
+    int fwd_wt;                   // (only whether)
+    int steps;                    // of 128 pixels per workgroup
+    int n_kt, total, per_xcd;
+};
+struct IgemmStreamPlan {
+    bool ok = false;
+    int cs = 0, fk = 0;
+    IgemmStreamArgs a{};
+};
+bool igemm_stream_exists(int cs, int fk);
+size_t igemm_stream_lds_bytes(const IgemmStreamPlan &p);
+int igemm_stream_widest();
+hipError_t launch_igemm_stream(const IgemmStreamPlan &p, const IgemmStreamArgs &a, hipStream_t stream);
 bool igemm_variant_exists(const IgemmVariant &v);
 // Whether the variant can sum its steps in groups (IgemmArgs::group).
 bool igemm_variant_groups(const IgemmVariant &v);
