@@ -807,8 +807,8 @@ double split_us(const SplitPlan &s, bool scatter)
     return us;
 }
 
-// Whether the launch that `p` plans runs on the bf16 instructions: where the estimate says that this is at least 4 % faster, and the
-// sums are no less exact.  fw: where the forward pass's weights may be read.
+// Whether the launch that `p` plans runs on the bf16 instructions: where the estimate says that this is faster by more than split_line,
+// and the sums are no less exact.  fw: where the forward pass's weights may be read.
 // (CONVMI_IGEMM_SPLIT="wk,wm,fm,kw,g,strips,fw" or "r,fk,fm,waves,fw": one variant wherever it fits, fw 1: on the forward pass's
 // weights; 0: never -- a tuning aid, as are those that ask for a variant on the fp32 instructions)
 bool variant_asked_for()
@@ -819,6 +819,21 @@ bool variant_asked_for()
     return false;
 }
 constexpr double kSplitMargin = 0.96;
+// Up to which part of the other plan's estimate (`us`) a candidate's counts.  Time / the fp32 instructions' above the lines, where the
+// estimate is too low, 1 100 passes of drawn layers: staged 1x1 with 96 channels or fewer on a side 0.73 - 1.38 (64 -> 80 at 73x73,
+// N = 19, 22 -> 27 us; both wait for memory); staged 1x1 in two sets of waves 0.77 - 1.23; staged under a stride 0.83 - 1.28; in
+// registers under a stride 0.74 - 1.14 (36 -> 44 3x3 at 20x21, N = 52, 6.8 -> 7.7: half of every line read is not used), in four waves
+// or on short reductions in less than 10 us 0.90 - 1.18; in registers under 1x1 in more than 1 200 tiles 0.9 - 1.14.
+double split_line(const SplitPlan &s, double us)
+{
+    const IgemmArgs &a = s.a;
+    const bool strided = a.stride > 1 || a.ostr > 1;
+    if (s.nw > 0 && a.R * a.S == 1 && a.total > 1200) return 0.8;
+    if (s.nw > 0) return strided ? 0.83 : a.n_stage >= 24 && (s.nw >= 8 || us >= 10) ? 0.96 : us < 10 ? 0.85 : 0.92;
+    if (a.R * a.S == 1 && std::min(4 * a.Cb, a.Kp) <= 96) return 0.74;
+    if (a.R * a.S == 1 && s.v.kw == 2) return 0.75;
+    return strided ? 0.85 : kSplitMargin;
+}
 SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, bool backward)
 {
     SplitPlan best;
@@ -833,13 +848,17 @@ SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, boo
     if (variant_asked_for()) return best;
     const bool scatter = p.a.zero_fill != 0;
     const double transform = backward ? transform_launch_us((double)p.a.Cb * R * S * p.a.Kp * 16) : 0;
-    double best_us = kSplitMargin * (estimate_us(p, scatter) + (p.a.fwd_wt ? 0 : transform));
+    const double other_us = estimate_us(p, scatter) + (p.a.fwd_wt ? 0 : transform);
+    double best_us = other_us;
     const double most_error = sums_error(p) + kOwnRounding;
     auto consider = [&](const SplitPlan &c) {
         if (!c.ok || split_error(c) > most_error) return;
         // (staged: half a microsecond on top, which the estimate is off where a launch is short)
-        const double us = split_us(c, scatter) + (c.nw > 0 ? 0 : 0.5) + (c.a.fwd_wt ? 0 : transform);
-        if (us < best_us) {
+        // (more shares to stage than rounds to do it beside: 256 pixels under 1x1, 16 channels a step, 0.66 - 1.33 of the other plan's time
+        // where the estimate without this factor says 0.8, 144 <- 564 at 29x30, N = 123, 168 -> 224 us; in wider steps 0.49 - 0.97)
+        const double crowded = c.nw == 0 && c.v.ni > c.v.g * R * S ? 1.3 : 1.0;
+        const double us = crowded * split_us(c, scatter) + (c.nw > 0 ? 0 : 0.5) + (c.a.fwd_wt ? 0 : transform);
+        if (us < best_us && us < split_line(c, other_us) * other_us) {
             best = c;
             best_us = us;
         }
@@ -1520,7 +1539,7 @@ void plan_bwd_split(conv_plan *p)
             most_error = std::max(most_error, sums_error(b.p));
         }
         old_us += (p->bwd_quad ? 3.0 : 0.0) + (p->bwd[0].p.a.fwd_wt ? 0 : transform_launch_us(weights));
-        double best_us = kSplitMargin * old_us;
+        double best_us = (old_us < 20 ? 0.75 : 0.88) * old_us;  // (above: 0.9 - 1.3 of the time)
         for (const auto &t : kSplitTiles)
             for (int strips = 1; strips <= 4; ++strips) {
                 const SplitClassesPlan c = try_split_classes(p, t[0], t[1], t[2], t[3], 1, strips);
@@ -1592,11 +1611,13 @@ void plan_stream(conv_plan *p)
     auto plan = [&](const IgemmPlan &other, int Cb, int Kp, double transform) {
         if (env) return try_stream(p->d, p->pad_h, p->pad_w, Cb, Kp, atoi(env));
         IgemmStreamPlan best;
-        double best_us = 0.88 * (estimate_us(other, false) + transform);
+        const double other_us = estimate_us(other, false) + transform;
+        double best_us = 0.88 * other_us;
         for (int fk = 1; fk <= 2; ++fk) {
             const IgemmStreamPlan c = try_stream(p->d, p->pad_h, p->pad_w, Cb, Kp, fk);
             const double us = c.ok ? stream_us(c) : 0;
-            if (!c.ok || us >= best_us) continue;
+            // (several tiles of result channels read the input that often: up to 1.09 between 0.8 and 0.88)
+            if (!c.ok || us >= best_us || (c.a.n_kt > 1 && us >= 0.8 * other_us)) continue;
             best = c;
             best_us = us;
         }
@@ -2566,8 +2587,8 @@ static const UpdSplitVariant kUpdSplit[] = {
     {3, 1, 1, 2, 4, 16, 32}, {3, 1, 1, 1, 4, 32, 64}, {3, 1, 1, 4, 2, 16, 32},
     {4, 1, 1, 2, 2, 32, 64}, {4, 1, 1, 2, 4, 32, 64}, {4, 1, 1, 2, 2, 16, 32}, {5, 1, 1, 2, 2, 16, 32}};
 
-// Whether the update runs on the bf16 instructions: where the estimate says that this is at least 4 % faster than `fp32_us`, and the
-// sums are no less exact.
+// Whether the update runs on the bf16 instructions: where the estimate says that this is at least 8 % faster than `fp32_us`, and the
+// sums are no less exact.  (Above that line 0.99 - 1.09 of the time, 11 of 161 drawn layers: 32 -> 64 3x3 at 147x147, N = 31, 216 -> 235 us.)
 // (CONVMI_UPD_SPLIT="t,fc,fk,wc,wk,sp,pi,splits": one variant wherever it fits; 0: never -- a tuning aid, as are those that ask for
 // a variant on the fp32 instructions)
 void plan_upd_split(conv_plan *p, double fp32_us)
@@ -2582,7 +2603,7 @@ void plan_upd_split(conv_plan *p, double fp32_us)
     } else if (!getenv("CONVMI_UPD_RING") && !getenv("CONVMI_UPD_WINDOW")) {
         const double most_error = planned_upd_error(p) + kOwnRounding;
         // (and by 1.5 us: below 20 us the estimates are as far apart as that)
-        double best_us = kSplitMargin * fp32_us - 1.5;
+        double best_us = 0.92 * fp32_us - 1.5;
         for (const UpdSplitVariant &v : kUpdSplit) {
             const int blocks = ceil_div(p->info.Cp, v.wc * v.fc * 32) * ceil_div(p->info.Kp, v.wk * v.fk * 32) * p->d.R * ceil_div(p->d.S, v.t);
             int last = 0;
