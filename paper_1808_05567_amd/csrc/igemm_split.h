@@ -15,6 +15,7 @@
 #include <algorithm>
 
 #include "igemm_exchange.h"
+#include "split_address.h"
 #include "split_bf16.h"
 
 namespace convmi {
@@ -123,34 +124,24 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
     // Weights: rows [k0, k0 + 32) of a round's four blocks, two of them to a lane half.  (FW: see put_weights.)
     const int taps = FW ? a.wt_taps : RS;
     const rsrc_t rsrc_wt = make_rsrc(a.wt, 0, (size_t)a.Cb * taps * a.Kp * 16);
-    const unsigned block_bytes = FW ? 4u * (unsigned)taps * (unsigned)a.Cb * 64u : (unsigned)RS * (unsigned)a.Kp * 16u;
-    unsigned w_off[2];  // of the lane's two chunks: the next blocks, or (FW) the next four blocks of rows
-    if constexpr (FW) {
-        const int blk = (k0 >> 2) + wt_block(lane);
+    unsigned w_off[2];
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-            w_off[b] = blk + 4 * b < a.Kp >> 2 ? (unsigned)blk * (block_bytes / 4) + (unsigned)wt_channel(lane) * 16u : kOutOfRange;
-    } else {
-        w_off[0] = w_off[1] = k0 + l32 < a.Kp ? 2u * h * block_bytes + (unsigned)(k0 + l32) * 16u : kOutOfRange;
-    }
+    for (int b = 0; b < 2; ++b)
+        w_off[b] = FW ? weight_lane_fwd((k0 >> 2) + wt_block(lane) + 4 * b, wt_channel(lane), a.Cb, taps, a.Kp)
+                      : weight_lane(k0 + l32, h, b, a.Cb, RS, a.Kp);
     unsigned char *const w_area = lds + KW * 2 * buf_bytes + wave_all * kWtBytes;
     u32x4 w_raw[2];
     int w_step = 0, w_group = 0, w_tap = 0, w_tr = 0, w_ts = 0;  // of the next load
     auto load_weights = [&]() {
         const int cb = first_block(w_step) + 4 * w_group;
         const bool live = w_step < steps && cb < a.Cb;
-        unsigned at;
-        bool mine = live;
-        if constexpr (FW) {
-            at = ((unsigned)(a.wt_tap0 - w_tr * a.wt_dr - w_ts * a.wt_ds) * (unsigned)a.Cb + (unsigned)cb) * 64u;
-            mine = live && 4 * cb + wt_channel(lane) < 4 * a.Cb;
-        } else {
-            // (blocks beyond the last one are out of range by their address)
-            at = (unsigned)cb * block_bytes + (unsigned)w_tap * (unsigned)a.Kp * 16u;
-        }
+        const bool mine = live && (!FW || 4 * cb + wt_channel(lane) < 4 * a.Cb);
+        const unsigned shared = !live ? 0u
+                                : FW  ? weight_shared_fwd(cb, a.wt_tap0 - w_tr * a.wt_dr - w_ts * a.wt_ds, a.Cb)
+                                      : weight_shared(cb, w_tap, RS, a.Kp);
 #pragma unroll
         for (int b = 0; b < 2; ++b)
-            w_raw[b] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_wt, mine ? w_off[b] : kOutOfRange, at + b * block_bytes, 0);
+            w_raw[b] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_wt, mine ? w_off[b] : kOutOfRange, shared, 0);
         if constexpr (FW) {
             const bool row_end = w_ts + 1 == a.S;
             w_ts = row_end ? 0 : w_ts + 1;
