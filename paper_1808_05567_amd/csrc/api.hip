@@ -748,13 +748,16 @@ SplitPlan try_reg_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, 
 static const int kSplitTiles[][4] = {{4, 1, 4, 1}, {4, 1, 2, 1}, {2, 2, 4, 1}, {2, 2, 2, 1}, {4, 1, 4, 2}, {4, 1, 2, 2}, {2, 2, 4, 2}, {2, 2, 2, 2}};
 static const int kRegSplitTiles[][3] = {{1, 1, 4}, {1, 1, 8}, {1, 1, 16}, {2, 1, 4}, {2, 1, 8}, {1, 2, 4}, {2, 2, 4}, {2, 2, 8}};
 
-// Error of its sums in the same units (chain_error): an MFMA rounds the sum of the large products once for sixteen channels; what
-// the small ones add to it is nothing beside that.
+// What the left-out products add to a sum's error, in the units of chain_error: 0.03 where they are of random sign, 0.2 where all of
+// them leave out the same (measured, split_bf16.h).
+constexpr double kLeftOut = 0.2;
+// Error of its sums in the same units: an MFMA rounds the sum of the large products once for sixteen channels; the small ones' own
+// rounding is nothing beside that.
 double split_error(const SplitPlan &s)
 {
     const IgemmArgs &a = s.a;
-    if (s.nw > 0) return ceil_div(a.st_per, s.nw) / 2.0 + std::log2((double)s.nw) / 2 + (a.ksplit > 1 ? a.ksplit / 2.0 : 0) + 0.5;
-    return ceil_div(a.n_stage, s.v.kw) * s.v.g * a.R * a.S / 2.0 + (s.v.kw - 1) / 2.0 + 0.5;
+    if (s.nw > 0) return ceil_div(a.st_per, s.nw) / 2.0 + std::log2((double)s.nw) / 2 + (a.ksplit > 1 ? a.ksplit / 2.0 : 0) + 0.5 + kLeftOut;
+    return ceil_div(a.n_stage, s.v.kw) * s.v.g * a.R * a.S / 2.0 + (s.v.kw - 1) / 2.0 + 0.5 + kLeftOut;
 }
 
 // What a launch on the bf16 instructions takes, in microseconds, without the launch that transforms a backward pass's weights: the form of
@@ -2545,11 +2548,12 @@ UpdSplitPlan try_upd_split(const conv_plan *p, const UpdSplitVariant &v, int spl
     return s;
 }
 
-// Error of its sums in the units of planned_upd_error: an MFMA rounds the sum of the large products once for sixteen pixels.
+// Error of its sums in the units of planned_upd_error: an MFMA rounds the sum of the large products once for sixteen pixels, and what
+// is left out.
 double upd_split_error(const conv_plan *p, const UpdArgs &a)
 {
     const int chains = upd_reduce_chains(p->info.dwt_bytes / sizeof(float), a.splits);
-    return std::min((double)a.rows_per_split, (double)p->d.N * a.P * a.Q) / 32 + 0.5 +
+    return std::min((double)a.rows_per_split, (double)p->d.N * a.P * a.Q) / 32 + 0.5 + kLeftOut +
            (a.splits > 1 ? ceil_div(a.splits, chains) / 2.0 + std::log2((double)chains) / 2 : 0);
 }
 

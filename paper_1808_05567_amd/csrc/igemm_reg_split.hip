@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM == 1 ? 4 : FK * FM == 2 ? 3 : 2) v
 #pragma unroll
                     for (int i = 0; i < FK; ++i) as[i] = get_weights(area + i * kWtBytes, lane);
                 }
-                static_for<0, 6>([&](auto t) {
+                static_for<0, kSplitProducts>([&](auto t) {
 #pragma unroll
                     for (int i = 0; i < FK; ++i)
 #pragma unroll

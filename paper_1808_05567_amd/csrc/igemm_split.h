@@ -188,11 +188,11 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
     auto round = [&](int s, const unsigned char *at, const unsigned char *next_at, auto item_tag) {
         constexpr int ITEM = decltype(item_tag)::value;
         // (the weights first, so that the next ones are requested early: they are wanted a round from here)
-        constexpr int NM = 6 * FM, NW = NM / 2;
+        constexpr int NP = kSplitProducts, NM = NP * FM, NW = NM / 2;
         Bf16x3 next, item;
         float rest[2];
         static_for<0, NM>([&](auto kc) {
-            constexpr int k = decltype(kc)::value, j = k / 6, i = k % 6;
+            constexpr int k = decltype(kc)::value, j = k / NP, i = k % NP;
             mma_split<i>(A, Bf16x3{B[0], B[1], B[2]}, big[j], small[j]);
             if constexpr (i < 3) ahead[i] = reinterpret_cast<const u32x4 *>((j + 1 < FM ? at : next_at) + bpos[(j + 1) % FM])[i];
             if constexpr (k < NW)
@@ -208,7 +208,7 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
                 stage_item(ITEM, (s + 1) & 1, item);
                 load_item(ITEM, s + 2);
             }
-            if constexpr (i == 5) {
+            if constexpr (i == NP - 1) {
 #pragma unroll
                 for (int t = 0; t < 3; ++t) B[t] = ahead[t];
             }

@@ -1,12 +1,18 @@
 // fp32 operands as sums of three bf16 numbers, for products of fp32 tensors on the bf16 matrix instructions.
 //
-// x = h + m + l: h is x rounded to 8 significant bits, x - h has at most 16 of them, m takes the upper 8 and l what is
-// left, so the sum is exact.  Of the nine products of two such numbers six are formed, h*h, h*m, m*h, m*m, h*l, l*h; the other
-// three are below 2^-25 of the product, and of random sign.  Six bf16 MFMAs of 16 reduction indices take 192 clocks where
-// fp32 ones take 512.  The sums are no less exact for it: an fp32 MFMA rounds the sum once per product, a bf16 one once
-// per 16 (at most), and the five small products go into a sum of their own.  Measured against 64 bits, one chain of n
-// products, uniform * normal values, error of the fp32 MFMAs / of this: n = 16 7.4e-8 / 3.1e-8, 256 2.9e-7 / 8.6e-8, 4608
-// 1.2e-6 / 4.1e-7, 36864 3.5e-6 / 1.2e-6 (all six in one sum: 3.3e-8, 2.3e-7, 1.1e-6, 3.2e-6).
+// (The decomposition: G. Henry, P. T. P. Tang and A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", ARITH 2019.)  x = h + m + l: h is x rounded to 8 significant bits, m is x - h rounded to 8, l what is
+// left, at most 6 bits, so the sum is exact; |m| <= 2^-8 and |l| <= 2^-17 of the power of two below |x|.  Of the nine products of
+// two such numbers six are formed, h*h, h*m, m*h, m*m, h*l, l*h.  The other three are together at most 2^-24 (1 + 2^-9) of the
+// product, what rounding it to fp32 may cost, and zero where the product has 24 bits or fewer (m is zero up to 8 bits of an operand, l up to 16).
+// Six bf16 MFMAs of 16 reduction indices take 192 clocks where fp32 ones take 512.  An fp32 MFMA rounds the sum once per product, a bf16
+// one once per 16 (at most), and the five small products go into a sum of their own.
+// Measured against 64 bits, one chain of n products, uniform * normal values, error of the fp32 MFMAs / of this: n = 16 7.4e-8 / 3.1e-8,
+// 256 2.9e-7 / 8.6e-8, 4608 1.2e-6 / 4.1e-7, 36864 3.5e-6 / 1.2e-6 (all six in one sum: 3.3e-8, 2.3e-7, 1.1e-6, 3.2e-6).  Sums whose
+// products all leave out the same (constant tensors), n = 4 3.2e-8 / 2.4e-8, 16 1.0e-7 / 3.5e-8, 256 2.4e-7 / 3.5e-8; sums of a single
+// product other than zero 2.47e-8 / 2.51e-8, at most 1.0 / 1.42 times 2^-24 (mantissas just above one, which leave out the most:
+// 3.40e-8 / 3.57e-8).  (m cut off instead of rounded: 2.7e-8, at most 2.25.  m*l and l*m formed too: 2.47e-8, and 28 images 3x3 128 ->
+// 128 at 28x28 123 -> 145 us, 256 of 512 -> 1024 1x1 stride 2 at 28x28 1 010 -> 1 156.)
 //
 // What three bf16 numbers do not hold: infinities (x - h is NaN), values that round to infinity, and the last bits of values
 // below 2^-109.  All of the first two make a sum infinite or NaN; such sums, and
@@ -36,10 +42,11 @@ static __device__ __forceinline__ void split_piece(const u32x4 (&raw)[2], Bf16x3
         asm volatile("" : "+v"(rest[0]), "+v"(rest[1]));  // (here, not where it is used)
         s.h[p] = h;
     } else {
-        const unsigned a = __float_as_uint(rest[0]), b = __float_as_uint(rest[1]);
-        const float la = rest[0] - __uint_as_float(a & 0xFFFF0000u), lb = rest[1] - __uint_as_float(b & 0xFFFF0000u);
-        unsigned m = __builtin_amdgcn_perm(b, a, 0x07060302), l = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302);
-        asm volatile("" : "+v"(m), "+v"(l));
+        unsigned m = pack_bf16x2(rest[0], rest[1]);
+        asm volatile("" : "+v"(m));
+        const float la = rest[0] - __uint_as_float(m << 16), lb = rest[1] - __uint_as_float(m & 0xFFFF0000u);
+        unsigned l = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302);
+        asm volatile("" : "+v"(l));
         s.m[p] = m;
         s.l[p] = l;
     }
@@ -56,6 +63,7 @@ static __device__ __forceinline__ void mma_bf16(const u32x4 &a, const u32x4 &b, 
     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 // big += h*h, small += the five others: product I of the six
+constexpr int kSplitProducts = 6;
 template <int I>
 static __device__ __forceinline__ void mma_split(const Bf16x3 &a, const Bf16x3 &b, f32x16 &big, f32x16 &small)
 {

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(WC *WK * 64, 2) void upd_split_kernel(const UpdArgs
 
     // A stage is Q16 * T * FC * FK blocks of six MFMAs.  Beside them, pinned: the operands of the block that follows are read, the
     // next stage is converted, one piece behind an MFMA, and the stage after that is requested.
-    constexpr int NBLK = Q16 * T * FC * FK, NM = 6 * NBLK, NITEM = NII + NIO, PIECES = NITEM * kSplitPieces;
+    constexpr int NBLK = Q16 * T * FC * FK, NM = kSplitProducts * NBLK, NITEM = NII + NIO, PIECES = NITEM * kSplitPieces;
     constexpr int NC = NM * 3 / 4;  // MFMAs beside which the pieces stand
     for (int st = 0; st < stages; ++st) {
         const unsigned char *const buf = lds + (st & 1) * BUF;
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(WC *WK * 64, 2) void upd_split_kernel(const UpdArgs
         O[0][0] = read_out(buf, 0, 0);
         I[0][0] = read_in(buf, 0, 0, 0);
         static_for<0, NM>([&](auto kc) {
-            constexpr int k = decltype(kc)::value, b = k / 6, m = k % 6;
+            constexpr int k = decltype(kc)::value, b = k / kSplitProducts, m = k % kSplitProducts;
             // blocks of a tap in snake order: (0,0) (0,1) (1,1) (1,0)
             constexpr int u = b / (FC * FK), e = b % (FC * FK), i = e / FK, j = i % 2 == 0 ? e % FK : FK - 1 - e % FK;
             constexpr int q = u / T, t = u % T;

@@ -195,3 +195,53 @@ def test_no_less_exact_than_the_fp32_instructions(shape, which):
         finally:
             L.close()
     assert err[1] <= 1.1 * err[0], err  # (the spread between inputs)
+
+
+def _structured(kind, rows, cols, n, rng):
+    """Two factors, rows x n and cols x n, of sums over n: few random products, one product other than zero, or all alike (then
+    what the products leave out adds up); mantissas just above one leave out the most."""
+    if kind == "short":
+        return rng.standard_normal((rows, n)), rng.standard_normal((cols, n))
+    a = rng.uniform(1, 1.0078, (rows, 1 if kind == "constant" else n)) * np.ones((1, n))
+    if kind == "constant":
+        return a, rng.uniform(1, 1.0078, (cols, 1)) * np.ones((1, n))
+    b = np.zeros((cols, n))
+    b[np.arange(cols), rng.integers(n, size=cols)] = rng.uniform(1, 1.0078, cols)
+    return a, b
+
+
+@pytest.mark.parametrize("kind,n", [("short", 16), ("short", 64), ("constant", 16), ("constant", 64), ("constant", 256), ("single", 16), ("single", 256)])
+@pytest.mark.parametrize("which", ["fwd", "bwd", "upd"])
+def test_sums_with_nothing_to_average_out(which, kind, n):
+    """The products that are not formed are at most what rounding a product to fp32 costs, 2^-24 (1 + 2^-9) of it, and no sum is
+    less exact for it than on the fp32 instructions, but for one product alone: what is left out of that is m*l and l*m with m spread over
+    2^-8 and l over 2^-17 of either sign, at most sqrt(2) 2^-25 / 3 = 1.41e-8 in the mean, beside its rounding."""
+    rng = np.random.default_rng(17)
+    rows, cols = (64, 64) if which == "upd" else (1024, 64)
+    a, b = (x.astype(np.float32) for x in _structured(kind, rows, cols, n, rng))
+    ref, mag = (f(a).astype(np.float64) @ f(b).astype(np.float64).T for f in (lambda x: x, np.abs))
+    if which == "upd":  # a: input channels over pixels, b: output channels
+        side = int(n ** 0.5)
+        shape, variants, switch = (1, 64, 64, side, side, 1, 1, 1, 0), ["1,1,1,2,2,32,32,1", "1,2,2,2,2,16,16,1"], "CONVMI_UPD_SPLIT"
+        kw = dict(I=a.reshape(1, 64, side, side), dO=b.reshape(1, 64, side, side))
+        back = lambda g: g[:, :, 0, 0].T
+    else:  # a: pixels, b: the result's channels
+        shape = (1, n, cols, 32, 32, 1, 1, 1, 0) if which == "fwd" else (1, cols, n, 32, 32, 1, 1, 1, 0)
+        variants, switch = ["4,1,4,1,1", "2,2,2,1,2", "r,1,1,4"], "CONVMI_IGEMM_SPLIT"
+        x = np.ascontiguousarray(a.T).reshape(1, n, 32, 32)
+        kw = dict(I=x, Wt=b.reshape(cols, n, 1, 1)) if which == "fwd" else dict(dO=x, Wt=np.ascontiguousarray(b.T).reshape(n, cols, 1, 1))
+        back = lambda g: g[0].reshape(cols, -1).T
+    err = {}
+    for v in ["0"] + variants:
+        L = _layer(shape, **{switch: v})
+        try:
+            assert (" on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1, "upd": 2}[which])) == (v != "0"), v
+            got = back(run_pass(L, which, **kw)).astype(np.float64)
+        finally:
+            L.close()
+        err[v] = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        # left out, and one rounding of the sum for sixteen products, the small ones' sum and the result
+        roundings = 1 + (0 if kind == "single" else n / 16 + 1)
+        if v != "0":
+            assert (np.abs(got - ref) <= 2.0 ** -24 * ((1 + 2.0 ** -9) * mag + roundings * (1 + 2.0 ** -7) * mag)).all(), v
+            assert err[v] <= (np.hypot(err["0"], 1.41e-8) if kind == "single" else err["0"]), (v, err)
