@@ -5,13 +5,7 @@
 
 namespace convmi {
 
-// Sums of fp32 tensors on the bf16 instructions, the largest of which is t, that are to be formed again: infinite or NaN ones,
-// or nothing but tiny ones (2^-80: whatever is lost of a value below 2^-109 is out of reach of the 24 bits of a larger
-// result unless it meets one beyond 2^28).
-static __device__ __forceinline__ bool sum_needs_fp32(float t)
-{
-    return !(t < __builtin_inff()) || (t > 0.0f && t < 0x1p-80f);
-}
+static __device__ __forceinline__ bool any_nan(const f32x4 &v) { return v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]; }
 
 // Workgroup -> tile (channel tile kt, pixel tile mt) and, where the reduction is split over workgroups, copy sp:
 // dealt over the XCDs as in igemm_kernel.  False: nothing to do.
@@ -45,10 +39,9 @@ static __device__ __forceinline__ float widened(const void *base, size_t i)
 }
 
 // Four consecutive channels of one pixel, krow .. krow + 3 at (n, oj, oi), summed over steps [u0, u1) one product at a time;
-// a step is a tap of CBS channel blocks.  Taps outside the image are left out (`inside_only`) or zeros.  FW: the forward pass's weights.
+// a step is a tap of CBS channel blocks.  Taps outside the image are left out.  FW: the forward pass's weights.
 template <int DT, int CBS, bool FW = false>
-static __device__ __forceinline__ f32x4 sum_one_by_one(const IgemmArgs &a, int n, int oj, int oi, int krow, int u0, int u1,
-                                                       bool inside_only)
+static __device__ __forceinline__ f32x4 sum_inside_image(const IgemmArgs &a, int n, int oj, int oi, int krow, int u0, int u1)
 {
     constexpr int V = Elem<DT>::V;
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
@@ -57,14 +50,13 @@ static __device__ __forceinline__ f32x4 sum_one_by_one(const IgemmArgs &a, int n
     for (int u = u0; u < u1; ++u) {
         const int cp = u / RS, tap = u - cp * RS, r = tap / a.S, s = tap - r * a.S;
         const int y = oj * a.stride - a.pad_h + r, x = oi * a.cstride - a.pad_w + s;
-        const bool inside = y >= 0 && y < a.H && x >= 0 && x < a.W;
-        if (inside_only && !inside) continue;
+        if (y < 0 || y >= a.H || x < 0 || x >= a.W) continue;
         for (int cb = CBS * cp; cb < min(CBS * cp + CBS, a.Cb); ++cb) {
             const size_t in = ((size_t)n * a.Cb + cb) * a.H * a.W + (size_t)y * a.W + x;
             const size_t wt = FW ? ((size_t)(krow / V) * a.wt_taps + (a.wt_tap0 - r * a.wt_dr - s * a.wt_ds)) * a.Cb * V + (size_t)cb * V
                                  : ((size_t)cb * RS + tap) * a.Kp + krow;
             for (int c = 0; c < V; ++c) {
-                const float v = inside ? widened<DT>(a.in, in * V + c) : 0.0f;
+                const float v = widened<DT>(a.in, in * V + c);
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
                     sum[t] = fmaf(v, widened<DT>(a.wt, FW ? (wt + c) * V + krow % V + t : (wt + t) * V + c), sum[t]);
@@ -74,11 +66,9 @@ static __device__ __forceinline__ f32x4 sum_one_by_one(const IgemmArgs &a, int n
     return sum;
 }
 
-// Which sums add_and_store has formed again, by again(n, oj, oi, krow): none, those that are NaN, or those of fp32 tensors on
-// the bf16 instructions that are infinite, NaN or so small that bits of the operands may be lost (split_bf16.h).
-enum { SUMS_AS_THEY_ARE = 0, SUMS_NAN_AGAIN = 1, SUMS_SPLIT_AGAIN = 2 };
-// FK x FM fragments of NW waves.
-template <int DT, int FK, int FM, int NW, int AGAIN, class F>
+// FK x FM fragments of NW waves.  EXACT: a sum that is NaN is replaced by again(n, oj, oi, krow) in plans that ask for it
+// (IgemmArgs::exact).
+template <int DT, int FK, int FM, int NW, bool EXACT, class F>
 static __device__ __forceinline__ void add_and_store(const IgemmArgs &a, const f32x16 (&acc)[FK][FM], unsigned char *lds,
                                                      int k0, int m0, int sp, F &&again)
 {
@@ -182,15 +172,8 @@ static __device__ __forceinline__ void add_and_store(const IgemmArgs &a, const f
             if (tg < G) {
                 f32x4 v = wave_sum<0, NW>([&](int w) { return xch[(tg * NW + w) * 256 + ch]; });
                 const Place p = place(q);
-                if constexpr (AGAIN == SUMS_SPLIT_AGAIN) {
-                    float most = 0.0f;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) most = __builtin_elementwise_maximum(most, __builtin_fabsf(v[t]));
-                    if (p.ok && sum_needs_fp32(most)) v = again(p.n, p.oj, p.oi, p.krow);
-                }
-                if constexpr (AGAIN == SUMS_NAN_AGAIN) {
-                    if (p.ok && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]))
-                        v = again(p.n, p.oj, p.oi, p.krow);
+                if constexpr (EXACT) {
+                    if (a.exact && p.ok && any_nan(v)) v = again(p.n, p.oj, p.oi, p.krow);
                 }
                 if (!FUSED && a.ksplit > 1) {
                     Elem<CONV_F32>::store4(ro, p.ok ? p.pos * SC : kOutOfRange, 0, v[0], v[1], v[2], v[3]);

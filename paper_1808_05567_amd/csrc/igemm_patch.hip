@@ -274,7 +274,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_patch_ker
     // (the patches are done with before the sums take their place)
     wait_all_memory();
     __syncthreads();
-    add_and_store<DT, FK, FM, NW, SUMS_AS_THEY_ARE>(a, acc, lds, k0, m0, sp, [](int, int, int, int) { return f32x4{}; });
+    add_and_store<DT, FK, FM, NW, false>(a, acc, lds, k0, m0, sp, [](int, int, int, int) { return f32x4{}; });
 }
 
 constexpr int kPatchRing = 3;  // taps of the ring of weights

@@ -255,8 +255,8 @@ __global__ __launch_bounds__(NW * 64, FK * FM <= 2 ? 4 : 2) void igemm_reg_kerne
                 for (int j = 0; j < FM; ++j) acc[i][j] = sum[i][j];
         }
     }
-    add_and_store<DT, FK, FM, NW, EXACT ? SUMS_NAN_AGAIN : SUMS_AS_THEY_ARE>(a, acc, lds, k0, m0, sp, [&](int n, int oj, int oi, int krow) {
-        return sum_one_by_one<DT, 2>(a, n, oj, oi, krow, sbeg, sbeg + nst, true);
+    add_and_store<DT, FK, FM, NW, EXACT>(a, acc, lds, k0, m0, sp, [&](int n, int oj, int oi, int krow) {
+        return sum_inside_image<DT, 2>(a, n, oj, oi, krow, sbeg, sbeg + nst);
     });
 }
 

@@ -7,6 +7,7 @@
 // turns; the fp32 instructions take FK * FM * 512.
 #include <algorithm>
 
+#include "igemm_fp32_again.h"
 #include "split_bf16.h"
 
 namespace convmi {
@@ -150,13 +151,25 @@ __global__ __launch_bounds__(NW * 64, FK * FM == 1 ? 4 : FK * FM == 2 ? 3 : 2) v
             }
         }
     }
-    if constexpr (FW) __syncthreads();  // (the weights are done with before the sums take their place)
+    float most = 0.0f;
 #pragma unroll
     for (int i = 0; i < FK; ++i)
 #pragma unroll
-        for (int j = 0; j < FM; ++j) big[i][j] += small[i][j];
-    add_and_store<CONV_F32, FK, FM, NW, SUMS_SPLIT_AGAIN>(a, big, lds, k0, m0, sp, [&](int n, int oj, int oi, int krow) {
-        return sum_one_by_one<CONV_F32, 4, FW>(a, n, oj, oi, krow, sbeg, sbeg + nst, a.exact != 0);
+        for (int j = 0; j < FM; ++j) {
+            big[i][j] += small[i][j];
+            most = max_magnitude(most, big[i][j]);
+        }
+    // Infinite, NaN or tiny sums: the wave's share again.
+    if (__builtin_expect(sums_need_fp32(most), 0)) {
+        static_for<0, FK * FM>([&](auto fc) {
+            constexpr int i = decltype(fc)::value / FM, j = decltype(fc)::value % FM;
+            const int m = m0 + j * 32 + l32, n = fast_div(m, inv_PQ), rem = m - mul24(n, PQ), oj = fast_div(rem, inv_Q);
+            big[i][j] = fragment_in_fp32<FW>(a, n, oj, rem - mul24(oj, a.Q), m < npix, k0 + i * 32 + l32, u0, u1);
+        });
+    }
+    if constexpr (FW) __syncthreads();  // (the weights are done with before the sums take their place)
+    add_and_store<CONV_F32, FK, FM, NW, true>(a, big, lds, k0, m0, sp, [&](int n, int oj, int oi, int krow) {
+        return sum_inside_image<CONV_F32, 4, FW>(a, n, oj, oi, krow, sbeg, sbeg + nst);
     });
 }
 

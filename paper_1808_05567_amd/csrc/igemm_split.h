@@ -15,6 +15,7 @@
 #include <algorithm>
 
 #include "igemm_exchange.h"
+#include "igemm_fp32_again.h"
 #include "split_address.h"
 #include "split_bf16.h"
 
@@ -365,17 +366,18 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
         }
         return;
     }
-    // Infinite, NaN or tiny sums: again, one product at a time.
+    // Infinite, NaN or tiny sums: all of the wave's again.
     for (int j = 0; j < FO; ++j) {
         const Pixel p = pixel(m_wave + j * 32);
         const unsigned at = place(p);
-        f32x16 v{};
-        if (p.ok)
+        f32x16 v = fragment_in_fp32<FW>(a, p.n, p.oj, p.oi, p.ok, k0 + l32, 0, (a.Cb + 3) / 4 * RS);
+        if (a.exact && p.ok)
 #pragma unroll
             for (int vq = 0; vq < 4; ++vq) {
                 const int row = k0 + 8 * vq + 4 * h;
-                if (row >= a.Kp) continue;
-                const f32x4 x = sum_one_by_one<CONV_F32, 4, FW>(a, p.n, p.oj, p.oi, row, 0, (a.Cb + 3) / 4 * RS, a.exact != 0);
+                const f32x4 was = {v[4 * vq], v[4 * vq + 1], v[4 * vq + 2], v[4 * vq + 3]};
+                if (row >= a.Kp || !any_nan(was)) continue;
+                const f32x4 x = sum_inside_image<CONV_F32, 4, FW>(a, p.n, p.oj, p.oi, row, 0, (a.Cb + 3) / 4 * RS);
 #pragma unroll
                 for (int t = 0; t < 4; ++t) v[4 * vq + t] = x[t];
             }

@@ -15,8 +15,8 @@
 // 128 at 28x28 123 -> 145 us, 256 of 512 -> 1024 1x1 stride 2 at 28x28 1 010 -> 1 156.)
 //
 // What three bf16 numbers do not hold: infinities (x - h is NaN), values that round to infinity, and the last bits of values
-// below 2^-109.  All of the first two make a sum infinite or NaN; such sums, and
-// tiny ones, are formed again in fp32 (sum_needs_fp32).
+// below 2^-109.  All of the first two make a sum infinite or NaN; a wave with such sums, or
+// tiny ones, forms its own again on the fp32 instructions (sum_needs_fp32).
 #pragma once
 #include "igemm_exchange.h"
 
@@ -118,6 +118,13 @@ static __device__ __forceinline__ float max_magnitude(float t, const f32x16 &v)
     for (int i = 0; i < 16; i += 2)
         t = __builtin_elementwise_maximum(__builtin_elementwise_maximum(t, __builtin_fabsf(v[i])), __builtin_fabsf(v[i + 1]));
     return t;
+}
+// Sums of fp32 tensors on the bf16 instructions, the largest of which is t, that are to be formed again: infinite or NaN ones,
+// or nothing but tiny ones (2^-80: whatever is lost of a value below 2^-109 is out of reach of the 24 bits of a larger
+// result unless it meets one beyond 2^28).
+static __device__ __forceinline__ bool sum_needs_fp32(float t)
+{
+    return !(t < __builtin_inff()) || (t > 0.0f && t < 0x1p-80f);
 }
 // Whether a wave whose lanes' largest results are t forms them again.
 static __device__ __forceinline__ bool sums_need_fp32(float t) { return __any(sum_needs_fp32(t)) != 0; }

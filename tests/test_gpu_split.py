@@ -245,3 +245,46 @@ def test_sums_with_nothing_to_average_out(which, kind, n):
         if v != "0":
             assert (np.abs(got - ref) <= 2.0 ** -24 * ((1 + 2.0 ** -9) * mag + roundings * (1 + 2.0 ** -7) * mag)).all(), v
             assert err[v] <= (np.hypot(err["0"], 1.41e-8) if kind == "single" else err["0"]), (v, err)
+
+
+def _time_us(run):
+    run()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        run()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3)
+    return min(times)
+
+
+SLOWEST = [((28, 128, 128, 28, 28, 3, 3, 1, 1), "fwd"), ((28, 128, 128, 28, 28, 3, 3, 1, 1), "bwd"), ((32, 512, 512, 7, 7, 3, 3, 1, 1), "fwd"),
+           ((32, 512, 512, 7, 7, 3, 3, 1, 1), "bwd"), ((64, 512, 1024, 28, 28, 1, 1, 2, 0), "fwd"), ((64, 512, 1024, 28, 28, 1, 1, 2, 0), "bwd"),
+           ((32, 512, 512, 7, 7, 3, 3, 1, 1), "upd"), ((64, 64, 64, 56, 56, 3, 3, 1, 1), "upd"), ((64, 512, 1024, 28, 28, 1, 1, 2, 0), "upd")]
+
+
+@pytest.mark.parametrize("shape,which", SLOWEST, ids=lambda s: s if isinstance(s, str) else "x".join(map(str, s)))
+def test_nan_and_tiny_tensors_take_no_multiple_of_the_fp32_instructions_time(shape, which):
+    """Sums that the bf16 instructions cannot form are formed again on the fp32 instructions: both passes together, 2 to 3 times what the
+    plan on the fp32 instructions takes; at most 4, against runs that differ.  (One product at a time it was 5 to 30.)"""
+    took = {}
+    for env in ("0", None):
+        L = _layer(shape, **({} if env is None else dict(CONVMI_IGEMM_SPLIT=env, CONVMI_UPD_SPLIT=env)))
+        try:
+            assert (" on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1, "upd": 2}[which])) == (env is None)
+            src = L.out_blk if which == "bwd" else L.in_blk
+            for t in (L.in_blk, L.out_blk, L.wt_blk):
+                t.normal_()
+            run = {"fwd": L.fwd, "bwd": L.bwd_data, "upd": L.upd}[which]
+            for kind in ("nan", "tiny"):
+                if kind == "tiny":
+                    src.normal_().mul_(1e-38)
+                else:
+                    src.fill_(float("nan"))
+                took[env, kind] = _time_us(run)
+        finally:
+            L.close()
+    for kind in ("nan", "tiny"):
+        assert took[None, kind] < 4 * took["0", kind], took
