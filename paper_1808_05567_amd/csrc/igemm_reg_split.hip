@@ -115,6 +115,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM == 1 ? 4 : FK * FM == 2 ? 3 : 2) v
         }
     };
 
+    unsigned lost = 0;  // bits of the operands that no bf16 number holds
     f32x16 big[FK][FM], small[FK][FM];
 #pragma unroll
     for (int i = 0; i < FK; ++i)
@@ -131,11 +132,11 @@ __global__ __launch_bounds__(NW * 64, FK * FM == 1 ? 4 : FK * FM == 2 ? 3 : 2) v
                 Bf16x3 as[FK], bs[FM];
 #pragma unroll
                 for (int i = 0; i < FK; ++i) {
-                    as[i] = split8(A[d][i]);
+                    as[i] = split8<false>(A[d][i], lost);
                     if constexpr (FW) put_weights(area + i * kWtBytes, lane, as[i]);
                 }
 #pragma unroll
-                for (int j = 0; j < FM; ++j) bs[j] = split8(B[d][j]);
+                for (int j = 0; j < FM; ++j) bs[j] = split8<false>(B[d][j], lost);
                 load(A[d], B[d]);
                 if constexpr (FW) {
 #pragma unroll
@@ -151,6 +152,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM == 1 ? 4 : FK * FM == 2 ? 3 : 2) v
             }
         }
     }
+    mark_if_lost(lost, big[0]);
     float most = 0.0f;
 #pragma unroll
     for (int i = 0; i < FK; ++i)

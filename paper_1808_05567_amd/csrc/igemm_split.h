@@ -157,6 +157,7 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
 #pragma unroll
     for (int j = 0; j < FM; ++j) bpos[j] = h * plane_bytes + pixel((wave_m * FM + j) * 32 + l32).pos * kPosBytes;
 
+    unsigned lost = 0, lost_in = 0;  // bits of the weights and of the input's share that no bf16 number holds
     f32x16 big[FM], small[FM];
 #pragma unroll
     for (int j = 0; j < FM; ++j) big[j] = small[j] = f32x16{};
@@ -171,10 +172,10 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
             return w;
         }
     };
-    Bf16x3 A = weights_landed(split8(w_raw));
+    Bf16x3 A = weights_landed(split8<false>(w_raw, lost));
     load_weights();
     static_for<0, NI>([&](auto ic) {
-        stage_item(ic, 0, split8(in_raw[ic]));
+        stage_item(ic, 0, split8<true>(in_raw[ic], lost_in));
         load_item(ic, 1);
     });
     lds_barrier();
@@ -197,14 +198,14 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
             mma_split<i>(A, Bf16x3{B[0], B[1], B[2]}, big[j], small[j]);
             if constexpr (i < 3) ahead[i] = reinterpret_cast<const u32x4 *>((j + 1 < FM ? at : next_at) + bpos[(j + 1) % FM])[i];
             if constexpr (k < NW)
-                static_for<k * kSplitPieces / NW, (k + 1) * kSplitPieces / NW>([&](auto pc) { split_piece<decltype(pc)::value>(w_raw, next, rest); });
+                static_for<k * kSplitPieces / NW, (k + 1) * kSplitPieces / NW>([&](auto pc) { split_piece<decltype(pc)::value, false>(w_raw, next, rest, lost); });
             if constexpr (k == NW - 1) {
                 load_weights();
                 next = weights_landed(next);
             }
             if constexpr (ITEM >= 0 && k >= NW)
                 static_for<(k - NW) * kSplitPieces / (NM - NW), (k - NW + 1) * kSplitPieces / (NM - NW)>(
-                    [&](auto pc) { split_piece<decltype(pc)::value>(in_raw[ITEM], item, rest); });
+                    [&](auto pc) { split_piece<decltype(pc)::value, true>(in_raw[ITEM], item, rest, lost_in); });
             if constexpr (ITEM >= 0 && k == NM - 1) {
                 stage_item(ITEM, (s + 1) & 1, item);
                 load_item(ITEM, s + 2);
@@ -240,7 +241,7 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
                 round(s, at, next_at, ic);
                 at = next_at;
             } else {  // (a step of few taps)
-                stage_item(ic, (s + 1) & 1, split8(in_raw[ic]));
+                stage_item(ic, (s + 1) & 1, split8<true>(in_raw[ic], lost_in));
                 load_item(ic, s + 2);
             }
         });
@@ -252,6 +253,7 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
         lds_barrier();
     }
 
+    mark_if_lost(lost, big);
     // The sets' sums: each adds and stores half of the fragments.
     constexpr int FO = FM / KW;
     static_assert(FM % KW == 0 && KW <= 2, "two sets take half of the fragments each");

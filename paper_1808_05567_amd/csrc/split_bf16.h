@@ -15,8 +15,11 @@
 // 128 at 28x28 123 -> 145 us, 256 of 512 -> 1024 1x1 stride 2 at 28x28 1 010 -> 1 156.)
 //
 // What three bf16 numbers do not hold: infinities (x - h is NaN), values that round to infinity, and the last bits of values
-// below 2^-109.  All of the first two make a sum infinite or NaN; a wave with such sums, or
-// tiny ones, forms its own again on the fp32 instructions (sum_needs_fp32).
+// below 2^-109.  All of the first two make a sum infinite or NaN.  So do the last: a wave that finds bits which no l holds makes l NaN
+// in operands that it converts for others, and its sums at the end where the operands are its own.  A wave with such sums, or with
+// nothing but tiny ones, forms its own again on the fp32 instructions (sum_needs_fp32).  (The look at the operands takes four to six of
+// 50 instructions for eight values: 28 images 3x3 128 -> 128 at 28x28 123.5 -> 126 us, 256 of 512 -> 1024 1x1 stride 2 1 027 -> 1 055.
+// A guard on the results alone misses operands of 2^-120 that meet 2^50, 1e-4 off.)
 #pragma once
 #include "igemm_exchange.h"
 
@@ -27,10 +30,12 @@ struct Bf16x3 {
 };
 
 // Eight numbers, in eight pieces of five or six instructions that stand between MFMAs: pieces 2*p and 2*p + 1 make pair p, the
-// first of it in the lower half of h, m, l.  `rest` carries x - h from one to the other.
+// first of it in the lower half of h, m, l.  `rest` carries x - h from one to the other.  `lost` collects the bits that no l holds, in
+// its lower half.  SHARED: the last piece makes the last pair's l NaN if the eight have any (one pair: whoever multiplies it
+// forms all its sums again).
 constexpr int kSplitPieces = 8;
-template <int I>
-static __device__ __forceinline__ void split_piece(const u32x4 (&raw)[2], Bf16x3 &s, float (&rest)[2])
+template <int I, bool SHARED>
+static __device__ __forceinline__ void split_piece(const u32x4 (&raw)[2], Bf16x3 &s, float (&rest)[2], unsigned &lost)
 {
     constexpr int p = I / 2;
     if constexpr (I % 2 == 0) {
@@ -44,18 +49,21 @@ static __device__ __forceinline__ void split_piece(const u32x4 (&raw)[2], Bf16x3
     } else {
         unsigned m = pack_bf16x2(rest[0], rest[1]);
         asm volatile("" : "+v"(m));
-        const float la = rest[0] - __uint_as_float(m << 16), lb = rest[1] - __uint_as_float(m & 0xFFFF0000u);
-        unsigned l = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302);
-        asm volatile("" : "+v"(l));
+        const unsigned la = __float_as_uint(rest[0] - __uint_as_float(m << 16)), lb = __float_as_uint(rest[1] - __uint_as_float(m & 0xFFFF0000u));
+        unsigned l = __builtin_amdgcn_perm(lb, la, 0x07060302);
+        lost = SHARED && p == 0 ? la | lb : lost | la | lb;
+        if constexpr (SHARED && p == 3) l = (unsigned short)lost != 0 ? 0x7FC07FC0u : l;
+        asm volatile("" : "+v"(l), "+v"(lost));
         s.m[p] = m;
         s.l[p] = l;
     }
 }
-static __device__ __forceinline__ Bf16x3 split8(const u32x4 (&raw)[2])
+template <bool SHARED>
+static __device__ __forceinline__ Bf16x3 split8(const u32x4 (&raw)[2], unsigned &lost)
 {
     Bf16x3 s;
     float rest[2];
-    static_for<0, kSplitPieces>([&](auto i) { split_piece<decltype(i)::value>(raw, s, rest); });
+    static_for<0, kSplitPieces>([&](auto i) { split_piece<decltype(i)::value, SHARED>(raw, s, rest, lost); });
     return s;
 }
 static __device__ __forceinline__ void mma_bf16(const u32x4 &a, const u32x4 &b, f32x16 &c)
@@ -119,15 +127,22 @@ static __device__ __forceinline__ float max_magnitude(float t, const f32x16 &v)
         t = __builtin_elementwise_maximum(__builtin_elementwise_maximum(t, __builtin_fabsf(v[i])), __builtin_fabsf(v[i + 1]));
     return t;
 }
-// Sums of fp32 tensors on the bf16 instructions, the largest of which is t, that are to be formed again: infinite or NaN ones,
-// or nothing but tiny ones (2^-80: whatever is lost of a value below 2^-109 is out of reach of the 24 bits of a larger
-// result unless it meets one beyond 2^28).
+// Sums of fp32 tensors on the bf16 instructions, the largest of which is t, that are to be formed again: infinite or NaN ones, or
+// nothing but tiny ones, whose small products are denormal (2^-100: the least of them stands 2^-24 below the sum, at 2^-124).
 static __device__ __forceinline__ bool sum_needs_fp32(float t)
 {
-    return !(t < __builtin_inff()) || (t > 0.0f && t < 0x1p-80f);
+    return !(t < __builtin_inff()) || (t > 0.0f && t < 0x1p-100f);
 }
 // Whether a wave whose lanes' largest results are t forms them again.
 static __device__ __forceinline__ bool sums_need_fp32(float t) { return __any(sum_needs_fp32(t)) != 0; }
+// The sums of a wave that lost bits of its own operands are NaN from here on.
+template <int N>
+static __device__ __forceinline__ void mark_if_lost(unsigned lost, f32x16 (&sums)[N])
+{
+    if (__builtin_expect(__any((unsigned short)lost != 0) != 0, 0))
+#pragma unroll
+        for (int j = 0; j < N; ++j) sums[j][0] = __builtin_nanf("");
+}
 
 // Barrier of the workgroup behind which the waves' LDS operations are done; loads into registers stay in flight.
 static __device__ __forceinline__ void lds_barrier()

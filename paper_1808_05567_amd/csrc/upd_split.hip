@@ -184,10 +184,11 @@ __global__ __launch_bounds__(WC *WK * 64, 2) void upd_split_kernel(const UpdArgs
 #pragma unroll
             for (int j = 0; j < FK; ++j) big[t][i][j] = small[t][i][j] = f32x16{};
 
+    unsigned lost;
     lds_barrier();  // (the zeros are there)
     load_stage();
-    static_for<0, NII>([&](auto i) { put(in_at[i], lds, split8(in_raw[i])); });
-    static_for<0, NIO>([&](auto i) { put(out_at[i], lds, split8(out_raw[i])); });
+    static_for<0, NII>([&](auto i) { put(in_at[i], lds, split8<true>(in_raw[i], lost)); });
+    static_for<0, NIO>([&](auto i) { put(out_at[i], lds, split8<true>(out_raw[i], lost)); });
     load_stage();
     place_pixels();
     lds_barrier();
@@ -220,10 +221,10 @@ __global__ __launch_bounds__(WC *WK * 64, 2) void upd_split_kernel(const UpdArgs
                 static_for<k * PIECES / NC, (k + 1) * PIECES / NC>([&](auto pc) {
                     constexpr int piece = decltype(pc)::value % kSplitPieces, it = decltype(pc)::value / kSplitPieces;
                     if constexpr (it < NII) {
-                        split_piece<piece>(in_raw[it], item, rest);
+                        split_piece<piece, true>(in_raw[it], item, rest, lost);
                         if constexpr (piece == kSplitPieces - 1) put(in_at[it], next, item);
                     } else {
-                        split_piece<piece>(out_raw[it - NII], item, rest);
+                        split_piece<piece, true>(out_raw[it - NII], item, rest, lost);
                         if constexpr (piece == kSplitPieces - 1) put(out_at[it - NII], next, item);
                     }
                 });

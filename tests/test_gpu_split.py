@@ -146,14 +146,17 @@ def test_infinities_and_nan_as_on_the_fp32_instructions(which, switch, variants)
 
 
 @pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd", "upd"])
-@pytest.mark.parametrize("exponents", [(-60, -50), (-108, 0), (-118, 10), (100, -20)], ids=str)
+@pytest.mark.parametrize("exponents", [(-60, -50), (-50, -48), (-108, 0), (-118, 10), (100, -20), (-116, 40), (-120, 50), (-124, 50)], ids=str)
 def test_scale_does_not_matter(which, switch, variants, exponents):
-    """Results near and below the smallest bf16 numbers: powers of two times the operands give the same error (the fp32
-    instructions round a product of 2^-110 and less to fewer bits too, so not below that)."""
+    """Operands and results near and below the smallest bf16 numbers: powers of two times the operands give the same error (the fp32
+    instructions round a product of 2^-110 and less to fewer bits too, and operands of 2^-124 are denormal from 2^-2 of the mean on,
+    so not below that).  The scaled operands are rounded to fp32 first, and the reference is theirs."""
     shape = (2, 40, 48, 12, 13, 3, 3, 1, 1)
     I, Wt, dO = make_inputs(shape, F32, layer_id=55)
     a, b = {"fwd": (I, Wt), "bwd": (dO, Wt), "upd": (I, dO)}[which]
     refs = {"fwd": lambda: oracle.fwd(I, Wt, 1, 1), "bwd": lambda: oracle.bwd_data(dO, Wt, 12, 13, 1, 1), "upd": lambda: oracle.upd(I, dO, 3, 3, 1, 1)}
+    for x, e in zip((a, b), exponents):  # (in place: what is left of it in fp32, scaled back for the oracle)
+        x[...] = np.ldexp(np.ldexp(x, e).astype(np.float32).astype(np.float64), -e)
     ref = refs[which]()
     a *= np.float32(2.0 ** exponents[0])
     b *= np.float32(2.0 ** exponents[1])
@@ -165,6 +168,60 @@ def test_scale_does_not_matter(which, switch, variants, exponents):
             assert rel_l2(run_pass(L, which, **kw).astype(np.float64) * scale, ref) < 1e-6, v
         finally:
             L.close()
+
+
+@pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd", "upd"])
+def test_tiny_values_among_others(which, switch, variants):
+    """One channel of 2^-120 beside ordinary ones, in either operand, and one that only another's 2^60 brings back: every channel of the
+    result is as exact as in a tensor of its own.  And values between 2^-108 and 2^-107, whose last bf16 numbers are denormal."""
+    shape = (2, 40, 48, 12, 13, 3, 3, 1, 1)
+    rng = np.random.default_rng(11)
+    I, Wt, dO = make_inputs(shape, F32, layer_id=57)
+    few = 2.0 ** -108 * rng.uniform(1, 2, I.shape)
+    tiny = np.float32(2.0 ** -120)
+    cases = []
+    for kind in ("a row", "a term", "denormal parts"):
+        x, w, g = I.copy(), Wt.copy(), dO.copy()
+        if kind == "denormal parts":
+            x = few.astype(np.float32)
+            g = (2.0 ** -108 * rng.uniform(1, 2, dO.shape)).astype(np.float32)
+            if which == "upd":
+                g = (dO * np.float32(2.0 ** 40)).astype(np.float32)
+            w *= np.float32(2.0 ** 40)
+        elif kind == "a row":  # (of the result: a channel of its weights, or of dO, or of the input)
+            w[5] *= tiny
+            w[:, 7] *= tiny
+            if which == "upd":
+                x[:, 7] *= tiny
+                g[:, 5] *= tiny
+        else:  # (a term of every sum of a row, the others zero)
+            x[:, 3] *= tiny
+            g[:, 3] *= tiny
+            w[9] = 0
+            w[9, 3] = Wt[9, 3] * np.float32(2.0 ** 60)
+            w[:, 9] = 0
+            w[3, 9] = Wt[3, 9] * np.float32(2.0 ** 60)
+            if which == "upd":
+                g[:, 9] *= np.float32(2.0 ** 60)
+        cases.append((kind, x, w, g))
+    for kind, x, w, g in cases:
+        X, W, G = (torch.from_numpy(t).double() for t in (x, w, g))
+        if which == "fwd":
+            ref, kw = torch.nn.functional.conv2d(X, W, padding=1), dict(I=x, Wt=w)
+        elif which == "bwd":
+            ref, kw = torch.nn.grad.conv2d_input(X.shape, W, G, padding=1), dict(dO=g, Wt=w)
+        else:
+            ref, kw = torch.nn.grad.conv2d_weight(X, W.shape, G, padding=1), dict(I=x, dO=g)
+        per_channel = lambda t: np.sqrt(np.square(np.moveaxis(t, 1, 0).reshape(t.shape[1], -1) * 2.0 ** 60).sum(1)) + 1e-300
+        rows = lambda t: np.sqrt(np.square(t.reshape(t.shape[0], -1) * 2.0 ** 60).sum(1)) + 1e-300
+        for v in variants:
+            L = _layer(shape, **{switch: v})
+            try:
+                d = run_pass(L, which, **kw).astype(np.float64) - ref.numpy()
+            finally:
+                L.close()
+            for norm in (per_channel, rows) if which == "upd" else (per_channel,):
+                assert (norm(d) <= 1e-6 * norm(ref.numpy())).all(), (kind, v, (norm(d) / norm(ref.numpy())).max())
 
 
 # Layer, pass: relative error (2-norm) against 64 bits of what the planner picks, no larger than on the fp32 instructions
