@@ -646,56 +646,75 @@ void share_over_xcds(IgemmArgs &a, double image, int taps)
     a.per_xcd = a.gk == 1 ? ceil_div(a.total * a.ksplit, 8) : a.kt_per * a.mq_per;
 }
 
-// A plan of the split kernel for the launch that `p` plans, R x S taps.
+// The staged input tile of the split kernel for the launch that `p` plans, R x S taps: what decides whether a variant serves it.
+struct SplitTile {
+    bool ok = false, sampled = false;
+    int TQ = 0, Hs = 0, LW = 0, LRW = 0, ni = 0;
+};
+SplitTile split_tile(const IgemmPlan &p, int R, int S, int wm, int fm, int g, int strips)
+{
+    SplitTile t;
+    const IgemmArgs &a = p.a;
+    // (a launch with a staged plan: its tensors are within 32-bit offsets)
+    if (!p.ok || a.no_taps || a.shuffle || a.cstride != a.stride || a.ostr_x != a.ostr) return t;
+    t.sampled = R * S == 1 && a.pad_h == 0 && a.pad_w == 0 && (a.P - 1) * (long long)a.stride < a.H &&
+                (a.Q - 1) * (long long)a.stride < a.W;
+    if (t.sampled && strips > 1) return t;
+    const int TM = wm * fm * 32;
+    t.TQ = ceil_div(a.Q, strips);
+    if ((strips - 1) * t.TQ >= a.Q) return t;
+    if (t.sampled) {
+        t.Hs = a.P;
+        t.LW = t.TQ;
+        t.LRW = TM;
+    } else {
+        // rows of an image: those its pixels read, without the rows of zeros below it that stand for the next image's above it too
+        const int rows = (a.P - 1) * a.stride + R;
+        t.Hs = rows - std::max(0, std::min(rows - a.pad_h - a.H, a.pad_h));
+        t.LW = (t.TQ - 1) * a.stride + S;
+        const long long touched = std::min<long long>((TM - 2) / t.TQ + 2, (long long)a.N * a.P);
+        const long long crossings = std::min<long long>(a.N - 1, ceil_div((int)touched - 1, a.P));
+        const long long LR = (touched - 1) * a.stride + crossings * std::max(0, t.Hs - a.P * a.stride) + R;
+        if (LR * t.LW > 4096) return t;
+        t.LRW = (int)LR * t.LW;
+    }
+    t.ni = ceil_div(2 * g * ceil_div(t.LRW, 64), 4);
+    t.ok = true;
+    return t;
+}
+
+// A plan of the split kernel.
 SplitPlan try_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, int wk, int wm, int fm, int kw, int g, int strips,
                     int least_ni = 0)
 {
     SplitPlan s;
-    const IgemmArgs &b = p.a;
-    // (a launch with a staged plan: its tensors are within 32-bit offsets)
-    if (!p.ok || b.no_taps || b.shuffle || b.cstride != b.stride || b.ostr_x != b.ostr) return s;
+    const SplitTile t = split_tile(p, R, S, wm, fm, g, strips);
+    if (!t.ok) return s;
+    s.v = IgemmSplitVariant{wk, wm, fm, kw, g, std::max(t.ni, least_ni), fw.taps > 0 ? 1 : 0};
+    if (!igemm_split_exists(s.v)) return s;
+    s.lds = igemm_split_lds_bytes(s.v, t.LRW);
+    if (s.lds > (size_t)kMaxLds) return s;
+    const int TK = wk * 32, TM = wm * fm * 32;
+    const long long pixels = (long long)p.a.N * p.a.P * t.TQ, tiles = ((pixels + TM - 1) / TM) * strips;
+    if (pixels >= (1LL << 30) || tiles * ceil_div(p.a.Kp, TK) >= (1 << 24)) return s;
     IgemmArgs &a = s.a;
-    a = b;
+    a = p.a;
     a.R = R;
     a.S = S;
     a.fwd_wt = a.group = 0;
     if (fw.taps > 0 && !forward_weights(a, fw.taps, fw.tap0, fw.dr, fw.ds)) return s;
     a.ksplit = 1;
-    a.sampled = R * S == 1 && a.pad_h == 0 && a.pad_w == 0 && (a.P - 1) * (long long)a.stride < a.H &&
-                (a.Q - 1) * (long long)a.stride < a.W;
-    if (a.sampled && strips > 1) return s;
-    const int TK = wk * 32, TM = wm * fm * 32;
+    a.sampled = t.sampled;
     a.n_qt = strips;
-    a.TQ = ceil_div(a.Q, strips);
-    if ((strips - 1) * a.TQ >= a.Q) return s;
+    a.TQ = t.TQ;
     a.TR = 0;
-    if (a.sampled) {
-        a.Hs = a.P;
-        a.LW = a.TQ;
-        a.LRW = TM;
-    } else {
-        // rows of an image: those its pixels read, without the rows of zeros below it that stand for the next image's above it too
-        const int rows = (a.P - 1) * a.stride + R;
-        a.Hs = rows - std::max(0, std::min(rows - a.pad_h - a.H, a.pad_h));
-        a.LW = (a.TQ - 1) * a.stride + S;
-        const long long touched = std::min<long long>((TM - 2) / a.TQ + 2, (long long)a.N * a.P);
-        const long long crossings = std::min<long long>(a.N - 1, ceil_div((int)touched - 1, a.P));
-        const long long LR = (touched - 1) * a.stride + crossings * std::max(0, a.Hs - a.P * a.stride) + R;
-        if (LR * a.LW > 4096) return s;
-        a.LRW = (int)LR * a.LW;
-    }
-    a.PLS = a.LRW;
-    const int ni = std::max(ceil_div(2 * g * ceil_div(a.LRW, 64), 4), least_ni);
-    s.v = IgemmSplitVariant{wk, wm, fm, kw, g, ni, a.fwd_wt};
-    if (!igemm_split_exists(s.v)) return s;
-    s.lds = igemm_split_lds_bytes(s.v, a.PLS);
-    if (s.lds > (size_t)kMaxLds) return s;
+    a.Hs = t.Hs;
+    a.LW = t.LW;
+    a.LRW = a.PLS = t.LRW;
     a.inv_P = 1.0f / (float)a.P;
     a.inv_Hs = 1.0f / (float)a.Hs;
     a.inv_LW = 1.0f / (float)a.LW;
     a.inv_TQ = 1.0f / (float)a.TQ;
-    const long long tiles = (((long long)a.N * a.P * a.TQ + TM - 1) / TM) * strips;
-    if ((long long)a.N * a.P * a.TQ >= (1LL << 30) || tiles * ceil_div(a.Kp, TK) >= (1 << 24)) return s;
     a.n_mt = (int)tiles;
     a.n_kt = ceil_div(a.Kp, TK);
     a.n_stage = ceil_div(a.Cb, 4 * g);
@@ -767,6 +786,10 @@ struct SplitTimes {
     double lone, busy;  // clocks of a workgroup alone on its CU, and of one among others
     int resident;
 };
+// Clocks of a staged workgroup: a round among others and alone, and what stands before and behind its rounds.
+double split_round(int fm, bool fwd_wt) { return (fm == 4 ? 814 : 560) + (fwd_wt ? 161 : 0); }
+double split_round_alone(int fm, bool fwd_wt) { return (fm == 4 ? 952 : 702) + (fwd_wt ? 253 : 0); }
+double split_start(int fm) { return 7244 + 775 * fm; }
 SplitTimes split_times(const SplitPlan &s, bool scatter)
 {
     const IgemmArgs &a = s.a;
@@ -786,8 +809,8 @@ SplitTimes split_times(const SplitPlan &s, bool scatter)
     const IgemmSplitVariant &v = s.v;
     const bool wide = v.fm == 4;
     const double steps = ceil_div(a.n_stage, v.kw), rounds = v.g * a.R * a.S, k = scatter ? 2.06 : 1.0;
-    t.busy = v.kw * steps * (rounds * ((wide ? 814 : 560) + fw * 161) + v.ni * 225 + 120) + 1417 * v.fm * v.kw * k;
-    t.lone = std::max(t.busy, (7244 + 775 * v.fm) * k + steps * (rounds * ((wide ? 952 : 702) + fw * 253) + v.ni * 262 + 281));
+    t.busy = v.kw * steps * (rounds * split_round(v.fm, a.fwd_wt != 0) + v.ni * 225 + 120) + 1417 * v.fm * v.kw * k;
+    t.lone = std::max(t.busy, split_start(v.fm) * k + steps * (rounds * split_round_alone(v.fm, a.fwd_wt != 0) + v.ni * 262 + 281));
     t.resident = std::max(1, std::min((int)(kMaxLds / s.lds), v.kw == 2 ? 1 : wide ? 2 : 3));
     return t;
 }
@@ -837,6 +860,11 @@ double split_line(const SplitPlan &s, double us)
     if (a.R * a.S == 1 && s.v.kw == 2) return 0.75;
     return strided ? 0.85 : kSplitMargin;
 }
+// Tiles of so many fragments, at the least.
+double split_tiles(const IgemmArgs &a, int wk, int fragments)
+{
+    return std::ceil((double)a.N * a.P * a.Q / (fragments * 32)) * ceil_div(a.Kp, wk * 32);
+}
 SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, bool backward)
 {
     SplitPlan best;
@@ -855,19 +883,30 @@ SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, boo
     double best_us = other_us;
     const double most_error = sums_error(p) + kOwnRounding;
     auto consider = [&](const SplitPlan &c) {
-        if (!c.ok || split_error(c) > most_error) return;
+        if (!c.ok) return;
         // (staged: half a microsecond on top, which the estimate is off where a launch is short)
         // (more shares to stage than rounds to do it beside: 256 pixels under 1x1, 16 channels a step, 0.66 - 1.33 of the other plan's time
         // where the estimate without this factor says 0.8, 144 <- 564 at 29x30, N = 123, 168 -> 224 us; in wider steps 0.49 - 0.97)
         const double crowded = c.nw == 0 && c.v.ni > c.v.g * R * S ? 1.3 : 1.0;
         const double us = crowded * split_us(c, scatter) + (c.nw > 0 ? 0 : 0.5) + (c.a.fwd_wt ? 0 : transform);
-        if (us < best_us && us < split_line(c, other_us) * other_us) {
+        if (us < best_us && us < split_line(c, other_us) * other_us && split_error(c) <= most_error) {
             best = c;
             best_us = us;
         }
     };
+    // (the tensors alone take longer: nothing to look at)
+    SplitPlan any;
+    any.a = p.a;
+    any.a.R = R;
+    any.a.S = S;
+    if (tensor_bytes(any.a, scatter) / 3.7e6 >= other_us) return best;
     for (const FwdWeights &w : {FwdWeights{}, fw}) {
         for (const auto &t : kSplitTiles) {
+            // (... or a launch whose rounds are dealt over all CUs, or one tile)
+            const double rounds = (double)ceil_div(p.a.Cb, 4) * R * S;
+            const double clocks = std::max(split_tiles(p.a, t[0], t[1] * t[2]) * rounds * split_round(t[2], w.taps > 0) / 256,
+                                           split_start(t[2]) + rounds / t[3] * split_round_alone(t[2], w.taps > 0));
+            if (clocks / 2.1e3 + 1.7 >= std::min(best_us, kSplitMargin * other_us) - (w.taps > 0 ? 0 : transform)) continue;
             for (int g = 1; g <= 2; ++g) {
                 if (g > 1 && R * S > 1) continue;
                 for (int strips = 1; strips <= 4; ++strips) consider(try_split(p, R, S, w, t[0], t[1], t[2], t[3], g, strips));
@@ -1464,29 +1503,29 @@ SplitClassesPlan try_split_classes(const conv_plan *p, int wk, int wm, int fm, i
     auto taps = [&](int i) { return p->bwd[i].x.R2 * p->bwd[i].x.S2; };
     std::stable_sort(order, order + p->n_bwd, [&](int i, int j) { return taps(i) > taps(j); });
     // (a variant's shares are those of the class that needs most)
-    int ni = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        int grid = 0, most = 0;
-        s.lds = 0;
-        for (int k = 0; k < 4; ++k) {
-            if (k >= p->n_bwd) {
-                s.c.end[k] = grid;
-                continue;
-            }
-            const int i = order[k];
-            const FwdWeights fw = class_weights(p, i);
-            if (fw.taps == 0) return SplitClassesPlan{};
-            const SplitPlan c = try_split(p->bwd[i].p, p->bwd[i].x.R2, p->bwd[i].x.S2, fw, wk, wm, fm, kw, g, strips, ni);
-            if (!c.ok) return SplitClassesPlan{};
-            s.c.cls[k] = c.a;
-            s.c.end[k] = grid += c.grid;
-            s.lds = std::max(s.lds, c.lds);
-            s.v = c.v;
-            most = std::max(most, c.v.ni);
-        }
-        ni = most;
+    int ni = 0, grid = 0;
+    for (int k = 0; k < p->n_bwd; ++k) {
+        const SplitTile t = split_tile(p->bwd[order[k]].p, p->bwd[order[k]].x.R2, p->bwd[order[k]].x.S2, wm, fm, g, strips);
+        if (!t.ok) return SplitClassesPlan{};
+        ni = std::max(ni, t.ni);
     }
-    s.ok = igemm_split_classes_exist(s.v);
+    if (!igemm_split_classes_exist(IgemmSplitVariant{wk, wm, fm, kw, g, ni, 1})) return SplitClassesPlan{};
+    for (int k = 0; k < 4; ++k) {
+        if (k >= p->n_bwd) {
+            s.c.end[k] = grid;
+            continue;
+        }
+        const int i = order[k];
+        const FwdWeights fw = class_weights(p, i);
+        if (fw.taps == 0) return SplitClassesPlan{};
+        const SplitPlan c = try_split(p->bwd[i].p, p->bwd[i].x.R2, p->bwd[i].x.S2, fw, wk, wm, fm, kw, g, strips, ni);
+        if (!c.ok) return SplitClassesPlan{};
+        s.c.cls[k] = c.a;
+        s.c.end[k] = grid += c.grid;
+        s.lds = std::max(s.lds, c.lds);
+        s.v = c.v;
+    }
+    s.ok = true;
     return s;
 }
 
@@ -1543,16 +1582,22 @@ void plan_bwd_split(conv_plan *p)
         }
         old_us += (p->bwd_quad ? 3.0 : 0.0) + (p->bwd[0].p.a.fwd_wt ? 0 : transform_launch_us(weights));
         double best_us = (old_us < 20 ? 0.75 : 0.88) * old_us;  // (above: 0.9 - 1.3 of the time)
-        for (const auto &t : kSplitTiles)
+        for (const auto &t : kSplitTiles) {
+            // (the rounds of all classes dealt over all CUs take longer: nothing to look at)
+            double clocks = 0;
+            for (int i = 0; i < p->n_bwd; ++i)
+                clocks += split_tiles(p->bwd[i].p.a, t[0], t[1] * t[2]) * ceil_div(p->bwd[i].p.a.Cb, 4) * p->bwd[i].x.R2 * p->bwd[i].x.S2;
+            if (clocks * split_round(t[2], true) / 256 / 2.1e3 + 1.2 >= best_us) continue;
             for (int strips = 1; strips <= 4; ++strips) {
                 const SplitClassesPlan c = try_split_classes(p, t[0], t[1], t[2], t[3], 1, strips);
-                if (!c.ok || classes_error(p, c) > most_error + kOwnRounding) continue;
+                if (!c.ok) continue;
                 const double us = classes_us(p, c);
-                if (us < best_us) {
+                if (us < best_us && classes_error(p, c) <= most_error + kOwnRounding) {
                     p->bwd_classes = c;
                     best_us = us;
                 }
             }
+        }
         return;
     }
     p->bwd_split = plan_split(p->bwd[0].p, p->bwd[0].x.R2, p->bwd[0].x.S2, class_weights(p, 0), true);
@@ -2511,22 +2556,30 @@ bool plan_upd_ring(conv_plan *p)
     return true;
 }
 
-// A plan of the update on the bf16 instructions, `splits` ranges of pixels.
+// Whether a variant of the update on the bf16 instructions serves the layer.
+bool upd_split_fits(const conv_plan *p, const UpdSplitVariant &v)
+{
+    const conv_desc_t &d = p->d;
+    const conv_info_t &f = p->info;
+    if (v.t == 1 ? v.pi != v.sp : false) return false;
+    const double npix = (double)d.N * f.P * f.Q;
+    // exact small divisions, 24-bit products, 32-bit byte offsets
+    if (npix >= 3.9e6 || (double)(d.N + 1) * f.P >= 3.9e6 || (double)d.H * d.W >= 8.0e6 || (double)f.in_bytes >= 4.0e9 ||
+        (double)f.out_bytes >= 4.0e9 || (double)f.dwt_bytes >= 4.0e9)
+        return false;
+    if (v.t > 1) {  // the positions under a stage
+        const long long crossings = (v.sp - 2) / f.Q + 1, gap = std::max(0, v.t - d.stride);
+        if ((v.sp - 1LL) * d.stride + v.t + crossings * gap > v.pi) return false;
+    }
+    return true;
+}
+// ... and its plan with `splits` ranges of pixels.
 UpdSplitPlan try_upd_split(const conv_plan *p, const UpdSplitVariant &v, int splits)
 {
     UpdSplitPlan s;
     const conv_desc_t &d = p->d;
     const conv_info_t &f = p->info;
-    if (!upd_split_exists(v) || splits < 1 || (v.t == 1 ? v.pi != v.sp : false)) return s;
     const double npix = (double)d.N * f.P * f.Q;
-    // exact small divisions, 24-bit products, 32-bit byte offsets
-    if (npix >= 3.9e6 || (double)(d.N + 1) * f.P >= 3.9e6 || (double)d.H * d.W >= 8.0e6 || (double)f.in_bytes >= 4.0e9 ||
-        (double)f.out_bytes >= 4.0e9 || (double)f.dwt_bytes >= 4.0e9)
-        return s;
-    if (v.t > 1) {  // the positions under a stage
-        const long long crossings = (v.sp - 2) / f.Q + 1, gap = std::max(0, v.t - d.stride);
-        if ((v.sp - 1LL) * d.stride + v.t + crossings * gap > v.pi) return s;
-    }
     UpdArgs &a = s.a;
     memset(&a, 0, sizeof(a));
     const int np = (int)npix;
@@ -2557,19 +2610,26 @@ double upd_split_error(const conv_plan *p, const UpdArgs &a)
            (a.splits > 1 ? ceil_div(a.splits, chains) / 2.0 + std::log2((double)chains) / 2 : 0);
 }
 
+// Clocks of a CU's matrix cores, LDS and vector units that a stage takes.
+double upd_split_stage(const UpdSplitVariant &v)
+{
+    const int waves = v.wc * v.wk, frags = v.t * v.fc * v.fk, q = v.sp / 16;
+    const double mfma = q * frags * 192.0, reads = q * (v.t * v.fc + v.fk) * 6.0;
+    const double items = ceil_div(v.wc * v.fc * 4 * v.pi, waves * 64) + ceil_div(v.wk * v.fk * 4 * v.sp, waves * 64);
+    return (0.25 * mfma + 116 * items + 8.35 * reads + 47) * (waves / 4.0);
+}
 // What such an update takes, in microseconds, the reduce launch included: the form of ring_estimate_us.  Fitted to 14 700 launches
 // (250 drawn layers, every variant, 192 ... 1024 workgroups; three sets of tensors in turn): rms error 10 %, the choice 2 % behind the
-// fastest.
-double upd_split_us(const conv_plan *p, const UpdSplitPlan &s)
+// fastest.  (From `limit` on, any bound beyond it will do.)
+double upd_split_us(const conv_plan *p, const UpdSplitPlan &s, double limit)
 {
     const UpdSplitVariant &v = s.v;
     const UpdArgs &a = s.a;
     const conv_info_t &f = p->info;
     const int waves = v.wc * v.wk, frags = v.t * v.fc * v.fk, q = v.sp / 16;
     const double simd = waves / 4.0, mfma = q * frags * 192.0, reads = q * (v.t * v.fc + v.fk) * 6.0;
-    const double items = ceil_div(v.wc * v.fc * 4 * v.pi, waves * 64) + ceil_div(v.wk * v.fk * 4 * v.sp, waves * 64);
     const double stages = ceil_div(a.rows_per_split, v.sp);
-    const double shared = (0.25 * mfma + 116 * items + 8.35 * reads + 47) * simd;
+    const double shared = upd_split_stage(v);
     const double busy = stages * shared + 399.0 * frags * simd;
     const double lone = std::max(busy, 4056 + 262.0 * frags + stages * std::max(0.94 * mfma + 23.8 * reads + 806, shared));
     // (waves per SIMD that the registers leave room for)
@@ -2580,16 +2640,10 @@ double upd_split_us(const conv_plan *p, const UpdSplitPlan &s)
     const double out_b = (double)f.out_bytes, in_b = p->d.R * p->d.S > 1 ? (double)f.in_bytes : (double)p->d.N * f.Cp * f.P * f.Q * 4;
     const double again = p->d.R * ceil_div(p->d.S, v.t), launch = 2.8;
     const double bound[3] = {t / 2.1e3 + launch, launch + (in_b * a.n_kt + out_b * a.n_ct) * again / 14.6e6, launch + (in_b + out_b) / 4.0e6};
-    double us = shaded(bound);
-    if (a.splits > 1) us += 2.9 + a.splits * (double)f.dwt_bytes * 2 / 4.84e6;
-    return us;
+    const double reduce = a.splits > 1 ? 2.9 + a.splits * (double)f.dwt_bytes * 2 / 4.84e6 : 0;
+    const double least = std::max(std::max(bound[0], bound[1]), bound[2]) + reduce;
+    return least >= limit ? least : shaded(bound) + reduce;
 }
-static const UpdSplitVariant kUpdSplit[] = {
-    {1, 2, 2, 2, 2, 16, 16}, {1, 2, 2, 4, 2, 16, 16}, {1, 2, 1, 2, 4, 32, 32}, {1, 2, 1, 2, 2, 32, 32}, {1, 1, 2, 2, 2, 32, 32},
-    {1, 1, 1, 2, 2, 32, 32}, {1, 1, 1, 2, 2, 64, 64}, {1, 2, 1, 4, 2, 16, 16}, {1, 1, 1, 4, 2, 32, 32},
-    {3, 1, 1, 2, 2, 32, 64}, {3, 1, 1, 2, 4, 32, 64}, {3, 1, 1, 2, 2, 16, 32}, {3, 1, 1, 2, 2, 16, 64}, {3, 1, 1, 2, 4, 16, 64},
-    {3, 1, 1, 2, 4, 16, 32}, {3, 1, 1, 1, 4, 32, 64}, {3, 1, 1, 4, 2, 16, 32},
-    {4, 1, 1, 2, 2, 32, 64}, {4, 1, 1, 2, 4, 32, 64}, {4, 1, 1, 2, 2, 16, 32}, {5, 1, 1, 2, 2, 16, 32}};
 
 // Whether the update runs on the bf16 instructions: where the estimate says that this is at least 8 % faster than `fp32_us`, and the
 // sums are no less exact.  (Above that line 0.99 - 1.09 of the time, 11 of 161 drawn layers: 32 -> 64 3x3 at 147x147, N = 31, 216 -> 235 us.)
@@ -2603,22 +2657,26 @@ void plan_upd_split(conv_plan *p, double fp32_us)
         UpdSplitVariant v{};
         int splits = 1;
         if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d,%d", &v.t, &v.fc, &v.fk, &v.wc, &v.wk, &v.sp, &v.pi, &splits) < 7) return;
-        p->upd_split = try_upd_split(p, v, splits);
+        if (splits >= 1 && upd_split_exists(v) && upd_split_fits(p, v)) p->upd_split = try_upd_split(p, v, splits);
     } else if (!getenv("CONVMI_UPD_RING") && !getenv("CONVMI_UPD_WINDOW")) {
         const double most_error = planned_upd_error(p) + kOwnRounding;
         // (and by 1.5 us: below 20 us the estimates are as far apart as that)
         double best_us = 0.92 * fp32_us - 1.5;
-        for (const UpdSplitVariant &v : kUpdSplit) {
+        for (int i = 0; const UpdSplitVariant *e = upd_split_variant(i); ++i) {
+            const UpdSplitVariant &v = *e;
             const int blocks = ceil_div(p->info.Cp, v.wc * v.fc * 32) * ceil_div(p->info.Kp, v.wk * v.fk * 32) * p->d.R * ceil_div(p->d.S, v.t);
+            // (a launch whose stages are dealt over all CUs, or of one workgroup, takes longer: nothing to look at)
+            const double clocks = std::max(blocks * ((double)p->d.N * p->info.P * p->info.Q / v.sp) * upd_split_stage(v) / 256, 4056.0);
+            if (clocks / 2.1e3 + 2.8 >= best_us || !upd_split_fits(p, v)) continue;
             int last = 0;
             for (const int target : {192, 256, 384, 512, 768, 1024}) {
                 const int splits = std::max(1, target / blocks);
                 if (splits == last) continue;
                 last = splits;
                 const UpdSplitPlan c = try_upd_split(p, v, splits);
-                if (!c.ok || upd_split_error(p, c.a) > most_error) continue;
-                const double us = upd_split_us(p, c);
-                if (us < best_us) {
+                if (!c.ok) continue;
+                const double us = upd_split_us(p, c, best_us);
+                if (us < best_us && upd_split_error(p, c.a) <= most_error) {
                     p->upd_split = c;
                     best_us = us;
                 }
@@ -2734,9 +2792,7 @@ void plan_upd_shared(conv_plan *p, double ring_us)
 {
     p->upd_shared = UpdSharedPlan{};
     if (p->d.dtype != CONV_BF16) return;
-    const char *env = getenv("CONVMI_UPD_SHARED");
-    const bool any = env && strcmp(env, "any") == 0;
-    if (env && !any) {
+    if (const char *env = getenv("CONVMI_UPD_SHARED")) {
         UpdSharedVariant v{};
         int splits = 1;
         if (sscanf(env, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &v.t, &v.st, &v.fc, &v.fk, &v.wc, &v.wk, &v.wp, &v.sp, &v.pi, &v.nb, &splits) < 10) return;
@@ -2744,7 +2800,7 @@ void plan_upd_shared(conv_plan *p, double ring_us)
     } else if (!getenv("CONVMI_UPD_RING") && !getenv("CONVMI_UPD_WINDOW")) {
         const double most_error = planned_upd_error(p) + kOwnRounding;
         double best_us = shared_line_us(p, ring_us);
-        if (any) best_us = 1e9;
+        if (best_us <= 0) return;
         for (int i = 0; const UpdSharedVariant *v = upd_shared_variant(i); ++i) {
             if ((v->t == 1) != (p->d.S == 1)) continue;
             const int blocks = ceil_div(p->info.Cp, v->wc * v->fc * 32) * ceil_div(p->info.Kp, v->wk * v->fk * 32) * p->d.R * ceil_div(p->d.S, v->t);
@@ -2754,9 +2810,9 @@ void plan_upd_shared(conv_plan *p, double ring_us)
                 if (splits == last) continue;
                 last = splits;
                 const UpdSharedPlan c = try_upd_shared(p, *v, splits);
-                if (!c.ok || upd_shared_error(p, c) > most_error) continue;
+                if (!c.ok) continue;
                 const double us = upd_shared_us(p, c);
-                if (us < best_us) {
+                if (us < best_us && upd_shared_error(p, c) <= most_error) {
                     p->upd_shared = c;
                     best_us = us;
                 }

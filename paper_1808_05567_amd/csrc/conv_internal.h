@@ -319,6 +319,7 @@ struct UpdSplitVariant {
     int t, fc, fk, wc, wk, sp, pi;
 };
 bool upd_split_exists(const UpdSplitVariant &v);
+const UpdSplitVariant *upd_split_variant(int i);  // the i-th, null behind the last
 size_t upd_split_lds_bytes(const UpdSplitVariant &v);
 hipError_t launch_upd_split(const UpdSplitVariant &v, const UpdArgs &a, int grid, hipStream_t stream);
 // bf16: (wc*fc*32) x (wk*fk*32) blocks under t taps of a filter row, both operands staged for all waves; st: 2 for more taps than one

@@ -353,6 +353,10 @@ static const UpdSplitEntry *find(const UpdSplitVariant &v)
     return nullptr;
 }
 bool upd_split_exists(const UpdSplitVariant &v) { return find(v) != nullptr; }
+const UpdSplitVariant *upd_split_variant(int i)
+{
+    return i >= 0 && i < (int)(sizeof(g_upd_split) / sizeof(g_upd_split[0])) ? &g_upd_split[i].v : nullptr;
+}
 
 size_t upd_split_lds_bytes(const UpdSplitVariant &v)
 {
