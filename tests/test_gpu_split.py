@@ -172,15 +172,16 @@ def test_scale_does_not_matter(which, switch, variants, exponents):
 
 @pytest.mark.parametrize("which,switch,variants", SPECIAL, ids=["fwd", "bwd", "upd"])
 def test_tiny_values_among_others(which, switch, variants):
-    """One channel of 2^-120 beside ordinary ones, in either operand, and one that only another's 2^60 brings back: every channel of the
-    result is as exact as in a tensor of its own.  And values between 2^-108 and 2^-107, whose last bf16 numbers are denormal."""
+    """One channel of 2^-120 beside ordinary ones, in either operand, one that only another's 2^60 brings back, and sums of 2^-120 beside
+    others of 2^-50: every channel of the result is as exact as in a tensor of its own.  And values between 2^-108 and 2^-107, whose
+    last bf16 numbers are denormal."""
     shape = (2, 40, 48, 12, 13, 3, 3, 1, 1)
     rng = np.random.default_rng(11)
     I, Wt, dO = make_inputs(shape, F32, layer_id=57)
     few = 2.0 ** -108 * rng.uniform(1, 2, I.shape)
     tiny = np.float32(2.0 ** -120)
     cases = []
-    for kind in ("a row", "a term", "denormal parts"):
+    for kind in ("a row", "a term", "a sum", "denormal parts"):
         x, w, g = I.copy(), Wt.copy(), dO.copy()
         if kind == "denormal parts":
             x = few.astype(np.float32)
@@ -188,6 +189,14 @@ def test_tiny_values_among_others(which, switch, variants):
             if which == "upd":
                 g = (dO * np.float32(2.0 ** 40)).astype(np.float32)
             w *= np.float32(2.0 ** 40)
+        elif kind == "a sum":  # (of operands that lose nothing, beside sums of 2^-50 whose small products are no denormal numbers)
+            x *= np.float32(2.0 ** -50)
+            g *= np.float32(2.0 ** -50)
+            w[5] *= np.float32(2.0 ** -70)
+            w[:, 7] *= np.float32(2.0 ** -70)
+            if which == "upd":
+                g = dO.copy()
+                g[:, 5] *= np.float32(2.0 ** -70)
         elif kind == "a row":  # (of the result: a channel of its weights, or of dO, or of the input)
             w[5] *= tiny
             w[:, 7] *= tiny

@@ -46,6 +46,31 @@ def test_matches_oracle(shape, rows):
         L.close()
 
 
+# The widest rows of three and of four chunks of the ring, and one more: more than eight steps a workgroup, so that the ring comes round.
+# Layer, then groups of 32 result channels that fit the LDS forward and backward.
+WIDE = [((3, 64, 32, 430, 255), "1", "12"), ((2, 40, 64, 700, 192), "12", "1"), ((2, 32, 40, 690, 191), "12", "12"), ((2, 32, 40, 690, 256), "", "")]
+
+
+@pytest.mark.parametrize("rows", ["1", "2"])
+@pytest.mark.parametrize("shape,fwd,bwd", WIDE, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else s or "none")
+def test_rows_that_leave_the_ring_no_slack(shape, fwd, bwd, rows):
+    N, C, K, H, W = shape
+    I, Wt, dO = make_inputs(shape + (3, 3, 1, 1), BF16, layer_id=74)
+    L = _layer(shape, rows)
+    try:
+        for which, pass_, fits in (("fwd", conv.PASS_FWD, fwd), ("bwd", conv.PASS_BWD_DATA, bwd)):
+            on = conv.conv_describe(L.h, pass_).partition(" instead=igemm_stream,")[2]
+            assert bool(on) == (rows in fits), (which, on)
+            if not on:
+                continue
+            assert int(on.partition("steps")[2].partition(",")[0]) > 8, on
+            print(shape, which, rows, flush=True)
+            ref = oracle.fwd(I, Wt, 1, 1) if which == "fwd" else oracle.bwd_data(dO, Wt, H, W, 1, 1)
+            assert_close(run_pass(L, which, **(dict(I=I, Wt=Wt) if which == "fwd" else dict(dO=dO, Wt=Wt))), ref, BF16, which)
+    finally:
+        L.close()
+
+
 def test_infinities_reach_the_pixels_around_them_only():
     shape = (2, 40, 64, 11, 13)
     I, Wt, _ = make_inputs(shape + (3, 3, 1, 1), BF16, layer_id=72)
