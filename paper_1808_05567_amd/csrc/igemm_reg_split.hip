@@ -161,7 +161,7 @@ __global__ __launch_bounds__(NW * 64, FK * FM == 1 ? 4 : FK * FM == 2 ? 3 : 2) v
             big[i][j] += small[i][j];
             most = max_magnitude(most, big[i][j]);
         }
-    // Infinite, NaN or tiny sums: the wave's share again.
+    // Infinite or NaN sums: the wave's share again.
     if (__builtin_expect(sums_need_fp32(most), 0)) {
         static_for<0, FK * FM>([&](auto fc) {
             constexpr int i = decltype(fc)::value / FM, j = decltype(fc)::value % FM;

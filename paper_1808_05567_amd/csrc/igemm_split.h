@@ -368,7 +368,7 @@ __device__ __forceinline__ void igemm_split_tile(const IgemmArgs &a, const int b
         }
         return;
     }
-    // Infinite, NaN or tiny sums: all of the wave's again.
+    // Infinite or NaN sums: all of the wave's again.
     for (int j = 0; j < FO; ++j) {
         const Pixel p = pixel(m_wave + j * 32);
         const unsigned at = place(p);

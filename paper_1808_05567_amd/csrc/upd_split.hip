@@ -268,7 +268,7 @@ __global__ __launch_bounds__(WC *WK * 64, 2) void upd_split_kernel(const UpdArgs
                 for (int j = 0; j < FK; ++j) store(big[t][i][j], t, i, j);
         return;
     }
-    // Infinite, NaN or tiny sums: the wave's block again on the fp32 instructions, a pixel to a lane half, straight from memory, all taps
+    // Infinite or NaN sums: the wave's block again on the fp32 instructions, a pixel to a lane half, straight from memory, all taps
     // together (five: one by one, for the registers).  All of a tensor NaN, 64 images 64 -> 64 3x3 at 56x56 309 us, 143 on the fp32
     // instructions alone; 512 -> 1024 1x1 stride 2 at 28x28 296 and 110 (fragment by fragment, a pair at a time: 699 and 667).  Four pairs of pixels are on their way while four multiply; chains of 32 pixels are
     // summed apart.
