@@ -849,13 +849,18 @@ constexpr double kSplitMargin = 0.96;
 // estimate is too low, 1 100 passes of drawn layers: staged 1x1 with 96 channels or fewer on a side 0.73 - 1.38 (64 -> 80 at 73x73,
 // N = 19, 22 -> 27 us; both wait for memory); staged 1x1 in two sets of waves 0.77 - 1.23; staged under a stride 0.83 - 1.28; in
 // registers under a stride 0.74 - 1.14 (36 -> 44 3x3 at 20x21, N = 52, 6.8 -> 7.7: half of every line read is not used), in four waves
-// or on short reductions in less than 10 us 0.90 - 1.18; in registers under 1x1 in more than 1 200 tiles 0.9 - 1.14.
+// or on short reductions in less than 10 us 0.90 - 1.18 (larger filters from 0.82 on 0.99 - 1.12: 64 -> 64 3x3 at 56x56, N = 2, 8.6 -> 9.6);
+// in eight waves under larger filters from 0.92 on 0.96 - 1.06, in the mean 1.003 (65 passes, 8 - 15 us; 1x1 0.95 - 0.97); in registers
+// under 1x1 in more than 1 200 tiles 0.9 - 1.14.
 double split_line(const SplitPlan &s, double us)
 {
     const IgemmArgs &a = s.a;
     const bool strided = a.stride > 1 || a.ostr > 1;
     if (s.nw > 0 && a.R * a.S == 1 && a.total > 1200) return 0.8;
-    if (s.nw > 0) return strided ? 0.83 : a.n_stage >= 24 && (s.nw >= 8 || us >= 10) ? 0.96 : us < 10 ? 0.85 : 0.92;
+    const bool filter = a.R * a.S > 1;
+    if (s.nw > 0 && strided) return 0.83;
+    if (s.nw > 0 && a.n_stage >= 24 && (s.nw >= 8 || us >= 10)) return filter && s.nw >= 8 ? 0.92 : 0.96;
+    if (s.nw > 0) return us >= 10 ? 0.92 : filter ? 0.82 : 0.85;
     if (a.R * a.S == 1 && std::min(4 * a.Cb, a.Kp) <= 96) return 0.74;
     if (a.R * a.S == 1 && s.v.kw == 2) return 0.75;
     return strided ? 0.85 : kSplitMargin;
@@ -877,6 +882,9 @@ SplitPlan plan_split(const IgemmPlan &p, int R, int S, const FwdWeights &fw, boo
         return f && fw.taps == 0 ? best : try_split(p, R, S, f ? fw : FwdWeights{}, wk, wm, fm, kw, g, strips);
     }
     if (variant_asked_for()) return best;
+    // (1x1 layers of one fragment of channels in the register-operand kernel, many tiles of pixels: it takes 0.5 - 0.7 of its estimate, and
+    // this 1.15 - 1.46 of that (from 880 tiles: 192 -> 32 at 35x35, N = 45, 11.9 -> 16.6 us, 316 -> 32 at 51x53, N = 90, 77 -> 113); up to 640 tiles 0.73 - 1.03)
+    if (p.reg && R * S == 1 && p.v.fk * p.v.fm == 1 && p.a.n_kt == 1 && p.a.total > 700) return best;
     const bool scatter = p.a.zero_fill != 0;
     const double transform = backward ? transform_launch_us((double)p.a.Cb * R * S * p.a.Kp * 16) : 0;
     const double other_us = estimate_us(p, scatter) + (p.a.fwd_wt ? 0 : transform);

@@ -531,3 +531,21 @@ def test_planning_what_runs_on_the_bf16_instructions_costs_less_than_the_rest_of
                 least[k][i] = min(least[k][i], time.perf_counter() - t0)
                 lib.conv_destroy(h)
     assert sum(least["with"]) < 1.8 * sum(least["without"]), {k: sum(v) / len(layers) for k, v in least.items()}
+
+
+# fp32, pass, layer: whether it runs on the bf16 instructions.  Beside each the time there and on the fp32 instructions, us.
+@pytest.mark.parametrize("which,shape,on", [
+    (0, (45, 192, 32, 35, 35, 1, 1, 1), False),   # 16.6, 11.9
+    (0, (23, 192, 32, 35, 35, 1, 1, 1), False),   # 10.8, 8.5
+    (1, (90, 32, 316, 51, 53, 1, 1, 1), False),   # 113, 77
+    (0, (166, 164, 32, 48, 51, 1, 1, 1), True),   # 84, 151
+    (0, (2, 64, 64, 56, 56, 3, 3, 1), False),     # 9.6, 8.6
+    (0, (1, 296, 276, 18, 18, 3, 3, 1), False),   # 13.1, 12.9
+    (0, (8, 512, 512, 7, 7, 3, 3, 1), True),
+    (0, (28, 128, 128, 28, 28, 3, 3, 1), True)], ids=str)  # 47, 73
+def test_fp32_layers_stay_on_the_fp32_instructions_where_those_are_faster(which, shape, on):
+    h = conv.conv_create(*shape, (shape[5] - 1) // 2, dtype=conv.CONV_F32)
+    try:
+        assert (" on_bf16x3=" in conv.conv_describe(h, which)) == on
+    finally:
+        conv.conv_destroy(h)
