@@ -19,8 +19,8 @@ what this device sustains on an MFMA issue loop, a 1 GiB copy and an L2 -> LDS
 streaming loop.  Prints ONE JSON line.
 
 --table additionally times every requested layer/pass on its own (in the cycling
-loop and repeated back to back) and writes a per-layer table (TFLOP/s, % of MFMA
-peak, % of the layer's roofline ceiling at the published and at the measured
+loop and repeated back to back) and writes a per-layer table (TFLOP/s, % of the peak
+of the MFMAs that it runs on, % of the layer's roofline ceiling at the published and at the measured
 ceilings) as JSON into --table-dir and as text to stderr.
 """
 from __future__ import annotations
@@ -40,6 +40,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 MFMA_PEAK = {"f32": 157.3, "bf16": 2500.0}   # TFLOP/s, dense, published MI355X figures
+SPLIT_PEAK = MFMA_PEAK["bf16"] / 6            # fp32 as three bf16 numbers: six bf16 products for one
 HBM_PEAK = 8.0                                # TB/s
 N_BATCH = 256
 
@@ -182,6 +183,17 @@ def written_bytes(l, N, es, which):
     if which == "bwd":
         return N * l.C * l.H * l.W * es
     return l.K * l.C * l.R * l.S * 4
+
+
+def runs_on(L, which):
+    """Kernel of the pass's main launch, and the peak of the matrix instructions that it issues (None: the tensors' type's)."""
+    from paper_1808_05567_amd import conv
+    text = conv.conv_describe(L.h, {"fwd": conv.PASS_FWD, "bwd": conv.PASS_BWD_DATA, "upd": conv.PASS_UPD}[which])
+    for mark, peak in ((" on_bf16x3=", SPLIT_PEAK), (" instead=", None)):
+        if mark in text:
+            return text.partition(mark)[2].partition(",")[0] + "_kernel", peak
+    name = "igemm_stem" if "resident_filter_lds=" in text else text.split()[0]
+    return name + "_kernel", None
 
 
 def layer_class(l):
@@ -365,7 +377,7 @@ def shader_clock_under(work, work_ms):
 
 def summarize(layers, N, dtype_name, wall, fwd, per, steps, traffic_file):
     """Whole-workload rate, per-class rates and the roofline block of the dominant kernel."""
-    peak = MFMA_PEAK[dtype_name]
+    on = {(l.id, w): runs_on(L, w) for l, L in layers for w in PASSES}
     flops_step = sum(3 * l.flops(N) for l, _ in layers)
     ms_per_step = wall * 1e3 / steps
     value = flops_step / (wall / steps) / 1e12
@@ -375,6 +387,11 @@ def summarize(layers, N, dtype_name, wall, fwd, per, steps, traffic_file):
         ms = sum((src or per)[(l.id, which)] for l in ls)
         return fl / (ms * 1e-3) / 1e12
 
+    def peak_of(ls, passes):
+        """The rate of these launches with each one's matrix instructions at their published peak."""
+        fl = [(l.flops(N), on[(l.id, w)][1] or MFMA_PEAK[dtype_name]) for l in ls for w in passes]
+        return sum(f for f, _ in fl) / sum(f / p for f, p in fl)
+
     per_class = {}
     for cls in sorted({layer_class(l) for l, _ in layers} if per else ()):
         ls = [l for l, _ in layers if layer_class(l) == cls]
@@ -382,13 +399,14 @@ def summarize(layers, N, dtype_name, wall, fwd, per, steps, traffic_file):
         allp = sum(3 * l.flops(N) for l in ls) / (sum(per[(l.id, w)] for l in ls for w in PASSES) * 1e-3) / 1e12
         per_class[cls] = {"layers": [l.id for l in ls],
                           "per_pass_tflops": {w: round(tf[w], 2) for w in PASSES},
-                          "per_pass_pct_of_mfma_peak": {w: round(100 * tf[w] / peak, 1) for w in PASSES},
-                          "tflops": round(allp, 2), "pct_of_mfma_peak": round(100 * allp / peak, 1)}
-    # Dominant kernel: the implicit-GEMM kernel (for a first layer its resident-filter form:
-    # the same tiles and MFMA layout).  A forward launch is exactly one launch of it,
-    # so the forward events of the timed steps are its launch durations: achieved =
+                          "per_pass_pct_of_mfma_peak": {w: round(100 * tf[w] / peak_of(ls, [w]), 1) for w in PASSES},
+                          "tflops": round(allp, 2), "pct_of_mfma_peak": round(100 * allp / peak_of(ls, PASSES), 1)}
+    # Dominant kernels: the implicit-GEMM kernels.  A forward launch is exactly one launch of one,
+    # so the forward events of the timed steps are their launch durations: achieved =
     # algorithmic flops of the forward launches / their summed duration.
     all_l = [l for l, _ in layers]
+    peak = peak_of(all_l, ["fwd"])
+    names = [on[(l.id, "fwd")][0] for l in all_l]
     achieved = rate(all_l, "fwd", fwd)
     # HBM bytes per implicit-GEMM launch (forward and backward launches together: the counter
     # run cannot tell them apart), from the committed rocprofv3 counter summary of this same
@@ -398,19 +416,23 @@ def summarize(layers, N, dtype_name, wall, fwd, per, steps, traffic_file):
         try:
             ks = json.load(open(traffic_file))["kernels"]
             ig = [(v["calls"], v["fetch_bytes"] + v["write_bytes"]) for k, v in ks.items()
-                  if "igemm_kernel" in k or "igemm_stem_kernel" in k]
+                  if "::igemm_" in k]
             traffic = round(sum(c * b for c, b in ig) / sum(c for c, _ in ig))
         except Exception:
             traffic = None
-    roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
+    roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": round(peak, 2), "unit": "TFLOP/s",
                 "frac": round(achieved / peak, 4), "traffic": traffic,
-                "kernel": "igemm_kernel (the forward launches of the workload's layers)",
+                "kernel": "the forward launches of the workload's layers: " +
+                          ", ".join("%d of %s" % (names.count(n), n) for n in sorted(set(names), key=lambda n: -names.count(n))),
+                "peak_is": "published dense MFMA peak: %g TFLOP/s for %s MFMAs%s" % (
+                    MFMA_PEAK[dtype_name], dtype_name, "; bf16's by six, %.1f, for fp32 as three bf16 numbers; by the flops that "
+                    "run on each" % SPLIT_PEAK if any(p for _, p in on.values()) else ""),
                 "per_pass_tflops": {w: round(rate(all_l, w), 2) for w in PASSES} if per else None}
     es = 2 if dtype_name == "bf16" else 4
     alg = {w: sum(algorithmic_bytes(l, N, es, w) for l in all_l) for w in PASSES}
     roofline["algorithmic_bytes_per_step"] = alg
     return {"value": round(value, 3), "ms_per_step": round(ms_per_step, 4),
-            "pct_of_mfma_peak": round(100 * value / peak, 2), "per_class": per_class,
+            "pct_of_mfma_peak": round(100 * value / peak_of(all_l, PASSES), 2), "per_class": per_class,
             "roofline": roofline}
 
 
@@ -661,8 +683,8 @@ def layer_table(args, layers, N, dtype_name, per, ceilings):
     import torch
     from paper_1808_05567_amd import conv as _conv
     es = 2 if dtype_name == "bf16" else 4
-    peak = MFMA_PEAK[dtype_name]
     m_peak = (ceilings or {}).get("mfma_%s_tflops" % dtype_name)
+    m_split = (ceilings or {}).get("mfma_bf16_tflops")
     m_rd = (ceilings or {}).get("hbm_read_tbps")
     m_wr = (ceilings or {}).get("hbm_write_tbps")
     warm, clk = {}, {}
@@ -683,19 +705,22 @@ def layer_table(args, layers, N, dtype_name, per, ceilings):
             c = shader_clock_under(lambda: launch(L, which), warm[(l.id, which)])
             clk[(l.id, which)] = c["median"] if c else 0
 
-    def row(l, which, ms, by, extra=None, wr=None):
+    def row(l, L, which, ms, by, extra=None, wr=None):
         tf = l.flops(N) / (ms * 1e-3) / 1e12
+        split = runs_on(L, which.partition("_")[0])[1]
+        peak = split or MFMA_PEAK[dtype_name]
         ceil = min(peak, l.flops(N) / by * HBM_PEAK)
         r = {"layer": l.id, "pass": which, "ms": round(ms, 4), "tflops": round(tf, 2),
              "pct_mfma_peak": round(100 * tf / peak, 1),
              "ceiling_tflops": round(ceil, 1), "pct_ceiling": round(100 * tf / ceil, 1),
              "alg_GBps": round(by / (ms * 1e-3) / 1e9, 1)}
-        if m_peak and m_rd and m_wr:
+        m_rate = m_split / 6 if split and m_split else m_peak
+        if m_rate and m_rd and m_wr:
             # (the measured ceiling: what is read at the measured read rate, what is written at
             # the measured write rate, one after the other)
             wr = written_bytes(l, N, es, which) if wr is None else wr
             secs = (by - wr) / (m_rd * 1e12) + wr / (m_wr * 1e12)
-            mc = min(m_peak, l.flops(N) / secs / 1e12)
+            mc = min(m_rate, l.flops(N) / secs / 1e12)
             r["measured_ceiling_tflops"] = round(mc, 1)
             r["pct_measured_ceiling"] = round(100 * tf / mc, 1)
         if extra:
@@ -705,7 +730,7 @@ def layer_table(args, layers, N, dtype_name, per, ceilings):
     rows = []
     for l, L in layers:
         for which in PASSES:
-            rows.append(row(l, which, per[(l.id, which)], algorithmic_bytes(l, N, es, which),
+            rows.append(row(l, L, which, per[(l.id, which)], algorithmic_bytes(l, N, es, which),
                             {"ms_warm": round(warm[(l.id, which)], 4), "shader_clock_mhz": clk[(l.id, which)]}))
     # forward pass with bias + residual + ReLU fused into its store, timed on its own
     # (dy_blk, a tensor of the output's shape, stands in for the residual)
@@ -723,7 +748,7 @@ def layer_table(args, layers, N, dtype_name, per, ceilings):
             evs.append((a0, a1))
         torch.cuda.synchronize()
         ms = sum(x.elapsed_time(y) for x, y in evs) / len(evs)
-        rows.append(row(l, "fwd_fused", ms,
+        rows.append(row(l, L, "fwd_fused", ms,
                         algorithmic_bytes(l, N, es, "fwd") + N * l.K * l.P * l.Q * es,
                         wr=written_bytes(l, N, es, "fwd")))
     # layout conversion, timed on its own (the passes work on resident blocked tensors)
