@@ -3590,7 +3590,7 @@ static void describe_classes(const SplitClassesPlan &s, char *buf, size_t buflen
     snprintf(buf + n, buflen - n, " on_bf16x3=igemm_split_classes,%dx%d,fm%d,sets%d,groups%d,shares%d,strips%d,workgroups%d,lds%zu", s.v.wk, s.v.wm,
              s.v.fm, s.v.kw, s.v.g, s.v.ni, s.c.cls[0].n_qt, s.c.end[3], s.lds);
 }
-static conv_status_t describe_fp32_update(conv_handle_t h, char *buf, size_t buflen)
+static conv_status_t describe_update(conv_handle_t h, char *buf, size_t buflen)
 {
     if (h->upd_ring) {
         snprintf(buf, buflen,
@@ -3716,7 +3716,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
     }
     if (pass == 2 && h->upd_split.ok) {
         // (the plan on the fp32 instructions, then what runs in its place)
-        describe_fp32_update(h, buf, buflen);
+        describe_update(h, buf, buflen);
         const UpdSplitVariant &v = h->upd_split.v;
         const size_t n = strlen(buf);
         snprintf(buf + n, buflen - n, " on_bf16x3=upd_split,taps%d,%dx%d,waves_%dx%d,stage%d,positions%d,copies%d,workgroups%d", v.t, v.fc, v.fk,
@@ -3725,7 +3725,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
     }
     if (pass == 2 && h->upd_shared.ok) {
         // (the plan without the kernel that stages for all waves, then that kernel's)
-        describe_fp32_update(h, buf, buflen);
+        describe_update(h, buf, buflen);
         const UpdSharedVariant &v = h->upd_shared.v;
         const size_t n = strlen(buf);
         snprintf(buf + n, buflen - n, " instead=upd_shared,taps%d,stride%d,%dx%d,waves_%dx%dx%d,stage%d,positions%d,buffers%d,copies%d,workgroups%d",
@@ -3734,7 +3734,7 @@ conv_status_t conv_describe(conv_handle_t h, int32_t pass, char *buf, size_t buf
     }
     if (pass == 2) {
         if (!h->upd_ok) return CONV_EUNSUPPORTED;
-        return describe_fp32_update(h, buf, buflen);
+        return describe_update(h, buf, buflen);
     }
     return CONV_EINVAL;
 }

@@ -15,7 +15,8 @@
 //
 // Against the kernels of one wave to a block (upd_ring.hip, upd_window.hip) an operand comes through the L2 once for a block of up to
 // 256 x 256 channels, not of 64 x 64; against the row kernel no row is padded to runs of eight pixels and no tap is made by shifts.
-// What bounds it: bytes from the L2, 16 to 20 a clock and CU (288 -> 384 3x3 stride 2: 9 TB/s), for wide blocks the MFMAs, 0.54 of the
+// What bounds it: the way of its operands from the L2, 16 to 20 bytes a clock and CU (288 -> 384 3x3 stride 2, N = 32: 414 MB of lines, 11.5 TB/s,
+// 67 MB of them from memory; a loop that only streams gets 32 - 38), for wide blocks the MFMAs, 0.54 of the
 // time at 1.7 GHz; LDS a quarter.  Measured, reduce launch included: 288 -> 384 3x3 stride 2 at 35x35, N = 32 / 92, 42 -> 36 and 113 ->
 // 89 us; 504 -> 284 1x7 at 23x21, N = 27, 57 -> 41; 632 -> 40 7x1 at 59x60, N = 18, 113 -> 89.
 #include <algorithm>

@@ -11,7 +11,8 @@
 // What bounds it: T*FC*FK * 192 clocks of MFMAs a wave and 16 pixels, next to which stand the conversions, 88 vector instructions for
 // 16 values of a lane, and the transposing reads, six per operand; two or three waves share a SIMD and take turns.  Measured:
 // 28 images of 128 -> 128 3x3 at 28x28 76 -> 45 us; 64 of 256 -> 256 3x3 at 14x14 138 -> 86; 256 of 512 -> 1024 1x1 stride 2 at
-// 28x28 415 -> 302; 64 of 192 -> 192 1x7 at 17x17 109 -> 67 (upd_ring.hip and upd_f32_1x1.hip before).
+// 28x28 415 -> 302; 64 of 192 -> 192 1x7 at 17x17 109 -> 67 (upd_ring.hip and upd_f32_1x1.hip before; the look for bits that are lost,
+// 3 % of it, not yet in).
 #include <algorithm>
 
 #include "split_bf16.h"
