@@ -255,6 +255,54 @@ def test_tiny_values_among_others(which, switch, variants):
                 assert (norm(d) <= 1e-6 * norm(ref.numpy())).all(), (kind, v, (norm(d) / norm(ref.numpy())).max())
 
 
+# Where sums formed again meet strides, sampled pixels, cells of zeros, residue classes, strips and two sets of waves
+AGAIN = [((3, 36, 52, 15, 13, 1, 1, 2, 0), "fwd", ["4,1,4,1,2,1", "2,2,2,2,1,1", "r,1,1,8"]), ((3, 36, 52, 15, 13, 1, 1, 2, 0), "upd", ["1,2,1,4,2,16,16", "1,1,1,2,2,64,64"]),
+         ((3, 36, 52, 15, 13, 1, 1, 2, 0), "bwd", ["4,1,2,1,1,1,0", "2,2,2,2,1,1,1", "r,1,1,4,0", "r,2,2,4,1"]),
+         ((2, 40, 36, 13, 12, 3, 3, 2, 1), "fwd", ["4,1,2,2,1,2", "2,2,4,1,1,1", "r,2,1,4"]), ((2, 40, 36, 13, 12, 3, 3, 2, 1), "bwd", ["4,1,4,1,1,1", "4,1,2,2,1,1", "2,2,2,1,1,1"]),
+         ((2, 40, 36, 13, 12, 3, 3, 2, 1), "upd", ["3,1,1,2,4,16,64", "1,1,2,2,2,32,32"]), ((2, 36, 40, 9, 21, 1, 7, 1, (0, 3)), "fwd", ["4,1,2,1,1,3", "r,1,2,4"]),
+         ((2, 36, 40, 9, 21, 1, 7, 1, (0, 3)), "bwd", ["2,2,2,2,1,2,1", "r,2,2,8,1"]), ((2, 36, 40, 9, 21, 1, 7, 1, (0, 3)), "upd", ["4,1,1,2,2,32,64", "5,1,1,2,2,16,32"])]
+
+
+@pytest.mark.parametrize("kind", ["all NaN", "one NaN", "lost bits"])
+@pytest.mark.parametrize("shape,which,variants", AGAIN, ids=lambda s: s if isinstance(s, str) else "x".join(map(str, s)).replace(" ", "") if isinstance(s, tuple) else "")
+def test_sums_formed_again_under_every_geometry(shape, which, variants, kind):
+    """Operands of 2^-120 that meet 2^50 against the oracle, and NaN (of one value, or of all) where the fp32 instructions have them."""
+    N, C, K, H, W, R, S, stride, pad = shape
+    I, Wt, dO = make_inputs(shape, F32, layer_id=59)
+    a, b = {"fwd": (I, Wt), "bwd": (dO, Wt), "upd": (I, dO)}[which]
+    switch = "CONVMI_UPD_SPLIT" if which == "upd" else "CONVMI_IGEMM_SPLIT"
+    if kind == "lost bits":
+        a[...] = np.ldexp(np.ldexp(a, -120).astype(np.float32).astype(np.float64), 120)  # (what is left of it in fp32)
+        ref = {"fwd": lambda: oracle.fwd(I, Wt, stride, pad), "bwd": lambda: oracle.bwd_data(dO, Wt, H, W, stride, pad),
+               "upd": lambda: oracle.upd(I, dO, R, S, stride, pad)}[which]()
+        a *= np.float32(2.0 ** -120)
+        b *= np.float32(2.0 ** 50)
+    elif kind == "all NaN":
+        a[...] = np.nan
+    else:
+        a.reshape(-1)[a.size // 2 + 3] = np.nan
+    kw = {"fwd": dict(I=I, Wt=Wt), "bwd": dict(dO=dO, Wt=Wt), "upd": dict(I=I, dO=dO)}[which]
+    got = {}
+    for v in ["0"] + variants:
+        L = _layer(shape, **{switch: v})
+        try:
+            assert (" on_bf16x3=" in conv.conv_describe(L.h, {"fwd": 0, "bwd": 1, "upd": 2}[which])) == (v != "0"), v
+            print(shape, which, v, kind, flush=True)
+            got[v] = run_pass(L, which, **kw).astype(np.float64)
+        finally:
+            L.close()
+    for v in variants:
+        if kind == "lost bits":
+            assert_close(np.ldexp(got[v], 70), ref, F32, v)
+        else:
+            nan = np.isnan(got["0"])
+            assert np.array_equal(np.isnan(got[v]), nan), v
+            if np.where(nan, 0, got["0"]).any():
+                assert_close(np.where(nan, 0, got[v]), np.where(nan, 0, got["0"]), F32, v)
+            else:  # (all NaN but the cells of zeros)
+                assert not np.where(nan, 0, got[v]).any(), v
+
+
 # Layer, pass: relative error (2-norm) against 64 bits of what the planner picks, no larger than on the fp32 instructions
 EXACT = [((28, 128, 128, 28, 28, 3, 3, 1, 1), "fwd"), ((16, 512, 512, 7, 7, 3, 3, 1, 1), "bwd"), ((8, 1024, 256, 14, 14, 1, 1, 1, 0), "fwd"),
          ((28, 128, 128, 28, 28, 3, 3, 1, 1), "upd"), ((16, 256, 512, 28, 28, 1, 1, 2, 0), "upd"), ((32, 64, 64, 56, 56, 3, 3, 1, 1), "upd"),
