@@ -2773,11 +2773,27 @@ double upd_shared_us(const conv_plan *p, const UpdSharedPlan &s)
     return us;
 }
 
+// What the row kernel takes for seven rows, in microseconds: a band's start, its pairs of runs, the chunks of 64 channels' rows and the halo
+// around them, and the partial copies.  Fitted to 482 drawn layers: rms error 4 %, with two groups of pixels 6.
+double row_update_us(const conv_plan *p)
+{
+    const UpdArgs &a = p->ua;
+    const UpdRowsVariant &v = p->urv;
+    const bool groups = v.wp > 1;
+    const double bands = (double)ceil_div(a.rows_per_split, a.TR) * ceil_div(p->upd_grid, 256) * p->upd_strips;
+    const double pairs = ceil_div(ceil_div(a.TR * a.runs, 2), v.wp), width = (double)p->d.W / p->upd_strips;
+    const double chunks = 4.0e-3 * (v.wc * (a.TR + p->d.R - 1) + v.wk * a.TR) * width;
+    const double copies = (double)a.splits * p->upd_strips * p->info.dwt_bytes * 2 / 5.0e6;
+    return groups ? bands * (0.956 + 0.114 * pairs + 0.238 * chunks) + 2.38 * copies : bands * (0.594 + 0.280 * pairs + 0.0944 * chunks) + 1.09 * copies;
+}
+
 // Whether both operands are staged for all waves, and up to which estimate: lines between its time / the other kernel's, both
 // measured in turn over 500 drawn layers and 500 of these families (C, K = 96 ... 720, N = 16 ... 256, three sets of tensors):
-//   - seven rows or columns: in the row kernel's place everywhere (57 layers, 0.59 - 1.0, in the mean 0.79, one 1.11; 632 -> 40 7x1
-//     at 59x60, N = 18, 113 -> 89 us; 504 -> 284 1x7 at 23x21, N = 27, 57 -> 41); in the ring kernel's place up to 0.87 of its
-//     estimate (0.45 - 0.95, one 1.08; beyond, 0.88 - 1.22);
+//   - seven columns: in the row kernel's place everywhere (205 layers, 0.59 - 0.92, in the mean 0.80; 504 -> 284 1x7 at 23x21, N = 27,
+//     57 -> 41 us); in the ring kernel's place up to 0.87 of its estimate (60 layers, 0.55 - 0.93);
+//   - seven rows: in the row kernel's place up to 0.94 of row_update_us (482 layers: 0.41 - 1.14, in the mean 0.75, nine above 1.04; beyond,
+//     0.98 - 1.53: 140 -> 48 at 46x48, N = 139, 90 -> 136, 624 -> 52 at 58x56, N = 87, 277 -> 385); in the ring kernel's up to 0.83 of its
+//     estimate (0.44 - 1.13, in the mean 0.82; beyond, 0.93 - 1.16);
 //   - 3x3 with stride 2 from 1e10 operations (below, 0.8 - 1.6 whatever the estimates say): up to 1.15 times the window kernel's
 //     estimate (0.81 - 1.01, in the mean 0.91, 288 -> 384 at 35x35, N = 32, 42 -> 36; beyond, 0.92 - 1.22); up to 0.74 times the ring
 //     kernel's for 64 x 64 blocks (0.70 - 0.95; beyond, 0.77 - 1.27); and in the row kernel's place where its runs of eight pixels
@@ -2787,7 +2803,9 @@ double shared_line_us(const conv_plan *p, double ring_us)
 {
     const conv_desc_t &d = p->d;
     const double everywhere = 1.0e9;
-    if (d.R * d.S == 7) return p->upd_ring ? 0.87 * ring_us : p->upd_rows ? everywhere : 0;
+    if (d.R * d.S == 7 && p->upd_ring) return (d.R == 7 ? 0.83 : 0.87) * ring_us;
+    if (d.R * d.S == 7 && p->upd_rows) return d.R == 7 ? 0.94 * row_update_us(p) : everywhere;
+    if (d.R * d.S == 7) return 0;
     const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)p->info.P * p->info.Q;
     if (d.R != 3 || d.S != 3 || d.stride != 2 || flops < 1.0e10) return 0;
     if (p->upd_ring) return p->upd_window ? 1.15 * ring_us : p->urv.fc * p->urv.fk >= 4 ? 0.74 * ring_us : 0;

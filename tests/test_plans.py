@@ -549,3 +549,20 @@ def test_fp32_layers_stay_on_the_fp32_instructions_where_those_are_faster(which,
         assert (" on_bf16x3=" in conv.conv_describe(h, which)) == on
     finally:
         conv.conv_destroy(h)
+
+
+# bf16 updates of seven rows: whether both operands are staged for all waves.  Beside each the time with and without, us.
+@pytest.mark.parametrize("shape,on", [
+    ((139, 140, 48, 46, 48), False),   # 136, 90
+    ((87, 624, 52, 58, 56), False),    # 385, 277
+    ((218, 308, 264, 28, 31), False),  # 413, 345
+    ((32, 84, 264, 47, 48), False),    # 63, 55
+    ((84, 708, 140, 25, 27), True),    # 122, 295
+    ((80, 200, 460, 33, 34), True),    # 139, 284
+    ((18, 632, 40, 59, 60), True)], ids=str)  # 89, 113
+def test_updates_of_seven_rows_are_staged_for_all_waves_where_that_is_faster(shape, on):
+    h = conv.conv_create(*shape, 7, 1, 1, (3, 0), dtype=conv.CONV_BF16)
+    try:
+        assert (" instead=upd_shared," in conv.conv_describe(h, conv.PASS_UPD)) == on
+    finally:
+        conv.conv_destroy(h)
