@@ -2796,7 +2796,8 @@ double row_update_us(const conv_plan *p)
 //     estimate (0.44 - 1.13, in the mean 0.82; beyond, 0.93 - 1.16);
 //   - 3x3 with stride 2 from 1e10 operations (below, 0.8 - 1.6 whatever the estimates say): up to 1.15 times the window kernel's
 //     estimate (0.81 - 1.01, in the mean 0.91, 288 -> 384 at 35x35, N = 32, 42 -> 36; beyond, 0.92 - 1.22); up to 0.74 times the ring
-//     kernel's for 64 x 64 blocks (0.70 - 0.95; beyond, 0.77 - 1.27); and in the row kernel's place where its runs of eight pixels
+//     kernel's for 64 x 64 blocks (0.65 - 1.09, in the mean 0.84; beyond, 0.77 - 1.27), 0.70 times with at most 64 channels in (0.85 - 1.1, in the
+//     mean 0.96; beyond, 1.02), never with at most 64 out, half of a block (50 layers, 1.02 - 1.29: 332 -> 52 at 60x63, N = 166, 151 -> 182); and in the row kernel's place where its runs of eight pixels
 //     fill a row badly, or the row is long (0.66 - 0.98, in the mean 0.84; 288 -> 384 at 35x35, N = 92, 113 -> 89; else 0.9 - 1.16);
 //   - other filters: 1x1 0.85 - 1.19, 3x3 with stride 1 0.9 - 1.5, 5x5 1.15: not built for them.
 double shared_line_us(const conv_plan *p, double ring_us)
@@ -2808,7 +2809,8 @@ double shared_line_us(const conv_plan *p, double ring_us)
     if (d.R * d.S == 7) return 0;
     const double flops = 2.0 * d.N * d.K * d.C * d.R * d.S * (double)p->info.P * p->info.Q;
     if (d.R != 3 || d.S != 3 || d.stride != 2 || flops < 1.0e10) return 0;
-    if (p->upd_ring) return p->upd_window ? 1.15 * ring_us : p->urv.fc * p->urv.fk >= 4 ? 0.74 * ring_us : 0;
+    if (p->upd_ring && p->upd_window) return 1.15 * ring_us;
+    if (p->upd_ring) return p->urv.fc * p->urv.fk < 4 || d.K <= 64 ? 0 : (d.C <= 64 ? 0.70 : 0.74) * ring_us;
     const int Q = p->info.Q;
     return p->upd_rows && (Q >= 29 || ceil_div(Q, 8) * 8 >= 1.14 * Q) ? everywhere : 0;
 }

@@ -566,3 +566,20 @@ def test_updates_of_seven_rows_are_staged_for_all_waves_where_that_is_faster(sha
         assert (" instead=upd_shared," in conv.conv_describe(h, conv.PASS_UPD)) == on
     finally:
         conv.conv_destroy(h)
+
+
+@pytest.mark.parametrize("shape,on", [
+    ((166, 332, 52, 60, 63), False),   # 182, 151
+    ((163, 728, 40, 44, 47), False),   # 199, 172
+    ((248, 64, 204, 33, 33), False),   # 38, 33
+    ((99, 636, 592, 12, 12), True),    # 38, 58
+    ((224, 96, 88, 49, 48), True)], ids=str)  # 52, 74
+def test_strided_updates_of_few_channels_keep_the_ring_kernel(shape, on):
+    lines = []
+    for pad in (0, 1):
+        h = conv.conv_create(*shape, 3, 3, 2, pad, dtype=conv.CONV_BF16)
+        try:
+            lines.append(" instead=upd_shared," in conv.conv_describe(h, conv.PASS_UPD))
+        finally:
+            conv.conv_destroy(h)
+    assert lines == [on, on] if not on else any(lines), lines
